@@ -120,7 +120,7 @@ def kernel_work(kernel: str, n: np.ndarray, m: np.ndarray, d: int, elt: int, ite
                 return "hbm", nbytes, "GB/s", HBM_PEAK_GBS
             return "mfma", flops, "TFLOP/s", BF16_MFMA_TFLOPS
         return "alu", flops, "TFLOP/s", FP64_VECTOR_TFLOPS
-    if kernel in ("k_sinkhorn", "k_sinkhorn_regs", "k_sinkhorn_c32", "k_sinkhorn_tall"):
+    if kernel in ("k_sinkhorn", "k_sinkhorn_regs", "k_sinkhorn_c32", "k_sinkhorn_tall", "k_sinkhorn_strips"):
         # Sinkhorn is arithmetic on the augmented matrix wherever that matrix lives: two sweeps
         # of multiply-adds per iteration, counted over the whole batch and priced against the
         # fp64 vector peak.  (What the multi-workgroup kernels of the large pages stream from
@@ -243,7 +243,7 @@ def bench_side(rt, torch, synth, steps: int, cfg: int, batch=None, rooflines: bo
                kernels_ms={k_: round(v, 4) for k_, v in kernels.items()})
     if rooflines:
         roof = {}
-        for k_ in ("k_norms", "k_sinkhorn_regs", "k_sinkhorn_c32", "k_sinkhorn_tall", "k_sinkhorn", "k_scores", "k_merge"):
+        for k_ in ("k_norms", "k_sinkhorn_regs", "k_sinkhorn_c32", "k_sinkhorn_tall", "k_sinkhorn_strips", "k_sinkhorn", "k_scores", "k_merge"):
             if kernels.get(k_, 0.0) < 0.02 * ms:      # a kernel that has nothing to do on this workload
                 continue
             bound, amount, unit, peak = kernel_work(k_, n_h, keep_h, D, elt, iters, eps, z)

@@ -70,17 +70,16 @@ enum {
   RTP_DEV_IMAGE_TOO_LONG = 2, /* some image has more than max_tokens tokens */
   RTP_DEV_BAD_IMAGE = 4,      /* rtprune_text_density: a page's size is negative, above the stated
                                  maximum, not a multiple of the patch size, or overruns its pixel span */
-  RTP_DEV_SYNC_TIMEOUT = 8    /* the Sinkhorn kernel that spreads a tall image over several workgroups gave
+  RTP_DEV_SYNC_TIMEOUT = 8    /* a Sinkhorn kernel that spreads a large image over several workgroups gave
                                  up waiting for one of them (they must all be resident at once: only a GPU
-                                 kept busy for seconds by other work can cause it); the images it serves
+                                 kept busy for seconds by other work can cause it); the images they serve
                                  - in batches with images above 512 tokens, those that no one-workgroup
-                                 shape holds, with up to 128 pruned tokens and 3584 kept ones, up to
-                                 576 and 1152, or up to 960 and 1280 - have no valid plan, pairing or
-                                 merged rows in this call's outputs */
+                                 shape holds, with up to 1792 pruned tokens - have no valid plan, pairing
+                                 or merged rows in this call's outputs */
 };
 
 /* Two environment variables are read at each call, for tests only (they change no result):
- *   RTPRUNE_SYNC_SPIN_LIMIT      polls a workgroup of that kernel spends on one wait before it gives
+ *   RTPRUNE_SYNC_SPIN_LIMIT      polls a workgroup of those kernels spends on one wait before it gives
  *                                up (default: 20 000 000, seconds); a value of 1 forces the give-up path
  *   RTPRUNE_SWEEP_STREAM_16THS   0 .. 16: how many of every 16 strips the streaming Sinkhorn kernels
  *                                read with non-temporal loads (default: worked out on the device from

@@ -22,6 +22,7 @@
 #include "sinkhorn_dual.hpp"
 #include "sinkhorn_sweep.hpp"
 #include "sinkhorn_cluster.hpp"
+#include "sinkhorn_strip.hpp"
 #include "scores_mfma.hpp"
 #include "scores_tiled.hpp"
 #include "merge_lds.hpp"
@@ -92,7 +93,7 @@ Layout make_layout(int B, long long total, int max_tokens, int D, int rmax) {
     L.sw_ydust = take(sizeof(double) * 2 * B);
     L.sw_bestv = take(sizeof(float) * L.strip_cap);
     L.sw_besti = take(sizeof(int32_t) * L.strip_cap);
-    L.cluster_part = take(sizeof(double) * kClusterPartDoubles);
+    L.cluster_part = take(sizeof(double) * kClusterAreaDoubles);
   } else {
     L.sw_x = L.sw_y = L.sw_colpart = L.sw_xpart = L.sw_ysum = L.sw_ydust = L.sw_bestv = L.sw_besti = 0;
     L.cluster_part = 0;
@@ -190,9 +191,9 @@ int compute_units() {
 // When enabled, each kernel launch is bracketed by two HIP events recorded on
 // the launch stream; rtprune_profile_summary() turns them into per-kernel totals.
 
-enum KernelId { KID_PREPARE, KID_NORMS, KID_SELECT, KID_SCAN, KID_SCORES, KID_CLASSIFY, KID_SINKHORN_REGS, KID_SINKHORN_C32, KID_SINKHORN_TALL, KID_SINKHORN, KID_MERGE, KID_DENSITY_PREPARE, KID_DENSITY_SOBEL, KID_DENSITY_FINISH, KID_SPLICE, KID_COUNT };
+enum KernelId { KID_PREPARE, KID_NORMS, KID_SELECT, KID_SCAN, KID_SCORES, KID_CLASSIFY, KID_SINKHORN_REGS, KID_SINKHORN_C32, KID_SINKHORN_TALL, KID_SINKHORN_STRIPS, KID_SINKHORN, KID_MERGE, KID_DENSITY_PREPARE, KID_DENSITY_SOBEL, KID_DENSITY_FINISH, KID_SPLICE, KID_COUNT };
 const char* const kKernelNames[KID_COUNT] = {"k_prepare", "k_norms", "k_select", "k_scan",
-                                             "k_scores", "k_classify", "k_sinkhorn_regs", "k_sinkhorn_c32", "k_sinkhorn_tall", "k_sinkhorn",
+                                             "k_scores", "k_classify", "k_sinkhorn_regs", "k_sinkhorn_c32", "k_sinkhorn_tall", "k_sinkhorn_strips", "k_sinkhorn",
                                              "k_merge", "k_density_prepare", "k_density_sobel",
                                              "k_density_finish", "k_splice"};
 struct ProfRec { int kid; hipEvent_t start, stop; };
@@ -302,6 +303,21 @@ int cluster_slots_per_xcd(int groups) {
   return std::min(kClusterMaxSlots / 8, per_xcd / std::max(groups, 1));
 }
 
+// The same for the strip kernel, in all: slots that fit half an XCD keep to one XCD, larger ones
+// take consecutive workgroups.
+int strip_slots(int groups) {
+  const int cus = compute_units();
+  groups = std::max(groups, 1);
+  if (groups <= kStripXcdGroups) return 8 * std::min(kStripMaxSlots / 8, cus / 8 / groups);
+  return std::min(kStripMaxSlots, cus / groups);
+}
+
+// The strip kernel's words, when the call's mode has it: behind the cluster kernel's buffers.
+int32_t* strip_words(const Layout& L, void* ws, int mode) {
+  if (!mode_strip_shape(mode)) return nullptr;
+  return reinterpret_cast<int32_t*>(at<double>(ws, L.cluster_part) + kClusterPartDoubles);
+}
+
 // RTPRUNE_SWEEP_STREAM_16THS = 0 .. 16 fixes the share of strips that the sweep kernels read with
 // streaming loads (for tests: a batch whose matrices exceed the memory-side cache takes seconds
 // of oracle time); unset, the share follows from the matrices' size.
@@ -329,15 +345,39 @@ int cluster_spin_limit() {
 // the 512-row register shapes have any).
 void set_sinkhorn_mode(DevParams& p, const Layout& L, const rtprune_batch* in) {
   const int f32 = p.k32 ? kModeF32 : 0;   // exp's range fits fp32: registers may hold the matrix as fp32
-  // the multi-workgroup kernel that keeps a matrix on chip runs one workgroup per compute
-  // unit, in clusters of eight per XCD
+  // The multi-workgroup kernels that keep a matrix on chip run one workgroup per compute unit.
   // Under a fixed retention the largest image the batch can hold bounds the others' kept and
-  // pruned counts; when the multi-workgroup kernel can take it, a cluster slot needs no more
-  // workgroups than that image does (more slots then share the chip), and no image is beyond the
-  // on-chip kernels.
+  // pruned counts; when one of them can take it, a slot needs no more workgroups than that image
+  // does (more slots then share the chip), and no image is beyond the on-chip kernels.  Under a
+  // dynamic one the clamp bounds the pruned sets: slots of eight workgroups of 144 x 576, or
+  // sixteen of 80 x 960 when the clamp allows more.
   const int m_top = p.dynamic ? 0 : kept_count(p.ratio, in->max_tokens), r_top = in->max_tokens - m_top;
-  const bool top_fits = !p.dynamic && m_top > 0 && cluster_fits(m_top, r_top);
-  const int groups = top_fits ? cluster_groups(m_top, std::max(r_top, 1)) : kClusterDefaultGroups;
+  const int r_most = p.dynamic ? params_pruned_bound(p, in->max_tokens) : r_top;
+  int groups = kClusterDefaultGroups, strip = kStripNone, strip_top = 0, strip_eighths = 0, strips = 0;
+  bool top_fits = false;
+  if (L.sweep && f32) {
+    if (!p.dynamic && cluster_shape(m_top, r_top) >= 0) {
+      // (of 224-row workgroups a smaller image may need more than a longest one of 448-row ones)
+      groups = cluster_shape(m_top, r_top) == 0 ? std::max(cluster_groups(m_top, r_top), 1) : kClusterMaxGroups;
+      top_fits = m_top > 0;
+    } else {
+      strip = p.dynamic && r_most > StripA::kCols ? kShapeStripB : strip_for(r_most);
+      if (p.dynamic && r_most <= kClusterCols) strip = kStripNone;
+      strip_eighths = strip_rows(strip) / 8;
+      strip_top = p.dynamic ? (strip == kShapeStripB ? 16 : 8) : (m_top + strip_rows(strip) - 1) / strip_rows(strip);
+      // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
+      // iteration) instead of 144 while every image still has its workgroups at once.  One image,
+      // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
+      const int thin = (m_top + 63) / 64;
+      if (!p.dynamic && strip == kShapeStripA && in->B <= strip_slots(thin) && thin <= kStripDirect) {
+        strip_eighths = 8;
+        strip_top = thin;
+      }
+      if (strip_top > 256 || strip_slots(strip_top) == 0) strip = kStripNone;
+      strips = strip ? (strip << kModeStripShift) | (strip_top << kModeStripGroupsShift) | (strip_eighths << kModeStripRowsShift) : 0;
+      top_fits = !p.dynamic && m_top > 0 && strip && strip_fits(m_top, r_top, strips);
+    }
+  }
   const int cluster = (L.sweep && f32 && cluster_slots_per_xcd(groups) > 0) ? (kModeCluster | (groups << kModeGroupsShift)) : 0;
   // The streaming kernels cost two launches per iteration whether or not an image needs them,
   // and only the device knows the sizes, so they are issued when the batch's shape and the
@@ -351,16 +391,16 @@ void set_sinkhorn_mode(DevParams& p, const Layout& L, const rtprune_batch* in) {
   const bool beyond = p.dynamic ? in->max_tokens - 1 > kClusterRows : !top_fits;
   const int sweep = (L.sweep && (!cluster || beyond)) ? kModeSweep : 0;
   p.k32 = p.k32 && sweep;                 // the sweep kernels' copy in memory is fp32
-  p.mode = (L.sweep ? kModeLarge : 0) | f32 | cluster | sweep;
+  p.mode = (L.sweep ? kModeLarge : 0) | f32 | cluster | strips | sweep;
 }
 
 // `work` non-null: the same launch also builds the Sinkhorn work lists.
 int launch_scan(const rtprune_batch* in, const int32_t* keep, int32_t* out_off, long long* plan_off,
-                const int32_t* status, hipStream_t s, int32_t* work = nullptr, int mode = 0) {
+                const int32_t* status, hipStream_t s, int32_t* work = nullptr, int32_t* strip = nullptr, int mode = 0) {
   ProfScope prof(KID_SCAN, s);
   if (work)
     hipLaunchKernelGGL(k_scan_classify, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, out_off, plan_off, work,
-                       mode, status);
+                       strip, mode, status);
   else
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, out_off, plan_off, status);
   return launched();
@@ -450,7 +490,7 @@ bool scores_on_matrix_cores(const rtprune_batch* in) {
 int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel, const int32_t* keep,
               const long long* plan_off, const Layout& L, void* ws, double* scores_out, float* plan,
               int32_t* pair, int max_pruned_hint, bool classified, hipStream_t s,
-              const ScanJob& job = ScanJob{0, nullptr, nullptr, nullptr, 0, 0}) {
+              const ScanJob& job = ScanJob{0, nullptr, nullptr, nullptr, nullptr, 0, 0}) {
   if (in->B == 0 || in->total_tokens == 0) return RTP_OK;
   DevParams p = p_in;
   set_sinkhorn_mode(p, L, in);
@@ -459,7 +499,8 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
   int32_t* work = at<int32_t>(ws, L.work);
   if (!classified) {
     ProfScope prof(KID_CLASSIFY, s);
-    hipLaunchKernelGGL(k_classify, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, work, p.mode, st);
+    hipLaunchKernelGGL(k_classify, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, work,
+                       strip_words(L, ws, p.mode), p.mode, st);
     RTP_TRY(launched());
   }
   RTP_TRY(in->dtype == RTP_BF16
@@ -488,6 +529,17 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
                          at<double>(ws, L.cluster_part), spx, groups, cluster_spin_limit(), at<int32_t>(ws, L.status)};
     ProfScope prof(KID_SINKHORN_TALL, s);
     hipLaunchKernelGGL(k_sinkhorn_large, dim3(cluster_blocks + in->B), dim3(kClusterThreads), 0, s, CA, cluster_blocks);
+  }
+  if (const int shape = mode_strip_shape(p.mode)) {
+    // (again one workgroup per compute unit of the slots in use: all resident together)
+    const int groups = mode_strip_groups(p.mode), slots = std::min(strip_slots(groups), (in->B + 7) / 8 * 8);
+    const StripArgs TA{A, strip_words(L, ws, p.mode), slots, groups, cluster_spin_limit(), at<int32_t>(ws, L.status)};
+    const dim3 grid(slots * groups), block(kStripThreads);
+    ProfScope prof(KID_SINKHORN_STRIPS, s);
+    if (shape == kShapeStripA) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
+    else if (shape == kShapeStripB) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
+    else if (shape == kShapeStripC) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
+    else hipLaunchKernelGGL(k_sinkhorn_strips<StripD>, grid, block, 0, s, TA);
   }
   RTP_TRY(launched());
   // The general kernel takes what no shape above does.  With the fp32-held shapes
@@ -643,10 +695,10 @@ int launch_stage1(const rtprune_batch* in, const DevParams& p, int mode, const f
   // the prefix sums and work lists: by an extra workgroup of the score pass when that runs
   // on the matrix-core kernel (`job`), else by a launch of their own
   if (scores_on_matrix_cores(in)) {
-    *job = ScanJob{1, out_offsets, plan_off, work, mode, L.plan_stride};
+    *job = ScanJob{1, out_offsets, plan_off, work, strip_words(L, ws, mode), mode, L.plan_stride};
     return RTP_OK;
   }
-  return launch_scan(in, keep, out_offsets, plan_off, status, s, work, mode);
+  return launch_scan(in, keep, out_offsets, plan_off, status, s, work, strip_words(L, ws, mode), mode);
 }
 
 }  // namespace
@@ -928,7 +980,8 @@ extern "C" int rtprune_merge(const rtprune_batch* in, const int32_t* sel_idx,
   RTP_TRY(launch_prepare(in, status, s));
   if (in->B > 0) {
     ProfScope prof(KID_CLASSIFY, s);
-    hipLaunchKernelGGL(k_classify, dim3(1), dim3(256), 0, s, in->offsets, keep_counts, in->B, work, 0, status);
+    hipLaunchKernelGGL(k_classify, dim3(1), dim3(256), 0, s, in->offsets, keep_counts, in->B, work,
+                       static_cast<int32_t*>(nullptr), 0, status);
     RTP_TRY(launched());
   }
   return launch_merge(in, p, sel_idx, keep_counts, out_offsets, plan, plan_off, out, kPrunedUnknown, status, work, s);
@@ -953,7 +1006,7 @@ extern "C" int rtprune_prune(const rtprune_batch* in, const float* density,
   float* plan = at<float>(workspace, L.plan);
   DevParams pm = p;
   set_sinkhorn_mode(pm, L, in);
-  ScanJob job{0, nullptr, nullptr, nullptr, 0, 0};
+  ScanJob job{0, nullptr, nullptr, nullptr, nullptr, 0, 0};
   RTP_TRY(launch_stage1(in, p, pm.mode, density, ratio, keep, sel, out_offsets, plan_off, L, workspace, s, &job));
   // fixed retention: R <= N - ceil(ratio N - 1e-3) <= (1 - ratio) N + 1 for every image
   const int max_pruned = p.dynamic ? kPrunedFromClamp
@@ -1046,7 +1099,7 @@ extern "C" int rtprune_prune_splice(const rtprune_batch* in, const float* densit
   // before the first kernel that writes to the caller's arrays)
   DevParams pm = p;
   set_sinkhorn_mode(pm, L, in);
-  ScanJob job{0, nullptr, nullptr, nullptr, 0, 0};
+  ScanJob job{0, nullptr, nullptr, nullptr, nullptr, 0, 0};
   RTP_TRY(launch_stage1(in, p, pm.mode, density, ratio, keep, sel, nullptr, plan_off, L, workspace, s, &job, &t));
   hipLaunchKernelGGL(k_splice_scan, dim3(1), dim3(256), 0, s, t, keep, in->B, seq_offsets, visual_start, status);
   RTP_TRY(launched());

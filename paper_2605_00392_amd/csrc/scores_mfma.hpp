@@ -55,6 +55,7 @@ struct ScanJob {
   int32_t* out_offsets;        // may be null
   long long* plan_offsets;
   int32_t* work;
+  int32_t* strip;              // the strip kernel's words (may be null)
   int mode;
   long long stride;
 };
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_scores_mfma(
     static_assert(kScoreThreads == 256, "scan_images and classify_images are written for workgroups of 256 threads");
     scan_images(offsets, keep, B, job.out_offsets, job.plan_offsets, stage, job.stride);
     __syncthreads();
-    classify_images(offsets, keep, B, job.work, job.mode, stage);
+    classify_images(offsets, keep, B, job.work, job.strip, job.mode, stage);
     return;
   }
   // Images are taken last to first: the norm pass before this one walks them first

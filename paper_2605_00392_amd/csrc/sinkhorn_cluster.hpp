@@ -17,12 +17,9 @@
 // per iteration, and an iteration costs a few microseconds of exchange instead of
 // two kernel launches.
 //
-// Images with more than 128 pruned tokens take other strips: 144 rows x 576 columns
-// (the 1083-token pages of which 560 are kept: four workgroups) or 80 rows x 960
-// columns (the 2137-token pages: sixteen workgroups, half an XCD), a wave per row slot
-// with its 64 lanes across the columns.  A slot has as many workgroups as the largest
-// image of the launch needs (the host knows it under a fixed retention), so that more
-// slots share the chip.
+// A slot has as many workgroups as the largest image of the launch needs (the host knows it
+// under a fixed retention), so that more slots share the chip.  Images with more than 128
+// pruned tokens have a kernel of their own (sinkhorn_strip.hpp).
 //
 // The exchange.  The workgroups of all slots are resident together: the kernel is
 // launched with one workgroup per compute unit and no more (each needs a CU's whole
@@ -48,31 +45,24 @@
 
 namespace rtp {
 
-constexpr int kClusterMaxGroups = 16;                      // workgroups per cluster slot, at most
+constexpr int kClusterMaxGroups = 8;                       // workgroups per cluster slot, at most
 constexpr int kClusterDefaultGroups = 8;                   // when the host cannot bound the images' sizes
 constexpr int kClusterThreads = 512;
 using ClusterShape = TeamWideA;                            // 448 rows x 128 columns per workgroup
 using ClusterShapeHalf = TeamShape<8, 4, 7, 8>;            // 224 rows x 128 columns per workgroup
-using ClusterShapeWide = TeamStripWide;                    // 144 rows x 576 columns per workgroup
-using ClusterShapeWider = TeamStripWider;                  // 80 rows x 960 columns per workgroup
 static_assert(8 * ClusterShape::kMaxM == kClusterRows && ClusterShape::kMaxR == kClusterCols &&
-              8 * ClusterShapeHalf::kMaxM == kClusterHalfRows && ClusterShapeHalf::kMaxR == kClusterCols &&
-              8 * ClusterShapeWide::kMaxM == kClusterWideRows && ClusterShapeWide::kMaxR == kClusterWideCols &&
-              16 * ClusterShapeWider::kMaxM == kClusterWiderRows && ClusterShapeWider::kMaxR == kClusterWiderCols,
+              8 * ClusterShapeHalf::kMaxM == kClusterHalfRows && ClusterShapeHalf::kMaxR == kClusterCols,
               "the shapes sinkhorn_variant assumes");
 template <typename S> constexpr int cluster_part_of() { return S::TC * (S::CPT + 1); }   // values a workgroup publishes
-constexpr int kClusterPart = cluster_part_of<ClusterShapeWider>();         // 1024 (640 and 144 for the others)
-static_assert(cluster_part_of<ClusterShape>() <= kClusterPart && cluster_part_of<ClusterShapeWide>() <= kClusterPart &&
-                  cluster_part_of<ClusterShapeHalf>() <= kClusterPart,
-              "exchange buffers are sized for the widest shape");
+constexpr int kClusterPart = cluster_part_of<ClusterShape>();              // 144
+static_assert(cluster_part_of<ClusterShapeHalf>() == kClusterPart, "the same buffers for both shapes");
 // LDS of a cluster workgroup: the waves' partial column sums (reused for the pairing's
 // candidates), their totals, the latest x per row, a flag
 template <typename S> constexpr int cluster_lds_of() {
   return (S::W * S::TC * (S::CPT + 1) + S::TC * (S::CPT + 1) + S::TR * S::RPT) * 8 + 16;
 }
-constexpr int cluster_max(int a, int b) { return a > b ? a : b; }
-constexpr int kClusterLdsBytes = cluster_max(cluster_lds_of<ClusterShapeWider>(),
-                                             cluster_max(cluster_lds_of<ClusterShapeWide>(), cluster_lds_of<ClusterShape>()));
+constexpr int kClusterLdsBytes = cluster_lds_of<ClusterShape>();
+static_assert(cluster_lds_of<ClusterShapeHalf>() <= kClusterLdsBytes, "LDS of either shape");
 constexpr int kClusterMaxSlots = 64;                       // cluster slots of a launch (8 per XCD)
 // synchronisation words, after the work lists: one arrival counter per slot, then the give-up word
 constexpr int kClusterSyncWords = kClusterMaxSlots + 1;
@@ -82,6 +72,9 @@ static_assert(kClusterSyncWords == kWorkStreamWord, "the list builder zeroes the
 constexpr int kClusterMaxBlocks = 256;
 constexpr int kClusterSumBufs = 4, kClusterKeyBufs = 2, kClusterBufs = kClusterSumBufs + kClusterKeyBufs;
 constexpr size_t kClusterPartDoubles = static_cast<size_t>(kClusterMaxBlocks) * kClusterBufs * kClusterPart;
+// the workspace area they lie in; the strip kernel's words (at most 65 535 images) follow them there
+constexpr size_t kClusterAreaDoubles = static_cast<size_t>(kClusterMaxBlocks) * kClusterBufs * 1024;
+static_assert(kClusterPartDoubles * 8 + (kStripList + kMaxImages) * 4 <= kClusterAreaDoubles * 8, "both fit the area");
 // what a partial sum's place holds until the sum has been published: no sum has this bit pattern (a NaN)
 constexpr long long kClusterNotYet = -1;
 
@@ -238,29 +231,18 @@ __device__ __forceinline__ bool sinkhorn_cluster_image(const ClusterArgs& C, int
         xs[rslot][a] = 0.0;
         continue;
       }
-      // (the widest shape widens a row's entries a second time for the column sums rather than
-      // hold 15 widened values across the row's reduction: registers)
-      constexpr bool kWidenTwice = CPT > 9;
-      double kd[kWidenTwice ? 1 : CPT];
+      double kd[CPT];
       double acc = 0.0;
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         forget_origin(K[a][c]);
-        const double k = static_cast<double>(K[a][c]);
-        if constexpr (!kWidenTwice) kd[c] = k;
-        acc = fma(k, y[c], acc);
+        kd[c] = static_cast<double>(K[a][c]);
+        acc = fma(kd[c], y[c], acc);
       }
       acc = group_sum<LOG_TC>(acc);
       const double xa = (rslot + TR * a < m_loc) ? rcp64(acc + row_dust) : 0.0;
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        if constexpr (kWidenTwice) {
-          forget_origin(K[a][c]);
-          t[c] = fma(static_cast<double>(K[a][c]), xa, t[c]);
-        } else {
-          t[c] = fma(kd[c], xa, t[c]);
-        }
-      }
+      for (int c = 0; c < CPT; ++c) t[c] = fma(kd[c], xa, t[c]);
       t[CPT] += xa;
       xs[rslot][a] = xa;
       if (a % 2 == 1) __builtin_amdgcn_sched_barrier(0);
@@ -302,7 +284,7 @@ __device__ __forceinline__ bool sinkhorn_cluster_image(const ClusterArgs& C, int
       const int cs = e / (CPT + 1), c = e - cs * (CPT + 1);
       const double* all = part + (gi & 3) * per_slot * kClusterPart + e;
       // all workgroups' values requested together (from a clamped position past the last), added in rank order
-      constexpr int kGroups = S::kMaxM >= 144 ? 8 : kClusterMaxGroups;   // as many as the shape's images can have
+      constexpr int kGroups = kClusterMaxGroups;
       double v[kGroups];
       for (int spin = 0;; ++spin) {
         bool ready = true;
@@ -474,11 +456,9 @@ __device__ __forceinline__ void sinkhorn_cluster_block(const ClusterArgs& C, int
     const int groups = cluster_groups(m, r);           // (at most per_slot: sinkhorn_variant has seen to it)
     const bool last = k + slots >= count;
     if (rank < groups) {
-      const int shape = cluster_shape(m, r);
-      const bool ok = shape == 0   ? sinkhorn_cluster_image<ClusterShapeHalf>(C, b, rank, groups, counter, part, arrived, seq, gi, lds)
-                      : shape == 3 ? sinkhorn_cluster_image<ClusterShape>(C, b, rank, groups, counter, part, arrived, seq, gi, lds)
-                      : shape == 1 ? sinkhorn_cluster_image<ClusterShapeWide>(C, b, rank, groups, counter, part, arrived, seq, gi, lds)
-                                   : sinkhorn_cluster_image<ClusterShapeWider>(C, b, rank, groups, counter, part, arrived, seq, gi, lds);
+      const bool ok = cluster_shape(m, r) == 0
+                          ? sinkhorn_cluster_image<ClusterShapeHalf>(C, b, rank, groups, counter, part, arrived, seq, gi, lds)
+                          : sinkhorn_cluster_image<ClusterShape>(C, b, rank, groups, counter, part, arrived, seq, gi, lds);
       if (!ok) return;
     } else {
       arrived += groups;                               // what the image's meeting, which it stays out of, adds to the count

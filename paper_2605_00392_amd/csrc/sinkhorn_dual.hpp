@@ -351,18 +351,20 @@ __device__ __forceinline__ void sinkhorn_dual48_image(const SinkhornArgs& A, int
 // Work lists for the register-resident kernels: `work` holds kWorkLists counts
 // (one per shape, indexed by variant id) followed by as many lists of B image
 // indices each.  One workgroup; list order follows image order.
-constexpr int kClassifyLdsBytes = kWorkLists * 256 * 4;   // LDS classify_images works in
+// `strip`: the strip kernel's words (null: the call does not launch it).
+constexpr int kClassifyLdsBytes = (kWorkLists + 1) * 256 * 4;   // LDS classify_images works in
 __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offsets,
                                                 const int32_t* __restrict__ keep, int B,
-                                                int32_t* __restrict__ work, int mode, void* lds) {
-  constexpr int NV = kWorkLists;
-  int (*cnt)[256] = static_cast<int (*)[256]>(lds);   // [NV][256]
+                                                int32_t* __restrict__ work, int32_t* __restrict__ strip, int mode,
+                                                void* lds) {
+  constexpr int NV = kWorkLists, NS = NV + 1;         // (the last one: the strip kernel's)
+  int (*cnt)[256] = static_cast<int (*)[256]>(lds);   // [NS][256]
   const int tid = threadIdx.x;
   const int span = (B + 255) / 256;
   const int b0 = min(B, tid * span), b1 = min(B, b0 + span);
-  int c[NV];
+  int c[NS];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) c[v] = 0;
+  for (int v = 0; v < NS; ++v) c[v] = 0;
   __shared__ unsigned long long sweep_cells;      // entries of the sweep kernels' matrices, padding included
   if (tid == 0) sweep_cells = 0;
   __syncthreads();
@@ -375,26 +377,27 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
 #pragma unroll
       for (int u = 0; u < NV; ++u) c[u] += (u == v);
     }
+    c[NV] += n > 0 && v == kVariantStrip;
     if (n > 0 && v == kVariantSweep) cells += static_cast<unsigned long long>(m) * k32_pitch(n - m);
     if (n > 0 && n - m > kTiledMinPruned) c[kListTiled] += 1;
     if (n > 0 && merge_is_mid(n - m)) c[kListMid] += 1;
   }
 #pragma unroll
-  for (int v = 0; v < NV; ++v) cnt[v][tid] = c[v];
+  for (int v = 0; v < NS; ++v) cnt[v][tid] = c[v];
   if (cells) atomicAdd(&sweep_cells, cells);
   __syncthreads();
   for (int o = 1; o < 256; o <<= 1) {
-    int add[NV];
+    int add[NS];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) add[v] = tid >= o ? cnt[v][tid - o] : 0;
+    for (int v = 0; v < NS; ++v) add[v] = tid >= o ? cnt[v][tid - o] : 0;
     __syncthreads();
 #pragma unroll
-    for (int v = 0; v < NV; ++v) cnt[v][tid] += add[v];
+    for (int v = 0; v < NS; ++v) cnt[v][tid] += add[v];
     __syncthreads();
   }
-  int at[NV];
+  int at[NS];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) at[v] = cnt[v][tid] - c[v];
+  for (int v = 0; v < NS; ++v) at[v] = cnt[v][tid] - c[v];
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
@@ -404,13 +407,16 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
       for (int u = 0; u < NV; ++u)
         if (u == v) work[NV + u * B + at[u]++] = b;
     }
+    if (strip && n > 0 && v == kVariantStrip) strip[kStripList + at[NV]++] = b;
     if (n > 0 && n - m > kTiledMinPruned) work[NV + kListTiled * B + at[kListTiled]++] = b;
     if (n > 0 && merge_is_mid(n - m)) work[NV + kListMid * B + at[kListMid]++] = b;
   }
   if (tid == 255) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) work[v] = cnt[v][255];
+    if (strip) strip[kStripCount] = cnt[NV][255];
   }
+  if (strip && tid >= kStripCounters && tid < kStripList) strip[tid] = 0;
   // the cluster kernel's arrival counters and give-up word start at zero
   if (tid < kWorkStreamWord) work[NV * (1 + B) + tid] = 0;
   if (tid == kWorkStreamWord) {
@@ -424,11 +430,11 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
 
 __global__ __launch_bounds__(256) void k_classify(const int32_t* __restrict__ offsets,
                                                   const int32_t* __restrict__ keep, int B,
-                                                  int32_t* __restrict__ work, int mode,
+                                                  int32_t* __restrict__ work, int32_t* __restrict__ strip, int mode,
                                                   const int32_t* __restrict__ status) {
   if (status[0]) return;
   __shared__ __align__(16) unsigned char lds[kClassifyLdsBytes];
-  classify_images(offsets, keep, B, work, mode, lds);
+  classify_images(offsets, keep, B, work, strip, mode, lds);
 }
 
 // Both of the above in one launch, for the fused calls.
@@ -436,14 +442,14 @@ __global__ __launch_bounds__(256) void k_scan_classify(const int32_t* __restrict
                                                        const int32_t* __restrict__ keep, int B,
                                                        int32_t* __restrict__ out_offsets,
                                                        long long* __restrict__ plan_offsets,
-                                                       int32_t* __restrict__ work, int mode,
-                                                       const int32_t* __restrict__ status) {
+                                                       int32_t* __restrict__ work, int32_t* __restrict__ strip,
+                                                       int mode, const int32_t* __restrict__ status) {
   if (status[0]) return;
   __shared__ __align__(16) unsigned char lds[kClassifyLdsBytes];   // (the two run one after the other)
   static_assert(kScanLdsBytes <= kClassifyLdsBytes, "shared work area");
   scan_images(offsets, keep, B, out_offsets, plan_offsets, lds);
   __syncthreads();
-  classify_images(offsets, keep, B, work, mode, lds);
+  classify_images(offsets, keep, B, work, strip, mode, lds);
 }
 
 // All register-resident Sinkhorn work of a batch in one launch.  Workgroups are

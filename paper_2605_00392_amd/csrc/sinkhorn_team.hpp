@@ -85,10 +85,16 @@ using TeamTall32 = TeamShape<8, 3, 19, 4>;  // R <= 32
 using TeamWideA = TeamShape<8, 4, 14, 8>;   // M <= 448, R <= 128
 using TeamWideB = TeamShape<8, 5, 24, 6>;   // M <= 384, R <= 192
 using TeamWideC = TeamShape<8, 5, 20, 7>;   // M <= 320, R <= 224
-// A strip of a larger image in the multi-workgroup kernel (sinkhorn_cluster.hpp) when it has
-// more than 128 pruned tokens: a wave per row slot, the 64 lanes across the columns.
-using TeamStripWide = TeamShape<8, 6, 18, 9>;   // 144 rows x 576 columns per workgroup
-using TeamStripWider = TeamShape<8, 6, 10, 15>;  // 80 rows x 960 columns per workgroup
+// A workgroup's strip of a larger image in k_sinkhorn_strips (sinkhorn_strip.hpp), when it has
+// more than 128 pruned tokens: eight waves of RPT rows each, the 64 lanes across the columns.
+template <int RPT_, int CPT_>
+struct StripShape {
+  static constexpr int RPT = RPT_, CPT = CPT_, kRows = 8 * RPT, kCols = 64 * CPT;
+};
+using StripA = StripShape<18, 9>;    // 144 rows x 576 columns per workgroup
+using StripB = StripShape<10, 15>;   // 80 rows x 960 columns
+using StripC = StripShape<8, 22>;    // 64 rows x 1408 columns
+using StripD = StripShape<6, 28>;    // 48 rows x 1792 columns
 // The one- and two-wave kernels (sinkhorn_wave.hpp): kRows augmented rows per
 // lane, kCols augmented columns.
 struct WaveShape {
@@ -112,10 +118,16 @@ constexpr int kSinkhornBlockWaves = 8;   // waves of a k_sinkhorn_regs workgroup
 constexpr int kDualRows = 512, kDualCols = 32;
 constexpr int kVariantA = 0, kVariantDual = 1, kVariantDual48 = 2, kVariantB = 3, kVariantC = 4,
               kVariantPair = 5, kVariantSweep = 6, kVariantTall = 7, kVariantTeamTall = 8, kVariantWideA = 9,
-              kVariantWideB = 10, kVariantWideC = 11, kVariantC32 = 12, kVariantCluster = 13, kGeneralVariant = 14;
+              kVariantWideB = 10, kVariantWideC = 11, kVariantC32 = 12, kVariantCluster = 13, kGeneralVariant = 14,
+              kVariantStrip = 16;
 // The work lists k_classify builds: one per register-resident shape above, and
 // one of the images whose scores and merge go to the tiled matrix-core kernels.
+// (The strip kernel's list lies elsewhere: StripWords.)
 constexpr int kListTiled = 14, kListMid = 15, kWorkLists = 16;
+// Words of the strip kernel, in device memory that only it uses: how many images it has, arrival
+// counters of its slots and a give-up word (zero when it starts), and the list of its images.
+constexpr int kStripMaxSlots = 64;
+constexpr int kStripCount = 0, kStripCounters = 1, kStripGaveUp = kStripCounters + kStripMaxSlots, kStripList = kStripGaveUp + 1;
 // after the lists: synchronisation words of the multi-workgroup Sinkhorn kernel (arrival counters
 // of its cluster slots, a give-up word), zeroed by whoever builds the lists, and one word for the
 // sweep kernels: how many of every 16 strips they read with streaming loads (kWorkStreamWord)
@@ -134,31 +146,77 @@ constexpr long long kSweepResidentBytes = 200ll * 1000 * 1000;
 // taller matrices on chip (sinkhorn_cluster.hpp).
 // kModeSweep: the launches of the streaming multi-workgroup kernels (sinkhorn_sweep.hpp) are issued.
 constexpr int kModeLarge = 1, kModeF32 = 2, kModeCluster = 4, kModeSweep = 8;
-// bits 8-12 of `mode`: workgroups per cluster slot of the multi-workgroup kernel in this launch
-// (1 to 16); an image that would need more is not that kernel's
+// bits 8-11 of `mode`: workgroups per cluster slot of the multi-workgroup kernel in this launch
+// (1 to 8); an image that would need more is not that kernel's
 constexpr int kModeGroupsShift = 8;
-__host__ __device__ inline int mode_cluster_groups(int mode) { return (mode >> kModeGroupsShift) & 31; }
-// (that kernel's shapes: up to eight workgroups of 224 or 448 rows with at most 128 pruned tokens,
-// up to eight of 144 rows with at most 576, up to sixteen of 80 rows with at most 960)
+__host__ __device__ inline int mode_cluster_groups(int mode) { return (mode >> kModeGroupsShift) & 15; }
+// (that kernel's shapes: up to eight workgroups of 224 or 448 rows with at most 128 pruned tokens)
 constexpr int kClusterRows = 8 * 448, kClusterCols = 128;
 constexpr int kClusterHalfRows = 8 * 224;
-constexpr int kClusterWideRows = 8 * 144, kClusterWideCols = 576;
-constexpr int kClusterWiderRows = 16 * 80, kClusterWiderCols = 960;
-// which of them an image takes (0 .. 3; -1: none).  With at most 128 pruned tokens the strips are
-// 224 rows high while eight of them cover the image (half the arithmetic per workgroup and
-// iteration for the same exchange), else 448.
+// Which of them an image takes (0, 1; -1: none).  The workgroups take 224 rows while eight of them
+// cover the image (half the arithmetic per workgroup and iteration for the same exchange), else 448.
 __host__ __device__ inline int cluster_shape(int m, int r) {
-  if (m <= kClusterHalfRows && r <= kClusterCols) return 0;
-  if (m <= kClusterRows && r <= kClusterCols) return 3;
-  if (m <= kClusterWideRows && r <= kClusterWideCols) return 1;
-  if (m <= kClusterWiderRows && r <= kClusterWiderCols) return 2;
-  return -1;
+  return m <= kClusterHalfRows && r <= kClusterCols ? 0 : m <= kClusterRows && r <= kClusterCols ? 1 : -1;
 }
-__host__ __device__ inline bool cluster_fits(int m, int r) { return cluster_shape(m, r) >= 0; }
 // workgroups the kernel spreads such an image over
 __host__ __device__ inline int cluster_groups(int m, int r) {
-  const int shape = cluster_shape(m, r);
-  return shape == 0 ? (m + 223) / 224 : shape == 3 ? (m + 447) / 448 : shape == 1 ? (m + 143) / 144 : (m + 79) / 80;
+  return cluster_shape(m, r) == 0 ? (m + 223) / 224 : (m + 447) / 448;
+}
+__host__ __device__ inline bool cluster_fits(int m, int r, int mode) {
+  return cluster_shape(m, r) >= 0 && cluster_groups(m, r) <= mode_cluster_groups(mode);
+}
+// The strip kernel: one strip shape for all of a call's images (bits 12-14 of `mode`; none: the
+// kernel is not launched), as many strips as an image's rows take, up to the slot's workgroups
+// (bits 16-24).
+constexpr int kModeStripShift = 12, kModeStripGroupsShift = 16;
+__host__ __device__ inline int mode_strip_groups(int mode) { return (mode >> kModeStripGroupsShift) & 511; }
+enum { kStripNone = 0, kShapeStripA = 1, kShapeStripB = 2, kShapeStripC = 3, kShapeStripD = 4 };
+__host__ __device__ inline int mode_strip_shape(int mode) { return (mode >> kModeStripShift) & 7; }
+__host__ __device__ inline int strip_cols(int shape) {
+  return shape == kShapeStripA ? StripA::kCols : shape == kShapeStripB ? StripB::kCols
+       : shape == kShapeStripC ? StripC::kCols : shape == kShapeStripD ? StripD::kCols : 0;
+}
+__host__ __device__ inline int strip_rows(int shape) {
+  return shape == kShapeStripA ? StripA::kRows : shape == kShapeStripB ? StripB::kRows
+       : shape == kShapeStripC ? StripC::kRows : StripD::kRows;
+}
+// the narrowest that holds `r` columns (kStripNone: none)
+__host__ __device__ inline int strip_for(int r) {
+  return r <= StripA::kCols ? kShapeStripA : r <= StripB::kCols ? kShapeStripB : r <= StripC::kCols ? kShapeStripC
+       : r <= StripD::kCols ? kShapeStripD : kStripNone;
+}
+// A strip image's workgroups exchange their sums in the image's own slot of the kernel matrix,
+// whose m r doubles hold fp32 entries: the upper end is free.  A few workgroups read all the
+// others' column sums (one trip); of more of them each is handed the sums of its share of
+// the columns and everybody reads back the finished y (two trips, but 1 / groups of the reading).
+// `strip_share`: columns (and the sum of x) a workgroup owns.
+constexpr int kStripDirect = 16, kStripBufs = 4;
+// (Measured: 64 pages of 1083 tokens, 4 workgroups each, 0.60 ms direct, 0.81 in shares; 32 pages of
+// 2137 tokens, 16 each, 1.46 and 1.64; the wider shapes' registers leave no room for the direct reading.)
+__host__ __device__ inline bool strip_direct(int groups, int mode) {
+  return mode_strip_shape(mode) <= kShapeStripB && groups <= kStripDirect;
+}
+__host__ __device__ inline int strip_share(int r, int groups) { return (r + groups) / groups; }   // ceil((r + 1) / groups)
+__host__ __device__ inline long long strip_exchange_doubles(int r, int groups, int mode) {
+  if (groups <= 1) return 0;
+  const long long keys = static_cast<long long>(groups) * r;
+  if (strip_direct(groups, mode)) return static_cast<long long>(kStripBufs) * groups * (r + 1) + keys;
+  return static_cast<long long>(kStripBufs) * (groups + 1) * strip_share(r, groups) * groups + keys;
+}
+constexpr int kStripAlign = 16;   // doubles
+__host__ __device__ inline bool strip_exchange_fits(int m, int r, int groups, int mode) {
+  const long long entries = 2 + static_cast<long long>(m) * ((r + 3) & ~3) / 2;   // (one double of alignment, see k32_base)
+  return entries + strip_exchange_doubles(r, groups, mode) + 2 * kStripAlign <= static_cast<long long>(m) * r;
+}
+// Rows of a workgroup in this launch (bits 25-29 of `mode`: eighths): the shape's, or fewer when
+// that leaves most of the chip idle.
+constexpr int kModeStripRowsShift = 25;
+__host__ __device__ inline int mode_strip_rows(int mode) { return ((mode >> kModeStripRowsShift) & 31) * 8; }
+__host__ __device__ inline int strip_groups(int m, int mode) { return (m + mode_strip_rows(mode) - 1) / mode_strip_rows(mode); }
+__host__ __device__ inline bool strip_fits(int m, int r, int mode) {
+  if (m <= 0 || r > strip_cols(mode_strip_shape(mode))) return false;
+  const int groups = strip_groups(m, mode);
+  return groups <= mode_strip_groups(mode) && (groups == 1 || strip_exchange_fits(m, r, groups, mode));
 }
 // The multi-workgroup sweep kernels (sinkhorn_sweep.hpp) take up to this many
 // pruned tokens.
@@ -172,11 +230,11 @@ __host__ __device__ inline int sinkhorn_variant(int m, int r, int mode) {
   if (m + 1 <= kDualRows && r + 1 <= kDualCols) return kVariantDual;
   if ((mode & kModeLarge) && TallShape::fits(m, r)) return kVariantTall;
   if ((mode & kModeLarge) && (mode & kModeF32) && TeamTall::fits(m, r)) return kVariantTeamTall;
-  // rows beyond the shapes above with at most 128 pruned tokens, or up to 1152 rows with at most
-  // 576: a cluster of workgroups that keeps the matrix on chip
-  if ((mode & kModeLarge) && (mode & kModeF32) && (mode & kModeCluster) && cluster_fits(m, r) &&
-      cluster_groups(m, r) <= mode_cluster_groups(mode))
+  // rows or columns beyond the shapes above: several workgroups that keep the matrix on chip
+  if ((mode & kModeLarge) && (mode & kModeF32) && (mode & kModeCluster) && cluster_fits(m, r, mode))
     return kVariantCluster;
+  if ((mode & kModeLarge) && (mode & kModeF32) && mode_strip_shape(mode) && strip_fits(m, r, mode))
+    return kVariantStrip;
   // when the sweep kernels run anyway (their launches are paid for) they also
   // take the images of the slowest register shapes, which otherwise set the
   // duration of the register-resident launch
@@ -213,7 +271,7 @@ __device__ __forceinline__ int kernel_layout(const DevParams& p, int m, int r) {
   if (v == kVariantSweep) return p.k32 ? kKernelRowsF32 : kKernelRowsF64;
   // (these are only chosen under kModeF32)
   if (v == kVariantTeamTall || v == kVariantWideA || v == kVariantWideB || v == kVariantWideC || v == kVariantC32 ||
-      v == kVariantCluster)
+      v == kVariantCluster || v == kVariantStrip)
     return kKernelRowsF32;
   return (v == kVariantA || v == kVariantPair || v == kVariantTall) ? kKernelColsF64 : kKernelRowsF64;
 }

@@ -307,6 +307,31 @@ def test_multi_workgroup_resident_sinkhorn_widest_strips_at_their_edges(override
     assert rep.max_score_abs <= hz.SCORE_ATOL
 
 
+@pytest.mark.parametrize("top,shapes,iters", [
+    # strips of 64 rows x 1408 columns, 24 to a slot (more than an XCD's half: consecutive workgroups)
+    ((1500, 1400), [(64, 1408), (65, 1408), (1492, 1408), (40, 1000), (2, 1200), (700, 961), (300, 130), (900, 128)], 7),
+    # strips of 48 rows x 1792 columns, 27 to a slot; 1793 columns are the general kernel's
+    ((1250, 1750), [(48, 1792), (49, 1792), (1208, 1792), (1200, 129), (97, 300), (60, 1793)], 6),
+    ((1250, 1750), [(48, 1792), (433, 1409)], 0),
+    # one image or two: strips of 64 rows x 576 columns; one trip's exchange up to sixteen
+    # workgroups and 4608 sums, two trips beyond
+    ((1000, 287), [], 9),
+    ((1024, 287), [(1, 200), (64, 576), (65, 576)], 9),
+    ((420, 280), [(129, 300)], 1),
+])
+def test_multi_workgroup_strips_at_their_edges(top, shapes, iters):
+    """The strip shapes beyond the first two and the thin strips of small batches, on both sides of
+    their limits: the longest image and the retention choose the shape of the launch."""
+    shapes = [top] + shapes
+    batch = _clustered([m + r for m, r in shapes], 64, "f32", 43, iters=iters, ratio=top[0] / (top[0] + top[1]))
+    assert batch.max_tokens == sum(top)
+    keep = [m for m, _ in shapes]
+    s = hz.run_staged(batch, keep_counts_in=keep)
+    assert s["status"] == 0
+    rep = hz.compare_batch(batch, s, staged=True, keep_counts=keep)
+    _log(rep, f"strips {top}")
+
+
 def test_multi_workgroup_resident_sinkhorn_wide_strips_fill_the_chip():
     """A fixed retention under which the longest image takes four strips: slots of four workgroups,
     64 of them, more images than slots, through the fused call (no launches of the streaming
