@@ -24,6 +24,7 @@
 #include "sinkhorn_cluster.hpp"
 #include "sinkhorn_strip.hpp"
 #include "scores_mfma.hpp"
+#include "scores_f64.hpp"
 #include "scores_tiled.hpp"
 #include "merge_lds.hpp"
 #include "merge_tiled.hpp"
@@ -438,7 +439,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
   if constexpr (std::is_same<T, bf16_t>::value) {
     // matrix-core path: its 32-term fp32 partial sums leave an error of about
     // 6e-8 sqrt(32 / D) of the cosine, which the pairing's near-tie band covers from
-    // D = 1024 up; narrower tokens take the fp64 vector kernel.
+    // D = 1024 up; narrower tokens take the fp64 matrix units (k_scores_f64).
     if (in->D % 128 == 0 && in->D >= kMfmaMinWidth) {
       // matrix-core path (an image's workgroups on one XCD: B rounded up to eight)
       const int tiles_s = (in->max_tokens + kScoreRows - 1) / kScoreRows;
@@ -470,21 +471,17 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
       return launched();
     }
   }
-  const int tiles = (in->max_tokens + kScoreRowsPerBlock - 1) / kScoreRowsPerBlock;
-  const dim3 grid(tiles, in->B), block(256);
-  if (in->D <= 1280)
-    hipLaunchKernelGGL((k_scores<T, 5>), grid, block, 0, s, tok, in->offsets, in->D, sel, keep, plan_off,
-                       sq, p, kmat, L.plan_cap, scores_out, st);
-  else
-    hipLaunchKernelGGL((k_scores<T, 16>), grid, block, 0, s, tok, in->offsets, in->D, sel, keep,
-                       plan_off, sq, p, kmat, L.plan_cap, scores_out, st);
+  // the fp64 matrix units.  A workgroup walks an image's pruned rows 64 at a time; large pruned sets
+  // are dealt to several (up to 16: every image of the batch gets that many, needed or not)
+  const int tiles = (in->max_tokens + kScoreF64Rows - 1) / kScoreF64Rows;
+  const int rmax = std::max(1, pruned_bound(in, p, max_pruned_hint));
+  const int groups = max_pruned_hint >= 0 ? std::min(16, (rmax + kScoreF64Cols - 1) / kScoreF64Cols) : rmax > 512 ? 4 : 1;
+  const long long blocks = static_cast<long long>(tiles) * groups * in->B + (job.on ? 1 : 0);
+  if (blocks > 0x7fffffffLL) return RTP_EUNSUPPORTED;
+  hipLaunchKernelGGL(k_scores_f64<T>, dim3(static_cast<unsigned>(blocks)), dim3(kScoreF64Threads), 0, s, tok,
+                     in->offsets, in->B, in->D, sel, keep, plan_off, sq, p, kmat, L.plan_cap, scores_out, tiles, groups,
+                     job, st);
   return launched();
-}
-
-// Whether the score pass of a batch runs on the matrix-core kernel, whose launch can
-// carry the fused calls' scan job.
-bool scores_on_matrix_cores(const rtprune_batch* in) {
-  return in->dtype == RTP_BF16 && in->D % 128 == 0 && in->D >= kMfmaMinWidth && in->B > 0 && in->total_tokens > 0;
 }
 
 int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel, const int32_t* keep,
@@ -693,8 +690,8 @@ int launch_stage1(const rtprune_batch* in, const DevParams& p, int mode, const f
   }
   RTP_TRY(launch_select(in, p, density, nullptr, 1, L, ws, nullptr, ratio, keep, sel, s));
   // the prefix sums and work lists: by an extra workgroup of the score pass when that runs
-  // on the matrix-core kernel (`job`), else by a launch of their own
-  if (scores_on_matrix_cores(in)) {
+  // (`job`), else by a launch of their own
+  if (in->B > 0 && in->total_tokens > 0) {
     *job = ScanJob{1, out_offsets, plan_off, work, strip_words(L, ws, mode), mode, L.plan_stride};
     return RTP_OK;
   }

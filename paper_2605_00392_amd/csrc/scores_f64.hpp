@@ -1,0 +1,133 @@
+// Scores and kernel matrix (Eq. 3, Appendix C) on the fp64 matrix units: fp32 tokens, and
+// bf16 tokens of widths the bf16 matrix-core kernels do not take.  K_ij = exp((S_ij - shift) / eps).
+//
+// A token element is exact in fp64 and so is the product of two of them, and the matrix unit
+// accumulates in fp64, so S is as good as the vector unit's.  v_mfma_f64_16x16x4 takes from lane
+// l one element of row l % 16 of either operand, at one of four contraction indices (l / 16); which
+// index is immaterial as long as both operands agree, so a lane loads four consecutive elements
+// (the four lanes of a row 16 of them) and four instructions use them up.
+//
+// Workgroup = 16 kept rows x up to 64 pruned rows (one to four tiles of 16), the contraction split
+// over its four waves, whose partial tiles meet in LDS: a single page of a few tokens is then a
+// quarter of the row's length deep instead of all of it, and has four waves per 16 rows.  Bound by
+// the latency of that chain for few tokens and by the matrix unit (64 cycles per instruction) for many.
+// Measured against one wave per kept row with lane sums per dot product: one 64-token fp32 image
+// 58 -> 11 us, 48 pages of up to 400 fp32 tokens 184 -> 34 us.
+#pragma once
+#include "common.hpp"
+#include "scores_mfma.hpp"
+
+namespace rtp {
+
+constexpr int kScoreF64Rows = 16, kScoreF64Cols = 64, kScoreF64Threads = 256;
+typedef double doublex4_t __attribute__((ext_vector_type(4)));
+
+// This wave's partial tiles: contraction steps s0 .. s1 - 1 of 16 elements.  `arow`, `brow`: this
+// lane's kept row and its pruned row of each tile.
+template <typename T, int NT>
+__device__ __forceinline__ void scores_f64_tiles(const T* arow, const T* const (&brow)[4], int D, int s0, int s1, int lane,
+                                                 doublex4_t (&acc)[4]) {
+  typedef typename Raw4<T>::type raw_t;
+  constexpr int kDepth = NT == 4 ? 2 : 4;            // steps whose loads are in flight together
+#pragma unroll
+  for (int u = 0; u < NT; ++u) acc[u] = doublex4_t{0.0, 0.0, 0.0, 0.0};
+  for (int s = s0; s < s1; s += kDepth) {
+    raw_t a[kDepth], b[kDepth][NT];
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q) {
+      const int k = min(16 * (s + q) + 4 * (lane >> 4), D - 4);
+      a[q] = *reinterpret_cast<const raw_t*>(arow + k);
+#pragma unroll
+      for (int u = 0; u < NT; ++u) b[q][u] = *reinterpret_cast<const raw_t*>(brow[u] + k);
+    }
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q) {
+      float x[4];
+      unpack4(a[q], x);
+      // past the last step or the row's end: a zero operand is enough (the other one is a finite
+      // copy, or as little a number as the row it is a copy of)
+      const bool inside = s + q < s1 && 16 * (s + q) + 4 * (lane >> 4) < D;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = inside ? x[e] : 0.f;
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        float y[4];
+        unpack4(b[q][u], y);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(x[e]), static_cast<double>(y[e]), acc[u], 0, 0, 0);
+      }
+    }
+  }
+}
+
+// Launched over `tiles` row tiles x `groups` groups of column tiles x B workgroups (linear ids),
+// plus one when `job.on` (as in k_scores_mfma).
+template <typename T>
+__global__ __launch_bounds__(kScoreF64Threads) void k_scores_f64(
+    const T* __restrict__ tokens, const int32_t* __restrict__ offsets, int B, int D, const int32_t* __restrict__ sel_idx,
+    const int32_t* __restrict__ keep, const long long* __restrict__ plan_offsets, const double* __restrict__ norm64,
+    DevParams p, double* __restrict__ kmat, long long plan_cap, double* __restrict__ scores_out, int tiles, int groups,
+    ScanJob job, const int32_t* __restrict__ status) {
+  if (status[0]) return;
+  __shared__ __align__(16) double part[4][4][256];       // [wave][tile][16 x 16]
+  if (job.on && blockIdx.x == gridDim.x - 1) {
+    static_assert(kClassifyLdsBytes <= sizeof(part) && kScanLdsBytes <= sizeof(part), "the job works in the tiles' area");
+    static_assert(kScoreF64Threads == 256, "scan_images and classify_images are written for workgroups of 256 threads");
+    scan_images(offsets, keep, B, job.out_offsets, job.plan_offsets, part, job.stride);
+    __syncthreads();
+    classify_images(offsets, keep, B, job.work, job.strip, job.mode, part);
+    return;
+  }
+  const int tile = blockIdx.x % tiles, rest = blockIdx.x / tiles;
+  const int group = rest % groups, b = rest / groups;
+  const int lo = offsets[b];
+  const int n = offsets[b + 1] - lo;
+  const int m = min(max(keep[b], 0), n), r = n - m;
+  const int i0 = tile * kScoreF64Rows;
+  if (r <= 0 || i0 >= m || group * kScoreF64Cols >= r) return;
+  const long long po = job.on ? plan_slot(offsets, b, job.stride) : plan_offsets[b];
+  if (!plan_fits(po, m, r, plan_cap)) return;
+  const int k_layout = kernel_layout(p, m, r);
+  const int32_t* sel = sel_idx + lo;
+  const double inv_eps = 1.0 / p.eps;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int steps = (D + 15) / 16, per_wave = (steps + 3) / 4;
+  const int s0 = wave * per_wave, s1 = min(steps, s0 + per_wave);
+  const T* arow = tokens + static_cast<size_t>(lo + clamp_index(sel[min(i0 + (lane & 15), m - 1)], n)) * D;
+  const int ie = tid >> 4, je = tid & 15;                // the entry of a tile this thread finishes
+  const double ni = norm64[lo + clamp_index(sel[min(i0 + ie, m - 1)], n)];
+
+  for (int j0 = group * kScoreF64Cols; j0 < r; j0 += groups * kScoreF64Cols) {
+    const int ntiles = min(4, (r - j0 + 15) >> 4);
+    const T* brow[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      brow[u] = tokens + static_cast<size_t>(lo + clamp_index(sel[m + min(j0 + 16 * u + (lane & 15), r - 1)], n)) * D;
+    doublex4_t acc[4];
+    if (ntiles == 1) scores_f64_tiles<T, 1>(arow, brow, D, s0, s1, lane, acc);
+    else if (ntiles == 2) scores_f64_tiles<T, 2>(arow, brow, D, s0, s1, lane, acc);
+    else scores_f64_tiles<T, 4>(arow, brow, D, s0, s1, lane, acc);
+    // accumulator element v of lane l is (kept row l / 16 + 4 v, pruned row l % 16) of its tile
+    if (j0 != group * kScoreF64Cols) __syncthreads();    // the previous columns' tiles are still being read
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (u < ntiles) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) part[wave][u][16 * ((lane >> 4) + 4 * v) + (lane & 15)] = acc[u][v];
+      }
+    __syncthreads();
+    for (int u = 0; u < ntiles; ++u) {
+      const int i = i0 + ie, j = j0 + 16 * u + je;
+      if (i < m && j < r) {
+        const double dot = (part[0][u][tid] + part[1][u][tid]) + (part[2][u][tid] + part[3][u][tid]);
+        const double nj = norm64[lo + clamp_index(sel[m + j], n)];
+        const double s = dot / fmax(ni * nj, kTinyNorm * kTinyNorm);
+        store_kernel(kmat, po, i, j, m, r, exp_nonpositive((s - p.shift) * inv_eps), k_layout);
+        if (scores_out) scores_out[po + static_cast<long long>(i) * r + j] = s;
+      }
+    }
+  }
+}
+
+}  // namespace rtp

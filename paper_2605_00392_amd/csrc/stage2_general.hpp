@@ -1,9 +1,8 @@
-// Stage 2 and the merge, general-shape kernels: every image size and token
-// width within the library's limits goes through these; they keep the Sinkhorn
-// kernel matrix in global memory (L2-resident) and use plain fp64 / fp32 vector
-// arithmetic.
+// Sinkhorn and the merge, general-shape kernels: every image size and token
+// width within the library's limits that no kernel of its own takes goes through
+// these; they keep the Sinkhorn kernel matrix in global memory (L2-resident) and
+// use plain fp64 / fp32 vector arithmetic.
 //
-//   k_scores   K_ij = exp((S_ij - shift) / eps), S = cosine of Eq. 3
 //   k_sinkhorn T multiplicative Sinkhorn iterations on the dustbin-augmented
 //              kernel (Appendix C in the exponentiated variables
 //              x = exp(u), y = exp(v)), the plan, and the hard pairing
@@ -13,72 +12,6 @@
 #include "sinkhorn_team.hpp"
 
 namespace rtp {
-
-constexpr int kScoreRowsPerBlock = 16;
-
-// Workgroup = 4 waves, each wave owns kept rows of a 16-row tile and walks all
-// pruned rows; a (kept, pruned) dot product is accumulated in fp64 across the
-// wave's lanes.  Lane layout as in k_norms.
-template <typename T, int KMAX>
-__global__ __launch_bounds__(256) void k_scores(
-    const T* __restrict__ tokens, const int32_t* __restrict__ offsets, int D,
-    const int32_t* __restrict__ sel_idx, const int32_t* __restrict__ keep,
-    const long long* __restrict__ plan_offsets, const double* __restrict__ norm64, DevParams p,
-    double* __restrict__ kmat, long long plan_cap, double* __restrict__ scores_out,
-    const int32_t* __restrict__ status) {
-  if (status[0]) return;
-  const int b = blockIdx.y;
-  const int lo = offsets[b];
-  const int n = offsets[b + 1] - lo;
-  const int m = min(max(keep[b], 0), n), r = n - m;
-  const int i0 = blockIdx.x * kScoreRowsPerBlock;
-  if (r <= 0 || i0 >= m) return;
-  if (!plan_fits(plan_offsets[b], m, r, plan_cap)) return;
-  const int i1 = min(m, i0 + kScoreRowsPerBlock);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ngroups = D >> 2;
-  const long long po = plan_offsets[b];
-  const int k_layout = kernel_layout(p, m, r);
-  const int32_t* sel = sel_idx + lo;
-  const double inv_eps = 1.0 / p.eps;
-
-  for (int i = i0 + wave; i < i1; i += 4) {
-    const int ti = clamp_index(sel[i], n);
-    const T* rowi = tokens + static_cast<size_t>(lo + ti) * D;
-    float xi[KMAX][4];
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      const int g = lane + kWave * k;
-      if (g < ngroups) load4(rowi + 4 * g, xi[k]);
-      else xi[k][0] = xi[k][1] = xi[k][2] = xi[k][3] = 0.f;
-    }
-    const double ni = norm64[lo + ti];
-    for (int j = 0; j < r; ++j) {
-      const int tj = clamp_index(sel[m + j], n);
-      const T* rowj = tokens + static_cast<size_t>(lo + tj) * D;
-      double dot = 0.0;
-#pragma unroll
-      for (int k = 0; k < KMAX; ++k) {
-        const int g = lane + kWave * k;
-        if (g < ngroups) {
-          float xj[4];
-          load4(rowj + 4 * g, xj);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            dot = fma(static_cast<double>(xi[k][e]), static_cast<double>(xj[e]), dot);
-        }
-      }
-      dot = wave_sum(dot);
-      if (lane == 0) {
-        const double nj = norm64[lo + tj];
-        const double s = dot / fmax(ni * nj, kTinyNorm * kTinyNorm);
-        const long long at = static_cast<long long>(i) * r + j;
-        store_kernel(kmat, po, i, j, m, r, exp_nonpositive((s - p.shift) * inv_eps), k_layout);
-        if (scores_out) scores_out[po + at] = s;
-      }
-    }
-  }
-}
 
 // One workgroup of 1024 threads per image.  With K = exp((S - shift)/eps) on the
 // kept x pruned block and kz = exp((z - shift)/eps) on the dustbin row, column
