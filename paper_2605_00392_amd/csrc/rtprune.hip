@@ -504,7 +504,13 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
               ? launch_scores_t<bf16_t>(in, p, sel, keep, plan_off, L, ws, scores_out, max_pruned_hint, work, job, s)
               : launch_scores_t<float>(in, p, sel, keep, plan_off, L, ws, scores_out, max_pruned_hint, work, job, s));
   SinkhornArgs A{in->offsets, keep, plan_off, p, kmat, L.plan_cap, plan, pair};
-  {
+  // In a batch with tall images and cluster slots the short shapes' images go into
+  // k_sinkhorn_large's launch, when the call can have none of the other shapes of k_sinkhorn_regs
+  // (more than 31 pruned tokens and at most 512 rows): up to 128 pruned tokens those are the tall
+  // team's and the clusters', beyond that the strips' or the streaming kernels'.
+  const bool folded = (p.mode & kModeCluster) && max_pruned_hint != kPrunedUnknown &&
+                      (pruned_bound(in, p, max_pruned_hint) <= kClusterCols || mode_strip_shape(p.mode) || (p.mode & kModeSweep));
+  if (!folded) {
     ProfScope prof(KID_SINKHORN_REGS, s);
     hipLaunchKernelGGL(k_sinkhorn_regs, dim3(in->B), dim3(kDualThreads), 0, s, A, work, in->B, compute_units(), st);
   }
@@ -525,7 +531,8 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
     const ClusterArgs CA{A, work, in->B, work + kWorkLists * (1 + static_cast<size_t>(in->B)),
                          at<double>(ws, L.cluster_part), spx, groups, cluster_spin_limit(), at<int32_t>(ws, L.status)};
     ProfScope prof(KID_SINKHORN_TALL, s);
-    hipLaunchKernelGGL(k_sinkhorn_large, dim3(cluster_blocks + in->B), dim3(kClusterThreads), 0, s, CA, cluster_blocks);
+    hipLaunchKernelGGL(k_sinkhorn_large, dim3(cluster_blocks + in->B), dim3(kClusterThreads), 0, s, CA, cluster_blocks,
+                       compute_units(), folded ? 1 : 0);
   }
   if (const int shape = mode_strip_shape(p.mode)) {
     // (again one workgroup per compute unit of the slots in use: all resident together)

@@ -452,6 +452,39 @@ __global__ __launch_bounds__(256) void k_scan_classify(const int32_t* __restrict
   classify_images(offsets, keep, B, work, strip, mode, lds);
 }
 
+// The two- and one-wave images, the shortest-running roles: workgroup `blk` of theirs.  `others`: how
+// many workgroups the launch's other roles have.
+// Two-wave images: four per workgroup, or - when the whole launch then still has
+// no more workgroups than the chip has CUs (a workgroup of these kernels fills a
+// CU's registers, so a surplus one waits for a CU to come free) - two, on the
+// first four waves, so that each wave has a SIMD to itself: the iteration is
+// bound by instruction issue (1.3 -> 0.7 us).  Waves without an image end at
+// once; a wave that has ended no longer counts at the workgroup's barriers.
+__device__ __forceinline__ void sinkhorn_short_block(const SinkhornArgs& A, const int32_t* __restrict__ work, int B,
+                                                     int cus, int others, int blk) {
+  constexpr int NV = kWorkLists;
+  constexpr int kWavesPerBlock = kDualThreads / 64;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int nA = work[kVariantA];
+  const int nP = work[kVariantPair];
+  others += (nA + kWavesPerBlock - 1) / kWavesPerBlock;
+  const int per_block = others + (nP + 1) / 2 <= cus ? 2 : kWavesPerBlock / PairShape::kWaves;
+  int cnt = (nP + per_block - 1) / per_block;
+  if (blk < cnt) {
+    const int slot = wave / PairShape::kWaves, idx = blk * per_block + slot;
+    if (slot >= per_block || idx >= nP) return;
+    sinkhorn_waves_image<PairShape>(A, work[NV + kVariantPair * B + idx], slot, wave % PairShape::kWaves, lane);
+    return;
+  }
+  blk -= cnt;
+  // one-wave images, eight per workgroup: the shortest-running role, handed out last
+  cnt = (nA + kWavesPerBlock - 1) / kWavesPerBlock;
+  if (blk < cnt) {
+    const int idx = blk * kWavesPerBlock + wave;
+    if (idx < nA) sinkhorn_waves_image<WaveShape>(A, work[NV + kVariantA * B + idx], wave, 0, lane);
+  }
+}
+
 // All register-resident Sinkhorn work of a batch in one launch.  Workgroups are
 // handed out longest-running role first: the wide teams, team C, team B, two-copy (48 columns),
 // two-copy (32 columns), two-wave (two or four images per workgroup), one-wave (eight
@@ -461,7 +494,6 @@ __global__ __launch_bounds__(kDualThreads) void k_sinkhorn_regs(SinkhornArgs A,
                                                                const int32_t* __restrict__ status) {
   if (status[0]) return;
   constexpr int NV = kWorkLists;
-  constexpr int kWavesPerBlock = kDualThreads / 64;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int blk = blockIdx.x;
   int cnt = work[kVariantWideC];
@@ -491,38 +523,18 @@ __global__ __launch_bounds__(kDualThreads) void k_sinkhorn_regs(SinkhornArgs A,
   cnt = work[kVariantDual];
   if (blk < cnt) { sinkhorn_dual_image(A, work[NV + kVariantDual * B + blk]); return; }
   blk -= cnt;
-  // Two-wave images: four per workgroup, or - when the whole launch then still has
-  // no more workgroups than the chip has CUs (a workgroup of this kernel fills a
-  // CU's registers, so a surplus one waits for a CU to come free) - two, on the
-  // first four waves, so that each wave has a SIMD to itself: the iteration is
-  // bound by instruction issue (1.3 -> 0.7 us).  Waves without an image end at
-  // once; a wave that has ended no longer counts at the workgroup's barriers.
-  const int nA = work[kVariantA];
-  const int nP = work[kVariantPair];
-  const int others = work[kVariantWideA] + work[kVariantWideB] + work[kVariantWideC] + work[kVariantC] +
-                     work[kVariantB] + work[kVariantDual48] +
-                     (nA + kWavesPerBlock - 1) / kWavesPerBlock + work[kVariantDual];
-  const int per_block = others + (nP + 1) / 2 <= cus ? 2 : kWavesPerBlock / PairShape::kWaves;
-  cnt = (nP + per_block - 1) / per_block;
-  if (blk < cnt) {
-    const int slot = wave / PairShape::kWaves, idx = blk * per_block + slot;
-    if (slot >= per_block || idx >= nP) return;
-    sinkhorn_waves_image<PairShape>(A, work[NV + kVariantPair * B + idx], slot, wave % PairShape::kWaves, lane);
-    return;
-  }
-  blk -= cnt;
-  // one-wave images, eight per workgroup: the shortest-running role, handed out last
-  cnt = (nA + kWavesPerBlock - 1) / kWavesPerBlock;
-  if (blk < cnt) {
-    const int idx = blk * kWavesPerBlock + wave;
-    if (idx < nA) sinkhorn_waves_image<WaveShape>(A, work[NV + kVariantA * B + idx], wave, 0, lane);
-  }
+  sinkhorn_short_block(A, work, B, cus,
+                       work[kVariantWideA] + work[kVariantWideB] + work[kVariantWideC] + work[kVariantC] +
+                           work[kVariantB] + work[kVariantDual48] + work[kVariantDual],
+                       blk);
 }
 
-// The tall shapes (more than 512 rows), one image per workgroup, the longer-running
-// role first: workgroup `blk` of that part of k_sinkhorn_large's launch (sinkhorn_cluster.hpp).
+// The images of one workgroup or less in a batch with tall ones, the longest-running role first:
+// workgroup `blk` of that part of k_sinkhorn_large's launch (sinkhorn_cluster.hpp).  The tall
+// shapes (more than 512 rows), then, when `all` is set, the shorter images, which are then all of
+// k_sinkhorn_regs's two-copy (32 columns), two-wave and one-wave shapes.
 __device__ __forceinline__ void sinkhorn_tall_block(const SinkhornArgs& A, const int32_t* __restrict__ work, int B,
-                                                    int blk) {
+                                                    int cus, int blk, bool all) {
   constexpr int NV = kWorkLists;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int cnt = work[kVariantTeamTall];
@@ -537,7 +549,12 @@ __device__ __forceinline__ void sinkhorn_tall_block(const SinkhornArgs& A, const
   }
   blk -= cnt;
   cnt = work[kVariantTall];
-  if (blk < cnt) sinkhorn_waves_image<TallShape>(A, work[NV + kVariantTall * B + blk], 0, wave, lane);
+  if (blk < cnt) { sinkhorn_waves_image<TallShape>(A, work[NV + kVariantTall * B + blk], 0, wave, lane); return; }
+  if (!all) return;
+  blk -= cnt;
+  cnt = work[kVariantDual];
+  if (blk < cnt) { sinkhorn_dual_image(A, work[NV + kVariantDual * B + blk]); return; }
+  sinkhorn_short_block(A, work, B, cus, work[kVariantTeamTall] + work[kVariantTall] + cnt, blk - cnt);
 }
 
 // Team C's images held as fp32, one at a time per workgroup, two workgroups per
