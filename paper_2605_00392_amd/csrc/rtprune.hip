@@ -20,6 +20,7 @@
 #include "stage2_general.hpp"
 #include "sinkhorn_team.hpp"
 #include "sinkhorn_dual.hpp"
+#include "sinkhorn_quad.hpp"
 #include "sinkhorn_sweep.hpp"
 #include "sinkhorn_cluster.hpp"
 #include "sinkhorn_strip.hpp"
@@ -518,7 +519,7 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
   // batches with large images the sweep kernels take them)
   if ((p.mode & kModeF32) && !(p.mode & kModeLarge) && pruned_bound(in, p, max_pruned_hint) >= 48) {
     ProfScope prof(KID_SINKHORN_C32, s);
-    hipLaunchKernelGGL(k_sinkhorn_c32, dim3(std::min(in->B, 2 * compute_units())), dim3(kDualThreads), 0, s, A, work,
+    hipLaunchKernelGGL(k_sinkhorn_c32, dim3(std::min(in->B, 2 * compute_units())), dim3(kQuadThreads), 0, s, A, work,
                        in->B, st);
   }
   if (p.mode & kModeLarge) {

@@ -68,9 +68,8 @@ struct TeamShape {
 // to the general kernel (variant kGeneralVariant).
 using TeamB = TeamShape<8, 2, 4, 10>;    // M <= 512,  R <= 40
 using TeamC = TeamShape<8, 3, 8, 8>;     // M <= 512,  R <= 64
-// Team C's columns with six rows per lane and the kernel matrix held as fp32
-// (when its range allows): half the registers, so that two workgroups share a
-// compute unit and one's waits are filled by the other (k_sinkhorn_c32).
+// The limits of k_sinkhorn_c32 (sinkhorn_quad.hpp), which holds the kernel matrix as fp32 when its
+// range allows; its four waves hold twice these rows per lane.
 using TeamC32 = TeamShape<8, 3, 6, 8>;   // M <= 384,  R <= 64
 // Tall images (tiled pages with a few pruned tokens): the kernel matrix is held
 // as fp32 values, which the same range condition as for the sweep kernels allows,
