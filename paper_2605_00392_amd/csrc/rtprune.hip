@@ -25,7 +25,7 @@
 #include "sinkhorn_cluster.hpp"
 #include "sinkhorn_strip.hpp"
 #include "scores_mfma.hpp"
-#include "scores_f64.hpp"
+#include "scores_split.hpp"
 #include "scores_tiled.hpp"
 #include "merge_lds.hpp"
 #include "merge_tiled.hpp"
@@ -440,12 +440,22 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
   if constexpr (std::is_same<T, bf16_t>::value) {
     // matrix-core path: its 32-term fp32 partial sums leave an error of about
     // 6e-8 sqrt(32 / D) of the cosine, which the pairing's near-tie band covers from
-    // D = 1024 up; narrower tokens take the fp64 matrix units (k_scores_f64).
+    // D = 1024 up; narrower tokens take the fp64 matrix units (k_scores_split).
     if (in->D % 128 == 0 && in->D >= kMfmaMinWidth) {
       // matrix-core path (an image's workgroups on one XCD: B rounded up to eight)
       const int tiles_s = (in->max_tokens + kScoreRows - 1) / kScoreRows;
       const unsigned blocks = static_cast<unsigned>(tiles_s) * ((in->B + 7) / 8 * 8) + (job.on ? 1u : 0u);
-      hipLaunchKernelGGL(k_scores_mfma, dim3(blocks), dim3(kScoreThreads), 0, s, tok, in->offsets, in->B, in->D, sel,
+      const int tiles_16 = (in->max_tokens + kScoreF64Rows - 1) / kScoreF64Rows;
+      // Up to half a 128-row workgroup per compute unit the length of the contraction's serial chain
+      // decides: 16 rows a workgroup, the chain split over its waves.  Measured, 128-row / split: one
+      // page of 400 tokens with 63 pruned 36 / 15 us, 16 such pages 36 / 24, 64 such 38 / 57; 32 pages
+      // of 256 with 41 pruned 32 / 21; 64 pages of 400 with 7 pruned 36 / 33, 128 such 40 / 52.
+      if (2LL * tiles_s * in->B <= compute_units())
+        hipLaunchKernelGGL((k_scores_split<bf16_t, true>), dim3(tiles_16 * in->B + (job.on ? 1 : 0)),
+                           dim3(kScoreF64Threads), 0, s, tok, in->offsets, in->B, in->D, sel, keep, plan_off, sq, p,
+                           kmat, L.plan_cap, scores_out, tiles_16, 1, job, st);
+      else
+        hipLaunchKernelGGL(k_scores_mfma, dim3(blocks), dim3(kScoreThreads), 0, s, tok, in->offsets, in->B, in->D, sel,
                          keep, plan_off, sq, p, kmat, L.plan_cap, scores_out, tiles_s, job, st);
       RTP_TRY(launched());
       // images with many pruned tokens: the LDS-tiled kernel.  Largest pruned set
@@ -479,7 +489,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
   const int groups = max_pruned_hint >= 0 ? std::min(16, (rmax + kScoreF64Cols - 1) / kScoreF64Cols) : rmax > 512 ? 4 : 1;
   const long long blocks = static_cast<long long>(tiles) * groups * in->B + (job.on ? 1 : 0);
   if (blocks > 0x7fffffffLL) return RTP_EUNSUPPORTED;
-  hipLaunchKernelGGL(k_scores_f64<T>, dim3(static_cast<unsigned>(blocks)), dim3(kScoreF64Threads), 0, s, tok,
+  hipLaunchKernelGGL((k_scores_split<T, false>), dim3(static_cast<unsigned>(blocks)), dim3(kScoreF64Threads), 0, s, tok,
                      in->offsets, in->B, in->D, sel, keep, plan_off, sq, p, kmat, L.plan_cap, scores_out, tiles, groups,
                      job, st);
   return launched();

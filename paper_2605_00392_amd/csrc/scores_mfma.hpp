@@ -37,7 +37,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kMfmaMinWidth = 1024;   // token widths below this take k_scores_f64
+constexpr int kMfmaMinWidth = 1024;   // token widths below this take k_scores_split
 
 constexpr int kScoreThreads = 256;
 constexpr int kScoreRows = 128;                      // kept rows per workgroup

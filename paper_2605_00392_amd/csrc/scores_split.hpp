@@ -1,5 +1,6 @@
-// Scores and kernel matrix (Eq. 3, Appendix C) on the fp64 matrix units: fp32 tokens, and
-// bf16 tokens of widths the bf16 matrix-core kernels do not take.  K_ij = exp((S_ij - shift) / eps).
+// Scores and kernel matrix (Eq. 3, Appendix C) with the contraction split over a workgroup's waves:
+// on the fp64 matrix units for fp32 tokens and for bf16 tokens of widths the bf16 matrix-core
+// kernels do not take, on the bf16 matrix cores for small batches.  K_ij = exp((S_ij - shift) / eps).
 //
 // A token element is exact in fp64 and so is the product of two of them, and the matrix unit
 // accumulates in fp64, so S is as good as the vector unit's.  v_mfma_f64_16x16x4 takes from lane
@@ -61,10 +62,48 @@ __device__ __forceinline__ void scores_f64_tiles(const T* arow, const T* const (
   }
 }
 
+// The same for bf16 tokens on the bf16 matrix cores, steps of 64 elements: the partial products of 32
+// terms that k_scores_mfma forms (the same elements in each, see there), added in fp64.  Operands come
+// straight from memory in the instruction's order.
+template <int NT>
+__device__ __forceinline__ void scores_bf16_tiles(const bf16_t* arow, const bf16_t* const (&brow)[4], int D, int s0, int s1,
+                                                  int lane, doublex4_t (&acc)[4]) {
+  constexpr int kDepth = NT == 4 ? 2 : NT == 2 ? 3 : 5;
+#pragma unroll
+  for (int u = 0; u < NT; ++u) acc[u] = doublex4_t{0.0, 0.0, 0.0, 0.0};
+  for (int s = s0; s < s1; s += kDepth) {
+    bf16x8_t a[kDepth][2], b[kDepth][2][NT];
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 64 * min(s + q, s1 - 1) + 16 * (lane >> 4) + 8 * h;
+        a[q][h] = *reinterpret_cast<const bf16x8_t*>(arow + k);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) b[q][h][u] = *reinterpret_cast<const bf16x8_t*>(brow[u] + k);
+      }
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q) {
+      if (s + q >= s1) break;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+          const floatx4_t zero = {0.f, 0.f, 0.f, 0.f};
+          const floatx4_t c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q][h], b[q][h][u], zero, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[u][v] += static_cast<double>(c[v]);
+        }
+    }
+  }
+}
+
 // Launched over `tiles` row tiles x `groups` groups of column tiles x B workgroups (linear ids),
 // plus one when `job.on` (as in k_scores_mfma).
-template <typename T>
-__global__ __launch_bounds__(kScoreF64Threads) void k_scores_f64(
+// kBf16: on the bf16 matrix cores (bf16 tokens of the widths k_scores_mfma takes, images with up to
+// kTiledMinPruned pruned tokens).
+template <typename T, bool kBf16>
+__global__ __launch_bounds__(kScoreF64Threads) void k_scores_split(
     const T* __restrict__ tokens, const int32_t* __restrict__ offsets, int B, int D, const int32_t* __restrict__ sel_idx,
     const int32_t* __restrict__ keep, const long long* __restrict__ plan_offsets, const double* __restrict__ norm64,
     DevParams p, double* __restrict__ kmat, long long plan_cap, double* __restrict__ scores_out, int tiles, int groups,
@@ -86,13 +125,14 @@ __global__ __launch_bounds__(kScoreF64Threads) void k_scores_f64(
   const int m = min(max(keep[b], 0), n), r = n - m;
   const int i0 = tile * kScoreF64Rows;
   if (r <= 0 || i0 >= m || group * kScoreF64Cols >= r) return;
+  if (kBf16 && r > kTiledMinPruned) return;              // k_scores_tiled
   const long long po = job.on ? plan_slot(offsets, b, job.stride) : plan_offsets[b];
   if (!plan_fits(po, m, r, plan_cap)) return;
   const int k_layout = kernel_layout(p, m, r);
   const int32_t* sel = sel_idx + lo;
   const double inv_eps = 1.0 / p.eps;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int steps = (D + 15) / 16, per_wave = (steps + 3) / 4;
+  const int steps = kBf16 ? D / 64 : (D + 15) / 16, per_wave = (steps + 3) / 4;
   const int s0 = wave * per_wave, s1 = min(steps, s0 + per_wave);
   const T* arow = tokens + static_cast<size_t>(lo + clamp_index(sel[min(i0 + (lane & 15), m - 1)], n)) * D;
   const int ie = tid >> 4, je = tid & 15;                // the entry of a tile this thread finishes
@@ -105,16 +145,23 @@ __global__ __launch_bounds__(kScoreF64Threads) void k_scores_f64(
     for (int u = 0; u < 4; ++u)
       brow[u] = tokens + static_cast<size_t>(lo + clamp_index(sel[m + min(j0 + 16 * u + (lane & 15), r - 1)], n)) * D;
     doublex4_t acc[4];
-    if (ntiles == 1) scores_f64_tiles<T, 1>(arow, brow, D, s0, s1, lane, acc);
-    else if (ntiles == 2) scores_f64_tiles<T, 2>(arow, brow, D, s0, s1, lane, acc);
-    else scores_f64_tiles<T, 4>(arow, brow, D, s0, s1, lane, acc);
-    // accumulator element v of lane l is (kept row l / 16 + 4 v, pruned row l % 16) of its tile
+    if constexpr (kBf16) {
+      if (ntiles == 1) scores_bf16_tiles<1>(arow, brow, D, s0, s1, lane, acc);
+      else if (ntiles == 2) scores_bf16_tiles<2>(arow, brow, D, s0, s1, lane, acc);
+      else scores_bf16_tiles<4>(arow, brow, D, s0, s1, lane, acc);
+    } else {
+      if (ntiles == 1) scores_f64_tiles<T, 1>(arow, brow, D, s0, s1, lane, acc);
+      else if (ntiles == 2) scores_f64_tiles<T, 2>(arow, brow, D, s0, s1, lane, acc);
+      else scores_f64_tiles<T, 4>(arow, brow, D, s0, s1, lane, acc);
+    }
+    // accumulator element v of lane l is pruned row l % 16 and kept row l / 16 + 4 v (the fp64
+    // instruction) or 4 (l / 16) + v (the bf16 one) of its tile
     if (j0 != group * kScoreF64Cols) __syncthreads();    // the previous columns' tiles are still being read
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (u < ntiles) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) part[wave][u][16 * ((lane >> 4) + 4 * v) + (lane & 15)] = acc[u][v];
+        for (int v = 0; v < 4; ++v) part[wave][u][16 * (kBf16 ? 4 * (lane >> 4) + v : (lane >> 4) + 4 * v) + (lane & 15)] = acc[u][v];
       }
     __syncthreads();
     for (int u = 0; u < ntiles; ++u) {
@@ -122,7 +169,9 @@ __global__ __launch_bounds__(kScoreF64Threads) void k_scores_f64(
       if (i < m && j < r) {
         const double dot = (part[0][u][tid] + part[1][u][tid]) + (part[2][u][tid] + part[3][u][tid]);
         const double nj = norm64[lo + clamp_index(sel[m + j], n)];
-        const double s = dot / fmax(ni * nj, kTinyNorm * kTinyNorm);
+        double s;
+        if constexpr (kBf16) s = dot * (1.0 / fmax(ni, kTinyNorm)) * (1.0 / fmax(nj, kTinyNorm));   // (as k_scores_mfma)
+        else s = dot / fmax(ni * nj, kTinyNorm * kTinyNorm);
         store_kernel(kmat, po, i, j, m, r, exp_nonpositive((s - p.shift) * inv_eps), k_layout);
         if (scores_out) scores_out[po + static_cast<long long>(i) * r + j] = s;
       }

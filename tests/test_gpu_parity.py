@@ -523,6 +523,23 @@ def test_matrix_core_tiles_at_their_edges(counts, ratio):
     np.testing.assert_array_equal(f["out"][:rows], s["out"][:rows])
 
 
+@pytest.mark.parametrize("d,ratio", [(1024, 0.85), (1152, 0.55), (1280, 0.7)])
+def test_score_kernels_of_small_and_large_batches(d, ratio):
+    """Up to half a 128-row tile per compute unit the scores come from 16-row workgroups with the
+    contraction split over their waves (width / 64 steps over four waves: even and uneven shares),
+    beyond that from the 128-row ones: both against the oracle, at kept and pruned counts around
+    their 16-row tiles, and the same image alone and in the large batch gives the same rows."""
+    counts = [17, 31, 33, 64, 95, 100, 129, 140]
+    batch = _clustered(counts + [40 + i % 9 for i in range(260)], d, "bf16", 44, ratio=ratio, iters=9)
+    f = hz.run_prune(batch)
+    _log(hz.compare_batch(batch, f, images=range(0, 12)), f"scores of a large batch {d}")
+    small = synth.subset(batch, range(len(counts)))
+    g = hz.run_prune(small)
+    _log(hz.compare_batch(small, g), f"scores of a small batch {d}")
+    rows = int(g["out_offsets"][-1])
+    np.testing.assert_array_equal(f["out"][:rows], g["out"][:rows])
+
+
 @pytest.mark.parametrize("d", [128, 384, 512, 896])
 def test_tiled_scores_at_other_step_counts(d):
     """The tiled score kernel walks the width 64 elements a step, with three staging buffers
