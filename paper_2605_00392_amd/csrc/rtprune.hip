@@ -529,7 +529,7 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
   // batches with large images the sweep kernels take them)
   if ((p.mode & kModeF32) && !(p.mode & kModeLarge) && pruned_bound(in, p, max_pruned_hint) >= 48) {
     ProfScope prof(KID_SINKHORN_C32, s);
-    hipLaunchKernelGGL(k_sinkhorn_c32, dim3(std::min(in->B, 2 * compute_units())), dim3(kQuadThreads), 0, s, A, work,
+    hipLaunchKernelGGL(k_sinkhorn_c32, dim3(std::min(in->B, 2 * compute_units())), dim3(QuadPage::kThreads), 0, s, A, work,
                        in->B, st);
   }
   if (p.mode & kModeLarge) {

@@ -20,6 +20,7 @@
 // Two workgroup barriers per iteration, no lane shuffles.
 #pragma once
 #include "common.hpp"
+#include "sinkhorn_quad.hpp"
 #include "sinkhorn_team.hpp"
 #include "sinkhorn_wave.hpp"
 
@@ -542,8 +543,9 @@ __device__ __forceinline__ void sinkhorn_tall_block(const SinkhornArgs& A, const
     const int img = work[NV + kVariantTeamTall * B + blk];
     const int n_img = A.offsets[img + 1] - A.offsets[img];
     const int r_img = n_img - min(max(A.keep[img], 0), max(n_img, 0));
-    if (r_img <= TeamTall32::kMaxR) sinkhorn_team_image<TeamTall32, float>(A, img, wave, lane);
-    else if (r_img <= TeamTall48::kMaxR) sinkhorn_team_image<TeamTall48, float>(A, img, wave, lane);
+    __shared__ __align__(16) QuadLds<8> lds;
+    if (r_img <= QuadTall32::kMaxR) sinkhorn_quad_image<QuadTall32>(A, img, lds);
+    else if (r_img <= QuadTall48::kMaxR) sinkhorn_quad_image<QuadTall48>(A, img, lds);
     else sinkhorn_team_image<TeamTall, float>(A, img, wave, lane);
     return;
   }

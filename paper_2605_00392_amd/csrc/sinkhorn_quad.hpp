@@ -1,7 +1,7 @@
 // Sinkhorn (Appendix C) for images with up to 64 pruned tokens and 384 kept rows beyond the
 // smaller shapes (48 to 64 pruned in practice: the paper's own average retention leaves 63 of 400),
 // the kernel matrix held as fp32: a workgroup of four waves per image, two workgroups per compute
-// unit.
+// unit (QuadPage, described here; the other shapes differ in the numbers).
 //
 // A wave is laid out as eight column slots (lane bits 5, 4, 3) x eight row slots (bits 0 to 2); lane
 // (cs, rs) holds 12 rows (8 w + rs, then every 32) x 8 columns (cs, then every 8).  Rows go four at a
@@ -16,20 +16,31 @@
 // the 590 instructions per wave and iteration).  Eight waves of six rows per lane, every row with a
 // reduction and a reciprocal of its own, issued 3560 instructions per image and iteration against
 // 2360 here.  1024 pages of 400 tokens, 337 kept, 100 iterations: 0.668 -> 0.527 ms;
-// one such page alone: 0.196 -> 0.156 ms.
+// one such page alone: 0.196 -> 0.156 ms.  With eight waves the same body takes the tall images with
+// 16 to 48 pruned tokens: 128 ragged tiled pages, 50 iterations, k_sinkhorn_large 0.186 -> 0.157 ms.
 #pragma once
 #include "common.hpp"
 #include "sinkhorn_team.hpp"
 
 namespace rtp {
 
-constexpr int kQuadThreads = 256;
+// W waves, RPT rows x CPT columns per lane: M <= 8 W RPT, R <= 8 CPT.
+template <int W_, int RPT_, int CPT_>
+struct QuadShape {
+  static constexpr int W = W_, RPT = RPT_, CPT = CPT_, kThreads = 64 * W, kMaxM = 8 * W * RPT, kMaxR = 8 * CPT;
+  static_assert(RPT % 4 == 0 && CPT <= 8, "rows go four at a time; a lane per column");
+};
+using QuadPage = QuadShape<4, 12, 8>;      // M <= 384,  R <= 64: k_sinkhorn_c32
+static_assert(QuadPage::kMaxM == TeamC32::kMaxM && QuadPage::kMaxR == TeamC32::kMaxR, "the limits sinkhorn_variant assumes");
+using QuadTall48 = QuadShape<8, 20, 6>;    // M <= 1280, R <= 48: tall images of k_sinkhorn_large
+using QuadTall32 = QuadShape<8, 20, 4>;    // M <= 1280, R <= 32
+template <int W>
 struct QuadLds {
   static constexpr int kPitch = 72;        // doubles per row slot: the eight row slots' entries of a column fall into different banks
-  double part[4][8][kPitch];               // a wave's column sums by row slot (keys for the pairing at the end)
-  double wave_sum[2][4][64];               // the waves' totals, by iteration parity
-  double x_sum[2][4];
-  double y[4][64];                         // every wave's copy
+  double part[W][8][kPitch];               // a wave's column sums by row slot (keys for the pairing at the end)
+  double wave_sum[2][W][64];               // the waves' totals, by iteration parity
+  double x_sum[2][W];
+  double y[W][64];                         // every wave's copy
 };
 
 // {a of the lanes with the bit clear, a of the lanes with it set} in every lane, for lane bit 5 / 4.
@@ -60,8 +71,9 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b, QuadLds& L) {
-  constexpr int RPT = TeamC32::RPT * 2, CPT = 8, kBatches = RPT / 4;
+template <typename S>
+__device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b, QuadLds<S::W>& L) {
+  constexpr int W = S::W, RPT = S::RPT, CPT = S::CPT, kBatches = RPT / 4, kStep = 8 * W;   // kStep: rows between a lane's
   const DevParams& p = A.p;
   const int tt = threadIdx.x, tw = __builtin_amdgcn_readfirstlane(tt >> 6), lane = tt & 63;
   const int cs = lane >> 3, rs = lane & 7;
@@ -69,10 +81,10 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
   const int n = A.offsets[b + 1] - lo;
   if (n <= 0) return;
   const int m = min(max(A.keep[b], 0), n), r = n - m;
-  if (!TeamC32::fits(m, r)) return;                          // uniform over the workgroup
+  if (m > S::kMaxM || r > S::kMaxR) return;                  // uniform over the workgroup
   int32_t* __restrict__ pair_out = A.pair_out;
   if (pair_out)
-    for (int i = tt; i < m; i += kQuadThreads) pair_out[lo + i] = i;
+    for (int i = tt; i < m; i += S::kThreads) pair_out[lo + i] = i;
   if (r <= 0 || m <= 0) return;
   const long long po = A.plan_offsets[b];
   if (!plan_fits(po, m, r, A.plan_cap)) return;
@@ -83,7 +95,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
   float K[RPT][CPT];
 #pragma unroll
   for (int a = 0; a < RPT; ++a) {
-    const float* row = Kg + min(row0 + 32 * a, m - 1) * pitch;
+    const float* row = Kg + min(row0 + kStep * a, m - 1) * pitch;
 #pragma unroll
     for (int c = 0; c < CPT; ++c) K[a][c] = row[min(cs + 8 * c, r - 1)];
   }
@@ -91,7 +103,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
   for (int a = 0; a < RPT; ++a)
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-      K[a][c] = (row0 + 32 * a < m && cs + 8 * c < r) ? K[a][c] : 0.f;
+      K[a][c] = (row0 + kStep * a < m && cs + 8 * c < r) ? K[a][c] : 0.f;
       forget_origin(K[a][c]);
     }
 
@@ -113,7 +125,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
     for (int c = 0; c < CPT; ++c) t[c] = 0.0;
 #pragma unroll
     for (int q = 0; q < kBatches; ++q) {
-      if (128 * q >= m) continue;                            // no row of this batch exists (the same for every thread)
+      if (4 * kStep * q >= m) continue;                          // no row of this batch exists (the same for every thread)
       double kd[4][CPT], s[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -126,7 +138,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
         }
       }
       const double sum = add_xor_lane<8>(halve16(halve32(s[0], s[2]), halve32(s[1], s[3])));
-      const double xv = row0 + 32 * (4 * q + u_own) < m ? rcp64(sum + row_dust) : 0.0;
+      const double xv = row0 + kStep * (4 * q + u_own) < m ? rcp64(sum + row_dust) : 0.0;
       x_own[q] = xv;
       xs += xv;
       double x[4];
@@ -153,8 +165,12 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
     {
       const double (*w)[64] = L.wave_sum[it & 1];
       const double* xw = L.x_sum[it & 1];
-      const double col = (w[0][lane] + w[1][lane]) + (w[2][lane] + w[3][lane]);
-      const double sum_x = (xw[0] + xw[1]) + (xw[2] + xw[3]);
+      double col = (w[0][lane] + w[1][lane]) + (w[2][lane] + w[3][lane]);
+      double sum_x = (xw[0] + xw[1]) + (xw[2] + xw[3]);
+      if constexpr (W == 8) {
+        col += (w[4][lane] + w[5][lane]) + (w[6][lane] + w[7][lane]);
+        sum_x += (xw[4] + xw[5]) + (xw[6] + xw[7]);
+      }
       y_mine = lane < r ? rcp64(col + kz * x_dust) : 0.0;
       L.y[tw][lane] = y_mine;
       y_dust = static_cast<double>(m) * rcp64(kz * (sum_x + x_dust));
@@ -172,7 +188,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
 #pragma unroll
   for (int c = 0; c < CPT; ++c) { bv[c] = -1.f; bi[c] = 0x7fffffff; }
   float* rows = reinterpret_cast<float*>(&L.part[tw][0][0]);  // the wave's eight rows of the plan, turned to whole rows
-  constexpr int kRowPitch = 2 * QuadLds::kPitch;
+  constexpr int kRowPitch = 2 * QuadLds<W>::kPitch;
   int row0_p = row0;
   forget_origin(row0_p);
 #pragma unroll
@@ -181,7 +197,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
     spread_rows(x_own[q], x);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = row0_p + 32 * (4 * q + u);
+      const int i = row0_p + kStep * (4 * q + u);
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         const float v = static_cast<float>(x[u] * static_cast<double>(K[4 * q + u][c]) * y[c]);
@@ -192,7 +208,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
       if (P && lane < r) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          const int ik = 8 * tw + k + 32 * (4 * q + u);
+          const int ik = 8 * tw + k + kStep * (4 * q + u);
           if (ik < m) P[ik * r + lane] = rows[k * kRowPitch + lane];
         }
       }
@@ -202,7 +218,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
   if (!pair_out) return;
   // a column's best as a key (value bits, then the lower row): plan entries are >= 0, so their bit
   // patterns order like their values; "no row" (-1) is below all
-  long long (*keys)[QuadLds::kPitch] = reinterpret_cast<long long (*)[QuadLds::kPitch]>(L.part[tw]);
+  long long (*keys)[QuadLds<W>::kPitch] = reinterpret_cast<long long (*)[QuadLds<W>::kPitch]>(L.part[tw]);
 #pragma unroll
   for (int c = 0; c < CPT; ++c)
     keys[rs][cs + 8 * c] = (static_cast<long long>(__float_as_int(bv[c])) << 32) | static_cast<unsigned>(0x7fffffff - bi[c]);
@@ -216,7 +232,7 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
   __syncthreads();
   if (tw == 0 && lane < r) {
 #pragma unroll
-    for (int w = 1; w < 4; ++w) best = of_wave[64 * w + lane] > best ? of_wave[64 * w + lane] : best;
+    for (int w = 1; w < W; ++w) best = of_wave[64 * w + lane] > best ? of_wave[64 * w + lane] : best;
     const float dust = static_cast<float>(x_dust * kz * y_mine);
     pair_out[lo + m + lane] = dust > __int_as_float(static_cast<int>(best >> 32)) ? -1 : 0x7fffffff - static_cast<int>(best);
   }
@@ -224,14 +240,14 @@ __device__ __forceinline__ void sinkhorn_quad_image(const SinkhornArgs& A, int b
 
 // The images of list kVariantC32, one at a time per workgroup, two workgroups per compute unit (at most 256
 // registers per lane), which take the list in turns.
-__global__ __launch_bounds__(kQuadThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_c32(
+__global__ __launch_bounds__(QuadPage::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_c32(
     SinkhornArgs A, const int32_t* __restrict__ work, int B, const int32_t* __restrict__ status) {
   if (status[0]) return;
-  __shared__ __align__(16) QuadLds L;
+  __shared__ __align__(16) QuadLds<QuadPage::W> L;
   const int cnt = work[kVariantC32];
   for (int blk = blockIdx.x; blk < cnt; blk += gridDim.x) {
     if (blk != static_cast<int>(blockIdx.x)) __syncthreads();   // the previous image's LDS is still being read
-    sinkhorn_quad_image(A, work[kWorkLists + kVariantC32 * B + blk], L);
+    sinkhorn_quad_image<QuadPage>(A, work[kWorkLists + kVariantC32 * B + blk], L);
   }
 }
 
