@@ -23,16 +23,25 @@ constexpr int kMergeWaveRows = 4;    // kept rows a wave merges at a time
 constexpr int kMergeLdsBytes = 30 * 1024;
 constexpr int kMergeMaxChunk = 64;   // pruned rows per LDS chunk, at most one per lane
 
-// EXACT: D == 256 KMAX, every lane owns exactly KMAX groups (no bounds tests).
-template <typename T, int KMAX, bool EXACT>
+// EXACT: the width is 256 KMAX, every lane owns exactly KMAX groups (no bounds tests).
+// SLICED (with EXACT): the workgroup does 256 KMAX features of its rows, from 256 KMAX blockIdx.z on,
+// with all pruned rows staged at once: in small batches, where a workgroup of whole rows walks a
+// page's pruned rows twelve at a time with most of the chip idle.  The sums' order is the same.
+template <typename T, int KMAX, bool EXACT, bool SLICED = false>
 __global__ __launch_bounds__(256) void k_merge_lds(
     const T* __restrict__ tokens, const int32_t* __restrict__ offsets, int D,
     const int32_t* __restrict__ sel_idx, const int32_t* __restrict__ keep,
     const int32_t* __restrict__ out_offsets, const float* __restrict__ plan,
     const long long* __restrict__ plan_offsets, float alpha, int max_tokens, MergeSkip skip, T* __restrict__ out,
     const int32_t* __restrict__ status) {
+  static_assert(EXACT || !SLICED, "slices have no remainder");
   typedef typename Raw4<T>::type raw_t;
   constexpr int NB = kMergeWaveRows;
+  const int width = SLICED ? 256 * KMAX : D;       // features of a row that are this workgroup's
+  if constexpr (SLICED) {
+    tokens += static_cast<size_t>(width) * blockIdx.z;
+    out += static_cast<size_t>(width) * blockIdx.z;
+  }
   constexpr int kPassRows = 4 * NB;                // rows the workgroup finishes per pass
   if (status && status[0]) return;
   __shared__ __attribute__((aligned(16))) unsigned char lds_raw[kMergeLdsBytes];
@@ -45,11 +54,11 @@ __global__ __launch_bounds__(256) void k_merge_lds(
   const int i0 = blockIdx.x * kMergeBlockRows;
   if (i0 >= m || merge_elsewhere(skip, r)) return;   // larger pruned sets: the matrix-core kernels
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int ngroups = D >> 2;
+  const int ngroups = width >> 2;
   const int32_t* sel = sel_idx + lo;
   const float* P = (r > 0) ? plan + plan_offsets[b] : nullptr;
   const size_t obase = static_cast<size_t>(out_offsets[b]);
-  const int chunk = min(min(kMergeMaxChunk, kMergeLdsBytes / static_cast<int>(D * sizeof(T))), max(r, 1));
+  const int chunk = min(min(kMergeMaxChunk, kMergeLdsBytes / static_cast<int>(width * sizeof(T))), max(r, 1));
   const int nchunks = (r + chunk - 1) / chunk;
 
   for (int pass = 0; pass < kMergeBlockRows / kPassRows; ++pass) {
@@ -82,30 +91,28 @@ __global__ __launch_bounds__(256) void k_merge_lds(
         pl[u] = (lane < jn && ia + u < m) ? P[static_cast<long long>(ia + u) * r + j0 + lane] : 0.f;
       if (nchunks > 1 || pass == 0) {
         if (nchunks > 1) __syncthreads();          // the previous chunk is still being read
-        // each wave stages whole pruned rows, two at a time: one load for the token
+        // each wave stages whole pruned rows, kAtOnce at a time: one load for the token
         // indices, then the rows' loads back to back, then the LDS writes
+        constexpr int kAtOnce = KMAX == 1 ? 8 : 2;
         const int p_tok = clamp_index(sel[m + j0 + min(lane, jn - 1)], n);
-        for (int j = 2 * wave; j < jn; j += 8) {
-          const int ja = j, jb = min(j + 1, jn - 1);
-          const T* ra = tokens + static_cast<size_t>(lo + __builtin_amdgcn_readlane(p_tok, ja)) * D;
-          const T* rb = tokens + static_cast<size_t>(lo + __builtin_amdgcn_readlane(p_tok, jb)) * D;
-          raw_t va_[KMAX], vb_[KMAX];
+        for (int j = kAtOnce * wave; j < jn; j += 4 * kAtOnce) {
+          raw_t v[kAtOnce][KMAX];
 #pragma unroll
-          for (int k = 0; k < KMAX; ++k) {
-            const int g = lane + kWave * k;
-            if (EXACT || g < ngroups) {
-              va_[k] = *reinterpret_cast<const raw_t*>(ra + 4 * g);
-              vb_[k] = *reinterpret_cast<const raw_t*>(rb + 4 * g);
+          for (int q = 0; q < kAtOnce; ++q) {
+            const T* row = tokens + static_cast<size_t>(lo + __builtin_amdgcn_readlane(p_tok, min(j + q, jn - 1))) * D;
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+              const int g = lane + kWave * k;
+              if (EXACT || g < ngroups) v[q][k] = *reinterpret_cast<const raw_t*>(row + 4 * g);
             }
           }
 #pragma unroll
-          for (int k = 0; k < KMAX; ++k) {
-            const int g = lane + kWave * k;
-            if (EXACT || g < ngroups) {
-              *reinterpret_cast<raw_t*>(lds + ja * D + 4 * g) = va_[k];
-              *reinterpret_cast<raw_t*>(lds + jb * D + 4 * g) = vb_[k];
+          for (int q = 0; q < kAtOnce; ++q)
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+              const int g = lane + kWave * k;
+              if (EXACT || g < ngroups) *reinterpret_cast<raw_t*>(lds + min(j + q, jn - 1) * width + 4 * g) = v[q][k];
             }
-          }
         }
         __syncthreads();
       }
@@ -119,7 +126,7 @@ __global__ __launch_bounds__(256) void k_merge_lds(
           const int g = lane + kWave * k;
           if (EXACT || g < ngroups) {
             float xj[4];
-            unpack4(*reinterpret_cast<const raw_t*>(lds + j * D + 4 * g), xj);
+            unpack4(*reinterpret_cast<const raw_t*>(lds + j * width + 4 * g), xj);
 #pragma unroll
             for (int u = 0; u < NB; ++u)
 #pragma unroll

@@ -635,7 +635,14 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
   ProfScope prof(KID_MERGE, s);
   if (in->D <= 1280) {
     const dim3 g2((in->max_tokens + kMergeBlockRows - 1) / kMergeBlockRows, in->B);
-    if (in->D == 1280)
+    // Up to three 16-row workgroups on two compute units, a workgroup per 256 features of them.
+    // Measured, whole rows / slices: one page of 400 tokens with 63 pruned 28 / 14 us, 4 such pages
+    // 28 / 18, 16 such 42 / 36, 48 such 83 / 87; 32 pages of 256 with 41 pruned 31 / 34.
+    if (in->D % 256 == 0 && 2LL * g2.x * in->B <= 3LL * compute_units())
+      hipLaunchKernelGGL((k_merge_lds<T, 1, true, true>), dim3(g2.x, g2.y, in->D / 256), block, 0, s, tok, in->offsets,
+                         in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens, skip, static_cast<T*>(out),
+                         status);
+    else if (in->D == 1280)
       hipLaunchKernelGGL((k_merge_lds<T, 5, true>), g2, block, 0, s, tok, in->offsets, in->D, sel, keep,
                          out_off, plan, plan_off, alpha, in->max_tokens, skip, static_cast<T*>(out), status);
     else
