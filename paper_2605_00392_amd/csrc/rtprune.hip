@@ -375,7 +375,10 @@ void set_sinkhorn_mode(DevParams& p, const Layout& L, const rtprune_batch* in) {
         strip_eighths = 8;
         strip_top = thin;
       }
-      if (strip_top > 256 || strip_slots(strip_top) == 0) strip = kStripNone;
+      // (A slot waits until all its workgroups are resident.  Of several such calls on streams of
+      // their own each can hold compute units with one slot that is not complete yet; a quarter of
+      // the chip at most per slot lets four of them, one per hardware queue, always go on.)
+      if (strip_top > compute_units() / 4 || strip_slots(strip_top) == 0) strip = kStripNone;
       strips = strip ? (strip << kModeStripShift) | (strip_top << kModeStripGroupsShift) | (strip_eighths << kModeStripRowsShift) : 0;
       top_fits = !p.dynamic && m_top > 0 && strip && strip_fits(m_top, r_top, strips);
     }
