@@ -456,7 +456,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
       if (2LL * tiles_s * in->B <= compute_units())
         hipLaunchKernelGGL((k_scores_split<bf16_t, true>), dim3(tiles_16 * in->B + (job.on ? 1 : 0)),
                            dim3(kScoreF64Threads), 0, s, tok, in->offsets, in->B, in->D, sel, keep, plan_off, sq, p,
-                           kmat, L.plan_cap, scores_out, tiles_16, 1, job, st);
+                           kmat, L.plan_cap, scores_out, tiles_16, 1, 0, job, st);
       else
         hipLaunchKernelGGL(k_scores_mfma, dim3(blocks), dim3(kScoreThreads), 0, s, tok, in->offsets, in->B, in->D, sel,
                          keep, plan_off, sq, p, kmat, L.plan_cap, scores_out, tiles_s, job, st);
@@ -490,12 +490,18 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
   const int tiles = (in->max_tokens + kScoreF64Rows - 1) / kScoreF64Rows;
   const int rmax = std::max(1, pruned_bound(in, p, max_pruned_hint));
   const int groups = max_pruned_hint >= 0 ? std::min(16, (rmax + kScoreF64Cols - 1) / kScoreF64Cols) : rmax > 512 ? 4 : 1;
-  const long long blocks = static_cast<long long>(tiles) * groups * in->B + (job.on ? 1 : 0);
-  if (blocks > 0x7fffffffLL) return RTP_EUNSUPPORTED;
-  hipLaunchKernelGGL((k_scores_split<T, false>), dim3(static_cast<unsigned>(blocks)), dim3(kScoreF64Threads), 0, s, tok,
-                     in->offsets, in->B, in->D, sel, keep, plan_off, sq, p, kmat, L.plan_cap, scores_out, tiles, groups,
-                     job, st);
-  return launched();
+  // a launch has fewer than 2^32 threads: as many images to one as that leaves room for
+  // (tiles * groups <= 512 * 16, so it is hundreds at least)
+  constexpr long long kLaunchBlocks = (1LL << 32) / kScoreF64Threads - 1;
+  const int per_image = tiles * groups, per_launch = static_cast<int>((kLaunchBlocks - 1) / std::max(per_image, 1));
+  for (int b0 = 0; b0 < in->B; b0 += per_launch) {
+    const ScanJob here = b0 == 0 ? job : ScanJob{0, nullptr, job.plan_offsets, nullptr, nullptr, 0, job.stride};
+    const unsigned blocks = static_cast<unsigned>(per_image) * std::min(per_launch, in->B - b0) + (here.on ? 1u : 0u);
+    hipLaunchKernelGGL((k_scores_split<T, false>), dim3(blocks), dim3(kScoreF64Threads), 0, s, tok, in->offsets, in->B,
+                       in->D, sel, keep, plan_off, sq, p, kmat, L.plan_cap, scores_out, tiles, groups, b0, here, st);
+    RTP_TRY(launched());
+  }
+  return RTP_OK;
 }
 
 int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel, const int32_t* keep,

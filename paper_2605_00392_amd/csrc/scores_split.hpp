@@ -98,8 +98,8 @@ __device__ __forceinline__ void scores_bf16_tiles(const bf16_t* arow, const bf16
   }
 }
 
-// Launched over `tiles` row tiles x `groups` groups of column tiles x B workgroups (linear ids),
-// plus one when `job.on` (as in k_scores_mfma).
+// Launched over `tiles` row tiles x `groups` groups of column tiles x the images from `first` on
+// (linear ids), plus one workgroup when `job.on` (as in k_scores_mfma).
 // kBf16: on the bf16 matrix cores (bf16 tokens of the widths k_scores_mfma takes, images with up to
 // kTiledMinPruned pruned tokens).
 template <typename T, bool kBf16>
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kScoreF64Threads) void k_scores_split(
     const T* __restrict__ tokens, const int32_t* __restrict__ offsets, int B, int D, const int32_t* __restrict__ sel_idx,
     const int32_t* __restrict__ keep, const long long* __restrict__ plan_offsets, const double* __restrict__ norm64,
     DevParams p, double* __restrict__ kmat, long long plan_cap, double* __restrict__ scores_out, int tiles, int groups,
-    ScanJob job, const int32_t* __restrict__ status) {
+    int first, ScanJob job, const int32_t* __restrict__ status) {
   if (status[0]) return;
   __shared__ __align__(16) double part[4][4][256];       // [wave][tile][16 x 16]
   if (job.on && blockIdx.x == gridDim.x - 1) {
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kScoreF64Threads) void k_scores_split(
     return;
   }
   const int tile = blockIdx.x % tiles, rest = blockIdx.x / tiles;
-  const int group = rest % groups, b = rest / groups;
+  const int group = rest % groups, b = first + rest / groups;
   const int lo = offsets[b];
   const int n = offsets[b + 1] - lo;
   const int m = min(max(keep[b], 0), n), r = n - m;

@@ -254,6 +254,20 @@ def test_tall_register_shapes_at_their_edges():
     assert rep.max_score_abs <= hz.SCORE_ATOL
 
 
+def test_scores_of_more_workgroups_than_one_launch_takes():
+    """fp32 tokens, 16 384 images of which one is long: 18.5 million workgroups of the score pass,
+    where a launch takes fewer than 2^24 of 256 threads.  Images on both sides of where the second
+    launch begins."""
+    counts = [3] * 16383 + [4512]
+    batch = _clustered(counts, 8, "f32", 61, dynamic=1, ratio_min=0.6, iters=3)
+    f = hz.run_prune(batch)
+    assert f["rc"] == 0 and f["status"] == 0
+    assert (np.diff(batch.offsets) - f["keep"])[:-1].max() > 0
+    first = ((1 << 24) - 2) // (282 * 4)                         # images of the first launch
+    rep = hz.compare_batch(batch, f, images=[0, 1, 2, 5000] + list(range(first - 40, first + 40)) + [16382, 16383])
+    _log(rep, "two launches of the score pass")
+
+
 @pytest.mark.parametrize("override", [dict(), dict(iters=0), dict(iters=1), dict(iters=7), dict(eps=0.02),
                                       dict(eps=1.0, z=1.0, alpha=0.4)])
 def test_multi_workgroup_resident_sinkhorn_at_its_edges(override):
