@@ -337,6 +337,24 @@ int rtprune_text_density(const uint8_t* pixels, const int64_t* pixel_offsets,
                          const int32_t* patch_offsets, void* workspace,
                          size_t workspace_bytes, void* stream);
 
+/* Which Sinkhorn kernel takes images of kept[i] + pruned[i] tokens in a call on `B` images of at
+ * most `max_tokens` tokens under `params` (host arrays of n entries; no device is touched).
+ * own_counts: 0 for the fused calls, whose kept counts follow from `params`, 1 for rtprune_ot_pair,
+ * whose caller may give any.  route[i] is one of the values below, plus RTP_ROUTE_F32 when the
+ * kernel matrix is held as fp32 (fp64 otherwise; sums and scalings are fp64 everywhere). */
+enum {
+  RTP_ROUTE_NONE = 0,          /* nothing to do (no kept or no pruned token) */
+  RTP_ROUTE_ONE_WORKGROUP = 1, /* on chip, in one workgroup or part of one */
+  RTP_ROUTE_CLUSTER = 2,       /* on chip, in several workgroups of one XCD */
+  RTP_ROUTE_STRIPS = 3,        /* on chip, in strips over several workgroups */
+  RTP_ROUTE_STREAMED = 4,      /* streamed from memory every iteration, by the whole chip */
+  RTP_ROUTE_GENERAL = 5,       /* streamed by one workgroup: right and slow */
+  RTP_ROUTE_UNSERVED = 6,      /* by no kernel: such an image cannot occur in such a call */
+  RTP_ROUTE_F32 = 16
+};
+int rtprune_sinkhorn_routes(int32_t B, int32_t max_tokens, const rtprune_params* params, int32_t own_counts,
+                            int32_t n, const int32_t* kept, const int32_t* pruned, int32_t* route);
+
 /* Measurement aid (not part of the operator).  The switches are process-wide:
  * they may be flipped from any thread, and they apply to every call that starts
  * after the flip, on whichever thread; a program that prunes from several

@@ -38,6 +38,7 @@ using namespace rtp;
 namespace {
 
 constexpr size_t kAlign = 256;
+constexpr int kLargeTokens = 512;          // with more, an image can have more kept tokens than any 512-row register shape holds
 constexpr int kNormMinWorkgroups = 1024;   // the norm pass keeps at least this many workgroups when it merges chunks
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -83,8 +84,7 @@ Layout make_layout(int B, long long total, int max_tokens, int D, int rmax) {
   L.work = take(sizeof(int32_t) * (kWorkLists * (1 + static_cast<size_t>(B)) + kWorkSyncWords));
   L.kmat = take(sizeof(double) * L.plan_cap);
   L.plan = take(sizeof(float) * L.plan_cap);
-  // more than 512 tokens: an image can have more kept tokens than any register shape holds
-  L.sweep = max_tokens > 512 ? 1 : 0;
+  L.sweep = max_tokens > kLargeTokens ? 1 : 0;
   L.strip_cap = L.plan_cap / kSweepRows + total + 1;
   if (L.sweep) {
     L.sw_x = take(sizeof(double) * total);
@@ -316,7 +316,7 @@ int strip_slots(int groups) {
 
 // The strip kernel's words, when the call's mode has it: behind the cluster kernel's buffers.
 int32_t* strip_words(const Layout& L, void* ws, int mode) {
-  if (!mode_strip_shape(mode)) return nullptr;
+  if (!mode_strips(mode)) return nullptr;
   return reinterpret_cast<int32_t*>(at<double>(ws, L.cluster_part) + kClusterPartDoubles);
 }
 
@@ -345,7 +345,8 @@ int cluster_spin_limit() {
 // Which Sinkhorn kernels a call on this batch launches, and whether the sweep
 // kernels' matrices are stored in fp32 (only batches that may hold images beyond
 // the 512-row register shapes have any).
-void set_sinkhorn_mode(DevParams& p, const Layout& L, const rtprune_batch* in) {
+void set_sinkhorn_mode(DevParams& p, int B, int max_tokens) {
+  const bool large = max_tokens > kLargeTokens;
   const int f32 = p.k32 ? kModeF32 : 0;   // exp's range fits fp32: registers may hold the matrix as fp32
   // The multi-workgroup kernels that keep a matrix on chip run one workgroup per compute unit.
   // Under a fixed retention the largest image the batch can hold bounds the others' kept and
@@ -353,37 +354,37 @@ void set_sinkhorn_mode(DevParams& p, const Layout& L, const rtprune_batch* in) {
   // does (more slots then share the chip), and no image is beyond the on-chip kernels.  Under a
   // dynamic one the clamp bounds the pruned sets: slots of eight workgroups of 144 x 576, or
   // sixteen of 80 x 960 when the clamp allows more.
-  const int m_top = p.dynamic ? 0 : kept_count(p.ratio, in->max_tokens), r_top = in->max_tokens - m_top;
-  const int r_most = p.dynamic ? params_pruned_bound(p, in->max_tokens) : r_top;
-  int groups = kClusterDefaultGroups, strip = kStripNone, strip_top = 0, strip_eighths = 0, strips = 0;
-  bool top_fits = false;
-  if (L.sweep && f32) {
-    if (!p.dynamic && cluster_shape(m_top, r_top) >= 0) {
-      // (of 224-row workgroups a smaller image may need more than a longest one of 448-row ones)
-      groups = cluster_shape(m_top, r_top) == 0 ? std::max(cluster_groups(m_top, r_top), 1) : kClusterMaxGroups;
-      top_fits = m_top > 0;
-    } else {
-      strip = p.dynamic && r_most > StripA::kCols ? kShapeStripB : strip_for(r_most);
-      if (p.dynamic && r_most <= kClusterCols) strip = kStripNone;
-      strip_eighths = strip_rows(strip) / 8;
-      strip_top = p.dynamic ? (strip == kShapeStripB ? 16 : 8) : (m_top + strip_rows(strip) - 1) / strip_rows(strip);
-      // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
-      // iteration) instead of 144 while every image still has its workgroups at once.  One image,
-      // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
-      const int thin = (m_top + 63) / 64;
-      if (!p.dynamic && strip == kShapeStripA && in->B <= strip_slots(thin) && thin <= kStripDirect) {
-        strip_eighths = 8;
-        strip_top = thin;
-      }
-      // (A slot waits until all its workgroups are resident.  Of several such calls on streams of
-      // their own each can hold compute units with one slot that is not complete yet; a quarter of
-      // the chip at most per slot lets four of them, one per hardware queue, always go on.)
-      if (strip_top > compute_units() / 4 || strip_slots(strip_top) == 0) strip = kStripNone;
-      strips = strip ? (strip << kModeStripShift) | (strip_top << kModeStripGroupsShift) | (strip_eighths << kModeStripRowsShift) : 0;
-      top_fits = !p.dynamic && m_top > 0 && strip && strip_fits(m_top, r_top, strips);
+  const int m_top = p.dynamic ? 0 : kept_count(p.ratio, max_tokens), r_top = max_tokens - m_top;
+  const int r_most = p.dynamic ? params_pruned_bound(p, max_tokens) : r_top;
+  const bool top_clustered = !p.dynamic && m_top > 0 && cluster_shape(m_top, r_top) >= 0;
+  const int top_groups = top_clustered ? cluster_groups(m_top, r_top) : p.dynamic || m_top <= 0 ? 0 : wide_groups(m_top, r_top);
+  // workgroups that images held as fp32 may take, and whether all of them are (see held_f32)
+  const int wide = top_groups > 0 ? top_groups : kClusterDefaultGroups;
+  const bool beyond_wide = p.dynamic ? max_tokens - 1 > kClusterRows : top_groups == 0;
+  const int slot = std::min(wide, kClusterMaxGroups);
+  const int cluster = (large && f32 && cluster_slots_per_xcd(slot) > 0) ? (kModeCluster | (slot << kModeGroupsShift)) : 0;
+  const int held = (large && f32) ? (wide << kModeWideShift) | (beyond_wide || !cluster ? kModeHeldF32 : 0) : 0;
+  int strips = 0;
+  bool top_fits = top_clustered;
+  if (large && f32 && !top_clustered && (!p.dynamic || r_most > kClusterCols)) {
+    int strip = p.dynamic && r_most > StripA::kCols ? kShapeStripB : strip_for(r_most);
+    int most = p.dynamic ? (strip == kShapeStripB ? 16 : 8) : (m_top + strip_rows(strip, 0) - 1) / strip_rows(strip, 0);
+    // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
+    // iteration) instead of 144 while every image still has its workgroups at once.  One image,
+    // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
+    const int thin_groups = (m_top + kStripThinRows - 1) / kStripThinRows;
+    const bool thin = !p.dynamic && strip == kShapeStripA && B <= strip_slots(thin_groups) && thin_groups <= kStripDirect;
+    if (thin) most = thin_groups;
+    // (A slot waits until all its workgroups are resident.  Of several such calls on streams of
+    // their own each can hold compute units with one slot that is not complete yet; a quarter of
+    // the chip at most per slot lets four of them, one per hardware queue, always go on.)
+    if (!strip || most > std::min(kStripMaxGroups, compute_units() / 4) || strip_slots(most) == 0) {
+      strip = kShapeStripB;                // the longest image is the streaming kernels': shorter ones need not be
+      most = 16;
     }
+    strips = mode_strip_bit(strip) | (thin ? kModeStripThin : 0) | (most << kModeStripGroupsShift);
+    top_fits = !p.dynamic && m_top > 0 && strip_fits(m_top, r_top, strips | held);
   }
-  const int cluster = (L.sweep && f32 && cluster_slots_per_xcd(groups) > 0) ? (kModeCluster | (groups << kModeGroupsShift)) : 0;
   // The streaming kernels cost two launches per iteration whether or not an image needs them,
   // and only the device knows the sizes, so they are issued when the batch's shape and the
   // parameters say that images beyond the on-chip kernels are to be expected: a fixed
@@ -393,10 +394,10 @@ void set_sinkhorn_mode(DevParams& p, const Layout& L, const rtprune_batch* in) {
   // up beyond the on-chip kernels takes the one-workgroup general kernel, which is right and
   // slow.  Only the batch's shape and the parameters enter, so that the staged calls choose
   // the same kernels as the fused ones.
-  const bool beyond = p.dynamic ? in->max_tokens - 1 > kClusterRows : !top_fits;
-  const int sweep = (L.sweep && (!cluster || beyond)) ? kModeSweep : 0;
+  const bool beyond = p.dynamic ? max_tokens - 1 > kClusterRows : !top_fits;
+  const int sweep = (large && (!cluster || beyond)) ? kModeSweep : 0;
   p.k32 = p.k32 && sweep;                 // the sweep kernels' copy in memory is fp32
-  p.mode = (L.sweep ? kModeLarge : 0) | f32 | cluster | strips | sweep;
+  p.mode = (large ? kModeLarge : 0) | f32 | cluster | held | strips | sweep;
 }
 
 // `work` non-null: the same launch also builds the Sinkhorn work lists.
@@ -422,11 +423,11 @@ unsigned tiled_list_blocks(int tiles, int B) {
 // call's dynamic ratio, whose clamp bounds them; kPrunedUnknown: the kept counts
 // are the user's.
 constexpr int kPrunedFromClamp = -1, kPrunedUnknown = -2;
-int pruned_bound(const rtprune_batch* in, const DevParams& p, int hint) {
-  int rmax = in->max_tokens - 1;
+int pruned_bound(int max_tokens, const DevParams& p, int hint) {
+  int rmax = max_tokens - 1;
   if (hint >= 0) rmax = std::min(rmax, hint);
   else if (hint == kPrunedFromClamp && p.dynamic)
-    rmax = std::min(rmax, static_cast<int>((1.0 - static_cast<double>(p.ratio_min)) * in->max_tokens) + 1);
+    rmax = std::min(rmax, static_cast<int>((1.0 - static_cast<double>(p.ratio_min)) * max_tokens) + 1);
   return rmax;
 }
 
@@ -463,7 +464,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
       RTP_TRY(launched());
       // images with many pruned tokens: the LDS-tiled kernel.  Largest pruned set
       // the call can produce: the caller's bound, else what the retention clamp allows
-      const int rmax = pruned_bound(in, p, max_pruned_hint);
+      const int rmax = pruned_bound(in->max_tokens, p, max_pruned_hint);
       if (rmax > kTiledMinPruned) {
         // kept rows an image can have: what the fixed retention leaves of the longest one when
         // this call selected under it (then it also passed a bound), else all of its tokens
@@ -488,7 +489,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
   // the fp64 matrix units.  A workgroup walks an image's pruned rows 64 at a time; large pruned sets
   // are dealt to several (up to 16: every image of the batch gets that many, needed or not)
   const int tiles = (in->max_tokens + kScoreF64Rows - 1) / kScoreF64Rows;
-  const int rmax = std::max(1, pruned_bound(in, p, max_pruned_hint));
+  const int rmax = std::max(1, pruned_bound(in->max_tokens, p, max_pruned_hint));
   const int groups = max_pruned_hint >= 0 ? std::min(16, (rmax + kScoreF64Cols - 1) / kScoreF64Cols) : rmax > 512 ? 4 : 1;
   // a launch has fewer than 2^32 threads: as many images to one as that leaves room for
   // (tiles * groups <= 512 * 16, so it is hundreds at least)
@@ -504,13 +505,36 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
   return RTP_OK;
 }
 
+// Which of the Sinkhorn kernels that not every call needs a call launches (`rmax`: pruned_bound).
+// In a batch with tall images and cluster slots the short shapes' images go into
+// k_sinkhorn_large's launch instead of k_sinkhorn_regs's, when the call can have none of the latter's
+// other shapes (more than 31 pruned tokens and at most 512 rows): up to 128 pruned tokens those are
+// the tall team's and the clusters', beyond that the strips' or the streaming kernels'.
+bool regs_folded(const DevParams& p, int rmax, bool own_counts) {
+  return (p.mode & kModeCluster) && !own_counts && (rmax <= kClusterCols || mode_strips(p.mode) || (p.mode & kModeSweep));
+}
+// (its images have 48 to 64 pruned tokens: smaller sets go to the shapes above, and in
+// batches with large images the sweep kernels take them)
+bool launches_c32(const DevParams& p, int rmax) { return (p.mode & kModeF32) && !(p.mode & kModeLarge) && rmax >= 48; }
+// The general kernel takes what no shape above does.  With the fp32-held shapes
+// in use and at most 512 tokens per image those cover every image with up to 224
+// pruned tokens (64 / 128 / 192 / 224 pruned against 512 / 448 / 384 / 320 kept),
+// so a call that cannot produce a larger pruned set has nothing left for it.
+bool launches_general(const DevParams& p, int rmax) {
+  return !(p.mode & kModeF32) || (p.mode & kModeLarge) || rmax > TeamWideC::kMaxR;
+}
+// Largest pruned set under a fixed retention: R <= N - ceil(ratio N - 1e-3) <= (1 - ratio) N + 1.
+int fixed_pruned_bound(const DevParams& p, int max_tokens) {
+  return static_cast<int>((1.0 - static_cast<double>(p.ratio)) * max_tokens) + 1;
+}
+
 int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel, const int32_t* keep,
               const long long* plan_off, const Layout& L, void* ws, double* scores_out, float* plan,
               int32_t* pair, int max_pruned_hint, bool classified, hipStream_t s,
               const ScanJob& job = ScanJob{0, nullptr, nullptr, nullptr, nullptr, 0, 0}) {
   if (in->B == 0 || in->total_tokens == 0) return RTP_OK;
   DevParams p = p_in;
-  set_sinkhorn_mode(p, L, in);
+  set_sinkhorn_mode(p, in->B, in->max_tokens);
   const double* kmat = at<double>(ws, L.kmat);
   const int32_t* st = at<int32_t>(ws, L.status);
   int32_t* work = at<int32_t>(ws, L.work);
@@ -524,19 +548,13 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
               ? launch_scores_t<bf16_t>(in, p, sel, keep, plan_off, L, ws, scores_out, max_pruned_hint, work, job, s)
               : launch_scores_t<float>(in, p, sel, keep, plan_off, L, ws, scores_out, max_pruned_hint, work, job, s));
   SinkhornArgs A{in->offsets, keep, plan_off, p, kmat, L.plan_cap, plan, pair};
-  // In a batch with tall images and cluster slots the short shapes' images go into
-  // k_sinkhorn_large's launch, when the call can have none of the other shapes of k_sinkhorn_regs
-  // (more than 31 pruned tokens and at most 512 rows): up to 128 pruned tokens those are the tall
-  // team's and the clusters', beyond that the strips' or the streaming kernels'.
-  const bool folded = (p.mode & kModeCluster) && max_pruned_hint != kPrunedUnknown &&
-                      (pruned_bound(in, p, max_pruned_hint) <= kClusterCols || mode_strip_shape(p.mode) || (p.mode & kModeSweep));
+  const int rmost = pruned_bound(in->max_tokens, p, max_pruned_hint);
+  const bool folded = regs_folded(p, rmost, max_pruned_hint == kPrunedUnknown);
   if (!folded) {
     ProfScope prof(KID_SINKHORN_REGS, s);
     hipLaunchKernelGGL(k_sinkhorn_regs, dim3(in->B), dim3(kDualThreads), 0, s, A, work, in->B, compute_units(), st);
   }
-  // (its images have 48 to 64 pruned tokens: smaller sets go to the shapes above, and in
-  // batches with large images the sweep kernels take them)
-  if ((p.mode & kModeF32) && !(p.mode & kModeLarge) && pruned_bound(in, p, max_pruned_hint) >= 48) {
+  if (launches_c32(p, rmost)) {
     ProfScope prof(KID_SINKHORN_C32, s);
     hipLaunchKernelGGL(k_sinkhorn_c32, dim3(std::min(in->B, 2 * compute_units())), dim3(QuadPage::kThreads), 0, s, A, work,
                        in->B, st);
@@ -554,26 +572,20 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
     hipLaunchKernelGGL(k_sinkhorn_large, dim3(cluster_blocks + in->B), dim3(kClusterThreads), 0, s, CA, cluster_blocks,
                        compute_units(), folded ? 1 : 0);
   }
-  if (const int shape = mode_strip_shape(p.mode)) {
+  if (mode_strips(p.mode)) {
     // (again one workgroup per compute unit of the slots in use: all resident together)
     const int groups = mode_strip_groups(p.mode), slots = std::min(strip_slots(groups), (in->B + 7) / 8 * 8);
     const StripArgs TA{A, strip_words(L, ws, p.mode), slots, groups, cluster_spin_limit(), at<int32_t>(ws, L.status)};
     const dim3 grid(slots * groups), block(kStripThreads);
     ProfScope prof(KID_SINKHORN_STRIPS, s);
-    if (shape == kShapeStripA) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
-    else if (shape == kShapeStripB) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
-    else if (shape == kShapeStripC) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
+    if (p.mode & mode_strip_bit(kShapeStripA)) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
+    else if (p.mode & mode_strip_bit(kShapeStripB)) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
+    else if (p.mode & mode_strip_bit(kShapeStripC)) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
     else hipLaunchKernelGGL(k_sinkhorn_strips<StripD>, grid, block, 0, s, TA);
   }
   RTP_TRY(launched());
-  // The general kernel takes what no shape above does.  With the fp32-held shapes
-  // in use and at most 512 tokens per image those cover every image with up to 224
-  // pruned tokens (64 / 128 / 192 / 224 pruned against 512 / 448 / 384 / 320 kept),
-  // so a call that cannot produce a larger pruned set has nothing left for it.
-  const bool all_in_registers = (p.mode & kModeF32) && !(p.mode & kModeLarge) &&
-                                pruned_bound(in, p, max_pruned_hint) <= TeamWideC::kMaxR;
   ProfScope prof(KID_SINKHORN, s);   // (with the sweep launches below)
-  if (!all_in_registers) {
+  if (launches_general(p, rmost)) {
     hipLaunchKernelGGL(k_sinkhorn, dim3(in->B), dim3(1024), 0, s, in->offsets, keep, plan_off, p, kmat,
                        L.plan_cap, plan, pair, 1, p.mode, st);
     RTP_TRY(launched());
@@ -590,7 +602,7 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
     const dim3 grows(strips, in->B), gcols(cols, in->B);
     hipLaunchKernelGGL(k_sweep_init, gcols, dim3(kSweepColThreads), 0, s, SA, st);
     // columns per thread: enough for the largest pruned set the batch can hold
-    const int rmax = std::min(pruned_bound(in, p, max_pruned_hint), kSweepMaxR);
+    const int rmax = std::min(rmost, kSweepMaxR);
     const int ch = (std::max(rmax, 1) + kSweepThreads - 1) / kSweepThreads;
     auto rows = [&](auto final_tag, int parity) {
       constexpr bool kFinal = decltype(final_tag)::value;
@@ -632,7 +644,7 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
   const float alpha = static_cast<float>(p.alpha);
   // images with many pruned tokens go to the matrix-core kernel (bf16, width a
   // multiple of 128) when the call can produce any
-  const int rmax = pruned_bound(in, p, max_pruned_hint);
+  const int rmax = pruned_bound(in->max_tokens, p, max_pruned_hint);
   const bool tiled = std::is_same<T, bf16_t>::value && in->D % 128 == 0 && rmax > kTiledMinPruned;
   // and those with a middling number to the one that streams the kept rows, when the
   // call has the work lists (a workspace)
@@ -815,6 +827,35 @@ extern "C" int rtprune_profile_summary(char* buf, size_t cap) {
   out += "]";
   if (out.size() + 1 > cap) return RTP_EINVAL;
   std::memcpy(buf, out.c_str(), out.size() + 1);
+  return RTP_OK;
+}
+
+extern "C" int rtprune_sinkhorn_routes(int32_t B, int32_t max_tokens, const rtprune_params* params,
+                                       int32_t own_counts, int32_t n, const int32_t* kept, const int32_t* pruned,
+                                       int32_t* route) {
+  DevParams p;
+  RTP_TRY(check_params(params, &p));
+  if (B < 0 || max_tokens < 0 || n < 0 || (n > 0 && (!kept || !pruned || !route))) return RTP_EINVAL;
+  if (B > kMaxImages || max_tokens > kMaxTokens) return RTP_EUNSUPPORTED;
+  set_sinkhorn_mode(p, B, max_tokens);
+  const int rmax = pruned_bound(max_tokens, p, own_counts ? kPrunedUnknown
+                                               : p.dynamic ? kPrunedFromClamp : fixed_pruned_bound(p, max_tokens));
+  for (int32_t i = 0; i < n; ++i) {
+    const int m = kept[i], r = pruned[i];
+    if (m < 0 || r < 0 || m + r > max_tokens) return RTP_EINVAL;
+    if (m == 0 || r == 0) { route[i] = RTP_ROUTE_NONE; continue; }
+    const int v = sinkhorn_variant(m, r, p.mode);
+    const bool short_shape = v == kVariantA || v == kVariantPair || v == kVariantDual;
+    const bool tall = v == kVariantTall || v == kVariantTeamTall;
+    int to = RTP_ROUTE_ONE_WORKGROUP;
+    if (v == kVariantCluster) to = RTP_ROUTE_CLUSTER;
+    else if (v == kVariantStrip) to = RTP_ROUTE_STRIPS;
+    else if (v == kVariantSweep) to = RTP_ROUTE_STREAMED;
+    else if (v == kGeneralVariant) to = launches_general(p, rmax) ? RTP_ROUTE_GENERAL : RTP_ROUTE_UNSERVED;
+    else if (v == kVariantC32) to = launches_c32(p, rmax) ? RTP_ROUTE_ONE_WORKGROUP : RTP_ROUTE_UNSERVED;
+    else if (!tall && !short_shape && regs_folded(p, rmax, own_counts != 0)) to = RTP_ROUTE_UNSERVED;
+    route[i] = to | (kernel_is_f32(p, m, r) ? RTP_ROUTE_F32 : 0);
+  }
   return RTP_OK;
 }
 
@@ -1036,12 +1077,10 @@ extern "C" int rtprune_prune(const rtprune_batch* in, const float* density,
   long long* plan_off = at<long long>(workspace, L.plan_off);
   float* plan = at<float>(workspace, L.plan);
   DevParams pm = p;
-  set_sinkhorn_mode(pm, L, in);
+  set_sinkhorn_mode(pm, in->B, in->max_tokens);
   ScanJob job{0, nullptr, nullptr, nullptr, nullptr, 0, 0};
   RTP_TRY(launch_stage1(in, p, pm.mode, density, ratio, keep, sel, out_offsets, plan_off, L, workspace, s, &job));
-  // fixed retention: R <= N - ceil(ratio N - 1e-3) <= (1 - ratio) N + 1 for every image
-  const int max_pruned = p.dynamic ? kPrunedFromClamp
-                                   : static_cast<int>((1.0 - static_cast<double>(p.ratio)) * in->max_tokens) + 1;
+  const int max_pruned = p.dynamic ? kPrunedFromClamp : fixed_pruned_bound(p, in->max_tokens);
   RTP_TRY(launch_ot(in, p, sel, keep, plan_off, L, workspace, nullptr, plan, pair, max_pruned, true, s, job));
   return launch_merge(in, p, sel, keep, out_offsets, plan, plan_off, out, max_pruned, status,
                       at<int32_t>(workspace, L.work), s);
@@ -1129,13 +1168,12 @@ extern "C" int rtprune_prune_splice(const rtprune_batch* in, const float* densit
   // (the text offsets are checked after the norm pass has written the status word and
   // before the first kernel that writes to the caller's arrays)
   DevParams pm = p;
-  set_sinkhorn_mode(pm, L, in);
+  set_sinkhorn_mode(pm, in->B, in->max_tokens);
   ScanJob job{0, nullptr, nullptr, nullptr, nullptr, 0, 0};
   RTP_TRY(launch_stage1(in, p, pm.mode, density, ratio, keep, sel, nullptr, plan_off, L, workspace, s, &job, &t));
   hipLaunchKernelGGL(k_splice_scan, dim3(1), dim3(256), 0, s, t, keep, in->B, seq_offsets, visual_start, status);
   RTP_TRY(launched());
-  const int max_pruned = p.dynamic ? kPrunedFromClamp
-                                   : static_cast<int>((1.0 - static_cast<double>(p.ratio)) * in->max_tokens) + 1;
+  const int max_pruned = p.dynamic ? kPrunedFromClamp : fixed_pruned_bound(p, in->max_tokens);
   RTP_TRY(launch_ot(in, p, sel, keep, plan_off, L, workspace, nullptr, plan, pair, max_pruned, true, s, job));
   // the merge writes image b's kept rows at visual_start[b], between its text spans
   RTP_TRY(launch_merge(in, p, sel, keep, visual_start, plan, plan_off, seq, max_pruned, status,

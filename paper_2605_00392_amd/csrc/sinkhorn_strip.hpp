@@ -118,22 +118,23 @@ __device__ __forceinline__ bool strip_meet(const StripArgs& C, int32_t* counter,
 // Where image `b`'s workgroups exchange their values: the upper end of its kernel-matrix slot
 // (strip_exchange_fits).  The sums' buffers first, then those of y (shares only), then the
 // pairing keys, groups x r of them.
-__device__ __forceinline__ double* strip_area(const SinkhornArgs& A, long long po, int m, int r, int groups) {
-  const long long at = po + static_cast<long long>(m) * r - strip_exchange_doubles(r, groups, A.p.mode);
+__device__ __forceinline__ double* strip_area(const SinkhornArgs& A, int shape, long long po, int m, int r, int groups) {
+  const long long at = po + static_cast<long long>(m) * r - strip_exchange_doubles(shape, r, groups);
   return const_cast<double*>(A.kmat) + (at - at % kStripAlign);
 }
 
 // "Not yet" into workgroup `rank`'s part of image `b`'s exchange area, when it is a strip image.
+template <typename S>
 __device__ __forceinline__ void strip_clear(const StripArgs& C, int b, int rank) {
   const SinkhornArgs& A = C.S;
   const int n = A.offsets[b + 1] - A.offsets[b];
   const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
   if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) return;
   if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) return;
-  const int groups = strip_groups(m, A.p.mode);
+  const int groups = strip_groups(S::kShape, m, A.p.mode);
   if (groups <= 1 || rank >= groups) return;
-  double* area = strip_area(A, A.plan_offsets[b], m, r, groups);
-  const int total = static_cast<int>(strip_exchange_doubles(r, groups, A.p.mode) - static_cast<long long>(groups) * r);
+  double* area = strip_area(A, S::kShape, A.plan_offsets[b], m, r, groups);
+  const int total = static_cast<int>(strip_exchange_doubles(S::kShape, r, groups) - static_cast<long long>(groups) * r);
   const int each = (total + groups - 1) / groups;
   const int e1 = min(total, (rank + 1) * each);
   for (int e = rank * each + threadIdx.x; e < e1; e += kStripThreads) ex_not_yet(area + e);
@@ -203,11 +204,11 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   const int rows_per = (m + groups - 1) / groups;            // the rows dealt evenly
   const int row_base = rank * rows_per;
   const int m_loc = min(m - row_base, rows_per);             // >= 1: groups = ceil(m / rows per strip)
-  constexpr bool kMayDirect = kCols <= StripB::kCols;        // (strip_direct: the wider shapes never are)
-  const bool direct = kMayDirect && strip_direct(groups, p.mode);
+  constexpr bool kMayDirect = strip_direct(S::kShape, 1);    // (the wider shapes never are)
+  const bool direct = kMayDirect && strip_direct(S::kShape, groups);
   const int cw = strip_share(r, groups);                     // columns (the sum of x counted as column r) a workgroup owns
   const int own0 = rank * cw, own = max(0, min(cw, r + 1 - own0));
-  double* area = groups > 1 ? strip_area(A, po, m, r, groups) : nullptr;
+  double* area = groups > 1 ? strip_area(A, S::kShape, po, m, r, groups) : nullptr;
   const int sums_buf = direct ? groups * (r + 1) : groups * groups * cw;   // doubles of one buffer of sums
   double* ybufs = area + kStripBufs * sums_buf;
   long long* keys = reinterpret_cast<long long*>(direct ? ybufs : ybufs + kStripBufs * groups * cw);
@@ -561,8 +562,8 @@ __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) 
     // (every workgroup of the slot takes the same decisions: they read the same words)
     if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
     if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
-    const int groups = strip_groups(m, A.p.mode);   // (at most per_slot: strip_fits has seen to it)
-    strip_clear(C, b, rank);
+    const int groups = strip_groups(S::kShape, m, A.p.mode);   // (at most per_slot: strip_fits has seen to it)
+    strip_clear<S>(C, b, rank);
     arrived += per_slot;
     if (!strip_meet(C, counter, arrived, true, flag)) return;
     arrived += groups;

@@ -83,14 +83,15 @@ using TeamWideB = TeamShape<8, 5, 24, 6>;   // M <= 384, R <= 192
 using TeamWideC = TeamShape<8, 5, 20, 7>;   // M <= 320, R <= 224
 // A workgroup's strip of a larger image in k_sinkhorn_strips (sinkhorn_strip.hpp), when it has
 // more than 128 pruned tokens: eight waves of RPT rows each, the 64 lanes across the columns.
-template <int RPT_, int CPT_>
+enum { kStripNone = 0, kShapeStripA = 1, kShapeStripB = 2, kShapeStripC = 3, kShapeStripD = 4 };
+template <int SHAPE, int RPT_, int CPT_>
 struct StripShape {
-  static constexpr int RPT = RPT_, CPT = CPT_, kRows = 8 * RPT, kCols = 64 * CPT;
+  static constexpr int kShape = SHAPE, RPT = RPT_, CPT = CPT_, kRows = 8 * RPT, kCols = 64 * CPT;
 };
-using StripA = StripShape<18, 9>;    // 144 rows x 576 columns per workgroup
-using StripB = StripShape<10, 15>;   // 80 rows x 960 columns
-using StripC = StripShape<8, 22>;    // 64 rows x 1408 columns
-using StripD = StripShape<6, 28>;    // 48 rows x 1792 columns
+using StripA = StripShape<kShapeStripA, 18, 9>;    // 144 rows x 576 columns per workgroup
+using StripB = StripShape<kShapeStripB, 10, 15>;   // 80 rows x 960 columns
+using StripC = StripShape<kShapeStripC, 8, 22>;    // 64 rows x 1408 columns
+using StripD = StripShape<kShapeStripD, 6, 28>;    // 48 rows x 1792 columns
 // The one- and two-wave kernels (sinkhorn_wave.hpp): kRows augmented rows per
 // lane, kCols augmented columns.
 struct WaveShape {
@@ -161,25 +162,31 @@ __host__ __device__ inline int cluster_groups(int m, int r) {
 __host__ __device__ inline bool cluster_fits(int m, int r, int mode) {
   return cluster_shape(m, r) >= 0 && cluster_groups(m, r) <= mode_cluster_groups(mode);
 }
-// The strip kernel: one strip shape for all of a call's images (bits 12-14 of `mode`; none: the
-// kernel is not launched), as many strips as an image's rows take, up to the slot's workgroups
-// (bits 16-24).
-constexpr int kModeStripShift = 12, kModeStripGroupsShift = 16;
-__host__ __device__ inline int mode_strip_groups(int mode) { return (mode >> kModeStripGroupsShift) & 511; }
-enum { kStripNone = 0, kShapeStripA = 1, kShapeStripB = 2, kShapeStripC = 3, kShapeStripD = 4 };
-__host__ __device__ inline int mode_strip_shape(int mode) { return (mode >> kModeStripShift) & 7; }
+// The strip kernel.  Bits 12-15 of `mode`: the strip shapes it is launched for (an image takes the
+// narrowest of them that holds its columns); bit 16: shape A with 64 rows a workgroup instead of 144;
+// bits 17-23: how many workgroups an image may take.
+constexpr int kModeStripShift = 12, kModeStripThin = 1 << 16, kModeStripGroupsShift = 17, kStripMaxGroups = 64;
+__host__ __device__ inline int mode_strip_bit(int shape) { return shape ? 1 << (kModeStripShift + shape - 1) : 0; }
+__host__ __device__ inline int mode_strips(int mode) { return (mode >> kModeStripShift) & 15; }
+__host__ __device__ inline int mode_strip_groups(int mode) { return (mode >> kModeStripGroupsShift) & 127; }
 __host__ __device__ inline int strip_cols(int shape) {
   return shape == kShapeStripA ? StripA::kCols : shape == kShapeStripB ? StripB::kCols
        : shape == kShapeStripC ? StripC::kCols : shape == kShapeStripD ? StripD::kCols : 0;
 }
-__host__ __device__ inline int strip_rows(int shape) {
-  return shape == kShapeStripA ? StripA::kRows : shape == kShapeStripB ? StripB::kRows
-       : shape == kShapeStripC ? StripC::kRows : StripD::kRows;
+constexpr int kStripThinRows = 64;
+__host__ __device__ inline int strip_rows(int shape, int mode) {
+  return shape == kShapeStripA ? ((mode & kModeStripThin) ? kStripThinRows : StripA::kRows)
+       : shape == kShapeStripB ? StripB::kRows : shape == kShapeStripC ? StripC::kRows : StripD::kRows;
 }
-// the narrowest that holds `r` columns (kStripNone: none)
+// the narrowest that holds `r` columns (kStripNone: none); of all, and of those a call launches
 __host__ __device__ inline int strip_for(int r) {
   return r <= StripA::kCols ? kShapeStripA : r <= StripB::kCols ? kShapeStripB : r <= StripC::kCols ? kShapeStripC
        : r <= StripD::kCols ? kShapeStripD : kStripNone;
+}
+__host__ __device__ inline int strip_shape(int r, int mode) {
+  for (int shape = strip_for(r); shape && shape <= kShapeStripD; ++shape)
+    if (mode & mode_strip_bit(shape)) return shape;
+  return kStripNone;
 }
 // A strip image's workgroups exchange their sums in the image's own slot of the kernel matrix,
 // whose m r doubles hold fp32 entries: the upper end is free.  A few workgroups read all the
@@ -189,30 +196,42 @@ __host__ __device__ inline int strip_for(int r) {
 constexpr int kStripDirect = 16, kStripBufs = 4;
 // (Measured: 64 pages of 1083 tokens, 4 workgroups each, 0.60 ms direct, 0.81 in shares; 32 pages of
 // 2137 tokens, 16 each, 1.46 and 1.64; the wider shapes' registers leave no room for the direct reading.)
-__host__ __device__ inline bool strip_direct(int groups, int mode) {
-  return mode_strip_shape(mode) <= kShapeStripB && groups <= kStripDirect;
-}
+__host__ __device__ constexpr bool strip_direct(int shape, int groups) { return shape <= kShapeStripB && groups <= kStripDirect; }
 __host__ __device__ inline int strip_share(int r, int groups) { return (r + groups) / groups; }   // ceil((r + 1) / groups)
-__host__ __device__ inline long long strip_exchange_doubles(int r, int groups, int mode) {
+__host__ __device__ inline long long strip_exchange_doubles(int shape, int r, int groups) {
   if (groups <= 1) return 0;
   const long long keys = static_cast<long long>(groups) * r;
-  if (strip_direct(groups, mode)) return static_cast<long long>(kStripBufs) * groups * (r + 1) + keys;
+  if (strip_direct(shape, groups)) return static_cast<long long>(kStripBufs) * groups * (r + 1) + keys;
   return static_cast<long long>(kStripBufs) * (groups + 1) * strip_share(r, groups) * groups + keys;
 }
 constexpr int kStripAlign = 16;   // doubles
-__host__ __device__ inline bool strip_exchange_fits(int m, int r, int groups, int mode) {
+__host__ __device__ inline bool strip_exchange_fits(int shape, int m, int r, int groups) {
   const long long entries = 2 + static_cast<long long>(m) * ((r + 3) & ~3) / 2;   // (one double of alignment, see k32_base)
-  return entries + strip_exchange_doubles(r, groups, mode) + 2 * kStripAlign <= static_cast<long long>(m) * r;
+  return entries + strip_exchange_doubles(shape, r, groups) + 2 * kStripAlign <= static_cast<long long>(m) * r;
 }
-// Rows of a workgroup in this launch (bits 25-29 of `mode`: eighths): the shape's, or fewer when
-// that leaves most of the chip idle.
-constexpr int kModeStripRowsShift = 25;
-__host__ __device__ inline int mode_strip_rows(int mode) { return ((mode >> kModeStripRowsShift) & 31) * 8; }
-__host__ __device__ inline int strip_groups(int m, int mode) { return (m + mode_strip_rows(mode) - 1) / mode_strip_rows(mode); }
+__host__ __device__ inline int strip_groups(int shape, int m, int mode) {
+  return (m + strip_rows(shape, mode) - 1) / strip_rows(shape, mode);
+}
+// Whose matrices may be held as fp32 there (the rounding takes the plan's relative error against 64
+// bits from 2.6e-8 to 3.4e-8 for fp32 tokens and from 1.386e-7 to 1.405e-7 for bf16 ones, 1260 x 240):
+// every image's when the call's streaming kernels hold them so in any case (kModeHeldF32), else those
+// of up to 1152 x 576 and 1280 x 960 that take no more than this many workgroups of 144 or 80 rows
+// (bits 24-28).  Others stay with the general kernel, which holds 64 bits.
+constexpr int kModeWideShift = 24, kModeHeldF32 = 1 << 29;
+constexpr int kWideMaxRows = 1152, kWidestMaxRows = 1280;
+__host__ __device__ inline int mode_wide_groups(int mode) { return (mode >> kModeWideShift) & 31; }
+__host__ __device__ inline int wide_groups(int m, int r) {   // (0: beyond both)
+  return m <= kWideMaxRows && r <= StripA::kCols ? (m + StripA::kRows - 1) / StripA::kRows
+       : m <= kWidestMaxRows && r <= StripB::kCols ? (m + StripB::kRows - 1) / StripB::kRows : 0;
+}
+__host__ __device__ inline bool held_f32(int m, int r, int mode) {
+  return (mode & kModeHeldF32) || (wide_groups(m, r) > 0 && wide_groups(m, r) <= mode_wide_groups(mode));
+}
 __host__ __device__ inline bool strip_fits(int m, int r, int mode) {
-  if (m <= 0 || r > strip_cols(mode_strip_shape(mode))) return false;
-  const int groups = strip_groups(m, mode);
-  return groups <= mode_strip_groups(mode) && (groups == 1 || strip_exchange_fits(m, r, groups, mode));
+  const int shape = strip_shape(r, mode);
+  if (m <= 0 || !shape || !held_f32(m, r, mode)) return false;
+  const int groups = strip_groups(shape, m, mode);
+  return groups <= mode_strip_groups(mode) && (groups == 1 || strip_exchange_fits(shape, m, r, groups));
 }
 // The multi-workgroup sweep kernels (sinkhorn_sweep.hpp) take up to this many
 // pruned tokens.
@@ -229,7 +248,7 @@ __host__ __device__ inline int sinkhorn_variant(int m, int r, int mode) {
   // rows or columns beyond the shapes above: several workgroups that keep the matrix on chip
   if ((mode & kModeLarge) && (mode & kModeF32) && (mode & kModeCluster) && cluster_fits(m, r, mode))
     return kVariantCluster;
-  if ((mode & kModeLarge) && (mode & kModeF32) && mode_strip_shape(mode) && strip_fits(m, r, mode))
+  if ((mode & kModeLarge) && (mode & kModeF32) && mode_strips(mode) && strip_fits(m, r, mode))
     return kVariantStrip;
   // when the sweep kernels run anyway (their launches are paid for) they also
   // take the images of the slowest register shapes, which otherwise set the
@@ -262,7 +281,7 @@ __host__ __device__ inline int sinkhorn_variant(int m, int r, int mode) {
 //                   a load read 64 consecutive entries (row-major, they read 64 cache
 //                   lines: the loads alone took 15 to 25 us of a workgroup's time).
 constexpr int kKernelRowsF64 = 0, kKernelRowsF32 = 1, kKernelColsF64 = 2;
-__device__ __forceinline__ int kernel_layout(const DevParams& p, int m, int r) {
+__host__ __device__ __forceinline__ int kernel_layout(const DevParams& p, int m, int r) {
   const int v = sinkhorn_variant(m, r, p.mode);
   if (v == kVariantSweep) return p.k32 ? kKernelRowsF32 : kKernelRowsF64;
   // (these are only chosen under kModeF32)
@@ -271,7 +290,7 @@ __device__ __forceinline__ int kernel_layout(const DevParams& p, int m, int r) {
     return kKernelRowsF32;
   return (v == kVariantA || v == kVariantPair || v == kVariantTall) ? kKernelColsF64 : kKernelRowsF64;
 }
-__device__ __forceinline__ bool kernel_is_f32(const DevParams& p, int m, int r) {
+__host__ __device__ __forceinline__ bool kernel_is_f32(const DevParams& p, int m, int r) {
   return kernel_layout(p, m, r) == kKernelRowsF32;
 }
 // fp32 layout of image b's kernel matrix: rows padded to a multiple of four

@@ -20,6 +20,9 @@ RTP_OK, RTP_EINVAL, RTP_EUNSUPPORTED, RTP_EWORKSPACE, RTP_EHIP = range(5)
 RTP_F32, RTP_BF16 = 0, 1
 RTP_METRIC_L2NORM, RTP_METRIC_VARIANCE = 0, 1
 RTP_POSITIONS_CONSECUTIVE, RTP_POSITIONS_ORIGINAL = 0, 1
+(RTP_ROUTE_NONE, RTP_ROUTE_ONE_WORKGROUP, RTP_ROUTE_CLUSTER, RTP_ROUTE_STRIPS, RTP_ROUTE_STREAMED, RTP_ROUTE_GENERAL,
+ RTP_ROUTE_UNSERVED) = range(7)
+RTP_ROUTE_F32 = 16
 RTP_DEV_BAD_OFFSETS, RTP_DEV_IMAGE_TOO_LONG, RTP_DEV_BAD_IMAGE, RTP_DEV_SYNC_TIMEOUT = 1, 2, 4, 8
 
 EXPORTS = (
@@ -27,6 +30,7 @@ EXPORTS = (
     "rtprune_norms_topk", "rtprune_ot_pair", "rtprune_merge", "rtprune_prune", "rtprune_prune_splice",
     "rtprune_profile_enable", "rtprune_profile_summary", "rtprune_profile_only", "rtprune_copy_bytes",
     "rtprune_text_density_workspace_bytes", "rtprune_text_density", "rtprune_prune_static",
+    "rtprune_sinkhorn_routes",
 )
 RTPRUNE_STATIC_SCRATCH_BYTES = 64 << 20
 
@@ -106,6 +110,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.rtprune_text_density.restype = ctypes.c_int
     lib.rtprune_text_density.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, ctypes.c_float, vp, vp, vp,
                                          vp, ctypes.c_size_t, vp]
+    lib.rtprune_sinkhorn_routes.restype = ctypes.c_int
+    lib.rtprune_sinkhorn_routes.argtypes = [i32, i32, pp, i32, i32, vp, vp, vp]
     lib.rtprune_copy_bytes.restype = ctypes.c_int
     lib.rtprune_copy_bytes.argtypes = [vp, vp, ctypes.c_size_t, vp]
     if path is None:
@@ -287,6 +293,18 @@ def rtprune_profile_summary():
 
 def rtprune_copy_bytes(dst, src, nbytes: int, stream=None) -> int:
     return load_library().rtprune_copy_bytes(_addr(dst), _addr(src), nbytes, _stream(stream))
+
+
+def rtprune_sinkhorn_routes(B: int, max_tokens: int, params: rtprune_params, own_counts: int, kept, pruned):
+    """Returns ``(status, int32 array of RTP_ROUTE_ values)`` for host arrays of kept and pruned counts."""
+    import numpy as np
+    kept, pruned = (np.ascontiguousarray(a, dtype=np.int32) for a in (kept, pruned))
+    if kept.shape != pruned.shape or kept.ndim != 1:
+        raise RtpruneError("kept and pruned must be vectors of one length")
+    route = np.zeros(len(kept), np.int32)
+    rc = load_library().rtprune_sinkhorn_routes(B, max_tokens, ctypes.byref(params), int(own_counts), len(kept),
+                                                kept.ctypes.data, pruned.ctypes.data, route.ctypes.data)
+    return rc, route
 
 
 def rtprune_text_density_workspace_bytes(B: int, max_height: int, max_width: int, patch_h: int, patch_w: int):
