@@ -305,16 +305,7 @@ int cluster_slots_per_xcd(int groups) {
   return std::min(kClusterMaxSlots / 8, per_xcd / std::max(groups, 1));
 }
 
-// The same for the strip kernel, in all: slots that fit half an XCD keep to one XCD, larger ones
-// take consecutive workgroups.
-int strip_slots(int groups) {
-  const int cus = compute_units();
-  groups = std::max(groups, 1);
-  if (groups <= kStripXcdGroups) return 8 * std::min(kStripMaxSlots / 8, cus / 8 / groups);
-  return std::min(kStripMaxSlots, cus / groups);
-}
-
-// The strip kernel's words, when the call's mode has it: behind the cluster kernel's buffers.
+// The strip kernels' words, when the call's mode has any: behind the cluster kernel's buffers.
 int32_t* strip_words(const Layout& L, void* ws, int mode) {
   if (!mode_strips(mode)) return nullptr;
   return reinterpret_cast<int32_t*>(at<double>(ws, L.cluster_part) + kClusterPartDoubles);
@@ -342,18 +333,24 @@ int cluster_spin_limit() {
   return 20 * 1000 * 1000;
 }
 
+// Workgroups a strip image may take.
+int strip_most() { return std::min(kStripMaxGroups, compute_units() / 4); }
+
 // Which Sinkhorn kernels a call on this batch launches, and whether the sweep
 // kernels' matrices are stored in fp32 (only batches that may hold images beyond
 // the 512-row register shapes have any).
-void set_sinkhorn_mode(DevParams& p, int B, int max_tokens) {
+void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   const bool large = max_tokens > kLargeTokens;
   const int f32 = p.k32 ? kModeF32 : 0;   // exp's range fits fp32: registers may hold the matrix as fp32
   // The multi-workgroup kernels that keep a matrix on chip run one workgroup per compute unit.
   // Under a fixed retention the largest image the batch can hold bounds the others' kept and
-  // pruned counts; when one of them can take it, a slot needs no more workgroups than that image
-  // does (more slots then share the chip), and no image is beyond the on-chip kernels.  Under a
-  // dynamic one the clamp bounds the pruned sets: slots of eight workgroups of 144 x 576, or
+  // pruned counts; when one of them can take it, a cluster's slot needs no more workgroups than
+  // that image does (more slots then share the chip), and no image is beyond the on-chip kernels.
+  // Under a dynamic one the clamp bounds the pruned sets: eight workgroups of 144 x 576, or
   // sixteen of 80 x 960 when the clamp allows more.
+  // `own_counts`: the parameters bound nothing.  They still say what to expect (the staged calls of
+  // a pipeline with these parameters, which get the same kernels as the fused ones), but strips that
+  // hold up to 960 pruned tokens are launched whatever the parameters expect.
   const int m_top = p.dynamic ? 0 : kept_count(p.ratio, max_tokens), r_top = max_tokens - m_top;
   const int r_most = p.dynamic ? params_pruned_bound(p, max_tokens) : r_top;
   const bool top_clustered = !p.dynamic && m_top > 0 && cluster_shape(m_top, r_top) >= 0;
@@ -364,27 +361,37 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens) {
   const int slot = std::min(wide, kClusterMaxGroups);
   const int cluster = (large && f32 && cluster_slots_per_xcd(slot) > 0) ? (kModeCluster | (slot << kModeGroupsShift)) : 0;
   const int held = (large && f32) ? (wide << kModeWideShift) | (beyond_wide || !cluster ? kModeHeldF32 : 0) : 0;
-  int strips = 0;
+  int strips = 0, most = 0;
   bool top_fits = top_clustered;
   if (large && f32 && !top_clustered && (!p.dynamic || r_most > kClusterCols)) {
     int strip = p.dynamic && r_most > StripA::kCols ? kShapeStripB : strip_for(r_most);
-    int most = p.dynamic ? (strip == kShapeStripB ? 16 : 8) : (m_top + strip_rows(strip, 0) - 1) / strip_rows(strip, 0);
+    most = p.dynamic ? (strip == kShapeStripB ? 16 : 8) : (m_top + strip_rows(strip, 0) - 1) / strip_rows(strip, 0);
     // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
     // iteration) instead of 144 while every image still has its workgroups at once.  One image,
     // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
     const int thin_groups = (m_top + kStripThinRows - 1) / kStripThinRows;
-    const bool thin = !p.dynamic && strip == kShapeStripA && B <= strip_slots(thin_groups) && thin_groups <= kStripDirect;
+    const bool thin = !p.dynamic && strip == kShapeStripA && thin_groups <= kStripDirect &&
+                      B <= strip_slots(thin_groups, compute_units());
     if (thin) most = thin_groups;
     // (A slot waits until all its workgroups are resident.  Of several such calls on streams of
     // their own each can hold compute units with one slot that is not complete yet; a quarter of
     // the chip at most per slot lets four of them, one per hardware queue, always go on.)
-    if (!strip || most > std::min(kStripMaxGroups, compute_units() / 4) || strip_slots(most) == 0) {
+    const bool fits = strip && most <= strip_most() && strip_slots(most, compute_units()) > 0;
+    if (!fits) {
       strip = kShapeStripB;                // the longest image is the streaming kernels': shorter ones need not be
       most = 16;
     }
-    strips = mode_strip_bit(strip) | (thin ? kModeStripThin : 0) | (most << kModeStripGroupsShift);
-    top_fits = !p.dynamic && m_top > 0 && strip_fits(m_top, r_top, strips | held);
+    strips = mode_strip_bit(strip) | (thin ? kModeStripThin : 0);
+    top_fits = !p.dynamic && m_top > 0 && strip_fits(m_top, r_top, strips | (most << kModeStripGroupsShift) | held);
+    if (own_counts && fits && !p.dynamic) most = strip_most();
   }
+  if (large && f32 && own_counts) {
+    const int reach = std::min(max_tokens - 1, StripB::kCols);
+    if (!strips) most = p.dynamic ? 16 : strip_most();
+    if (!mode_strips(strips) || strip_cols(widest_strip(strips)) < reach)
+      strips |= mode_strip_bit(reach <= StripA::kCols ? kShapeStripA : kShapeStripB);
+  }
+  strips |= most << kModeStripGroupsShift;
   // The streaming kernels cost two launches per iteration whether or not an image needs them,
   // and only the device knows the sizes, so they are issued when the batch's shape and the
   // parameters say that images beyond the on-chip kernels are to be expected: a fixed
@@ -393,8 +400,12 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens) {
   // tokens; the clamp at 0.6 is a bound, not the rule) they are not: an image that does end
   // up beyond the on-chip kernels takes the one-workgroup general kernel, which is right and
   // slow.  Only the batch's shape and the parameters enter, so that the staged calls choose
-  // the same kernels as the fused ones.
-  const bool beyond = p.dynamic ? max_tokens - 1 > kClusterRows : !top_fits;
+  // the same kernels as the fused ones.  When the kept counts are the caller's, the longest image's
+  // fitting the strips says nothing: they are issued if it fits no strip of up to 1280 rows, unless
+  // the strips hold every image that the batch's shape allows.
+  const bool covered = mode_strips(strips) && max_tokens - 1 <= strip_cols(widest_strip(strips)) &&
+                       strip_groups(widest_strip(strips), max_tokens, strips) <= most;
+  const bool beyond = p.dynamic ? max_tokens - 1 > kClusterRows : own_counts ? beyond_wide && !covered : !top_fits;
   const int sweep = (large && (!cluster || beyond)) ? kModeSweep : 0;
   p.k32 = p.k32 && sweep;                 // the sweep kernels' copy in memory is fp32
   p.mode = (large ? kModeLarge : 0) | f32 | cluster | held | strips | sweep;
@@ -534,7 +545,7 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
               const ScanJob& job = ScanJob{0, nullptr, nullptr, nullptr, nullptr, 0, 0}) {
   if (in->B == 0 || in->total_tokens == 0) return RTP_OK;
   DevParams p = p_in;
-  set_sinkhorn_mode(p, in->B, in->max_tokens);
+  set_sinkhorn_mode(p, in->B, in->max_tokens, max_pruned_hint == kPrunedUnknown);
   const double* kmat = at<double>(ws, L.kmat);
   const int32_t* st = at<int32_t>(ws, L.status);
   int32_t* work = at<int32_t>(ws, L.work);
@@ -574,14 +585,20 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
   }
   if (mode_strips(p.mode)) {
     // (again one workgroup per compute unit of the slots in use: all resident together)
-    const int groups = mode_strip_groups(p.mode), slots = std::min(strip_slots(groups), (in->B + 7) / 8 * 8);
-    const StripArgs TA{A, strip_words(L, ws, p.mode), slots, groups, cluster_spin_limit(), at<int32_t>(ws, L.status)};
-    const dim3 grid(slots * groups), block(kStripThreads);
+    const int cus = compute_units();
+    int32_t* words = strip_words(L, ws, p.mode);
     ProfScope prof(KID_SINKHORN_STRIPS, s);
-    if (p.mode & mode_strip_bit(kShapeStripA)) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
-    else if (p.mode & mode_strip_bit(kShapeStripB)) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
-    else if (p.mode & mode_strip_bit(kShapeStripC)) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
-    else hipLaunchKernelGGL(k_sinkhorn_strips<StripD>, grid, block, 0, s, TA);
+    for (int shape = kShapeStripA; shape <= kShapeStripD; ++shape) {
+      if (!(p.mode & mode_strip_bit(shape))) continue;
+      const int groups = std::min(mode_strip_groups(p.mode), std::max(strip_groups(shape, in->max_tokens, p.mode), 1));
+      const StripArgs TA{A, words + (shape - 1) * kStripShapeWords, words + kStripList, cus, cluster_spin_limit(),
+                         at<int32_t>(ws, L.status)};
+      const dim3 grid(std::min(cus, (in->B + 7) / 8 * 8 * groups)), block(kStripThreads);
+      if (shape == kShapeStripA) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
+      else if (shape == kShapeStripB) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
+      else if (shape == kShapeStripC) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
+      else hipLaunchKernelGGL(k_sinkhorn_strips<StripD>, grid, block, 0, s, TA);
+    }
   }
   RTP_TRY(launched());
   ProfScope prof(KID_SINKHORN, s);   // (with the sweep launches below)
@@ -837,7 +854,7 @@ extern "C" int rtprune_sinkhorn_routes(int32_t B, int32_t max_tokens, const rtpr
   RTP_TRY(check_params(params, &p));
   if (B < 0 || max_tokens < 0 || n < 0 || (n > 0 && (!kept || !pruned || !route))) return RTP_EINVAL;
   if (B > kMaxImages || max_tokens > kMaxTokens) return RTP_EUNSUPPORTED;
-  set_sinkhorn_mode(p, B, max_tokens);
+  set_sinkhorn_mode(p, B, max_tokens, own_counts != 0);
   const int rmax = pruned_bound(max_tokens, p, own_counts ? kPrunedUnknown
                                                : p.dynamic ? kPrunedFromClamp : fixed_pruned_bound(p, max_tokens));
   for (int32_t i = 0; i < n; ++i) {
@@ -1077,7 +1094,7 @@ extern "C" int rtprune_prune(const rtprune_batch* in, const float* density,
   long long* plan_off = at<long long>(workspace, L.plan_off);
   float* plan = at<float>(workspace, L.plan);
   DevParams pm = p;
-  set_sinkhorn_mode(pm, in->B, in->max_tokens);
+  set_sinkhorn_mode(pm, in->B, in->max_tokens, false);
   ScanJob job{0, nullptr, nullptr, nullptr, nullptr, 0, 0};
   RTP_TRY(launch_stage1(in, p, pm.mode, density, ratio, keep, sel, out_offsets, plan_off, L, workspace, s, &job));
   const int max_pruned = p.dynamic ? kPrunedFromClamp : fixed_pruned_bound(p, in->max_tokens);
@@ -1168,7 +1185,7 @@ extern "C" int rtprune_prune_splice(const rtprune_batch* in, const float* densit
   // (the text offsets are checked after the norm pass has written the status word and
   // before the first kernel that writes to the caller's arrays)
   DevParams pm = p;
-  set_sinkhorn_mode(pm, in->B, in->max_tokens);
+  set_sinkhorn_mode(pm, in->B, in->max_tokens, false);
   ScanJob job{0, nullptr, nullptr, nullptr, nullptr, 0, 0};
   RTP_TRY(launch_stage1(in, p, pm.mode, density, ratio, keep, sel, nullptr, plan_off, L, workspace, s, &job, &t));
   hipLaunchKernelGGL(k_splice_scan, dim3(1), dim3(256), 0, s, t, keep, in->B, seq_offsets, visual_start, status);

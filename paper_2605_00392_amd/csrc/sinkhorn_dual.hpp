@@ -352,13 +352,13 @@ __device__ __forceinline__ void sinkhorn_dual48_image(const SinkhornArgs& A, int
 // Work lists for the register-resident kernels: `work` holds kWorkLists counts
 // (one per shape, indexed by variant id) followed by as many lists of B image
 // indices each.  One workgroup; list order follows image order.
-// `strip`: the strip kernel's words (null: the call does not launch it).
-constexpr int kClassifyLdsBytes = (kWorkLists + 1) * 256 * 4;   // LDS classify_images works in
+// `strip`: the strip kernels' words (null: the call does not launch any).
+constexpr int kClassifyLdsBytes = (kWorkLists + kStripShapes) * 256 * 4;   // LDS classify_images works in
 __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offsets,
                                                 const int32_t* __restrict__ keep, int B,
                                                 int32_t* __restrict__ work, int32_t* __restrict__ strip, int mode,
                                                 void* lds) {
-  constexpr int NV = kWorkLists, NS = NV + 1;         // (the last one: the strip kernel's)
+  constexpr int NV = kWorkLists, NS = NV + kStripShapes;   // (the last ones: the strip kernels')
   int (*cnt)[256] = static_cast<int (*)[256]>(lds);   // [NS][256]
   const int tid = threadIdx.x;
   const int span = (B + 255) / 256;
@@ -367,7 +367,9 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
 #pragma unroll
   for (int v = 0; v < NS; ++v) c[v] = 0;
   __shared__ unsigned long long sweep_cells;      // entries of the sweep kernels' matrices, padding included
+  __shared__ int strip_tops[kStripShapes];        // workgroups of the strip image that takes most of them
   if (tid == 0) sweep_cells = 0;
+  if (tid < kStripShapes) strip_tops[tid] = 0;
   __syncthreads();
   unsigned long long cells = 0;
   for (int b = b0; b < b1; ++b) {
@@ -378,7 +380,12 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
 #pragma unroll
       for (int u = 0; u < NV; ++u) c[u] += (u == v);
     }
-    c[NV] += n > 0 && v == kVariantStrip;
+    if (n > 0 && v == kVariantStrip) {
+      const int shape = strip_shape(n - m, mode);
+#pragma unroll
+      for (int u = 0; u < kStripShapes; ++u) c[NV + u] += u + 1 == shape;
+      atomicMax(&strip_tops[shape - 1], strip_groups(shape, m, mode));
+    }
     if (n > 0 && v == kVariantSweep) cells += static_cast<unsigned long long>(m) * k32_pitch(n - m);
     if (n > 0 && n - m > kTiledMinPruned) c[kListTiled] += 1;
     if (n > 0 && merge_is_mid(n - m)) c[kListMid] += 1;
@@ -399,6 +406,10 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   int at[NS];
 #pragma unroll
   for (int v = 0; v < NS; ++v) at[v] = cnt[v][tid] - c[v];
+#pragma unroll
+  for (int u = 1; u < kStripShapes; ++u)
+#pragma unroll
+    for (int w = 0; w < u; ++w) at[NV + u] += cnt[NV + w][255];   // (one list, shape after shape)
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
@@ -408,16 +419,28 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
       for (int u = 0; u < NV; ++u)
         if (u == v) work[NV + u * B + at[u]++] = b;
     }
-    if (strip && n > 0 && v == kVariantStrip) strip[kStripList + at[NV]++] = b;
+    if (strip && n > 0 && v == kVariantStrip) {
+      const int shape = strip_shape(n - m, mode);
+#pragma unroll
+      for (int u = 0; u < kStripShapes; ++u)
+        if (u + 1 == shape) strip[kStripList + at[NV + u]++] = b;
+    }
     if (n > 0 && n - m > kTiledMinPruned) work[NV + kListTiled * B + at[kListTiled]++] = b;
     if (n > 0 && merge_is_mid(n - m)) work[NV + kListMid * B + at[kListMid]++] = b;
   }
   if (tid == 255) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) work[v] = cnt[v][255];
-    if (strip) strip[kStripCount] = cnt[NV][255];
   }
-  if (strip && tid >= kStripCounters && tid < kStripList) strip[tid] = 0;
+  if (strip && tid < kStripShapes) {
+    int32_t* words = strip + tid * kStripShapeWords;
+    int first = 0;
+    for (int w = 0; w < tid; ++w) first += cnt[NV + w][255];
+    words[kStripCount] = cnt[NV + tid][255];
+    words[kStripTop] = strip_tops[tid];
+    words[kStripFirst] = first;
+    for (int e = kStripCounters; e < kStripShapeWords; ++e) words[e] = 0;
+  }
   // the cluster kernel's arrival counters and give-up word start at zero
   if (tid < kWorkStreamWord) work[NV * (1 + B) + tid] = 0;
   if (tid == kWorkStreamWord) {

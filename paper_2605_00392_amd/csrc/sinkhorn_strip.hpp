@@ -4,8 +4,9 @@
 //
 // The workgroups of all slots are resident together (one per compute unit and no more are
 // launched: each fills a compute unit's registers), a slot being as many workgroups as the
-// launch's largest image needs, and a slot works through its share of the list with all its
-// workgroups in step.  Slots of up to sixteen keep to one XCD.
+// largest of the launch's images needs (the list's builder counts them: a host that only knows the
+// parameters does not know them when the kept counts are the caller's), and a slot works through its
+// share of the list with all its workgroups in step.  Slots of up to sixteen keep to one XCD.
 //
 // A workgroup's eight waves hold RPT whole rows each, a lane the columns lane, lane + 64, ...  An
 // iteration is two passes over the registers, widening every entry at both uses:
@@ -50,17 +51,14 @@
 namespace rtp {
 
 constexpr int kStripThreads = 512;
-// Slots of up to this many workgroups keep to one XCD: a value reaches another workgroup in 0.27 to
-// 0.29 us there, in 0.37 to 0.50 us across XCDs (measured, one way).
-constexpr int kStripXcdGroups = 16;
 // what a value's place holds until the value has been published: no sum has this bit pattern (a NaN)
 constexpr long long kStripNotYet = -1;
 
 struct StripArgs {
   SinkhornArgs S;
-  int32_t* words;           // StripWords, prepared by the kernel that built the lists
-  int slots;                // launch: slots x groups_per_slot workgroups
-  int groups_per_slot;
+  int32_t* words;           // the shape's words, prepared by the kernel that built the lists
+  const int32_t* list;      // the strip images of the call, by shape
+  int cus;                  // compute units the slots may take
   int spin_limit;
   int32_t* status;
 };
@@ -541,19 +539,22 @@ __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) 
   if (C.status[0]) return;
   __shared__ __align__(16) unsigned char lds[strip_lds_of<S>()];
   int* flag = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 2;
-  const int per_slot = C.groups_per_slot, slots = C.slots, block = blockIdx.x;
-  int slot, rank;
-  if (per_slot <= kStripXcdGroups) {                   // one XCD per slot (slots is a multiple of eight)
+  const int count = C.words[kStripCount], per_slot = C.words[kStripTop], block = blockIdx.x;
+  if (count == 0) return;
+  int slots = strip_slots(per_slot, C.cus), slot, rank;
+  if (per_slot <= kStripXcdGroups) {                   // one XCD per slot
+    slots = min(slots, (count + 7) / 8 * 8);
     slot = (block & 7) * (slots >> 3) + (block >> 3) / per_slot;
     rank = (block >> 3) % per_slot;
   } else {
+    slots = min(slots, count);
     slot = block / per_slot;
     rank = block % per_slot;
   }
+  if (block >= slots * per_slot) return;
   const SinkhornArgs& A = C.S;
   int32_t* counter = C.words + kStripCounters + slot;
-  const int32_t* list = C.words + kStripList;
-  const int count = C.words[kStripCount];
+  const int32_t* list = C.list + C.words[kStripFirst];
   int arrived = 0;
   for (int k = slot; k < count; k += slots) {
     const int b = list[k];

@@ -121,10 +121,12 @@ constexpr int kVariantA = 0, kVariantDual = 1, kVariantDual48 = 2, kVariantB = 3
 // one of the images whose scores and merge go to the tiled matrix-core kernels.
 // (The strip kernel's list lies elsewhere: StripWords.)
 constexpr int kListTiled = 14, kListMid = 15, kWorkLists = 16;
-// Words of the strip kernel, in device memory that only it uses: how many images it has, arrival
-// counters of its slots and a give-up word (zero when it starts), and the list of its images.
-constexpr int kStripMaxSlots = 64;
-constexpr int kStripCount = 0, kStripCounters = 1, kStripGaveUp = kStripCounters + kStripMaxSlots, kStripList = kStripGaveUp + 1;
+// Words of the strip kernels, in device memory that only they use.  Per strip shape: how many images
+// it has, how many workgroups the one that needs most of them takes, where its images begin in the
+// list, arrival counters of its slots and a give-up word (zero when the kernel starts); then the list.
+constexpr int kStripMaxSlots = 64, kStripShapes = 4;
+constexpr int kStripCount = 0, kStripTop = 1, kStripFirst = 2, kStripCounters = 3, kStripGaveUp = kStripCounters + kStripMaxSlots,
+              kStripShapeWords = kStripGaveUp + 1, kStripList = kStripShapes * kStripShapeWords;
 // after the lists: synchronisation words of the multi-workgroup Sinkhorn kernel (arrival counters
 // of its cluster slots, a give-up word), zeroed by whoever builds the lists, and one word for the
 // sweep kernels: how many of every 16 strips they read with streaming loads (kWorkStreamWord)
@@ -188,6 +190,13 @@ __host__ __device__ inline int strip_shape(int r, int mode) {
     if (mode & mode_strip_bit(shape)) return shape;
   return kStripNone;
 }
+// the widest that a call launches
+__host__ __device__ inline int widest_strip(int mode) {
+  int widest = kStripNone;
+  for (int shape = kShapeStripA; shape <= kShapeStripD; ++shape)
+    if (mode & mode_strip_bit(shape)) widest = shape;
+  return widest;
+}
 // A strip image's workgroups exchange their sums in the image's own slot of the kernel matrix,
 // whose m r doubles hold fp32 entries: the upper end is free.  A few workgroups read all the
 // others' column sums (one trip); of more of them each is handed the sums of its share of
@@ -208,6 +217,15 @@ constexpr int kStripAlign = 16;   // doubles
 __host__ __device__ inline bool strip_exchange_fits(int shape, int m, int r, int groups) {
   const long long entries = 2 + static_cast<long long>(m) * ((r + 3) & ~3) / 2;   // (one double of alignment, see k32_base)
   return entries + strip_exchange_doubles(shape, r, groups) + 2 * kStripAlign <= static_cast<long long>(m) * r;
+}
+// Slots of `groups` workgroups that `cus` compute units hold, a workgroup each: up to half an XCD they
+// keep to one (a multiple of eight slots, eight XCDs assumed), larger ones take consecutive workgroups.
+// A value reaches another workgroup in 0.27 to 0.29 us in an XCD, in 0.37 to 0.50 us across (one way).
+constexpr int kStripXcdGroups = 16;
+__host__ __device__ inline int strip_slots(int groups, int cus) {
+  const int most = groups <= kStripXcdGroups ? cus / 8 / (groups > 0 ? groups : 1) : cus / groups;
+  if (groups <= kStripXcdGroups) return 8 * (most < kStripMaxSlots / 8 ? most : kStripMaxSlots / 8);
+  return most < kStripMaxSlots ? most : kStripMaxSlots;
 }
 __host__ __device__ inline int strip_groups(int shape, int m, int mode) {
   return (m + strip_rows(shape, mode) - 1) / strip_rows(shape, mode);

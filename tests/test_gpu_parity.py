@@ -346,6 +346,32 @@ def test_multi_workgroup_strips_at_their_edges(top, shapes, iters):
     _log(rep, f"strips {top}")
 
 
+@pytest.mark.parametrize("params,shapes,streams", [
+    # the parameters expect 341 pruned of 2137: two strip shapes and the streaming kernels in one call
+    (dict(ratio=0.84), [(1238, 899), (1796, 341), (560, 523), (145, 129), (81, 577), (80, 960), (300, 1100), (700, 100)], True),
+    # they expect clusters of up to 224 x 128 rows: strips all the same, nothing streamed
+    (dict(ratio=0.9), [(560, 523), (720, 363), (400, 683), (513, 130), (144, 577), (975, 108)], False),
+    (dict(dynamic=1, ratio_min=0.9), [(560, 523), (950, 133), (400, 683), (975, 108)], False),
+])
+def test_kept_counts_of_the_callers_own_in_several_strip_shapes(params, shapes, streams):
+    """Staged calls whose kept counts have nothing to do with the parameters: the strips take them by their
+    sizes, in slots as large as the images need, several images to a slot."""
+    shapes = shapes + [(m - 1 - k, r - k) for k in range(3) for m, r in shapes[1:]]
+    batch = _clustered([m + r for m, r in shapes], 64, "f32", 62, iters=7, **params)
+    keep = [m for m, _ in shapes]
+    rt.rtprune_profile_only(None)
+    rt.rtprune_profile_enable(1)
+    s = hz.run_staged(batch, keep_counts_in=keep)
+    rc, prof = rt.rtprune_profile_summary()
+    rt.rtprune_profile_enable(0)
+    assert s["status"] == 0 and rc == 0
+    launches = {r["kernel"]: r["launches"] for r in prof}
+    assert "k_sinkhorn_strips" in launches
+    to = rt.rtprune_sinkhorn_routes(len(shapes), batch.max_tokens, rt.make_params(batch.params), 1, keep, [r for _, r in shapes])[1]
+    assert (to[:3] & 15 == rt.RTP_ROUTE_STRIPS).all() and streams == bool((to & 15 == rt.RTP_ROUTE_STREAMED).any()), to
+    _log(hz.compare_batch(batch, s, staged=True, keep_counts=keep), f"own counts {params}")
+
+
 def test_multi_workgroup_resident_sinkhorn_wide_strips_fill_the_chip():
     """A fixed retention under which the longest image takes four strips: slots of four workgroups,
     64 of them, more images than slots, through the fused call (no launches of the streaming

@@ -79,7 +79,7 @@ def test_every_image_has_a_kernel_that_the_call_launches(own):
             assert not bad.any(), (n, params, batch, m[bad][:4], r[bad][:4])
 
 
-@pytest.mark.parametrize("own", [0])
+@pytest.mark.parametrize("own", [0, 1])
 def test_no_image_is_held_in_fewer_bits(own):
     rng = np.random.default_rng(2)
     for n, params in all_calls():
@@ -95,3 +95,31 @@ def test_no_image_is_held_in_fewer_bits(own):
             # kernels' fp32 one
             bad = several & chip & (to == rt.RTP_ROUTE_STREAMED)
             assert not bad.any(), (n, params, batch, m[bad][:4], r[bad][:4])
+
+
+def test_counts_of_the_callers_own_get_no_slower_kernel():
+    """The staged calls take any kept counts, whatever the parameters expect: an image that some launch of
+    several workgroups holds or streams under these parameters does not end up with the one-workgroup kernel."""
+    rng = np.random.default_rng(3)
+    for n, params in all_calls():
+        for batch in (1, 64, 1024):
+            m, r = images(n, params, rng, 1)
+            to, _ = routes(n, m, r, 1, batch, **params)
+            chip, streamed = on_chip_f32(n, m, r, params)
+            bad = (to == rt.RTP_ROUTE_GENERAL) & (chip | (streamed & (r <= 2048)))
+            assert not bad.any(), (n, params, batch, m[bad][:4], r[bad][:4])
+    for n, params, image in [(2137, dict(ratio=0.84), (1238, 899)), (4512, dict(ratio=0.84), (2783, 1729)),
+                             (4512, dict(ratio=0.7), (2783, 1729)), (1083, dict(ratio=0.9), (560, 523)),
+                             (1083, dict(ratio=1.0), (560, 523)), (1083, dict(dynamic=1, ratio_min=0.9), (560, 523))]:
+        to, _ = routes(n, [image[0]], [image[1]], 1, 64, **params)
+        assert to[0] in (rt.RTP_ROUTE_STRIPS, rt.RTP_ROUTE_STREAMED), (n, params, image, to)
+
+
+def test_staged_calls_of_a_pipeline_take_the_fused_calls_kernels():
+    rng = np.random.default_rng(4)
+    for n, params in all_calls():
+        for batch in (1, 64, 1024):
+            m, r = images(n, params, rng, 0)
+            fused, staged = routes(n, m, r, 0, batch, **params), routes(n, m, r, 1, batch, **params)
+            differ = (fused[0] != staged[0]) | (fused[1] != staged[1])
+            assert not differ.any(), (n, params, batch, m[differ][:4], r[differ][:4], fused[0][differ][:4], staged[0][differ][:4])
