@@ -346,8 +346,9 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   // Under a fixed retention the largest image the batch can hold bounds the others' kept and
   // pruned counts; when one of them can take it, a cluster's slot needs no more workgroups than
   // that image does (more slots then share the chip), and no image is beyond the on-chip kernels.
-  // Under a dynamic one the clamp bounds the pruned sets: eight workgroups of 144 x 576, or
-  // sixteen of 80 x 960 when the clamp allows more.
+  // Under a dynamic one the clamp bounds the pruned sets: strips of 144 x 576 and, when the clamp allows
+  // more columns, of 80 x 960 in a launch of their own.  (64 pages of 1100 x 150 beside one of 1500
+  // tokens, 100 iterations: all in 80 x 960, 15 column groups for 3, 2.87 ms; in 144 x 576 1.26 ms.)
   // `own_counts`: the parameters bound nothing.  They still say what to expect (the staged calls of
   // a pipeline with these parameters, which get the same kernels as the fused ones), but strips that
   // hold up to 960 pruned tokens are launched whatever the parameters expect.
@@ -364,8 +365,8 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   int strips = 0, most = 0;
   bool top_fits = top_clustered;
   if (large && f32 && !top_clustered && (!p.dynamic || r_most > kClusterCols)) {
-    int strip = p.dynamic && r_most > StripA::kCols ? kShapeStripB : strip_for(r_most);
-    most = p.dynamic ? (strip == kShapeStripB ? 16 : 8) : (m_top + strip_rows(strip, 0) - 1) / strip_rows(strip, 0);
+    int strip = p.dynamic ? kShapeStripA : strip_for(r_most);
+    most = p.dynamic ? kStripXcdGroups : (m_top + strip_rows(strip, 0) - 1) / strip_rows(strip, 0);
     // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
     // iteration) instead of 144 while every image still has its workgroups at once.  One image,
     // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
@@ -379,15 +380,16 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
     const bool fits = strip && most <= strip_most() && strip_slots(most, compute_units()) > 0;
     if (!fits) {
       strip = kShapeStripB;                // the longest image is the streaming kernels': shorter ones need not be
-      most = 16;
+      most = kStripXcdGroups;
     }
     strips = mode_strip_bit(strip) | (thin ? kModeStripThin : 0);
+    if (p.dynamic && r_most > StripA::kCols) strips |= mode_strip_bit(kShapeStripB);
     top_fits = !p.dynamic && m_top > 0 && strip_fits(m_top, r_top, strips | (most << kModeStripGroupsShift) | held);
     if (own_counts && fits && !p.dynamic) most = strip_most();
   }
   if (large && f32 && own_counts) {
     const int reach = std::min(max_tokens - 1, StripB::kCols);
-    if (!strips) most = p.dynamic ? 16 : strip_most();
+    if (!strips) most = p.dynamic ? kStripXcdGroups : strip_most();
     if (!mode_strips(strips) || strip_cols(widest_strip(strips)) < reach)
       strips |= mode_strip_bit(reach <= StripA::kCols ? kShapeStripA : kShapeStripB);
   }

@@ -372,6 +372,29 @@ def test_kept_counts_of_the_callers_own_in_several_strip_shapes(params, shapes, 
     _log(hz.compare_batch(batch, s, staged=True, keep_counts=keep), f"own counts {params}")
 
 
+def test_dynamic_retention_in_two_strip_shapes_through_the_fused_call():
+    """A clamp that allows more than 576 pruned tokens: pages of up to 576 pruned tokens in one strip shape, the
+    longest in the other, several images to a slot; fused = staged bit for bit."""
+    rng = np.random.default_rng(63)
+    counts = [int(c) for c in rng.integers(700, 1080, size=44)] + [1450, 1500]
+    batch = _clustered(counts, 64, "f32", 63, dynamic=1, ratio_min=0.55, phi_lo=0.0, phi_hi=1e-3, iters=6)
+    batch.density[-2:] = 0.0                                     # (these two at the clamp)
+    rt.rtprune_profile_only(None)
+    rt.rtprune_profile_enable(1)
+    f = hz.run_prune(batch)
+    rc, prof = rt.rtprune_profile_summary()
+    rt.rtprune_profile_enable(0)
+    assert f["rc"] == 0 and f["status"] == 0 and rc == 0
+    pruned = np.diff(batch.offsets) - f["keep"]
+    assert ((pruned > 128) & (pruned <= 576)).sum() > 32 and (pruned > 576).any(), pruned
+    ms = {r["kernel"]: r["total_ms"] for r in prof}
+    assert "k_sinkhorn_strips" in ms, ms
+    rep = hz.compare_batch(batch, f, images=list(range(0, 46, 5)) + [45])
+    _log(rep, "dynamic, two strip shapes")
+    s = hz.run_staged(batch)
+    _assert_fused_equals_staged(f, s, batch)
+
+
 def test_multi_workgroup_resident_sinkhorn_wide_strips_fill_the_chip():
     """A fixed retention under which the longest image takes four strips: slots of four workgroups,
     64 of them, more images than slots, through the fused call (no launches of the streaming
