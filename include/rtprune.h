@@ -71,16 +71,21 @@ enum {
   RTP_DEV_BAD_IMAGE = 4,      /* rtprune_text_density: a page's size is negative, above the stated
                                  maximum, not a multiple of the patch size, or overruns its pixel span */
   RTP_DEV_SYNC_TIMEOUT = 8    /* a Sinkhorn kernel that spreads a large image over several workgroups gave
-                                 up waiting for one of them (they must all be resident at once: only a GPU
-                                 kept busy for seconds by other work can cause it); the images they serve
-                                 - in batches with images above 512 tokens, those that no one-workgroup
-                                 shape holds, with up to 1792 pruned tokens - have no valid plan, pairing
-                                 or merged rows in this call's outputs */
+                                 up waiting for one of them, after seconds.  They must be resident at
+                                 once.  Up to four such calls at a time, one per hardware queue of a
+                                 process, never keep each other from that (a workgroup that waits leaves
+                                 its place in time); more queues, or several processes on the GPU, can,
+                                 and so can other work that fills the GPU for seconds.  The images these
+                                 kernels serve (rtprune_sinkhorn_routes: RTP_ROUTE_CLUSTER and
+                                 RTP_ROUTE_STRIPS, in batches with images above 512 tokens) have no valid
+                                 plan, pairing or merged rows in this call's outputs */
 };
 
-/* Two environment variables are read at each call, for tests only (they change no result):
+/* Three environment variables are read at each call, for tests only (they change no result):
  *   RTPRUNE_SYNC_SPIN_LIMIT      polls a workgroup of those kernels spends on one wait before it gives
- *                                up (default: 20 000 000, seconds); a value of 1 forces the give-up path
+ *                                up (default: 20 000 000, seconds); 0 forces the give-up path
+ *   RTPRUNE_STRIP_FORM_POLLS     polls after which the workgroups of a strip image that are not all there
+ *                                leave it to others (default: a 512th of the above, some 30 ms); 0: always
  *   RTPRUNE_SWEEP_STREAM_16THS   0 .. 16: how many of every 16 strips the streaming Sinkhorn kernels
  *                                read with non-temporal loads (default: worked out on the device from
  *                                the size of their matrices against the memory-side cache) */

@@ -328,13 +328,26 @@ int sweep_stream_override() {
 int cluster_spin_limit() {
   if (const char* e = std::getenv("RTPRUNE_SYNC_SPIN_LIMIT")) {
     const long v = std::strtol(e, nullptr, 10);
-    if (v > 0 && v < 0x7fffffffL) return static_cast<int>(v);
+    if (v >= 0 && v < 0x7fffffffL) return static_cast<int>(v);
   }
   return 20 * 1000 * 1000;
 }
 
-// Workgroups a strip image may take.
-int strip_most() { return std::min(kStripMaxGroups, compute_units() / 4); }
+// Polls for a strip slot to be complete before it is given up.  RTPRUNE_STRIP_FORM_POLLS overrides it,
+// for tests (0: every slot is given up).
+int strip_form_limit() {
+  if (const char* e = std::getenv("RTPRUNE_STRIP_FORM_POLLS")) {
+    const long v = std::strtol(e, nullptr, 10);
+    if (v >= 0 && v < 0x7fffffffL) return static_cast<int>(v);
+  }
+  return std::max(1, cluster_spin_limit() / 512);
+}
+
+// Workgroups a strip image may take (0: too few compute units for half an XCD's slots).
+int strip_most() {
+  const int cus = compute_units();
+  return cus < 8 * kStripXcdGroups ? 0 : std::min(kStripMaxGroups, cus / 4);
+}
 
 // Which Sinkhorn kernels a call on this batch launches, and whether the sweep
 // kernels' matrices are stored in fp32 (only batches that may hold images beyond
@@ -364,20 +377,19 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   const int held = (large && f32) ? (wide << kModeWideShift) | (beyond_wide || !cluster ? kModeHeldF32 : 0) : 0;
   int strips = 0, most = 0;
   bool top_fits = top_clustered;
-  if (large && f32 && !top_clustered && (!p.dynamic || r_most > kClusterCols)) {
+  const bool may_strip = large && f32 && strip_most() > 0;
+  if (may_strip && !top_clustered && (!p.dynamic || r_most > kClusterCols)) {
     int strip = p.dynamic ? kShapeStripA : strip_for(r_most);
-    most = p.dynamic ? kStripXcdGroups : (m_top + strip_rows(strip, 0) - 1) / strip_rows(strip, 0);
+    most = p.dynamic ? kStripXcdGroups : strip_groups(strip, m_top, 0);
     // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
     // iteration) instead of 144 while every image still has its workgroups at once.  One image,
     // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
-    const int thin_groups = (m_top + kStripThinRows - 1) / kStripThinRows;
+    const int thin_groups = strip_groups(kShapeStripA, m_top, kModeStripThin);
     const bool thin = !p.dynamic && strip == kShapeStripA && thin_groups <= kStripDirect &&
                       B <= strip_slots(thin_groups, compute_units());
     if (thin) most = thin_groups;
-    // (A slot waits until all its workgroups are resident.  Of several such calls on streams of
-    // their own each can hold compute units with one slot that is not complete yet; a quarter of
-    // the chip at most per slot lets four of them, one per hardware queue, always go on.)
-    const bool fits = strip && most <= strip_most() && strip_slots(most, compute_units()) > 0;
+    // (a quarter of the chip at most to an image: see sinkhorn_strip.hpp, who waits for whom)
+    const bool fits = strip && most <= strip_most();
     if (!fits) {
       strip = kShapeStripB;                // the longest image is the streaming kernels': shorter ones need not be
       most = kStripXcdGroups;
@@ -387,7 +399,7 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
     top_fits = !p.dynamic && m_top > 0 && strip_fits(m_top, r_top, strips | (most << kModeStripGroupsShift) | held);
     if (own_counts && fits && !p.dynamic) most = strip_most();
   }
-  if (large && f32 && own_counts) {
+  if (may_strip && own_counts) {
     const int reach = std::min(max_tokens - 1, StripB::kCols);
     if (!strips) most = p.dynamic ? kStripXcdGroups : strip_most();
     if (!mode_strips(strips) || strip_cols(widest_strip(strips)) < reach)
@@ -586,16 +598,18 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
                        compute_units(), folded ? 1 : 0);
   }
   if (mode_strips(p.mode)) {
-    // (again one workgroup per compute unit of the slots in use: all resident together)
+    // (again one workgroup per compute unit of the slots in use, and behind them those that take the
+    // images of slots that did not get complete)
     const int cus = compute_units();
     int32_t* words = strip_words(L, ws, p.mode);
     ProfScope prof(KID_SINKHORN_STRIPS, s);
     for (int shape = kShapeStripA; shape <= kShapeStripD; ++shape) {
       if (!(p.mode & mode_strip_bit(shape))) continue;
       const int groups = std::min(mode_strip_groups(p.mode), std::max(strip_groups(shape, in->max_tokens, p.mode), 1));
-      const StripArgs TA{A, words + (shape - 1) * kStripShapeWords, words + kStripList, cus, cluster_spin_limit(),
-                         at<int32_t>(ws, L.status)};
-      const dim3 grid(std::min(cus, (in->B + 7) / 8 * 8 * groups)), block(kStripThreads);
+      const int slot_blocks = std::min(cus, (in->B + 7) / 8 * 8 * groups);
+      const StripArgs TA{A, words + (shape - 1) * kStripShapeWords, cus, slot_blocks, strip_form_limit(),
+                         cluster_spin_limit(), at<int32_t>(ws, L.status)};
+      const dim3 grid(slot_blocks + groups), block(kStripThreads);
       if (shape == kShapeStripA) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
       else if (shape == kShapeStripB) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
       else if (shape == kShapeStripC) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
@@ -873,7 +887,7 @@ extern "C" int rtprune_sinkhorn_routes(int32_t B, int32_t max_tokens, const rtpr
     else if (v == kGeneralVariant) to = launches_general(p, rmax) ? RTP_ROUTE_GENERAL : RTP_ROUTE_UNSERVED;
     else if (v == kVariantC32) to = launches_c32(p, rmax) ? RTP_ROUTE_ONE_WORKGROUP : RTP_ROUTE_UNSERVED;
     else if (!tall && !short_shape && regs_folded(p, rmax, own_counts != 0)) to = RTP_ROUTE_UNSERVED;
-    route[i] = to | (kernel_is_f32(p, m, r) ? RTP_ROUTE_F32 : 0);
+    route[i] = to | (variant_layout(p, v) == kKernelRowsF32 ? RTP_ROUTE_F32 : 0);
   }
   return RTP_OK;
 }

@@ -92,10 +92,10 @@ __device__ __forceinline__ void scores_tile(const ScoresTiledArgs& A, int b, int
   if (i0 >= m || j0 >= r) return;
   if (!plan_fits(plan_offsets[b], m, r, plan_cap)) return;
   const long long po = plan_offsets[b];
-  const bool k_f32 = kernel_is_f32(p, m, r);
   // the sweep kernels' images and the widest strips' take exp through the fp32 unit; the other
   // on-chip shapes' entries are the fp64 exp rounded once
   const int variant = sinkhorn_variant(m, r, p.mode);
+  const bool k_f32 = variant_layout(p, variant) == kKernelRowsF32;
   const bool fast_exp = k_f32 && (variant == kVariantSweep || (variant == kVariantStrip && r > StripB::kCols));
   const int32_t* sel = sel_idx + lo;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;

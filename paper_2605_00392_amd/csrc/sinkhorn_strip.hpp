@@ -8,6 +8,17 @@
 // parameters does not know them when the kept counts are the caller's), and a slot works through its
 // share of the list with all its workgroups in step.  Slots of up to sixteen keep to one XCD.
 //
+// Who waits for whom.  Calls on other streams may hold compute units with workgroups that wait for
+// their own slots, so that no slot gets complete: three calls with 10 + 11 + 11 workgroups of slots of
+// sixteen fill an XCD, and slots across XCDs can each lack workgroups that another's keep out.  So no
+// slot waits for ever to be complete: before a slot's workgroups touch anything they meet, and one that
+// has waited too long (C.form_limit, some 30 ms) gives the slot up, for good and for all its workgroups,
+// which leave.  The images of slots given up are done by the launch's last `groups` workgroups,
+// which nobody else of the launch waits for and which do wait until they are all there.  They have
+// consecutive numbers, at most kStripMaxGroups / 8 = 8 of them on an XCD, so of four such calls (one per
+// hardware queue) at most 7 + 3 * 8 = 31 of an XCD's 32 compute units are held by workgroups that
+// wait for others of theirs (slots of sinkhorn_cluster.hpp: 7 each): the next always finds a place.
+//
 // A workgroup's eight waves hold RPT whole rows each, a lane the columns lane, lane + 64, ...  An
 // iteration is two passes over the registers, widening every entry at both uses:
 //   rows     a lane's share of the row sums of eight rows at a time; the 64 lanes' shares go
@@ -57,8 +68,9 @@ constexpr long long kStripNotYet = -1;
 struct StripArgs {
   SinkhornArgs S;
   int32_t* words;           // the shape's words, prepared by the kernel that built the lists
-  const int32_t* list;      // the strip images of the call, by shape
   int cus;                  // compute units the slots may take
+  int slot_blocks;          // workgroups of the launch that make up slots; the others are the last ones
+  int form_limit;           // polls for a slot to be complete (0: every slot is given up at once, for tests)
   int spin_limit;
   int32_t* status;
 };
@@ -113,6 +125,34 @@ __device__ __forceinline__ bool strip_meet(const StripArgs& C, int32_t* counter,
   return *s_flag != 0;
 }
 
+// Whether a slot is complete (all its workgroups resident) or has been given up: neither changes any
+// more.  `join`: this workgroup is one of the slot's.  Nothing has been touched yet, so a workgroup of
+// a slot given up just leaves.
+constexpr int kStripGivenUp = 1 << 30;     // in the slot's arrival counter (which stays below it: 65 535 images x 128)
+__device__ __forceinline__ bool strip_complete(int32_t* counter, int per_slot, int limit, bool join, int* s_flag) {
+  __syncthreads();                                     // the flag's last value has been read
+  if (threadIdx.x == 0) {
+    if (join && limit > 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int seen;
+    for (int spin = 0;; ++spin) {
+      seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((seen & kStripGivenUp) || seen >= per_slot) break;
+      if (spin >= limit) {                             // (a failed exchange: another arrival, or given up by another)
+        if (__hip_atomic_compare_exchange_strong(counter, &seen, seen | kStripGivenUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT)) {
+          seen |= kStripGivenUp;
+          break;
+        }
+        continue;
+      }
+      __builtin_amdgcn_s_sleep(2);
+    }
+    *s_flag = !(seen & kStripGivenUp);
+  }
+  __syncthreads();
+  return *s_flag != 0;
+}
+
 // Where image `b`'s workgroups exchange their values: the upper end of its kernel-matrix slot
 // (strip_exchange_fits).  The sums' buffers first, then those of y (shares only), then the
 // pairing keys, groups x r of them.
@@ -139,9 +179,10 @@ __device__ __forceinline__ void strip_clear(const StripArgs& C, int b, int rank)
 }
 
 // LDS of a strip workgroup: the waves' column sums (reused for the pairing's candidates), their
-// sums of x, the y (and the sum of x behind them), the received sums of the own columns.
+// sums of x, the y (and the sum of x behind them), the received sums of the own columns; flags, and the
+// slot's loop over its images while one is worked on.
 template <typename S> constexpr int strip_lds_of() {
-  return 8 * (8 * S::kCols + 8 + S::kCols + 2 + S::kCols + 258) + 32;
+  return 8 * (8 * S::kCols + 8 + S::kCols + 2 + S::kCols + 258) + 64;
 }
 // Workgroup barrier that orders LDS accesses only: published values still on their way are not
 // waited for, as __syncthreads would.
@@ -532,15 +573,18 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
 }
 
 // Slot s takes images s, s + slots, ... of the list.  The slot's arrival counter runs on through all
-// its meetings: one of all its workgroups before each image (the image's exchange area cleared), one
-// of the image's workgroups at its end (the pairing keys out).
+// its meetings: one when the slot is complete, one of all its workgroups before each image (the image's
+// exchange area cleared), one of the image's workgroups at its end (the pairing keys out).  The last
+// workgroups take the slots given up, one after another, with a counter of their own.
 template <typename S>
 __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) {
   if (C.status[0]) return;
   __shared__ __align__(16) unsigned char lds[strip_lds_of<S>()];
   int* flag = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 2;
-  const int count = C.words[kStripCount], per_slot = C.words[kStripTop], block = blockIdx.x;
+  int count = C.words[kStripCount], per_slot = C.words[kStripTop];
   if (count == 0) return;
+  const int block = blockIdx.x;
+  bool last = block >= C.slot_blocks;
   int slots = strip_slots(per_slot, C.cus), slot, rank;
   if (per_slot <= kStripXcdGroups) {                   // one XCD per slot
     slots = min(slots, (count + 7) / 8 * 8);
@@ -551,28 +595,57 @@ __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) 
     slot = block / per_slot;
     rank = block % per_slot;
   }
-  if (block >= slots * per_slot) return;
+  if (last) {
+    slot = 0;
+    rank = block - C.slot_blocks;
+    if (rank >= per_slot) return;
+    const int seen = static_cast<int>(threadIdx.x) < min(slots, count)   // (the slots that have images)
+                         ? __hip_atomic_load(C.words + kStripCounters + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                         : per_slot;
+    if (!__syncthreads_or((seen & kStripGivenUp) || seen < per_slot)) return;   // all complete: the usual case
+  } else if (block >= slots * per_slot || slot >= count) {
+    return;
+  }
   const SinkhornArgs& A = C.S;
-  int32_t* counter = C.words + kStripCounters + slot;
-  const int32_t* list = C.list + C.words[kStripFirst];
-  int arrived = 0;
-  for (int k = slot; k < count; k += slots) {
-    const int b = list[k];
-    const int n = A.offsets[b + 1] - A.offsets[b];
-    const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
-    // (every workgroup of the slot takes the same decisions: they read the same words)
-    if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
-    if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
-    const int groups = strip_groups(S::kShape, m, A.p.mode);   // (at most per_slot: strip_fits has seen to it)
-    strip_clear<S>(C, b, rank);
-    arrived += per_slot;
-    if (!strip_meet(C, counter, arrived, true, flag)) return;
-    arrived += groups;
-    if (rank < groups) {
-      if (!sinkhorn_strip_image<S>(C, b, rank, groups, counter, arrived, lds, flag)) return;
-    } else if (!strip_meet(C, counter, arrived, false, flag)) {
-      return;
+  int arrived = last ? 0 : per_slot, form_limit = C.form_limit;
+  // the loop's state, in LDS while an image is worked on: in registers it makes the kernels spill
+  // (4512-token pages 5.75 -> 5.90 ms a call)
+  int* at = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 12;
+  for (;;) {
+    if (strip_complete(C.words + kStripCounters + slot, per_slot, form_limit, !last, flag) != last) {
+      for (int k = slot; k < count; k += slots) {
+        const int b = C.words[kStripList - (S::kShape - 1) * kStripShapeWords + C.words[kStripFirst] + k];
+        const int n = A.offsets[b + 1] - A.offsets[b];
+        const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
+        // (every workgroup of the slot takes the same decisions: they read the same words)
+        if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
+        if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
+        const int groups = strip_groups(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
+        int32_t* counter = C.words + (last ? kStripLast : kStripCounters + slot);
+        strip_clear<S>(C, b, rank);
+        arrived += per_slot;
+        if (!strip_meet(C, counter, arrived, true, flag)) return;
+        arrived += groups;
+        if (rank < groups) {
+          if (threadIdx.x == 0) {
+            at[0] = slot, at[1] = k, at[2] = arrived, at[3] = slots, at[4] = count, at[5] = per_slot, at[6] = rank, at[7] = last, at[8] = form_limit;
+          }
+          if (!sinkhorn_strip_image<S>(C, b, rank, groups, counter, arrived, lds, flag)) return;
+          slot = __builtin_amdgcn_readfirstlane(at[0]);
+          k = __builtin_amdgcn_readfirstlane(at[1]);
+          arrived = __builtin_amdgcn_readfirstlane(at[2]);
+          slots = __builtin_amdgcn_readfirstlane(at[3]);
+          count = __builtin_amdgcn_readfirstlane(at[4]);
+          per_slot = __builtin_amdgcn_readfirstlane(at[5]);
+          rank = __builtin_amdgcn_readfirstlane(at[6]);
+          last = __builtin_amdgcn_readfirstlane(at[7]) != 0;
+          form_limit = __builtin_amdgcn_readfirstlane(at[8]);
+        } else if (!strip_meet(C, counter, arrived, false, flag)) {
+          return;
+        }
+      }
     }
+    if (!last || ++slot >= min(slots, count)) return;
   }
 }
 

@@ -123,9 +123,11 @@ constexpr int kVariantA = 0, kVariantDual = 1, kVariantDual48 = 2, kVariantB = 3
 constexpr int kListTiled = 14, kListMid = 15, kWorkLists = 16;
 // Words of the strip kernels, in device memory that only they use.  Per strip shape: how many images
 // it has, how many workgroups the one that needs most of them takes, where its images begin in the
-// list, arrival counters of its slots and a give-up word (zero when the kernel starts); then the list.
+// list, arrival counters of its slots and of the last workgroups, and a give-up word (zero when the
+// kernel starts); then the list.
 constexpr int kStripMaxSlots = 64, kStripShapes = 4;
-constexpr int kStripCount = 0, kStripTop = 1, kStripFirst = 2, kStripCounters = 3, kStripGaveUp = kStripCounters + kStripMaxSlots,
+constexpr int kStripCount = 0, kStripTop = 1, kStripFirst = 2, kStripCounters = 3, kStripLast = kStripCounters + kStripMaxSlots,
+              kStripGaveUp = kStripLast + 1,
               kStripShapeWords = kStripGaveUp + 1, kStripList = kStripShapes * kStripShapeWords;
 // after the lists: synchronisation words of the multi-workgroup Sinkhorn kernel (arrival counters
 // of its cluster slots, a give-up word), zeroed by whoever builds the lists, and one word for the
@@ -176,19 +178,14 @@ __host__ __device__ inline int strip_cols(int shape) {
        : shape == kShapeStripC ? StripC::kCols : shape == kShapeStripD ? StripD::kCols : 0;
 }
 constexpr int kStripThinRows = 64;
-__host__ __device__ inline int strip_rows(int shape, int mode) {
-  return shape == kShapeStripA ? ((mode & kModeStripThin) ? kStripThinRows : StripA::kRows)
-       : shape == kShapeStripB ? StripB::kRows : shape == kShapeStripC ? StripC::kRows : StripD::kRows;
-}
 // the narrowest that holds `r` columns (kStripNone: none); of all, and of those a call launches
 __host__ __device__ inline int strip_for(int r) {
   return r <= StripA::kCols ? kShapeStripA : r <= StripB::kCols ? kShapeStripB : r <= StripC::kCols ? kShapeStripC
        : r <= StripD::kCols ? kShapeStripD : kStripNone;
 }
 __host__ __device__ inline int strip_shape(int r, int mode) {
-  for (int shape = strip_for(r); shape && shape <= kShapeStripD; ++shape)
-    if (mode & mode_strip_bit(shape)) return shape;
-  return kStripNone;
+  const int narrowest = strip_for(r), launched = narrowest ? mode_strips(mode) >> (narrowest - 1) : 0;
+  return launched ? narrowest + __builtin_ctz(launched) : kStripNone;
 }
 // the widest that a call launches
 __host__ __device__ inline int widest_strip(int mode) {
@@ -214,9 +211,11 @@ __host__ __device__ inline long long strip_exchange_doubles(int shape, int r, in
   return static_cast<long long>(kStripBufs) * (groups + 1) * strip_share(r, groups) * groups + keys;
 }
 constexpr int kStripAlign = 16;   // doubles
+// (fits 32 bits: m r <= kMaxTokens^2 / 4.  The score kernels ask this once per tile, so the division in
+// strip_share is left to the few images that a bound without it does not settle.)
 __host__ __device__ inline bool strip_exchange_fits(int shape, int m, int r, int groups) {
-  const long long entries = 2 + static_cast<long long>(m) * ((r + 3) & ~3) / 2;   // (one double of alignment, see k32_base)
-  return entries + strip_exchange_doubles(shape, r, groups) + 2 * kStripAlign <= static_cast<long long>(m) * r;
+  const int room = m * r - 2 - m * ((r + 3) & ~3) / 2 - 2 * kStripAlign;   // (one double of alignment, see k32_base)
+  return kStripBufs * (groups + 1) * (r + groups) + groups * r <= room || strip_exchange_doubles(shape, r, groups) <= room;
 }
 // Slots of `groups` workgroups that `cus` compute units hold, a workgroup each: up to half an XCD they
 // keep to one (a multiple of eight slots, eight XCDs assumed), larger ones take consecutive workgroups.
@@ -227,8 +226,10 @@ __host__ __device__ inline int strip_slots(int groups, int cus) {
   if (groups <= kStripXcdGroups) return 8 * (most < kStripMaxSlots / 8 ? most : kStripMaxSlots / 8);
   return most < kStripMaxSlots ? most : kStripMaxSlots;
 }
-__host__ __device__ inline int strip_groups(int shape, int m, int mode) {
-  return (m + strip_rows(shape, mode) - 1) / strip_rows(shape, mode);
+__host__ __device__ inline int strip_groups(int shape, int m, int mode) {   // (divisions by constants)
+  return shape == kShapeStripA ? ((mode & kModeStripThin) ? (m + kStripThinRows - 1) / kStripThinRows : (m + StripA::kRows - 1) / StripA::kRows)
+       : shape == kShapeStripB ? (m + StripB::kRows - 1) / StripB::kRows
+       : shape == kShapeStripC ? (m + StripC::kRows - 1) / StripC::kRows : (m + StripD::kRows - 1) / StripD::kRows;
 }
 // Whose matrices may be held as fp32 there (the rounding takes the plan's relative error against 64
 // bits from 2.6e-8 to 3.4e-8 for fp32 tokens and from 1.386e-7 to 1.405e-7 for bf16 ones, 1260 x 240):
@@ -299,8 +300,7 @@ __host__ __device__ inline int sinkhorn_variant(int m, int r, int mode) {
 //                   a load read 64 consecutive entries (row-major, they read 64 cache
 //                   lines: the loads alone took 15 to 25 us of a workgroup's time).
 constexpr int kKernelRowsF64 = 0, kKernelRowsF32 = 1, kKernelColsF64 = 2;
-__host__ __device__ __forceinline__ int kernel_layout(const DevParams& p, int m, int r) {
-  const int v = sinkhorn_variant(m, r, p.mode);
+__host__ __device__ __forceinline__ int variant_layout(const DevParams& p, int v) {
   if (v == kVariantSweep) return p.k32 ? kKernelRowsF32 : kKernelRowsF64;
   // (these are only chosen under kModeF32)
   if (v == kVariantTeamTall || v == kVariantWideA || v == kVariantWideB || v == kVariantWideC || v == kVariantC32 ||
@@ -308,8 +308,8 @@ __host__ __device__ __forceinline__ int kernel_layout(const DevParams& p, int m,
     return kKernelRowsF32;
   return (v == kVariantA || v == kVariantPair || v == kVariantTall) ? kKernelColsF64 : kKernelRowsF64;
 }
-__host__ __device__ __forceinline__ bool kernel_is_f32(const DevParams& p, int m, int r) {
-  return kernel_layout(p, m, r) == kKernelRowsF32;
+__host__ __device__ __forceinline__ int kernel_layout(const DevParams& p, int m, int r) {
+  return variant_layout(p, sinkhorn_variant(m, r, p.mode));
 }
 // fp32 layout of image b's kernel matrix: rows padded to a multiple of four
 // entries (when there are at least eight columns) and the first row on a 16-byte

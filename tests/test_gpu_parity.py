@@ -460,6 +460,60 @@ def test_multi_workgroup_sinkhorn_gives_up_instead_of_waiting_for_ever(monkeypat
     _log(hz.compare_batch(batch, g), "after a timed-out call")
 
 
+# batches whose images go through the strips: (sizes, retention, iterations).  One trip's exchange in slots of
+# four workgroups, several images to a slot; in slots of sixteen; two trips in slots of 24 across the XCDs, several
+# images to a slot; a thin strip page.
+STRIP_BATCHES = {
+    "4 workgroups": ([1083] * 3 + list(range(800, 1070)), 560.0 / 1083.0, 5),
+    "16 workgroups": ([2137] + list(range(1700, 1900, 11)), 1238.0 / 2137.0, 5),
+    "24 workgroups": ([2900] + list(range(2860, 2895, 2)), 1500.0 / 2900.0, 4),
+    "one page": ([1156], 0.75, 9),
+}
+
+
+@pytest.mark.parametrize("name", list(STRIP_BATCHES))
+def test_strip_slots_that_do_not_get_complete_leave_their_images_to_the_last_workgroups(monkeypatch, name):
+    """A strip slot whose workgroups are not all resident in time is given up, and the launch's last workgroups do
+    its images.  With the host-side test switch every slot is given up: same bits as with none, and right."""
+    counts, ratio, iters = STRIP_BATCHES[name]
+    batch = _clustered(counts, 16, "f32", 64, ratio=ratio, iters=iters)
+    f = hz.run_prune(batch)
+    assert f["rc"] == 0 and f["status"] == 0
+    m, r = f["keep"], np.diff(batch.offsets) - f["keep"]
+    rc, to = rt.rtprune_sinkhorn_routes(len(counts), batch.max_tokens, rt.make_params(batch.params), 0, m, r)
+    assert rc == 0 and (to & 15 == rt.RTP_ROUTE_STRIPS).all()
+    _log(hz.compare_batch(batch, f, images=sorted({0, 1 % len(counts), len(counts) // 2, len(counts) - 1})), name)
+    monkeypatch.setenv("RTPRUNE_STRIP_FORM_POLLS", "0")
+    g = hz.run_prune(batch)
+    assert g["rc"] == 0 and g["status"] == 0
+    for k in ("out", "pair", "sel", "keep"):
+        np.testing.assert_array_equal(f[k], g[k])
+
+
+@pytest.mark.parametrize("name", list(STRIP_BATCHES))
+def test_strips_give_up_instead_of_waiting_for_ever(monkeypatch, name):
+    """The strips' own waits are bounded, in both forms of their exchange.  With no poll allowed the first meeting
+    gives up; with a few, workgroups in step may get through it and through some iterations: the call either says
+    that a wait timed out or is right to the last bit."""
+    counts, ratio, iters = STRIP_BATCHES[name]
+    batch = _clustered(counts[:6], 16, "f32", 65, ratio=ratio, iters=iters)
+    ref = hz.run_prune(batch)
+    assert ref["rc"] == 0 and ref["status"] == 0
+    _log(hz.compare_batch(batch, ref, images=[0]), name)
+    for polls in (0, 1, 2, 5):
+        monkeypatch.setenv("RTPRUNE_SYNC_SPIN_LIMIT", str(polls))
+        f = hz.run_prune(batch)
+        assert f["rc"] == 0 and f["status"] in ((0, rt.RTP_DEV_SYNC_TIMEOUT) if polls else (rt.RTP_DEV_SYNC_TIMEOUT,))
+        if f["status"] == 0:
+            np.testing.assert_array_equal(f["out"], ref["out"])
+        print(f"[{name}] {polls} polls: status {f['status']}", flush=True)
+        monkeypatch.delenv("RTPRUNE_SYNC_SPIN_LIMIT")
+        g = hz.run_prune(batch)
+        assert g["rc"] == 0 and g["status"] == 0
+        np.testing.assert_array_equal(g["out"], ref["out"])
+        np.testing.assert_array_equal(g["pair"], ref["pair"])
+
+
 @pytest.mark.parametrize("override", [dict(), dict(eps=0.02), dict(iters=0), dict(iters=1)])
 def test_wide_register_shapes_at_their_edges(override):
     """Images of at most 512 tokens with 65 to 225 pruned ones, on both sides of the
