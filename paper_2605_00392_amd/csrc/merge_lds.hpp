@@ -25,8 +25,9 @@ constexpr int kMergeMaxChunk = 64;   // pruned rows per LDS chunk, at most one p
 
 // EXACT: the width is 256 KMAX, every lane owns exactly KMAX groups (no bounds tests).
 // SLICED (with EXACT): the workgroup does 256 KMAX features of its rows, from 256 KMAX blockIdx.z on,
-// with all pruned rows staged at once: in small batches, where a workgroup of whole rows walks a
-// page's pruned rows twelve at a time with most of the chip idle.  The sums' order is the same.
+// with up to 60 pruned rows of bf16 or 30 of fp32 staged at once: in small batches, where a workgroup
+// of whole rows walks a page's pruned rows twelve (bf16) or six at a time with most of the chip idle.  The
+// sums' order is the same.
 template <typename T, int KMAX, bool EXACT, bool SLICED = false>
 __global__ __launch_bounds__(256) void k_merge_lds(
     const T* __restrict__ tokens, const int32_t* __restrict__ offsets, int D,

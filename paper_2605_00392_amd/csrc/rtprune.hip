@@ -425,15 +425,10 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   p.mode = (large ? kModeLarge : 0) | f32 | cluster | held | strips | sweep;
 }
 
-// `work` non-null: the same launch also builds the Sinkhorn work lists.
 int launch_scan(const rtprune_batch* in, const int32_t* keep, int32_t* out_off, long long* plan_off,
-                const int32_t* status, hipStream_t s, int32_t* work = nullptr, int32_t* strip = nullptr, int mode = 0) {
+                const int32_t* status, hipStream_t s) {
   ProfScope prof(KID_SCAN, s);
-  if (work)
-    hipLaunchKernelGGL(k_scan_classify, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, out_off, plan_off, work,
-                       strip, mode, status);
-  else
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, out_off, plan_off, status);
+  hipLaunchKernelGGL(k_scan, dim3(1), dim3(256), 0, s, in->offsets, keep, in->B, out_off, plan_off, status);
   return launched();
 }
 
@@ -691,7 +686,8 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
     const dim3 g2((in->max_tokens + kMergeBlockRows - 1) / kMergeBlockRows, in->B);
     // Up to three 16-row workgroups on two compute units, a workgroup per 256 features of them.
     // Measured, whole rows / slices: one page of 400 tokens with 63 pruned 28 / 14 us, 4 such pages
-    // 28 / 18, 16 such 42 / 36, 48 such 83 / 87; 32 pages of 256 with 41 pruned 31 / 34.
+    // 28 / 18, 16 such 42 / 36, 48 such 83 / 87; 32 pages of 256 with 41 pruned 31 / 34.  (The line,
+    // 384 workgroups, lies short of the 400 of 16 such pages; the last two have 1200 and 512.)
     if (in->D % 256 == 0 && 2LL * g2.x * in->B <= 3LL * compute_units())
       hipLaunchKernelGGL((k_merge_lds<T, 1, true, true>), dim3(g2.x, g2.y, in->D / 256), block, 0, s, tok, in->offsets,
                          in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens, skip, static_cast<T*>(out),
@@ -768,13 +764,13 @@ int launch_stage1(const rtprune_batch* in, const DevParams& p, int mode, const f
     RTP_TRY(launched());
   }
   RTP_TRY(launch_select(in, p, density, nullptr, 1, L, ws, nullptr, ratio, keep, sel, s));
-  // the prefix sums and work lists: by an extra workgroup of the score pass when that runs
-  // (`job`), else by a launch of their own
+  // the prefix sums and work lists: by an extra workgroup of the score pass (`job`); without tokens
+  // there is none, and no reader of the lists
   if (in->B > 0 && in->total_tokens > 0) {
     *job = ScanJob{1, out_offsets, plan_off, work, strip_words(L, ws, mode), mode, L.plan_stride};
     return RTP_OK;
   }
-  return launch_scan(in, keep, out_offsets, plan_off, status, s, work, strip_words(L, ws, mode), mode);
+  return launch_scan(in, keep, out_offsets, plan_off, status, s);
 }
 
 }  // namespace

@@ -49,7 +49,7 @@ constexpr int kScoreBufElems = (64 + kScoreRows) * kScorePitch;
 // lists, and the per-image slots of the kernel matrix and the plan, as an array for the
 // kernels after this one.  Nothing in this launch depends on it: with a job, an image's
 // slot is the closed form plan_slot(offsets, b, stride), which this kernel evaluates for
-// itself.  It takes a launch of its own (k_scan_classify) out of every fused call.
+// itself.  It saves every fused call a launch.
 struct ScanJob {
   int on;
   int32_t* out_offsets;        // may be null

@@ -461,21 +461,6 @@ __global__ __launch_bounds__(256) void k_classify(const int32_t* __restrict__ of
   classify_images(offsets, keep, B, work, strip, mode, lds);
 }
 
-// Both of the above in one launch, for the fused calls.
-__global__ __launch_bounds__(256) void k_scan_classify(const int32_t* __restrict__ offsets,
-                                                       const int32_t* __restrict__ keep, int B,
-                                                       int32_t* __restrict__ out_offsets,
-                                                       long long* __restrict__ plan_offsets,
-                                                       int32_t* __restrict__ work, int32_t* __restrict__ strip,
-                                                       int mode, const int32_t* __restrict__ status) {
-  if (status[0]) return;
-  __shared__ __align__(16) unsigned char lds[kClassifyLdsBytes];   // (the two run one after the other)
-  static_assert(kScanLdsBytes <= kClassifyLdsBytes, "shared work area");
-  scan_images(offsets, keep, B, out_offsets, plan_offsets, lds);
-  __syncthreads();
-  classify_images(offsets, keep, B, work, strip, mode, lds);
-}
-
 // The two- and one-wave images, the shortest-running roles: workgroup `blk` of theirs.  `others`: how
 // many workgroups the launch's other roles have.
 // Two-wave images: four per workgroup, or - when the whole launch then still has
