@@ -130,9 +130,9 @@ def kernel_work(kernel: str, n: np.ndarray, m: np.ndarray, d: int, elt: int, ite
 
 
 def sinkhorn_streamed_bytes(n: np.ndarray, m: np.ndarray, iters: int, eps: float, z: float) -> float:
-    """Bytes the multi-workgroup Sinkhorn kernels read per call: images beyond the
-    register-resident shapes (batches with images above 512 tokens only) have their kernel
-    matrix streamed once per iteration, in fp32 when exp's range allows."""
+    """Bytes the streaming Sinkhorn kernels read per call for the images given, of which those within
+    the one-workgroup shapes are not theirs: the kernel matrix once per iteration, in fp32 when exp's
+    range allows."""
     r = n - m
     if n.max(initial=0) <= 512:
         return 0.0
@@ -250,7 +250,10 @@ def bench_side(rt, torch, synth, steps: int, cfg: int, batch=None, rooflines: bo
             ach = amount / (kernels[k_] * 1e-3) / (1e9 if unit == "GB/s" else 1e12)
             roof[k_] = dict(bound=bound, achieved=round(ach, 2), peak=peak, unit=unit, frac=round(ach / peak, 4))
             if k_ == "k_sinkhorn":
-                streamed = sinkhorn_streamed_bytes(n_h, keep_h, iters, eps, z)
+                rc, route = rt.rtprune_sinkhorn_routes(B, db.max_tokens, p, 0, keep_h, n_h - keep_h)
+                rt.check(rc)
+                far = (route & 15) == rt.RTP_ROUTE_STREAMED
+                streamed = sinkhorn_streamed_bytes(n_h[far], keep_h[far], iters, eps, z)
                 if streamed > 0:
                     roof[k_]["streamed"] = dict(bytes_per_call=streamed, unit="GB/s",
                                                 rate=round(streamed / (kernels[k_] * 1e-3) / 1e9, 1))

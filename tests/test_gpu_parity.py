@@ -327,8 +327,7 @@ def test_multi_workgroup_resident_sinkhorn_widest_strips_at_their_edges(override
     # strips of 48 rows x 1792 columns, 27 to a slot; 1793 columns are the general kernel's
     ((1250, 1750), [(48, 1792), (49, 1792), (1208, 1792), (1200, 129), (97, 300), (60, 1793)], 6),
     ((1250, 1750), [(48, 1792), (433, 1409)], 0),
-    # one image or two: strips of 64 rows x 576 columns; one trip's exchange up to sixteen
-    # workgroups and 4608 sums, two trips beyond
+    # a few images: strips of 64 rows x 576 columns, up to sixteen workgroups and one trip's exchange
     ((1000, 287), [], 9),
     ((1024, 287), [(1, 200), (64, 576), (65, 576)], 9),
     ((420, 280), [(129, 300)], 1),
@@ -411,7 +410,10 @@ def test_multi_workgroup_resident_sinkhorn_wide_strips_fill_the_chip():
     ms = {r["kernel"]: r["total_ms"] for r in prof}
     # (the streaming kernels' 2 T + 3 launches are recorded under k_sinkhorn, with the general
     # kernel's one: far more than the 0.1 ms allowed here if they were issued)
-    assert "k_sinkhorn_tall" in ms and ms.get("k_sinkhorn", 0.0) < 0.1, ms
+    assert "k_sinkhorn_strips" in ms and ms.get("k_sinkhorn", 0.0) < 0.1, ms
+    rc, to = rt.rtprune_sinkhorn_routes(len(counts), batch.max_tokens, rt.make_params(batch.params), 0, f["keep"],
+                                        np.diff(batch.offsets) - f["keep"])
+    assert rc == 0 and (to & 15 == rt.RTP_ROUTE_STRIPS).all()
     rep = hz.compare_batch(batch, f, images=list(range(0, 71, 6)) + [70])
     _log(rep, "cluster wide strips, fused, 71 images")
     s = hz.run_staged(batch)
