@@ -13,9 +13,9 @@
 // another: one barrier per iteration.
 //
 // Bound by vector instruction issue (two multiply-adds and one conversion per entry are half of
-// the 590 instructions per wave and iteration).  Eight waves of six rows per lane, every row with a
-// reduction and a reciprocal of its own, issued 3560 instructions per image and iteration against
-// 2360 here.  1024 pages of 400 tokens, 337 kept, 100 iterations: 0.668 -> 0.527 ms;
+// the instructions).  Eight waves of six rows per lane, every row with a reduction and a reciprocal of
+// its own, issued 2970 instructions per image and iteration against 2030 here (counters, 337 kept of
+// 400).  1024 pages of 400 tokens, 337 kept, 100 iterations: 0.668 -> 0.527 ms;
 // one such page alone: 0.196 -> 0.156 ms.  With eight waves the same body takes the tall images with
 // 16 to 48 pruned tokens: 128 ragged tiled pages, 50 iterations, k_sinkhorn_large 0.186 -> 0.157 ms.
 #pragma once

@@ -31,7 +31,7 @@
 // 100 iterations: 64 pages of 1083 tokens (four workgroups of 144 x 576 each) 0.91 -> 0.60 ms, 32
 // pages of 2137 (sixteen of 80 x 960) 2.48 -> 1.46 ms against strips that gave every row a reduction
 // of its own over the 64 lanes and a reciprocal in all of them (28 instructions a row beside 27 for
-// its nine columns' arithmetic); 16 pages of 4512 tokens (58 of 48 x 1792) 6.72 -> 4.49 ms against
+// its nine columns' arithmetic); 16 pages of 4512 tokens (58 of 48 x 1792) 6.72 -> 3.92 ms against
 // streaming the matrices from memory every iteration.
 //
 // The exchange.  A few workgroups publish their column sums and everybody adds everybody's in
