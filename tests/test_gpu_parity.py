@@ -492,6 +492,34 @@ def test_strip_slots_that_do_not_get_complete_leave_their_images_to_the_last_wor
         np.testing.assert_array_equal(f[k], g[k])
 
 
+@pytest.mark.parametrize("names", [("16 workgroups",) * 4, ("16 workgroups", "24 workgroups", "4 workgroups", "24 workgroups")])
+def test_strip_calls_on_four_streams_at_once(names):
+    """Four calls at a time, a stream each, whose slots compete for the compute units: all end without a time-out
+    and with the bits of a call alone."""
+    jobs = []
+    for i, name in enumerate(names):
+        counts, ratio, iters = STRIP_BATCHES[name]
+        batch = _clustered(counts, 16, "f32", 70 + i, ratio=ratio, iters=40)
+        ref = hz.run_prune(batch)
+        assert ref["rc"] == 0 and ref["status"] == 0
+        db, p = rt.upload(batch), rt.make_params(batch.params)
+        ws = rt.alloc_workspace(db)
+        out = torch.zeros_like(db.tokens)
+        off = torch.zeros(db.B + 1, dtype=torch.int32, device="cuda:0")
+        pair = torch.zeros(db.total_tokens, dtype=torch.int32, device="cuda:0")
+        jobs.append((ref, db, p, ws, out, off, pair, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for ref, db, p, ws, out, off, pair, stream in jobs:
+            assert rt.rtprune_prune(db, None, p, out, off, None, None, pair, None, ws, stream=stream) == rt.RTP_OK
+    torch.cuda.synchronize()
+    for ref, db, p, ws, out, off, pair, stream in jobs:
+        assert hz.device_status(ws) == 0
+        rows = int(ref["out_offsets"][-1])
+        np.testing.assert_array_equal(out.cpu().numpy()[:rows], ref["out"][:rows])
+        np.testing.assert_array_equal(pair.cpu().numpy(), ref["pair"])
+
+
 @pytest.mark.parametrize("name", list(STRIP_BATCHES))
 def test_strips_give_up_instead_of_waiting_for_ever(monkeypatch, name):
     """The strips' own waits are bounded, in both forms of their exchange.  With no poll allowed the first meeting
