@@ -578,9 +578,12 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
 // workgroups take the slots given up, one after another, with a counter of their own.
 template <typename S>
 __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) {
-  if (C.status[0]) return;
   __shared__ __align__(16) unsigned char lds[strip_lds_of<S>()];
   int* flag = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 2;
+  // (all waves or none: a slot that gives up writes the word while the last workgroups may be starting)
+  if (threadIdx.x == 0) *flag = C.status[0];
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*flag)) return;
   int count = C.words[kStripCount], per_slot = C.words[kStripTop];
   if (count == 0) return;
   const int block = blockIdx.x;
