@@ -385,7 +385,7 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
     // iteration) instead of 144 while every image still has its workgroups at once.  One image,
     // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
     const int thin_groups = strip_groups(kShapeStripA, m_top, kModeStripThin);
-    const bool thin = !p.dynamic && strip == kShapeStripA && thin_groups <= kStripDirect &&
+    const bool thin = !p.dynamic && strip == kShapeStripA && thin_groups <= kStripThinTeams &&
                       B <= strip_slots(thin_groups, compute_units());
     if (thin) most = thin_groups;
     // (a quarter of the chip at most to an image: see sinkhorn_strip.hpp, who waits for whom)
@@ -601,10 +601,10 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
     for (int shape = kShapeStripA; shape <= kShapeStripD; ++shape) {
       if (!(p.mode & mode_strip_bit(shape))) continue;
       const int groups = std::min(mode_strip_groups(p.mode), std::max(strip_groups(shape, in->max_tokens, p.mode), 1));
-      const int slot_blocks = std::min(cus, (in->B + 7) / 8 * 8 * groups);
+      const int slot_blocks = kStripTeams * std::min(cus, (in->B + 7) / 8 * 8 * groups);
       const StripArgs TA{A, words + (shape - 1) * kStripShapeWords, cus, slot_blocks, strip_form_limit(),
                          cluster_spin_limit(), at<int32_t>(ws, L.status)};
-      const dim3 grid(slot_blocks + groups), block(kStripThreads);
+      const dim3 grid(slot_blocks + kStripTeams * groups), block(kStripThreads);
       if (shape == kShapeStripA) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
       else if (shape == kShapeStripB) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
       else if (shape == kShapeStripC) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);

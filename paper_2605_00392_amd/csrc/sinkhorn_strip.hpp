@@ -2,89 +2,91 @@
 // shapes of sinkhorn_cluster.hpp hold (the page sizes of other OCR models): the kernel matrix is
 // held as fp32 in the registers of several workgroups for all T iterations.
 //
-// The workgroups of all slots are resident together (one per compute unit and no more are
-// launched: each fills a compute unit's registers), a slot being as many workgroups as the
+// The workgroups of all slots are resident together (two per compute unit and no more are
+// launched: they fill its registers), a slot being as many compute units' as the
 // largest of the launch's images needs (the list's builder counts them: a host that only knows the
 // parameters does not know them when the kept counts are the caller's), and a slot works through its
-// share of the list with all its workgroups in step.  Slots of up to sixteen keep to one XCD.
+// share of the list with all its workgroups in step.  Slots of up to sixteen compute units keep to one XCD.
 //
 // Who waits for whom.  Calls on other streams may hold compute units with workgroups that wait for
-// their own slots, so that no slot gets complete: three calls with 10 + 11 + 11 workgroups of slots of
-// sixteen fill an XCD, and slots across XCDs can each lack workgroups that another's keep out.  So no
+// their own slots, so that no slot gets complete: three calls with slots of 10, 11 and 11 of sixteen
+// compute units fill an XCD, and slots across XCDs can each lack workgroups that another's keep out.  So no
 // slot waits for ever to be complete: before a slot's workgroups touch anything they meet, and one that
 // has waited too long (C.form_limit, some 30 ms) gives the slot up, for good and for all its workgroups,
-// which leave.  The images of slots given up are done by the launch's last `groups` workgroups,
+// which leave.  The images of slots given up are done by the launch's last workgroups, as many as a slot has,
 // which nobody else of the launch waits for and which do wait until they are all there.  They have
-// consecutive numbers, at most kStripMaxGroups / 8 = 8 of them on an XCD, so of four such calls (one per
-// hardware queue) at most 7 + 3 * 8 = 31 of an XCD's 32 compute units are held by workgroups that
-// wait for others of theirs (slots of sinkhorn_cluster.hpp: 7 each): the next always finds a place.
+// consecutive numbers, at most 2 kStripMaxGroups / 8 = 16 of them on an XCD, so of four such calls (one per
+// hardware queue) at most 15 + 3 * 16 = 63 of an XCD's 64 places are held by workgroups that
+// wait for others of theirs: the next always finds a place.  Slots of sinkhorn_cluster.hpp wait with up to 7
+// whole compute units each, which leaves c of them and 4 - c such calls 64 - 14 c >= 16 (4 - c) places: those
+// get on, and when they have left the clusters do.
 //
-// A workgroup's eight waves hold RPT whole rows each, a lane the columns lane, lane + 64, ...  An
-// iteration is two passes over the registers, widening every entry at both uses:
+// A workgroup's four waves hold RPT whole rows each, a lane the columns lane, lane + 64, ...; two workgroups
+// share a compute unit, as a rule of different images, so that one's exchange runs beside the other's
+// arithmetic.  An iteration is two passes over the registers, widening every entry at both uses:
 //   rows     a lane's share of the row sums of eight rows at a time; the 64 lanes' shares go
 //            through a reduce-scatter (halving exchanges) that leaves eight lanes with one row's
 //            total, so that the exchanges and the reciprocal are paid once for eight rows, and
 //            the x travel back through scalar registers;
-//   columns  sum_i x_i K_ij over the wave's rows, lane-local; the eight waves meet in LDS.
-// What bounds it: vector instruction issue in the two passes (two conversions and two multiply-adds
-// per entry, 3.7 us of an iteration), then the exchange (2 us in one trip, 6 in two).  Measured for
-// 100 iterations: 64 pages of 1083 tokens (four workgroups of 144 x 576 each) 0.91 -> 0.60 ms, 32
-// pages of 2137 (sixteen of 80 x 960) 2.48 -> 1.46 ms against strips that gave every row a reduction
-// of its own over the 64 lanes and a reciprocal in all of them (28 instructions a row beside 27 for
-// its nine columns' arithmetic); 16 pages of 4512 tokens (58 of 48 x 1792) 6.72 -> 3.92 ms against
-// streaming the matrices from memory every iteration.
+//   columns  sum_i x_i K_ij over the wave's rows, lane-local; the waves meet in LDS.
+// What bounds it: of an iteration's 12 600 clocks on 64 pages of 1083 tokens (two workgroups of 72 x 576 to a
+// compute unit) 4 500 are the two passes (two conversions and two multiply-adds per entry), the others the
+// exchange: sums to LDS and out 1 700, the trip 1 800, adding up and out again 1 200, the second trip
+// 2 000.  Against one workgroup of eight waves to a compute unit, with one trip among up to sixteen workgroups and
+// places put back to a "not yet" pattern (100 iterations): 32 pages of 2137 tokens 1.46 -> 1.20 ms, 16 pages of
+// 4512 3.90 -> 3.73, 64 pages of 1083 0.59 -> 0.59; one page of 2137 0.72 -> 0.52 ms, of 4512 0.85 -> 0.70.
+// Before those, strips that gave every row a reduction of its own: 0.91 (1083 tokens) and 2.48 ms (2137);
+// streaming the matrices from memory every iteration: 6.72 ms (4512).
 //
-// The exchange.  A few workgroups publish their column sums and everybody adds everybody's in
+// The exchange.  Up to four workgroups publish their column sums and everybody adds everybody's in
 // rank order.  With more of them (strip_direct) that means groups x (r + 1) doubles read by each
 // workgroup and iteration, so the columns are dealt out instead: a workgroup receives all the
 // others' sums for its share of the columns, adds them in a fixed order, takes the reciprocal and
 // publishes the finished y; everybody reads all y.  Two trips through memory instead of one, but
-// 2 (r + 1) values read instead of groups (r + 1).
-// Values travel as device-scope relaxed atomics, and a place holds a "not yet" pattern until its
-// value is there, so no counters and no barriers across workgroups; four buffers in turn (they lie
-// in the image's own kernel-matrix slot, see strip_exchange_doubles), cleared before the image:
-//   direct   a workgroup that publishes iteration i has seen everybody's sums of i - 1, whose
-//            owners had by then finished reading i - 2, so its place in the buffer of i - 2
-//            (= i + 2 modulo four) gets its "not yet" back now; the store is acknowledged (the
-//            wait before the next publication) before the sums of i + 1 go out, and nobody looks
-//            at the buffer of i + 2 before having seen those.
-//   shares   the only reader of a place in the sums' buffer i is the owner of the columns, which
-//            puts "not yet" back as soon as it has read it; that is acknowledged before the
-//            owner publishes the y of i + 1, without which nobody gets to iteration i + 2, let
-//            alone to the next use of the buffer, i + 4.  The y of i are put back by their owner
-//            once it has all the sums of i + 1, which every workgroup publishes after reading
-//            the y of i; acknowledged before the y of i + 2 go out, while the places are polled
-//            again for the y of i + 4, after those of i + 3 have been seen.
+// 2 (r + 1) values read instead of groups (r + 1).  (64 pages of 1083 tokens, eight workgroups each: 0.88 ms
+// with one trip, 0.81 with two at the time.)
+// Values travel as device-scope stores and loads past the caches, the loads straight into LDS, and carry in
+// their last bit which use of their place they belong to (the uses alternate), so no counters, no barriers
+// across workgroups and nothing put back.  (A sum's or y's last bit is 1e-16 of it; the reciprocal is good to 2e-15.)
+// The places lie in the image's own kernel-matrix slot, see strip_exchange_doubles, and are zero (of no use
+// yet) before the image:
+//   direct   two buffers in turn: a workgroup that publishes iteration i has seen everybody's sums of
+//            i - 1, whose owners had by then finished reading i - 2, which it overwrites.
+//   shares   one: the only reader of a sum is the owner of its column, who publishes the y of i after
+//            reading the sums of i, and nobody publishes sums of i + 1 before having read all y of i.
+//            The y of i are overwritten by their owner once it has all the sums of i + 1, which every
+//            workgroup publishes after reading the y of i.
+// A place is read by the same lane every iteration, so it is never seen to go back to an older use.
 #pragma once
 #include "common.hpp"
 #include "sinkhorn_team.hpp"
 
 namespace rtp {
 
-constexpr int kStripThreads = 512;
-// what a value's place holds until the value has been published: no sum has this bit pattern (a NaN)
-constexpr long long kStripNotYet = -1;
+constexpr int kStripThreads = 256, kStripWaves = kStripThreads / 64, kStripTeams = 2;   // workgroups to a compute unit
 
 struct StripArgs {
   SinkhornArgs S;
   int32_t* words;           // the shape's words, prepared by the kernel that built the lists
-  int cus;                  // compute units the slots may take
+  int cus;                  // compute units the slots may take, two workgroups on each
   int slot_blocks;          // workgroups of the launch that make up slots; the others are the last ones
   int form_limit;           // polls for a slot to be complete (0: every slot is given up at once, for tests)
   int spin_limit;
   int32_t* status;
 };
 
-__device__ __forceinline__ void ex_store(double* at, double v) {
-  __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Two places at once, `at` (even) doubles into an image's exchange area: device-scope stores of 16 bytes, of which
+// every 8 arrive whole.  A value's last bit says which use of its place it belongs to (`use`: 0 or 1).
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+constexpr int kExAgent = 16;   // (sc1: as far as all XCDs see it)
+__device__ __forceinline__ auto ex_resource(double* area) { return __builtin_amdgcn_make_buffer_rsrc(area, 0, 0x7fffffff, 0x00020000); }
+template <typename R>
+__device__ __forceinline__ void ex_store2(R ex, int at, double v0, double v1, uint32_t use) {
+  u32x4_t w = __builtin_bit_cast(u32x4_t, f64x2_t{v0, v1});
+  w[0] = (w[0] & ~1u) | use;
+  w[2] = (w[2] & ~1u) | use;
+  __builtin_amdgcn_raw_buffer_store_b128(w, ex, 8 * at, 0, kExAgent);
 }
-__device__ __forceinline__ void ex_not_yet(double* at) {
-  __hip_atomic_store(reinterpret_cast<long long*>(at), kStripNotYet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double ex_load(const double* at) {
-  return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ bool ex_missing(double v) { return __double_as_longlong(v) == kStripNotYet; }
 
 // Whether a poll that has failed `spin` times goes on (false: gave up, here or elsewhere).
 __device__ __forceinline__ bool ex_wait(const StripArgs& C, int spin) {
@@ -154,14 +156,13 @@ __device__ __forceinline__ bool strip_complete(int32_t* counter, int per_slot, i
 }
 
 // Where image `b`'s workgroups exchange their values: the upper end of its kernel-matrix slot
-// (strip_exchange_fits).  The sums' buffers first, then those of y (shares only), then the
-// pairing keys, groups x r of them.
+// (strip_exchange_fits).  The sums first, then the y (shares only).
 __device__ __forceinline__ double* strip_area(const SinkhornArgs& A, int shape, long long po, int m, int r, int groups) {
   const long long at = po + static_cast<long long>(m) * r - strip_exchange_doubles(shape, r, groups);
   return const_cast<double*>(A.kmat) + (at - at % kStripAlign);
 }
 
-// "Not yet" into workgroup `rank`'s part of image `b`'s exchange area, when it is a strip image.
+// Zeros (of no use yet) into workgroup `rank`'s part of image `b`'s exchange area, when it is a strip image.
 template <typename S>
 __device__ __forceinline__ void strip_clear(const StripArgs& C, int b, int rank) {
   const SinkhornArgs& A = C.S;
@@ -169,27 +170,80 @@ __device__ __forceinline__ void strip_clear(const StripArgs& C, int b, int rank)
   const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
   if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) return;
   if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) return;
-  const int groups = strip_groups(S::kShape, m, A.p.mode);
+  const int groups = strip_teams(S::kShape, m, A.p.mode);
   if (groups <= 1 || rank >= groups) return;
   double* area = strip_area(A, S::kShape, A.plan_offsets[b], m, r, groups);
-  const int total = static_cast<int>(strip_exchange_doubles(S::kShape, r, groups) - static_cast<long long>(groups) * r);
+  const int total = static_cast<int>(strip_exchange_doubles(S::kShape, r, groups));
   const int each = (total + groups - 1) / groups;
   const int e1 = min(total, (rank + 1) * each);
-  for (int e = rank * each + threadIdx.x; e < e1; e += kStripThreads) ex_not_yet(area + e);
+  for (int e = rank * each + threadIdx.x; e < e1; e += kStripThreads)
+    __hip_atomic_store(area + e, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// LDS of a strip workgroup: the waves' column sums (reused for the pairing's candidates), their
-// sums of x, the y (and the sum of x behind them), the received sums of the own columns; flags, and the
-// slot's loop over its images while one is worked on.
-template <typename S> constexpr int strip_lds_of() {
-  return 8 * (8 * S::kCols + 8 + S::kCols + 2 + S::kCols + 258) + 64;
-}
+// LDS of a strip workgroup.  First the waves' column sums, which the values received from the others (whole
+// pieces of 128 doubles, at most kReceive at a time) and in the end the pairing's candidates take the place of;
+// then the y with the sum of x behind them, the image's constants; flags, and the slot's loop over its images
+// while one is worked on.  Half a compute unit's 160 KB holds it.
+constexpr int kStripPiece = 128;
+template <typename S> struct StripLds {
+  static constexpr int kPitch = S::kCols + 2;          // of a wave's column sums: with its sum of x behind them, and a zero
+  static constexpr int kDirect = strip_direct(S::kShape, 1) ? kStripDirect * strip_row(S::kCols) : 0;
+  static constexpr int kShares = (S::kCols + 16 * kStripMaxGroups + kStripPiece - 1) / kStripPiece * kStripPiece;   // sums; behind them y
+  static constexpr int kReceive = kDirect > 2 * kShares ? kDirect : 2 * kShares;
+  static constexpr int kWaves = kStripWaves * kPitch;
+  static constexpr int kFirst = ((kReceive > kWaves ? kReceive : kWaves) + kStripPiece - 1) / kStripPiece * kStripPiece;
+  static constexpr int kBytes = 8 * (kFirst + S::kCols + 6) + 72;
+  static_assert(kBytes <= 160 * 1024 / kStripTeams, "a compute unit's workgroups share its LDS");
+};
+template <typename S> constexpr int strip_lds_of() { return StripLds<S>::kBytes; }
 // Workgroup barrier that orders LDS accesses only: published values still on their way are not
 // waited for, as __syncthreads would.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Before a first look, about as long as the values take to get here (64 clocks a unit; within an XCD, and
+// across).  A look at places that are being written costs more than the wait: 32 pages of 2137 tokens, 100
+// iterations, looking at once / after 4 units for the sums and 16 for the y: 1.50 / 1.19 ms; 16 pages of 4512
+// tokens, at once / after 12 and 20: 4.04 / 3.76.
+__device__ __forceinline__ void ex_pause(int units) {
+  for (int k = 0; k < units; k += 4) __builtin_amdgcn_s_sleep(4);
+}
+
+// `n` (even) published doubles from `src` into `rx`, straight from memory into LDS: wave `tw` takes every
+// kStripWaves-th piece of 128, requests them all, and asks again for a piece until all of it is of use
+// `use`; then `take(e, v0, v1)` gets values e and e + 1 of it.  No wave looks at another's pieces
+// (a barrier makes rx readable for all).  False: gave up.
+template <typename F>
+__device__ __forceinline__ bool strip_receive(const StripArgs& C, const double* src, int n, uint32_t use, double* rx, int tw,
+                                              int lane, F take) {
+  const int pieces = (n + kStripPiece - 1) / kStripPiece, last = n - 2;
+  auto request = [&](int k) {
+    const double* at = src + min(kStripPiece * k + 2 * lane, last);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)at,
+                                     (__attribute__((address_space(3))) void*)(rx + kStripPiece * k), 16, 0, kExAgent);
+  };
+#pragma unroll 1
+  for (int k = tw; k < pieces; k += kStripWaves) request(k);
+  int spin = 0;
+  bool seen = true;
+#pragma unroll 1
+  for (int k = tw; k < pieces; k += kStripWaves) {
+    f64x2_t v;
+    for (;;) {
+      __builtin_amdgcn_s_waitcnt(0);
+      asm volatile("" ::: "memory");
+      v = *reinterpret_cast<const f64x2_t*>(rx + kStripPiece * k + 2 * lane);
+      const u32x4_t w = __builtin_bit_cast(u32x4_t, v);
+      if (__ballot(((w[0] ^ use) | (w[2] ^ use)) & 1u) == 0) break;
+      if (!seen || !ex_wait(C, spin++)) { seen = false; break; }
+      request(k);
+    }
+    take(kStripPiece * k + 2 * lane, v[0], v[1]);
+  }
+  return seen;
 }
 
 // Row sums of eight rows (q[u]: this lane's share of row u): the total of row strip_row8(lane).
@@ -211,32 +265,41 @@ __device__ __forceinline__ double strip_reduce4(const double (&q)[8]) {
 __device__ __forceinline__ int strip_row4(int lane) { return 2 * (lane >> 5) + ((lane >> 4) & 1); }
 constexpr int strip_lane4(int u) { return 32 * (u >> 1) + 16 * (u & 1); }
 
-// The compiler forgets that it has seen rows a0 .. a0 + 7 (it would keep their entries' widened
-// copies otherwise).
+// A strip's entries in a lane's registers, two to an aligned pair of them.  (One by one the allocator
+// leaves no aligned pairs between them for the fp64 values and spills.)
 template <int RPT, int CPT>
-__device__ __forceinline__ void forget_rows(float (&K)[RPT][CPT], int a0) {
+struct StripEntries {
+  static_assert(RPT * CPT % 2 == 0, "whole pairs");
+  floatx2_t pair[RPT * CPT / 2];
+  __device__ __forceinline__ float get(int a, int c) const { return pair[(a * CPT + c) / 2][(a * CPT + c) % 2]; }
+  __device__ __forceinline__ void set(int a, int c, float v) { pair[(a * CPT + c) / 2][(a * CPT + c) % 2] = v; }
+  // The compiler forgets that it has seen rows a0 .. a1 - 1 (it would keep their entries' widened
+  // copies otherwise).
+  __device__ __forceinline__ void forget(int a0, int a1) {
 #pragma unroll
-  for (int a = 0; a < RPT; ++a)
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-      if (a >= a0 && a < a0 + 8) forget_origin(K[a][c]);
-}
+    for (int k = 0; k < RPT * CPT / 2; ++k)
+      if (k >= a0 * CPT / 2 && k < (a1 * CPT + 1) / 2) asm volatile("" : "+v"(pair[k]));
+  }
+};
 
 // One image on `groups` workgroups of a slot; this one is `rank` < groups.  `arrived`: the slot's
 // arrival count once they have all met at the image's end.  False: a wait was given up, leave the kernel.
 template <typename S>
 __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, int rank, int groups, int32_t* counter,
-                                                     int arrived, void* lds, int* s_flag) {
+                                                     int arrived, bool first, void* lds, int* s_flag) {
   constexpr int RPT = S::RPT, CPT = S::CPT, kCols = S::kCols, T = kStripThreads;
   constexpr int kChunks = (RPT + 7) / 8, kLast = RPT - 8 * (kChunks - 1);
   constexpr bool kKeepY = CPT <= 9;          // y in registers across the chunks of rows (else re-read from LDS)
   const SinkhornArgs& A = C.S;
   const DevParams& p = A.p;
   const int tt = threadIdx.x, tw = __builtin_amdgcn_readfirstlane(tt >> 6), lane = tt & 63;
-  const int lo = A.offsets[b];
-  const int n = A.offsets[b + 1] - lo;
-  const int m = min(max(A.keep[b], 0), n), r = n - m;        // (the list holds images with n > 0, r > 0 only)
-  const long long po = A.plan_offsets[b];
+  // (in scalar registers: the compiler does not see that these loads' values are the same in all lanes)
+  const int lo = __builtin_amdgcn_readfirstlane(A.offsets[b]);
+  const int n = __builtin_amdgcn_readfirstlane(A.offsets[b + 1]) - lo;
+  const int m = min(max(__builtin_amdgcn_readfirstlane(A.keep[b]), 0), n), r = n - m;   // (the list holds images with n > 0, r > 0 only)
+  const long long po_at = A.plan_offsets[b];
+  const long long po = static_cast<long long>((static_cast<unsigned long long>(static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(po_at >> 32)))) << 32) |
+                                              static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(po_at))));
   const float* __restrict__ Kg = k32_base(A.kmat, po);        // stored as fp32 (kKernelRowsF32)
   const int pitch = k32_pitch(r);
   int32_t* __restrict__ pair_out = A.pair_out;
@@ -246,34 +309,35 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   constexpr bool kMayDirect = strip_direct(S::kShape, 1);    // (the wider shapes never are)
   const bool direct = kMayDirect && strip_direct(S::kShape, groups);
   const int cw = strip_share(r, groups);                     // columns (the sum of x counted as column r) a workgroup owns
-  const int own0 = rank * cw, own = max(0, min(cw, r + 1 - own0));
+  const int own0 = rank * cw;
   double* area = groups > 1 ? strip_area(A, S::kShape, po, m, r, groups) : nullptr;
-  const int sums_buf = direct ? groups * (r + 1) : groups * groups * cw;   // doubles of one buffer of sums
-  double* ybufs = area + kStripBufs * sums_buf;
-  long long* keys = reinterpret_cast<long long*>(direct ? ybufs : ybufs + kStripBufs * groups * cw);
+  const int owned = strip_owned(r, cw);                      // doubles of y, and of a buffer of sums:
+  const int own = own0 < owned ? cw : 0;                     // (columns past the sum of x are zeros)
+  const int row = strip_row(r), sums_buf = groups * (direct ? row : owned);
+  // the pairing keys, `row` places to a workgroup: in a buffer of sums that everybody has read at the end
+  long long* keys = reinterpret_cast<long long*>(area + (direct ? p.iters % 2 * sums_buf : 0));
   if (pair_out)
     for (int i = tt; i < m_loc; i += T) pair_out[lo + row_base + i] = row_base + i;
 
-  double* xw = static_cast<double*>(lds);                    // [8][kCols]
-  double* xsum = xw + 8 * kCols;                             // [8]
-  double* ys = xsum + 8;                                     // [kCols] and the sum of x
-  double* red = ys + kCols + 2;                              // [groups][cw]
-  int* seen_words = reinterpret_cast<int*>(red + kCols + 258);   // [2]
+  constexpr int W = kStripWaves;
+  constexpr int kPitch = StripLds<S>::kPitch;
+  double* xw = static_cast<double*>(lds);                    // [W][kPitch]
+  double* ys = xw + StripLds<S>::kFirst;                     // [kCols] and the sum of x
+  double* rx = xw;                                           // received: [teams at a time][row], [groups][cw] or [owned]
+  int* seen_words = reinterpret_cast<int*>(ys + kCols + 6);  // [2]
 
-  float K[RPT][CPT];
+  // (buffer loads: a row that the workgroup does not have, or a column past the last one, reads as zero,
+  // with no mask and no address of its own in registers)
+  StripEntries<RPT, CPT> K;
 #pragma unroll
   for (int a = 0; a < RPT; ++a) {
-    const float* row = Kg + static_cast<long long>(row_base + min(8 * a + tw, m_loc - 1)) * pitch;
+    const bool there = W * a + tw < m_loc;
+    const float* at = Kg + static_cast<long long>(row_base + (there ? W * a + tw : 0)) * pitch;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(at), 0, there ? 4 * r : 0, 0x00020000);
 #pragma unroll
-    for (int c = 0; c < CPT; ++c) K[a][c] = row[min(64 * c + lane, r - 1)];
+    for (int c = 0; c < CPT; ++c) K.set(a, c, __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane + 256 * c, 0, 0)));
   }
-#pragma unroll
-  for (int a = 0; a < RPT; ++a)
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-      K[a][c] = (8 * a + tw < m_loc && 64 * c + lane < r) ? K[a][c] : 0.f;
-      forget_origin(K[a][c]);
-    }
+  K.forget(0, RPT);
 
   const double kz = exp((p.z - p.shift) / p.eps);
   const double x_init = exp(p.shift / p.eps);      // T = 0 leaves u = 0
@@ -282,11 +346,20 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   double xv[kChunks];                              // lanes strip_lane8(u) (last four or fewer rows: strip_lane4(u)): row 8 ch + u
 #pragma unroll
   for (int ch = 0; ch < kChunks; ++ch) xv[ch] = x_init;
-  const float inv_cw = 1.0f / static_cast<float>(cw);
+  if (tt == 0) {
+    ys[kCols + 2] = kz;
+    ys[kCols + 3] = static_cast<double>(r);
+    ys[kCols + 4] = static_cast<double>(m);
+    ys[kCols + 5] = static_cast<double>(1.0f / static_cast<float>(cw));
+  }
   __syncthreads();
 
   for (int it = 0; it < p.iters; ++it) {
-    const double row_dust = kz * y_dust;
+    if (first) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+    int fixed = kCols + 2;                             // (the image's constants are read anew: registers)
+    forget_origin(fixed);
+    const double row_dust = ys[fixed] * y_dust;
     double xs = 0.0, ly = 0.0;
     double t[kChunks > 1 ? CPT : 1];
     double y[kKeepY ? CPT : 1];
@@ -300,12 +373,12 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     }
 #pragma unroll
     for (int ch = 0; ch < kChunks; ++ch) {
-      if (ch > 0 && 64 * ch >= m_loc) continue;                // no row of this chunk exists (the same for every thread)
+      if (ch > 0 && 8 * W * ch >= m_loc) continue;                // no row of this chunk exists (the same for every thread)
       const bool four = ch == kChunks - 1 && kLast <= 4;       // (known when unrolled, like the bounds below)
       double q[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) q[u] = 0.0;
-      forget_rows(K, 8 * ch);
+      K.forget(8 * ch, min(8 * ch + 8, RPT));
       // (y from LDS comes in kAhead columns at a time, one group ahead)
       constexpr int kAhead = CPT > 15 && CPT <= 22 ? 4 : 2;       // (what fits the registers)
       double yn[kAhead];
@@ -331,12 +404,13 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
 #pragma unroll
             for (int u = 0; u < 8; ++u)
               if (8 * ch + u < RPT)
-                q[u] = fma(static_cast<double>(K[8 * ch + u < RPT ? 8 * ch + u : 0][c0 + c < CPT ? c0 + c : 0]), yc[c], q[u]);
+                q[u] = fma(static_cast<double>(K.get(8 * ch + u < RPT ? 8 * ch + u : 0, c0 + c < CPT ? c0 + c : 0)), yc[c], q[u]);
           }
       }
+      if (ch == 0) forget_origin(ly);       // (else the additions are put off to where ly is needed, with all y in registers until then)
       const double sum = four ? strip_reduce4(q) : strip_reduce8(q, lane);
       const int u_own = four ? strip_row4(lane) : strip_row8(lane);
-      xv[ch] = 8 * (8 * ch + u_own) + tw < m_loc ? rcp64(sum + row_dust) : 0.0;
+      xv[ch] = W * (8 * ch + u_own) + tw < m_loc ? rcp64(sum + row_dust) : 0.0;
       double x[8];                                               // the same in every lane (scalar registers)
 #pragma unroll
       for (int u = 0; u < 8; ++u)
@@ -344,146 +418,119 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
           x[u] = read_lane(xv[ch], four ? strip_lane4(u & 3) : strip_lane8(u));
           xs += x[u];
         }
-      forget_rows(K, 8 * ch);                                    // (entries are widened again, not kept widened)
+      K.forget(8 * ch, min(8 * ch + 8, RPT));                    // (entries are widened again, not kept widened)
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
         double acc = kChunks > 1 ? t[kChunks > 1 ? c : 0] : 0.0;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int a = 8 * ch + u;
-          if (a < RPT) acc = fma(static_cast<double>(K[a < RPT ? a : 0][c]), x[u], acc);
+          if (a < RPT) acc = fma(static_cast<double>(K.get(a < RPT ? a : 0, c)), x[u], acc);
         }
         if constexpr (kChunks > 1) t[c] = acc;
-        else xw[tw * kCols + 64 * c + lane] = acc;
+        else xw[tw * kPitch + 64 * c + lane] = acc;
         if (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
     if constexpr (kChunks > 1) {
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) xw[tw * kCols + 64 * c + lane] = t[c];
+      for (int c = 0; c < CPT; ++c) xw[tw * kPitch + 64 * c + lane] = t[c];
     }
-    if (lane == 0) xsum[tw] = xs;
+    __builtin_amdgcn_s_setprio(3);
+    if (lane < 2) xw[tw * kPitch + kCols + lane] = 0.0;
+    if (lane == 0) xw[tw * kPitch + r] = xs;           // (the columns past the last one are zero: this one is the sum of x)
     int& seen_all = seen_words[it & 1];                // (two words in turn: the next write of one is a whole iteration away)
     if (tt == 0) seen_all = 1;
     lds_barrier();
-    // this workgroup's sums: column e (the sum of x as column r) by thread e, e + 512, ...
-    constexpr int kE = (kCols + T) / T;                // r + 1 <= kCols + 1 columns
+    // this workgroup's sums: columns 2 k and 2 k + 1 (the sum of x as column r) by thread k, k + T, ...
     int te = tt;
+    const float inv_cw = static_cast<float>(ys[fixed + 3]);
     forget_origin(te);                                 // (the places' addresses are worked out anew: registers)
-    double part[kE];
+    auto own_sums = [&](int e) {
+      const f64x2_t* col = reinterpret_cast<const f64x2_t*>(xw + min(e, kCols));
+      f64x2_t acc = col[0];
 #pragma unroll
-    for (int l = 0; l < kE; ++l) {
-      const int e = te + T * l;
-      const double* col = e < r ? xw + min(e, kCols - 1) : xsum;
-      const int step = e < r ? kCols : 1;
-      double acc = 0.0;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) acc += col[w * step];
-      part[l] = acc;
-    }
-    const int buf = it & 3;
-    double* sums = area + buf * sums_buf;
-    if (groups > 1) {
-      __builtin_amdgcn_s_waitcnt(0);                   // what was put back last iteration has been acknowledged
-#pragma unroll
-      for (int l = 0; l < kE; ++l) {
-        const int e = te + T * l;
-        const int o = static_cast<int>((static_cast<float>(e) + 0.5f) * inv_cw);   // e / cw
-        if (e <= r) ex_store(sums + (direct ? rank * (r + 1) + e : (o * groups + rank) * cw + (e - o * cw)), part[l]);
+      for (int w = 1; w < W; ++w) {
+        const f64x2_t v = col[w * (kPitch / 2)];
+        acc[0] += v[0];
+        acc[1] += v[1];
       }
-      if (direct) {
-        double* ahead = area + ((it + 2) & 3) * sums_buf + rank * (r + 1);
-#pragma unroll
-        for (int l = 0; l < kE; ++l)
-          if (te + T * l <= r) ex_not_yet(ahead + te + T * l);
+      return acc;
+    };
+    const int sums = direct ? (it & 1) * sums_buf : 0; // (places are counted from `area`)
+    const uint32_t use = direct ? ~(it >> 1) & 1 : ~it & 1;
+    const auto ex = ex_resource(area);
+    if (groups > 1) {
+      const int published = direct ? row : owned;
+#pragma unroll 2
+      for (int e = 2 * te; e < published; e += 2 * T) {
+        const int o = static_cast<int>((static_cast<float>(e) + 0.5f) * inv_cw);   // e / cw
+        const f64x2_t v = own_sums(e);
+        ex_store2(ex, sums + (direct ? rank * row + e : (o * groups + rank) * cw + (e - o * cw)),
+                  e <= r ? v[0] : 0.0, e < r ? v[1] : 0.0, use);
       }
     }
     // (while the sums travel) the dustbins' scalings from the previous y
-    x_dust = static_cast<double>(r) * rcp64(kz * (wave_sum_dpp(ly) + y_dust));
-    const double col_dust = kz * x_dust;
+    x_dust = ys[fixed + 1] * rcp64(ys[fixed] * (wave_sum_dpp(ly) + y_dust));
+    const double col_dust = ys[fixed] * x_dust;
     bool seen = true;
-    if (kMayDirect && groups > 1 && direct) {
-      // everybody's sums of the own columns, four workgroups at a time, added in rank order
-#pragma unroll
-      for (int l = 0; l < kE; ++l) part[l] = 0.0;
-      for (int g0 = 0; g0 < groups; g0 += 4) {
-        double v[kE][4];
-        for (int spin = 0;; ++spin) {
-          bool ready = true;
-#pragma unroll
-          for (int l = 0; l < kE; ++l)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) v[l][g] = ex_load(sums + min(g0 + g, groups - 1) * (r + 1) + min(te + T * l, r));
-#pragma unroll
-          for (int l = 0; l < kE; ++l)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) ready = ready && !ex_missing(v[l][g]);
-          if (ready) break;
-          if (!seen || !ex_wait(C, spin)) { seen = false; break; }
-        }
-#pragma unroll
-        for (int l = 0; l < kE; ++l)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) part[l] += g0 + g < groups ? v[l][g] : 0.0;
+    auto keep = [&](int e, double v0, double v1) {     // y (and the sum of x) of columns e and e + 1
+      if (e <= r) ys[e < r ? e : kCols] = v0;
+      if (e + 1 <= r) ys[e + 1 < r ? e + 1 : kCols] = v1;
+    };
+    auto finish = [&](int e, double sum) { return e < r ? rcp64(sum + col_dust) : sum; };
+    if (groups == 1) {
+      for (int e = 2 * te; e <= r; e += 2 * T) {
+        const f64x2_t v = own_sums(e);
+        keep(e, finish(e, v[0]), finish(e + 1, v[1]));
       }
-    }
-    if (groups > 1 && !direct) {
-      constexpr int kLoads = (kCols + 256 + T - 1) / T;      // groups cw <= r + groups values
-      {
-        double* in = sums + rank * groups * cw;
-        double v[kLoads];
-        bool mine[kLoads];
-#pragma unroll
-        for (int l = 0; l < kLoads; ++l) {
-          const int e = te + T * l, g = static_cast<int>((static_cast<float>(e) + 0.5f) * inv_cw);
-          mine[l] = e < groups * cw && e - g * cw < own;
+    } else if (kMayDirect && direct) {
+      // everybody's sums, added in rank order
+      lds_barrier();                                   // (the waves' column sums have been read)
+      seen = strip_receive(C, area + sums, groups * row, use, rx, tw, lane, [](int, double, double) {});
+      lds_barrier();
+      for (int e = 2 * te; e < row; e += 2 * T) {
+        f64x2_t acc = *reinterpret_cast<const f64x2_t*>(rx + e);
+        for (int g = 1; g < groups; ++g) {
+          const f64x2_t v = *reinterpret_cast<const f64x2_t*>(rx + g * row + e);
+          acc[0] += v[0];
+          acc[1] += v[1];
         }
-        for (int spin = 0;; ++spin) {
-          bool ready = true;
-#pragma unroll
-          for (int l = 0; l < kLoads; ++l) v[l] = ex_load(in + (mine[l] ? te + T * l : 0));
-#pragma unroll
-          for (int l = 0; l < kLoads; ++l) ready = ready && !(mine[l] && ex_missing(v[l]));
-          if (ready) break;
-          if (!ex_wait(C, spin)) { seen = false; break; }
-        }
-#pragma unroll
-        for (int l = 0; l < kLoads; ++l)
-          if (mine[l]) red[te + T * l] = v[l];
-        lds_barrier();
-        // sixteen lanes add up a column
-        double* yout = ybufs + buf * groups * cw + own0;
-        for (int k = te >> 4; k < own; k += T / 16) {
-          double acc = 0.0;
-          for (int g = te & 15; g < groups; g += 16) acc += red[g * cw + k];
-          acc = group_sum<4>(acc);
-          if ((te & 15) == 0) ex_store(yout + k, own0 + k < r ? rcp64(acc + col_dust) : acc);
-        }
-        // put back: the sums just read, and the previous iteration's y (all the sums of this
-        // iteration are here, so everybody has read those)
-#pragma unroll
-        for (int l = 0; l < kLoads; ++l)
-          if (mine[l]) ex_not_yet(in + te + T * l);
-        double* ylast = ybufs + ((it + 3) & 3) * groups * cw + own0;
-        for (int k = te; k < own; k += T) ex_not_yet(ylast + k);
+        keep(e, finish(e, acc[0]), finish(e + 1, acc[1]));
       }
-      const double* yin = ybufs + buf * groups * cw;
-      for (int spin = 0;; ++spin) {
-        bool ready = true;
-#pragma unroll
-        for (int l = 0; l < kE; ++l) part[l] = ex_load(yin + min(te + T * l, r));
-#pragma unroll
-        for (int l = 0; l < kE; ++l) ready = ready && !ex_missing(part[l]);
-        if (ready) break;
-        if (!seen || !ex_wait(C, spin)) { seen = false; break; }
+    } else {
+      // the others' sums of the own columns
+      const int in = sums + rank * groups * cw;
+      lds_barrier();                                   // (the waves' column sums have been read)
+      ex_pause(groups <= kStripXcdGroups ? 0 : groups <= kStripTeams * kStripXcdGroups ? 4 : 12);
+      if (own > 0) seen = strip_receive(C, area + in, groups * cw, use, rx, tw, lane, [](int, double, double) {});
+      lds_barrier();
+      // 4, 16 or 32 lanes add up two columns: about all threads at work, each on as few workgroups' as that allows
+      const int yout = sums_buf + own0;
+      const int wide = cw <= 16 ? 5 : cw <= 32 ? 4 : 2, lanes = 1 << wide;
+      for (int k = 2 * (te >> wide); k < own; k += 2 * (T >> wide)) {
+        f64x2_t acc = {0.0, 0.0};
+#pragma unroll 4
+        for (int g = te & (lanes - 1); g < groups; g += lanes) {
+          const f64x2_t v = *reinterpret_cast<const f64x2_t*>(rx + g * cw + k);
+          acc[0] += v[0];
+          acc[1] += v[1];
+        }
+        double v0 = group_sum<2>(acc[0]), v1 = group_sum<2>(acc[1]);
+        if (wide >= 4) {
+          v0 += dpp_move<0x141>(v0);
+          v1 += dpp_move<0x141>(v1);
+          v0 += dpp_move<0x140>(v0);
+          v1 += dpp_move<0x140>(v1);
+        }
+        if (wide == 5) {
+          v0 = add_xor_lane<16>(v0);
+          v1 = add_xor_lane<16>(v1);
+        }
+        if ((te & (lanes - 1)) == 0) ex_store2(ex, yout + k, finish(own0 + k, v0), finish(own0 + k + 1, v1), use);
       }
-    }
-    const bool finished = groups > 1 && !direct;       // `part` holds y already
-#pragma unroll
-    for (int l = 0; l < kE; ++l) {
-      const int e = te + T * l;
-      const double v = finished || e >= r ? part[l] : rcp64(part[l] + col_dust);
-      if (e <= r) ys[e < r ? e : kCols] = v;
+      ex_pause(groups <= kStripTeams * kStripXcdGroups ? 16 : 20);
+      if (!strip_receive(C, area + sums_buf, owned, use, rx + StripLds<S>::kShares, tw, lane, keep)) seen = false;
     }
     if (!seen) seen_all = 0;
     lds_barrier();
@@ -494,14 +541,14 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       }
       return false;
     }
-    y_dust = static_cast<double>(m) * rcp64(kz * (ys[kCols] + x_dust));
+    y_dust = ys[fixed + 2] * rcp64(ys[fixed] * (ys[kCols] + x_dust));
   }
   __syncthreads();
 
   // ---- plan and this workgroup's best partner per column ----
   float* P = A.plan_out ? A.plan_out + po : nullptr;
-  float* pv = static_cast<float*>(lds);                        // [8][kCols], where the sums were
-  int* pi = reinterpret_cast<int*>(pv + 8 * kCols);            // [8][kCols]
+  float* pv = static_cast<float*>(lds);                        // [W][kCols], where the sums were
+  int* pi = reinterpret_cast<int*>(pv + W * kCols);            // [W][kCols]
   int lane_p = lane, row_p = row_base + tw;
   forget_origin(lane_p);                                       // (keeps the entries' offsets out of the loop's registers)
   forget_origin(row_p);
@@ -517,9 +564,9 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     int bi = 0x7fffffff;
 #pragma unroll
     for (int a = 0; a < RPT; ++a) {
-      const int i = row_p + 8 * a;
-      if (8 * a + tw < m_loc && j < r) {
-        const float v = static_cast<float>(x[a] * static_cast<double>(K[a][c]) * yj);
+      const int i = row_p + W * a;
+      if (W * a + tw < m_loc && j < r) {
+        const float v = static_cast<float>(x[a] * static_cast<double>(K.get(a, c)) * yj);
         if (P) P[static_cast<long long>(i) * r + j] = v;
         if (v > bv) { bv = v; bi = i; }
       }
@@ -535,15 +582,15 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       float bv = -1.f;
       int bi = 0x7fffffff;
 #pragma unroll
-      for (int w = 0; w < 8; ++w) {
+      for (int w = 0; w < W; ++w) {
         const float ov = pv[w * kCols + e];
         const int oi = pi[w * kCols + e];
         if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
       }
       if (groups == 1)
-        pair_out[lo + m + e] = static_cast<float>(x_dust * kz * ys[e]) > bv ? -1 : bi;
+        pair_out[lo + m + e] = static_cast<float>(x_dust * ys[kCols + 2] * ys[e]) > bv ? -1 : bi;
       else
-        __hip_atomic_store(keys + static_cast<long long>(rank) * r + e,
+        __hip_atomic_store(keys + rank * row + e,
                            (static_cast<long long>(__float_as_int(bv)) << 32) | static_cast<unsigned>(0x7fffffff - bi),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -556,7 +603,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       if (e >= r) break;
       long long best = static_cast<long long>(__float_as_int(-1.f)) << 32;
       for (int g = tt & 7; g < groups; g += 8) {
-        const long long key = __hip_atomic_load(keys + static_cast<long long>(g) * r + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const long long key = __hip_atomic_load(keys + g * row + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         best = key > best ? key : best;
       }
 #pragma unroll
@@ -566,7 +613,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       }
       if ((tt & 7) == 0)
         pair_out[lo + m + e] =
-            static_cast<float>(x_dust * kz * ys[e]) > __int_as_float(static_cast<int>(best >> 32)) ? -1 : 0x7fffffff - static_cast<int>(best);
+            static_cast<float>(x_dust * ys[kCols + 2] * ys[e]) > __int_as_float(static_cast<int>(best >> 32)) ? -1 : 0x7fffffff - static_cast<int>(best);
     }
   }
   return true;
@@ -577,19 +624,21 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
 // exchange area cleared), one of the image's workgroups at its end (the pairing keys out).  The last
 // workgroups take the slots given up, one after another, with a counter of their own.
 template <typename S>
-__global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) {
+__global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_strips(StripArgs C) {
   __shared__ __align__(16) unsigned char lds[strip_lds_of<S>()];
   int* flag = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 2;
   // (all waves or none: a slot that gives up writes the word while the last workgroups may be starting)
   if (threadIdx.x == 0) *flag = C.status[0];
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(*flag)) return;
-  int count = C.words[kStripCount], per_slot = C.words[kStripTop];
+  int count = C.words[kStripCount];
   if (count == 0) return;
+  const int units = C.words[kStripTop];
+  int per_slot = kStripTeams * units;
   const int block = blockIdx.x;
   bool last = block >= C.slot_blocks;
-  int slots = strip_slots(per_slot, C.cus), slot, rank;
-  if (per_slot <= kStripXcdGroups) {                   // one XCD per slot
+  int slots = strip_slots(units, C.cus), slot, rank;
+  if (units <= kStripXcdGroups) {                   // one XCD per slot
     slots = min(slots, (count + 7) / 8 * 8);
     slot = (block & 7) * (slots >> 3) + (block >> 3) / per_slot;
     rank = (block >> 3) % per_slot;
@@ -623,7 +672,7 @@ __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) 
         // (every workgroup of the slot takes the same decisions: they read the same words)
         if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
         if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
-        const int groups = strip_groups(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
+        const int groups = strip_teams(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
         int32_t* counter = C.words + (last ? kStripLast : kStripCounters + slot);
         strip_clear<S>(C, b, rank);
         arrived += per_slot;
@@ -633,7 +682,7 @@ __global__ __launch_bounds__(kStripThreads) void k_sinkhorn_strips(StripArgs C) 
           if (threadIdx.x == 0) {
             at[0] = slot, at[1] = k, at[2] = arrived, at[3] = slots, at[4] = count, at[5] = per_slot, at[6] = rank, at[7] = last, at[8] = form_limit;
           }
-          if (!sinkhorn_strip_image<S>(C, b, rank, groups, counter, arrived, lds, flag)) return;
+          if (!sinkhorn_strip_image<S>(C, b, rank, groups, counter, arrived, 2 * slot < slots, lds, flag)) return;
           slot = __builtin_amdgcn_readfirstlane(at[0]);
           k = __builtin_amdgcn_readfirstlane(at[1]);
           arrived = __builtin_amdgcn_readfirstlane(at[2]);

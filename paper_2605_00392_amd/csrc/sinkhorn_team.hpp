@@ -81,14 +81,15 @@ using TeamTall = TeamShape<8, 3, 19, 8>;  // M <= 1216, R <= 64
 using TeamWideA = TeamShape<8, 4, 14, 8>;   // M <= 448, R <= 128
 using TeamWideB = TeamShape<8, 5, 24, 6>;   // M <= 384, R <= 192
 using TeamWideC = TeamShape<8, 5, 20, 7>;   // M <= 320, R <= 224
-// A workgroup's strip of a larger image in k_sinkhorn_strips (sinkhorn_strip.hpp), when it has
-// more than 128 pruned tokens: eight waves of RPT rows each, the 64 lanes across the columns.
+// What a compute unit holds of a larger image in k_sinkhorn_strips (sinkhorn_strip.hpp), when it has
+// more than 128 pruned tokens: eight waves of RPT rows each, the 64 lanes across the columns.  Two
+// workgroups (teams) of four waves share it, as a rule of different images.
 enum { kStripNone = 0, kShapeStripA = 1, kShapeStripB = 2, kShapeStripC = 3, kShapeStripD = 4 };
 template <int SHAPE, int RPT_, int CPT_>
 struct StripShape {
-  static constexpr int kShape = SHAPE, RPT = RPT_, CPT = CPT_, kRows = 8 * RPT, kCols = 64 * CPT;
+  static constexpr int kShape = SHAPE, RPT = RPT_, CPT = CPT_, kRows = 8 * RPT, kTeamRows = 4 * RPT, kCols = 64 * CPT;
 };
-using StripA = StripShape<kShapeStripA, 18, 9>;    // 144 rows x 576 columns per workgroup
+using StripA = StripShape<kShapeStripA, 18, 9>;    // 144 rows x 576 columns per compute unit
 using StripB = StripShape<kShapeStripB, 10, 15>;   // 80 rows x 960 columns
 using StripC = StripShape<kShapeStripC, 8, 22>;    // 64 rows x 1408 columns
 using StripD = StripShape<kShapeStripD, 6, 28>;    // 48 rows x 1792 columns
@@ -122,7 +123,7 @@ constexpr int kVariantA = 0, kVariantDual = 1, kVariantDual48 = 2, kVariantB = 3
 // (The strip kernel's list lies elsewhere: StripWords.)
 constexpr int kListTiled = 14, kListMid = 15, kWorkLists = 16;
 // Words of the strip kernels, in device memory that only they use.  Per strip shape: how many images
-// it has, how many workgroups the one that needs most of them takes, where its images begin in the
+// it has, how many compute units the one that needs most of them takes, where its images begin in the
 // list, arrival counters of its slots and of the last workgroups, and a give-up word (zero when the
 // kernel starts); then the list.
 constexpr int kStripMaxSlots = 64, kStripShapes = 4;
@@ -167,8 +168,8 @@ __host__ __device__ inline bool cluster_fits(int m, int r, int mode) {
   return cluster_shape(m, r) >= 0 && cluster_groups(m, r) <= mode_cluster_groups(mode);
 }
 // The strip kernel.  Bits 12-15 of `mode`: the strip shapes it is launched for (an image takes the
-// narrowest of them that holds its columns); bit 16: shape A with 64 rows a workgroup instead of 144;
-// bits 17-23: how many workgroups an image may take.
+// narrowest of them that holds its columns); bit 16: shape A with 64 rows a compute unit instead of 144;
+// bits 17-23: how many compute units an image may take.
 constexpr int kModeStripShift = 12, kModeStripThin = 1 << 16, kModeStripGroupsShift = 17, kStripMaxGroups = 64;
 __host__ __device__ inline int mode_strip_bit(int shape) { return shape ? 1 << (kModeStripShift + shape - 1) : 0; }
 __host__ __device__ inline int mode_strips(int mode) { return (mode >> kModeStripShift) & 15; }
@@ -194,30 +195,48 @@ __host__ __device__ inline int widest_strip(int mode) {
     if (mode & mode_strip_bit(shape)) widest = shape;
   return widest;
 }
+// compute units an image takes of a shape's (divisions by constants) ...
+__host__ __device__ inline int strip_groups(int shape, int m, int mode) {
+  return shape == kShapeStripA ? ((mode & kModeStripThin) ? (m + kStripThinRows - 1) / kStripThinRows : (m + StripA::kRows - 1) / StripA::kRows)
+       : shape == kShapeStripB ? (m + StripB::kRows - 1) / StripB::kRows
+       : shape == kShapeStripC ? (m + StripC::kRows - 1) / StripC::kRows : (m + StripD::kRows - 1) / StripD::kRows;
+}
+// ... and workgroups: at most two to a compute unit.  Thin strips take as many as the one-trip exchange
+// allows while they have 32 rows each (16 of them hold the 1024 rows that thin strips are used for).
+constexpr int kStripThinTeams = 16;
+__host__ __device__ inline int strip_teams(int shape, int m, int mode) {
+  if (shape == kShapeStripA && (mode & kModeStripThin)) {
+    const int most = (m + kStripThinRows / 2 - 1) / (kStripThinRows / 2), least = (m + StripA::kTeamRows - 1) / StripA::kTeamRows;
+    return most <= kStripThinTeams ? most : least > kStripThinTeams ? least : kStripThinTeams;
+  }
+  return shape == kShapeStripA ? (m + StripA::kTeamRows - 1) / StripA::kTeamRows
+       : shape == kShapeStripB ? (m + StripB::kTeamRows - 1) / StripB::kTeamRows
+       : shape == kShapeStripC ? (m + StripC::kTeamRows - 1) / StripC::kTeamRows : (m + StripD::kTeamRows - 1) / StripD::kTeamRows;
+}
 // A strip image's workgroups exchange their sums in the image's own slot of the kernel matrix,
 // whose m r doubles hold fp32 entries: the upper end is free.  A few workgroups read all the
 // others' column sums (one trip); of more of them each is handed the sums of its share of
-// the columns and everybody reads back the finished y (two trips, but 1 / groups of the reading).
-// `strip_share`: columns (and the sum of x) a workgroup owns.
-constexpr int kStripDirect = 16, kStripBufs = 4;
-// (Measured: 64 pages of 1083 tokens, 4 workgroups each, 0.60 ms direct, 0.81 in shares; 32 pages of
-// 2137 tokens, 16 each, 1.46 and 1.64; the wider shapes' registers leave no room for the direct reading.)
-__host__ __device__ constexpr bool strip_direct(int shape, int groups) { return shape <= kShapeStripB && groups <= kStripDirect; }
-__host__ __device__ inline int strip_share(int r, int groups) { return (r + groups) / groups; }   // ceil((r + 1) / groups)
-__host__ __device__ inline long long strip_exchange_doubles(int shape, int r, int groups) {
-  if (groups <= 1) return 0;
-  const long long keys = static_cast<long long>(groups) * r;
-  if (strip_direct(shape, groups)) return static_cast<long long>(kStripBufs) * groups * (r + 1) + keys;
-  return static_cast<long long>(kStripBufs) * (groups + 1) * strip_share(r, groups) * groups + keys;
+// the columns and everybody reads back the finished y (two trips, but 1 / teams of the reading).
+// `strip_share`: columns (and the sum of x) a workgroup owns, whole pieces of 64 bytes; `strip_owned`: those of
+// all that own any.  A direct buffer's rows are even: values are read two at a time.
+constexpr int kStripDirect = 4;
+__host__ __device__ constexpr bool strip_direct(int shape, int teams) { return shape <= kShapeStripB && teams <= kStripDirect; }
+__host__ __device__ constexpr int strip_row(int r) { return (r + 2) & ~1; }
+__host__ __device__ inline int strip_share(int r, int teams) { return ((r + teams) / teams + 7) & ~7; }   // >= (r + 1) / teams
+__host__ __device__ inline int strip_owned(int r, int share) { return (r + share) / share * share; }       // <= r + 8 teams
+__host__ __device__ inline long long strip_exchange_doubles(int shape, int r, int teams) {
+  if (teams <= 1) return 0;
+  if (strip_direct(shape, teams)) return 2ll * teams * strip_row(r);      // two buffers
+  return (teams + 1ll) * strip_owned(r, strip_share(r, teams));
 }
 constexpr int kStripAlign = 16;   // doubles
 // (fits 32 bits: m r <= kMaxTokens^2 / 4.  The score kernels ask this once per tile, so the division in
 // strip_share is left to the few images that a bound without it does not settle.)
-__host__ __device__ inline bool strip_exchange_fits(int shape, int m, int r, int groups) {
+__host__ __device__ inline bool strip_exchange_fits(int shape, int m, int r, int teams) {
   const int room = m * r - 2 - m * ((r + 3) & ~3) / 2 - 2 * kStripAlign;   // (one double of alignment, see k32_base)
-  return kStripBufs * (groups + 1) * (r + groups) + groups * r <= room || strip_exchange_doubles(shape, r, groups) <= room;
+  return 2 * (teams + 1) * (r + 8 * teams) <= room || strip_exchange_doubles(shape, r, teams) <= room;
 }
-// Slots of `groups` workgroups that `cus` compute units hold, a workgroup each: up to half an XCD they
+// Slots of `groups` compute units (two workgroups each) that `cus` of them hold: up to half an XCD they
 // keep to one (a multiple of eight slots, eight XCDs assumed), larger ones take consecutive workgroups.
 // A value reaches another workgroup in 0.27 to 0.29 us in an XCD, in 0.37 to 0.50 us across (one way).
 constexpr int kStripXcdGroups = 16;
@@ -225,11 +244,6 @@ __host__ __device__ inline int strip_slots(int groups, int cus) {
   const int most = groups <= kStripXcdGroups ? cus / 8 / (groups > 0 ? groups : 1) : cus / groups;
   if (groups <= kStripXcdGroups) return 8 * (most < kStripMaxSlots / 8 ? most : kStripMaxSlots / 8);
   return most < kStripMaxSlots ? most : kStripMaxSlots;
-}
-__host__ __device__ inline int strip_groups(int shape, int m, int mode) {   // (divisions by constants)
-  return shape == kShapeStripA ? ((mode & kModeStripThin) ? (m + kStripThinRows - 1) / kStripThinRows : (m + StripA::kRows - 1) / StripA::kRows)
-       : shape == kShapeStripB ? (m + StripB::kRows - 1) / StripB::kRows
-       : shape == kShapeStripC ? (m + StripC::kRows - 1) / StripC::kRows : (m + StripD::kRows - 1) / StripD::kRows;
 }
 // Whose matrices may be held as fp32 there (the rounding takes the plan's relative error against 64
 // bits from 2.6e-8 to 3.4e-8 for fp32 tokens and from 1.386e-7 to 1.405e-7 for bf16 ones, 1260 x 240):
@@ -249,8 +263,8 @@ __host__ __device__ inline bool held_f32(int m, int r, int mode) {
 __host__ __device__ inline bool strip_fits(int m, int r, int mode) {
   const int shape = strip_shape(r, mode);
   if (m <= 0 || !shape || !held_f32(m, r, mode)) return false;
-  const int groups = strip_groups(shape, m, mode);
-  return groups <= mode_strip_groups(mode) && (groups == 1 || strip_exchange_fits(shape, m, r, groups));
+  const int teams = strip_teams(shape, m, mode);
+  return strip_groups(shape, m, mode) <= mode_strip_groups(mode) && (teams == 1 || strip_exchange_fits(shape, m, r, teams));
 }
 // The multi-workgroup sweep kernels (sinkhorn_sweep.hpp) take up to this many
 // pruned tokens.

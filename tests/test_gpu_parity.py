@@ -394,6 +394,21 @@ def test_dynamic_retention_in_two_strip_shapes_through_the_fused_call():
     _assert_fused_equals_staged(f, s, batch)
 
 
+@pytest.mark.parametrize("iters", [1, 2, 3, 6])
+def test_strips_of_half_a_compute_unit_at_their_edges(iters):
+    """Workgroups of 72 x 576 and 40 x 960: one of them, the last number of them that reads everybody's sums (four)
+    and the first that deals the columns out (five), more than an XCD's sixteen, and pruned counts whose
+    shares, rows of fours and pairs end unevenly."""
+    shapes = [(72, 300), (73, 576), (288, 573), (289, 574), (360, 575), (41, 577), (160, 960), (161, 959), (400, 958),
+              (640, 601), (641, 605), (1151, 133)]
+    batch = _clustered([m + r for m, r in shapes], 128, "bf16", 44, iters=iters, ratio=1280.0 / 2240.0)
+    keep = [m for m, _ in shapes]
+    s = hz.run_staged(batch, keep_counts_in=keep)
+    assert s["status"] == 0
+    rep = hz.compare_batch(batch, s, staged=True, keep_counts=keep)
+    _log(rep, f"half strips {iters}")
+
+
 def test_multi_workgroup_resident_sinkhorn_wide_strips_fill_the_chip():
     """A fixed retention under which the longest image takes four strips: slots of four workgroups,
     64 of them, more images than slots, through the fused call (no launches of the streaming
