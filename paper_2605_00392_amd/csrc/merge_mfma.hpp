@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kMergeMidThreads) __attribute__((amdgpu_waves_per_e
     for (long long item = blockIdx.x; item < items; item += gridDim.x) {
       __syncthreads();   // the previous tile's last LDS reads
       const int k = static_cast<int>(item / tiles_t);
-      merge_tile(TA, work[kWorkLists + kListTiled * B + k], static_cast<int>(item - static_cast<long long>(k) * tiles_t), lds);
+      merge_tile<kMergeTileCols>(TA, work[kWorkLists + kListTiled * B + k], static_cast<int>(item - static_cast<long long>(k) * tiles_t), lds);
     }
   }
   if (tiles_m > 0 && merge_mid_runs(work + kListMid, mid_min)) {

@@ -10,31 +10,36 @@
 // wants eight consecutive pruned rows of one feature per lane, so their tile is
 // transposed on its way into LDS.
 //
-// Workgroup = 4 waves as 2 x 2 on a tile of 128 kept rows x 128 features, 32
-// pruned rows per step, LDS double-buffered; a wave owns 64 x 64 = 4 x 4 matrix
-// tiles.  P's LDS rows are 64 bytes of payload on a pitch of 80.  A feature row of
-// the turned pruned rows has its four 16-byte pieces (eight pruned rows each) in
-// four of eight slots, slot = piece ^ (feature / 16 % 8), on a pitch of 144: the
-// 64 lanes of a turning 4-byte write (16 groups of eight features x 4 pairs of
-// pruned rows) then fall into 64 different banks (with the pieces in place they
-// fell into 8), and the fragment reads stay conflict-free.  The finished tile
+// Workgroup = 4 waves as 2 x 2 on a tile of 128 kept rows x 256 features (128 in small
+// batches, which then have tiles for twice as many workgroups), 32
+// pruned rows per step, LDS double-buffered, two workgroups per compute unit; a wave owns 64 rows x half of the features.  P's LDS
+// rows are 64 bytes of payload on a pitch of 80.  The finished tile
 // goes through LDS once more so that the kept rows are read and the merged rows
 // written 16 bytes per lane.
+//
+// What bounds it: 16 pages of 4512 tokens take 0.577 ms, 341 useful TFLOP/s and twice that executed (29 % of the
+// matrix cores' rate); a step's plan entries (16 four-byte loads a thread, their rows being 4-byte aligned) and
+// their split are paid once per 256 features.  Before, with 128 features and the pruned rows turned
+// by 4-byte LDS writes on their way from registers: 0.847 ms; 32 pages of 2137 tokens 0.422 -> 0.305, 64 of 1083
+// 0.274 -> 0.202.  One page of 4512 tokens: 0.118 with 256 features a tile, 0.100 with 128 (0.104 before).
 #pragma once
 #include "common.hpp"
 #include "scores_mfma.hpp"
+#include "scores_tiled.hpp"
 #include "sinkhorn_team.hpp"
 
 namespace rtp {
 
 constexpr int kMergeTileRows = 128;    // kept rows per workgroup tile
-constexpr int kMergeTileCols = 128;    // features per workgroup tile
+constexpr int kMergeTileCols = 256;    // features per workgroup tile (a width of 128 (2 k + 1) leaves half of the last)
+constexpr int kMergeThinCols = 128;    // of small batches
 constexpr int kMergeTileStep = 32;     // pruned rows per step
 constexpr int kMergeTilePitch = 80;    // LDS bytes per staged row of P (32 bf16 + padding)
-constexpr int kMergeTurnedPitch = 144; // LDS bytes per feature row of the turned pruned rows: eight 16-byte slots + padding
 constexpr int kMergeTiledThreads = 256;
-constexpr int kMergeTiledLdsBytes = 2 * 128 * (2 * kMergeTilePitch + kMergeTurnedPitch);   // merge_tile's LDS buffer (its staging tiles; the output tile fits too)
-constexpr int kMergeOutPitch = kMergeTileCols + 4;   // floats per row of the output staging tile
+constexpr int kMergeOperandBytes = kMergeTileRows * kMergeTilePitch;      // P hi or P lo of a step
+// merge_tile's LDS buffer: its staging tiles (P hi, P lo, pruned rows, twice); the output tile fits too
+constexpr int merge_tiled_lds(int cols) { return 2 * (2 * kMergeOperandBytes + kMergeTileStep * cols * 2); }
+constexpr int kMergeTiledLdsBytes = merge_tiled_lds(kMergeTileCols);
 
 // What both launch forms of the kernel pass on.
 struct MergeTiledArgs {
@@ -51,7 +56,16 @@ struct MergeTiledArgs {
   bf16_t* out;
 };
 
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef short s16x8_t __attribute__((ext_vector_type(8)));
+// A transposing read: lanes 16 g .. 16 g + 15 each read four consecutive values of a 4 x 16 block (lane i: row i / 4,
+// columns 4 (i % 4) .. + 3); lane n of them gets column n, the four rows in order.
+__device__ __forceinline__ s16x4_t read_turned(const unsigned char* at) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(const_cast<unsigned char*>(at)));
+}
+
 // Tile `tile` (kept-row tile major, feature tile minor) of image b.
+template <int COLS>
 __device__ __forceinline__ void merge_tile(const MergeTiledArgs& A, int b, int tile, unsigned char* lds) {
   const bf16_t* __restrict__ tokens = A.tokens;
   const int32_t* __restrict__ offsets = A.offsets;
@@ -69,43 +83,53 @@ __device__ __forceinline__ void merge_tile(const MergeTiledArgs& A, int b, int t
   const int m = min(max(A.keep[b], 0), n), r = n - m;
   if (r <= kTiledMinPruned) return;                  // k_merge_lds
   const int ti = tile / tiles_d, td = tile - ti * tiles_d;
-  const int i0 = ti * kMergeTileRows, d0 = td * kMergeTileCols;
+  const int i0 = ti * kMergeTileRows, d0 = td * COLS;
   if (i0 >= m) return;
   const int32_t* sel = sel_idx + lo;
   const float* __restrict__ P = plan + plan_offsets[b];
   const size_t obase = static_cast<size_t>(out_offsets[b]);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave >> 1, wn = wave & 1;
 
-  constexpr int kOperand = kMergeTileRows * kMergeTilePitch;          // P hi, P lo: one staged operand each
-  constexpr int kBuffer = 2 * kOperand + kMergeTileCols * kMergeTurnedPitch;   // [P hi, P lo, T^T]
-  constexpr int kStageBytes = 2 * kBuffer;
-  constexpr int kOutBytes = 64 * kMergeOutPitch * 4;                  // half of the output tile, fp32
-  static_assert(kMergeTiledLdsBytes >= kStageBytes && kMergeTiledLdsBytes >= kOutBytes, "the caller's LDS buffer");
+  constexpr int kOperand = kMergeOperandBytes;
+  constexpr int kRowBytes = 2 * COLS, kBuffer = 2 * kOperand + kMergeTileStep * kRowBytes;   // [P hi, P lo, T_prop]
+  constexpr int kOutPitch = COLS + 4;                                 // floats per row of the output tile, half of which:
+  static_assert(merge_tiled_lds(COLS) == 2 * kBuffer && 2 * kBuffer >= 64 * kOutPitch * 4, "the caller's LDS buffer");
+  constexpr int kUnits = COLS / 32;                                   // matrix tiles across a wave's half of the features
+  constexpr int kPieces = COLS / 8, kReqRows = 64 / kPieces, kReqs = 8 / kReqRows;   // 16-byte pieces of a row; a request's rows; a wave's requests
+  const int features = min(D - d0, COLS);                             // 256 or 128
 
   // staging of P: thread t takes entries 4 (t % 8) .. + 3 of the step for rows t / 8 + 32 q
   const int pj = 4 * (tid & 7), prow = tid >> 3;
   const float* pptr[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) pptr[q] = P + static_cast<long long>(min(i0 + prow + 32 * q, m - 1)) * r;
-  // staging of T_prop: thread t takes features 8 (t % 16) .. + 7 of the two pruned rows 2 (t / 16), + 1 of the step
-  const int tdg = tid & 15, tjp = tid >> 4;
+  // staging of T_prop: request q of a wave brings the step's rows 8 wave + kReqRows q and on, a row being kPieces pieces
+  // of 16 bytes that go to slots of blocks of two: block ^ (row % 4 + 4 (row / 8)), as far as there are blocks.  A
+  // transposing read's 16 rows of one block then lie in 16 (8) different blocks, all banks twice; in place
+  // they would share one.
+  const int trow = 8 * wave + lane / kPieces;
+  auto block_of = [](int row) { return ((row & 3) | ((row >> 3 & 3) << 2)) & (COLS / 16 - 1); };
+  const bf16_t* tbase = tokens + static_cast<size_t>(lo) * D + d0;
+  int trows[kReqs];                                    // of the step fetched next
+  auto find = [&](int j0) {
+#pragma unroll
+    for (int q = 0; q < kReqs; ++q) trows[q] = sel[m + min(j0 + trow + kReqRows * q, r - 1)];
+  };
+  const uint32_t lds_at = __builtin_amdgcn_readfirstlane(
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)lds)) + 2 * kOperand);
   float pv[4][4];
-  uint4 tv[2];
-  auto fetch = [&](int j0) {
+  auto fetch = [&](int buf, int j0) {
+#pragma unroll
+    for (int q = 0; q < kReqs; ++q) {
+      const int piece = (lane & 1) + 2 * ((lane % kPieces >> 1) ^ block_of(trow + kReqRows * q));
+      load_to_lds_16(tbase + static_cast<size_t>(clamp_index(trows[q], n)) * D + min(8 * piece, features - 8),
+                     lds_at + buf * kBuffer + (8 * wave + kReqRows * q) * kRowBytes);
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = j0 + pj + e;
-        pv[q][e] = pptr[q][min(j, r - 1)];
-      }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int j = min(j0 + 2 * tjp + h, r - 1);
-      tv[h] = *reinterpret_cast<const uint4*>(tokens + static_cast<size_t>(lo + clamp_index(sel[m + j], n)) * D +
-                                              d0 + 8 * tdg);
-    }
+      for (int e = 0; e < 4; ++e) pv[q][e] = pptr[q][min(j0 + pj + e, r - 1)];
   };
   auto stage = [&](int buf, int j0) {
     unsigned char* base = lds + buf * kBuffer;
@@ -116,111 +140,113 @@ __device__ __forceinline__ void merge_tile(const MergeTiledArgs& A, int b, int t
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (j0 + pj + e >= r) pv[q][e] = 0.f;
-      if (j0 + 2 * tjp >= r) tv[0] = make_uint4(0u, 0u, 0u, 0u);
-      if (j0 + 2 * tjp + 1 >= r) tv[1] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int q = 0; q < kReqs; ++q)
+        if (j0 + trow + kReqRows * q >= r)
+          *reinterpret_cast<uint4*>(base + 2 * kOperand + (8 * wave + kReqRows * q) * kRowBytes + 16 * lane) = make_uint4(0u, 0u, 0u, 0u);
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      float hi[4], lo4[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float v = pv[q][e];
-        hi[e] = bf16_to_f32(f32_to_bf16(v));
-        lo4[e] = v - hi[e];
-      }
       uint2 h2, l2;
-      h2.x = pack_bf16x2(hi[0], hi[1]);
-      h2.y = pack_bf16x2(hi[2], hi[3]);
-      l2.x = pack_bf16x2(lo4[0], lo4[1]);
-      l2.y = pack_bf16x2(lo4[2], lo4[3]);
+      h2.x = pack_bf16x2(pv[q][0], pv[q][1]);
+      h2.y = pack_bf16x2(pv[q][2], pv[q][3]);
+      l2.x = pack_bf16x2(pv[q][0] - __uint_as_float(h2.x << 16), pv[q][1] - __uint_as_float(h2.x & 0xffff0000u));
+      l2.y = pack_bf16x2(pv[q][2] - __uint_as_float(h2.y << 16), pv[q][3] - __uint_as_float(h2.y & 0xffff0000u));
       const int off = (prow + 32 * q) * kMergeTilePitch + 2 * pj;
       *reinterpret_cast<uint2*>(base + off) = h2;
       *reinterpret_cast<uint2*>(base + kOperand + off) = l2;
     }
-    // turned: feature row 8 tdg + e gets the pair (pruned row 2 tjp, 2 tjp + 1)
-    const uint32_t w0[4] = {tv[0].x, tv[0].y, tv[0].z, tv[0].w}, w1[4] = {tv[1].x, tv[1].y, tv[1].z, tv[1].w};
-    // features 8 tdg .. + 7 share feature / 16, hence the slot of this thread's piece tjp / 4
-    unsigned char* turned = base + 2 * kOperand + 8 * tdg * kMergeTurnedPitch +
-                            16 * ((tjp >> 2) ^ ((tdg >> 1) & 7)) + 4 * (tjp & 3);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t a = (e & 1) ? w0[e >> 1] >> 16 : w0[e >> 1] & 0xffffu;
-      const uint32_t c = (e & 1) ? w1[e >> 1] & 0xffff0000u : w1[e >> 1] << 16;
-      *reinterpret_cast<uint32_t*>(turned + e * kMergeTurnedPitch) = a | c;
-    }
   };
 
-  floatx4_t acc[4][4];
+  floatx4_t acc[4][kUnits];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc[t][u] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < kUnits; ++u) acc[t][u] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
-  // fragment: lane l reads the 16 bytes (eight consecutive pruned rows 8 (l / 16) .. + 7) of row l % 16
+  // fragments.  P: lane l reads the 16 bytes (eight consecutive pruned rows 8 (l / 16) .. + 7) of row l % 16.
+  // T_prop: read h of block u reads the four rows 8 g + 4 h .. + 3 of the 16 features for lanes 16 g .. 16 g + 15
+  // (lane: row (l % 16) / 4, features 4 (l % 4) .. + 3) and hands lane l feature l % 16 of all four.
   const int frag_off = (lane & 15) * kMergeTilePitch + 16 * (lane >> 4);
+  const int krow = 8 * (lane >> 4) + (lane >> 2 & 3);                  // of read 0
+  const int tr_row = 2 * kOperand + krow * kRowBytes + 8 * (lane & 3), tr_block = block_of(krow);
+  const bool mine = COLS / 2 * wn < features;                             // (the other half of the last tile does not exist)
   const int steps = (r + kMergeTileStep - 1) / kMergeTileStep;
-  fetch(0);
+  find(0);
+  fetch(0, 0);
+  find(kMergeTileStep);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   stage(0, 0);
   __syncthreads();
   for (int s = 0; s < steps; ++s) {
     const int buf = s & 1;
-    if (s + 1 < steps) fetch((s + 1) * kMergeTileStep);
-    const unsigned char* base = lds + buf * kBuffer;
-    uint4 fh[4], fl[4], fb[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      fh[t] = *reinterpret_cast<const uint4*>(base + (64 * wm + 16 * t) * kMergeTilePitch + frag_off);
-      fl[t] = *reinterpret_cast<const uint4*>(base + kOperand + (64 * wm + 16 * t) * kMergeTilePitch + frag_off);
-      fb[t] = *reinterpret_cast<const uint4*>(base + 2 * kOperand + (64 * wn + 16 * t + (lane & 15)) * kMergeTurnedPitch +
-                                              16 * ((lane >> 4) ^ ((4 * wn + t) & 7)));
+    if (s + 1 < steps) {
+      fetch(buf ^ 1, (s + 1) * kMergeTileStep);
+      find((s + 2) * kMergeTileStep);
     }
+    const unsigned char* base = lds + buf * kBuffer;
+    if (mine) {
+      uint4 fh[4], fl[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fh[t]),
-                                                            __builtin_bit_cast(bf16x8_t, fb[u]), acc[t][u], 0, 0, 0);
-        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fl[t]),
-                                                            __builtin_bit_cast(bf16x8_t, fb[u]), acc[t][u], 0, 0, 0);
+      for (int t = 0; t < 4; ++t) {
+        fh[t] = *reinterpret_cast<const uint4*>(base + (64 * wm + 16 * t) * kMergeTilePitch + frag_off);
+        fl[t] = *reinterpret_cast<const uint4*>(base + kOperand + (64 * wm + 16 * t) * kMergeTilePitch + frag_off);
       }
-    if (s + 1 < steps) stage(buf ^ 1, (s + 1) * kMergeTileStep);
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) {
+        const unsigned char* at = base + tr_row + 32 * ((kUnits * wn + u) ^ tr_block);
+        const s16x4_t b0 = read_turned(at), b1 = read_turned(at + 4 * kRowBytes);
+        const bf16x8_t fb = __builtin_bit_cast(bf16x8_t, s16x8_t{b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]});
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fh[t]), fb, acc[t][u], 0, 0, 0);
+          acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, fl[t]), fb, acc[t][u], 0, 0, 0);
+        }
+      }
+    }
+    if (s + 1 < steps) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      stage(buf ^ 1, (s + 1) * kMergeTileStep);
+    }
     __syncthreads();
   }
 
   // accumulator element v of lane l is (kept row 4 (l / 16) + v, feature l % 16) of its tile.
   // Half of the tile (64 kept rows) at a time: through LDS as fp32, then each
   // thread adds eight features of one kept row and writes them as 16 bytes.
-  // The thread's eight kept rows' pieces are all requested first (their indices together, then
+  // The thread's kept rows' pieces of it are requested first (their indices together, then
   // the rows together): two trips to memory instead of sixteen one after the other.
   float* ot = reinterpret_cast<float*>(lds);
-  const int dd = 8 * (tid & 15);
-  int krow[8];
+  constexpr int kOutRows = kMergeTiledThreads / kPieces, kOutPasses = 64 / kOutRows;
+  const int dd = 8 * (tid % kPieces), orow = tid / kPieces;
+  const bool there = dd < features;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) krow[k] = sel[min(i0 + (tid >> 4) + 16 * k, m - 1)];
-  uint4 kept[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    kept[k] = *reinterpret_cast<const uint4*>(tokens + static_cast<size_t>(lo + clamp_index(krow[k], n)) * D + d0 + dd);
   for (int half = 0; half < 2; ++half) {
+    int krows[kOutPasses];
+#pragma unroll
+    for (int k = 0; k < kOutPasses; ++k) krows[k] = sel[min(i0 + 64 * half + orow + kOutRows * k, m - 1)];
+    uint4 kept[kOutPasses];
+#pragma unroll
+    for (int k = 0; k < kOutPasses; ++k)
+      kept[k] = *reinterpret_cast<const uint4*>(tokens + static_cast<size_t>(lo + clamp_index(krows[k], n)) * D + d0 + min(dd, features - 8));
     __syncthreads();                                   // the previous use of this LDS is over
-    if (wm == half) {
+    if (wm == half && mine) {
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < kUnits; ++u)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            ot[(16 * t + 4 * (lane >> 4) + v) * kMergeOutPitch + 64 * wn + 16 * u + (lane & 15)] = acc[t][u][v];
+            ot[(16 * t + 4 * (lane >> 4) + v) * kOutPitch + COLS / 2 * wn + 16 * u + (lane & 15)] = acc[t][u][v];
     }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = (tid >> 4) + 16 * q;             // 0 .. 63
+    for (int q = 0; q < kOutPasses; ++q) {
+      const int row = orow + kOutRows * q;              // 0 .. 63
       const int i = i0 + 64 * half + row;
-      if (i >= m) continue;
-      const uint4 kr = half ? kept[4 + q] : kept[q];
-      const uint32_t kw[4] = {kr.x, kr.y, kr.z, kr.w};
-      const float* src = ot + row * kMergeOutPitch + dd;
+      if (i >= m || !there) continue;
+      const uint32_t kw[4] = {kept[q].x, kept[q].y, kept[q].z, kept[q].w};
+      const float* src = ot + row * kOutPitch + dd;
       uint32_t ow[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -234,11 +260,12 @@ __device__ __forceinline__ void merge_tile(const MergeTiledArgs& A, int b, int t
 
 // One workgroup per (tile, image): the staged call, and fused calls whose images
 // are known to be large.
-__global__ __launch_bounds__(kMergeTiledThreads) void k_merge_tiled(MergeTiledArgs A,
-                                                                   const int32_t* __restrict__ status) {
+template <int COLS>
+__global__ __launch_bounds__(kMergeTiledThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_merge_tiled(
+    MergeTiledArgs A, const int32_t* __restrict__ status) {
   if (status && status[0]) return;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kMergeTiledLdsBytes];
-  merge_tile(A, blockIdx.y, blockIdx.x, lds);
+  __shared__ __attribute__((aligned(16))) unsigned char lds[merge_tiled_lds(COLS)];
+  merge_tile<COLS>(A, blockIdx.y, blockIdx.x, lds);
 }
 
 }  // namespace rtp

@@ -711,15 +711,20 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
   RTP_TRY(launched());
   if constexpr (std::is_same<T, bf16_t>::value) {
     const int tiles_ti = (in->max_tokens + kMergeTileRows - 1) / kMergeTileRows;
-    const int tiles_td = in->D / kMergeTileCols;
+    // (pruned sets known to be large (fixed retention), or no work list: a workgroup per
+    // tile and image for the tiled kernel; else its list form shares a launch with the
+    // middling sets' kernel)
+    const bool tiled_grid = tiled && (max_pruned_hint >= 2 * kTiledMinPruned || !work || !status);
+    const int tiles_wide = (in->D + kMergeTileCols - 1) / kMergeTileCols;
+    // Narrow tiles while wide ones would not give every compute unit its two workgroups.
+    const bool thin = tiled_grid && static_cast<long long>(tiles_ti) * tiles_wide * in->B < 2LL * compute_units();
+    const int tiles_td = thin ? in->D / kMergeThinCols : tiles_wide;
     const MergeTiledArgs TA{tok, in->offsets, in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens,
                             tiles_td, static_cast<bf16_t*>(out)};
-    // pruned sets known to be large (fixed retention), or no work list: a workgroup per
-    // tile and image for the tiled kernel; else its list form shares a launch with the
-    // middling sets' kernel
-    const bool tiled_grid = tiled && (max_pruned_hint >= 2 * kTiledMinPruned || !work || !status);
-    if (tiled_grid)
-      hipLaunchKernelGGL(k_merge_tiled, dim3(tiles_ti * tiles_td, in->B), dim3(kMergeTiledThreads), 0, s, TA, status);
+    if (tiled_grid && thin)
+      hipLaunchKernelGGL(k_merge_tiled<kMergeThinCols>, dim3(tiles_ti * tiles_td, in->B), dim3(kMergeTiledThreads), 0, s, TA, status);
+    else if (tiled_grid)
+      hipLaunchKernelGGL(k_merge_tiled<kMergeTileCols>, dim3(tiles_ti * tiles_td, in->B), dim3(kMergeTiledThreads), 0, s, TA, status);
     const bool tiled_list = tiled && !tiled_grid;
     if (tiled_list || mid) {
       const MergeMidArgs MA{tok, in->offsets, in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens,

@@ -240,6 +240,20 @@ def test_streaming_kernels_with_a_share_of_streaming_loads(monkeypatch, share):
         _log(hz.compare_batch(batch, f, images=[2, 3]), "sweep, 5/16 streamed")
 
 
+@pytest.mark.parametrize("copies", [1, 12])
+@pytest.mark.parametrize("D", [128, 384, 1152])
+def test_tiled_merge_at_the_edges_of_its_tiles(D, copies):
+    """Tiles of 128 kept rows x 128 (small batches) or 256 features (others; a width that is an odd multiple of 128
+    leaves half of the last one), 32 pruned rows a step: row counts around the tile's, pruned counts around a step's."""
+    shapes = [(1, 65), (63, 96), (64, 97), (65, 127), (127, 128), (128, 129), (129, 66), (255, 95), (257, 160)] * copies
+    batch = _clustered([m + r for m, r in shapes], D, "bf16", 45, iters=12, ratio=0.55)
+    keep = [m for m, _ in shapes]
+    s = hz.run_staged(batch, keep_counts_in=keep)
+    assert s["status"] == 0
+    rep = hz.compare_batch(batch, s, staged=True, keep_counts=keep, images=list(range(9)) + [len(shapes) - 1])
+    _log(rep, f"tiled merge {D} {copies}")
+
+
 def test_tall_register_shapes_at_their_edges():
     """Kept and pruned counts on both sides of the limits of the two shapes that hold
     a tall image (more than 512 rows) in one workgroup's registers: 1535 x 15
