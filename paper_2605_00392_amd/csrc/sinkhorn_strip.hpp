@@ -38,13 +38,13 @@
 // Before those, strips that gave every row a reduction of its own: 0.91 (1083 tokens) and 2.48 ms (2137);
 // streaming the matrices from memory every iteration: 6.72 ms (4512).
 //
-// The exchange.  Up to four workgroups publish their column sums and everybody adds everybody's in
-// rank order.  With more of them (strip_direct) that means groups x (r + 1) doubles read by each
-// workgroup and iteration, so the columns are dealt out instead: a workgroup receives all the
+// The exchange.  While it is not much to read (strip_direct: 18 KB), everybody adds everybody's column sums in
+// rank order.  With more workgroups or columns than that, groups x (r + 1) doubles a
+// workgroup and iteration, the columns are dealt out instead: a workgroup receives all the
 // others' sums for its share of the columns, adds them in a fixed order, takes the reciprocal and
 // publishes the finished y; everybody reads all y.  Two trips through memory instead of one, but
-// 2 (r + 1) values read instead of groups (r + 1).  (64 pages of 1083 tokens, eight workgroups each: 0.88 ms
-// with one trip, 0.81 with two at the time.)
+// 2 (r + 1) values read instead of groups (r + 1).  (Eight workgroups of 523 columns, 64 images: 0.88 ms
+// with one trip, 0.81 with two at the time; up to six of 280: 0.540 and 0.577.)
 // Values travel as device-scope stores and loads past the caches, the loads straight into LDS, and carry in
 // their last bit which use of their place they belong to (the uses alternate), so no counters, no barriers
 // across workgroups and nothing put back.  (A sum's or y's last bit is 1e-16 of it; the reciprocal is good to 2e-15.)
@@ -187,7 +187,7 @@ __device__ __forceinline__ void strip_clear(const StripArgs& C, int b, int rank)
 constexpr int kStripPiece = 128;
 template <typename S> struct StripLds {
   static constexpr int kPitch = S::kCols + 2;          // of a wave's column sums: with its sum of x behind them, and a zero
-  static constexpr int kDirect = strip_direct(S::kShape, 1) ? kStripDirect * strip_row(S::kCols) : 0;
+  static constexpr int kDirect = strip_direct(S::kShape, 1, 1) ? kStripDirectDoubles : 0;
   static constexpr int kShares = (S::kCols + 16 * kStripMaxGroups + kStripPiece - 1) / kStripPiece * kStripPiece;   // sums; behind them y
   static constexpr int kReceive = kDirect > 2 * kShares ? kDirect : 2 * kShares;
   static constexpr int kWaves = kStripWaves * kPitch;
@@ -306,8 +306,8 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   const int rows_per = (m + groups - 1) / groups;            // the rows dealt evenly
   const int row_base = rank * rows_per;
   const int m_loc = min(m - row_base, rows_per);             // >= 1: groups = ceil(m / rows per strip)
-  constexpr bool kMayDirect = strip_direct(S::kShape, 1);    // (the wider shapes never are)
-  const bool direct = kMayDirect && strip_direct(S::kShape, groups);
+  constexpr bool kMayDirect = strip_direct(S::kShape, 1, 1);    // (the wider shapes never are)
+  const bool direct = kMayDirect && strip_direct(S::kShape, r, groups);
   const int cw = strip_share(r, groups);                     // columns (the sum of x counted as column r) a workgroup owns
   const int own0 = rank * cw;
   double* area = groups > 1 ? strip_area(A, S::kShape, po, m, r, groups) : nullptr;

@@ -219,14 +219,17 @@ __host__ __device__ inline int strip_teams(int shape, int m, int mode) {
 // the columns and everybody reads back the finished y (two trips, but 1 / teams of the reading).
 // `strip_share`: columns (and the sum of x) a workgroup owns, whole pieces of 64 bytes; `strip_owned`: those of
 // all that own any.  A direct buffer's rows are even: values are read two at a time.
-constexpr int kStripDirect = 4;
-__host__ __device__ constexpr bool strip_direct(int shape, int teams) { return shape <= kShapeStripB && teams <= kStripDirect; }
 __host__ __device__ constexpr int strip_row(int r) { return (r + 2) & ~1; }
+// (One trip while a workgroup then reads no more than this.)
+constexpr int kStripDirectDoubles = 2320;
+__host__ __device__ constexpr bool strip_direct(int shape, int r, int teams) {
+  return shape <= kShapeStripB && teams * strip_row(r) <= kStripDirectDoubles;
+}
 __host__ __device__ inline int strip_share(int r, int teams) { return ((r + teams) / teams + 7) & ~7; }   // >= (r + 1) / teams
 __host__ __device__ inline int strip_owned(int r, int share) { return (r + share) / share * share; }       // <= r + 8 teams
 __host__ __device__ inline long long strip_exchange_doubles(int shape, int r, int teams) {
   if (teams <= 1) return 0;
-  if (strip_direct(shape, teams)) return 2ll * teams * strip_row(r);      // two buffers
+  if (strip_direct(shape, r, teams)) return 2ll * teams * strip_row(r);      // two buffers
   return (teams + 1ll) * strip_owned(r, strip_share(r, teams));
 }
 constexpr int kStripAlign = 16;   // doubles

@@ -410,11 +410,11 @@ def test_dynamic_retention_in_two_strip_shapes_through_the_fused_call():
 
 @pytest.mark.parametrize("iters", [1, 2, 3, 6])
 def test_strips_of_half_a_compute_unit_at_their_edges(iters):
-    """Workgroups of 72 x 576 and 40 x 960: one of them, the last number of them that reads everybody's sums (four)
-    and the first that deals the columns out (five), more than an XCD's sixteen, and pruned counts whose
-    shares, rows of fours and pairs end unevenly."""
-    shapes = [(72, 300), (73, 576), (288, 573), (289, 574), (360, 575), (41, 577), (160, 960), (161, 959), (400, 958),
-              (640, 601), (641, 605), (1151, 133)]
+    """Workgroups of 72 x 576 and 40 x 960: one of them, the most that everybody reads everybody's sums of
+    (2320) and the first that deal the columns out, more than an XCD's, and pruned counts whose shares and
+    pairs end unevenly."""
+    shapes = [(72, 300), (73, 576), (288, 573), (289, 574), (360, 463), (360, 464), (41, 577), (160, 960), (161, 959),
+              (400, 958), (640, 601), (641, 605), (1151, 133), (1152, 145)]
     batch = _clustered([m + r for m, r in shapes], 128, "bf16", 44, iters=iters, ratio=1280.0 / 2240.0)
     keep = [m for m, _ in shapes]
     s = hz.run_staged(batch, keep_counts_in=keep)
