@@ -305,6 +305,18 @@ __device__ __forceinline__ double exp_nonpositive(double x) {
   return ldexp(q, static_cast<int>(k));
 }
 
+// Which image and tile a workgroup of a grid (tiles, images) works on.  Workgroups go to the eight XCDs in turn;
+// the first `xcd_images` images (a multiple of eight) are dealt so that all tiles of one run on one XCD and
+// its rows come into one L2.
+__device__ __forceinline__ void tile_of_grid(int xcd_images, int& image, int& tile) {
+  image = blockIdx.y;
+  tile = blockIdx.x;
+  if (image >= xcd_images) return;
+  const unsigned k = blockIdx.y * gridDim.x + blockIdx.x;
+  image = static_cast<int>((k & 7) + 8 * ((k >> 3) / gridDim.x));
+  tile = static_cast<int>((k >> 3) % gridDim.x);
+}
+
 // Index and extent guards for arrays that arrive from the caller (staged calls):
 // a wrong entry may give a wrong result but never an out-of-bounds access.
 __device__ __forceinline__ int clamp_index(int t, int n) { return min(max(t, 0), n - 1); }

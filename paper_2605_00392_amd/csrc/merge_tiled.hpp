@@ -54,6 +54,7 @@ struct MergeTiledArgs {
   float alpha;
   int max_tokens, tiles_d;
   bf16_t* out;
+  int xcd_images;   // tile_of_grid (the grid form)
 };
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
@@ -265,7 +266,9 @@ __global__ __launch_bounds__(kMergeTiledThreads) __attribute__((amdgpu_waves_per
     MergeTiledArgs A, const int32_t* __restrict__ status) {
   if (status && status[0]) return;
   __shared__ __attribute__((aligned(16))) unsigned char lds[merge_tiled_lds(COLS)];
-  merge_tile<COLS>(A, blockIdx.y, blockIdx.x, lds);
+  int image, tile;
+  tile_of_grid(A.xcd_images, image, tile);
+  merge_tile<COLS>(A, image, tile, lds);
 }
 
 }  // namespace rtp

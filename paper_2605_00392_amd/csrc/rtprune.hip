@@ -432,6 +432,15 @@ int launch_scan(const rtprune_batch* in, const int32_t* keep, int32_t* out_off, 
   return launched();
 }
 
+// Images whose tiles the tiled kernels' grids keep to one XCD each (tile_of_grid): whole eights of a batch of
+// equally long pages, or of one large enough that the XCDs' shares of ragged ones come out alike.  All tiles
+// spread / one XCD an image, scores and merge: 64 pages of 1083 tokens 200 / 170 and 203 / 192 us, 32 of 2137 270 / 254
+// and 311 / 292, 16 of 4512 448 / 428 and 574 / 563, 64 ragged of up to 700 81 / 72 and 77 / 74.
+int xcd_images(const rtprune_batch* in) {
+  const bool alike = 16 * static_cast<long long>(in->total_tokens) >= 15LL * in->B * in->max_tokens;
+  return alike || in->B >= 64 ? in->B & ~7 : 0;
+}
+
 // Workgroups of the list forms of the tiled kernels: eight per CU, or all tiles if fewer.
 unsigned tiled_list_blocks(int tiles, int B) {
   const long long all = static_cast<long long>(tiles) * B;
@@ -493,7 +502,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
         const int tiles_n = (rmax + kTileCols - 1) / kTileCols;
         const int tiles = tiles_m * tiles_n;
         const ScoresTiledArgs TA{tok, in->offsets, in->D, sel, keep, plan_off, sq, p, kmat, L.plan_cap, scores_out,
-                                 tiles_n};
+                                 tiles_n, xcd_images(in)};
         // pruned sets known to be large (fixed retention): a workgroup per tile and
         // image; sizes decided on the device, or barely above the threshold: a fixed
         // number of workgroups over the work list
@@ -720,7 +729,7 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
     const bool thin = tiled_grid && static_cast<long long>(tiles_ti) * tiles_wide * in->B < 2LL * compute_units();
     const int tiles_td = thin ? in->D / kMergeThinCols : tiles_wide;
     const MergeTiledArgs TA{tok, in->offsets, in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens,
-                            tiles_td, static_cast<bf16_t*>(out)};
+                            tiles_td, static_cast<bf16_t*>(out), xcd_images(in)};
     if (tiled_grid && thin)
       hipLaunchKernelGGL(k_merge_tiled<kMergeThinCols>, dim3(tiles_ti * tiles_td, in->B), dim3(kMergeTiledThreads), 0, s, TA, status);
     else if (tiled_grid)

@@ -49,6 +49,7 @@ struct ScoresTiledArgs {
   long long plan_cap;
   double* scores_out;
   int tiles_n;
+  int xcd_images;   // tile_of_grid (the grid form)
 };
 
 // Sixteen bytes per lane from memory straight into LDS: lane l's land at LDS byte address
@@ -328,7 +329,9 @@ __device__ __forceinline__ void scores_tile(const ScoresTiledArgs& A, int b, int
 // (the hardware hands out workgroups as CUs come free, which balances best).
 __global__ __launch_bounds__(kTiledThreads, 2) void k_scores_tiled(ScoresTiledArgs A, const int32_t* __restrict__ status) {
   if (status[0]) return;
-  scores_tile(A, blockIdx.y, blockIdx.x);
+  int image, tile;
+  tile_of_grid(A.xcd_images, image, tile);
+  scores_tile(A, image, tile);
 }
 
 // A fixed number of workgroups that walk the tiles of the images on the tiled
