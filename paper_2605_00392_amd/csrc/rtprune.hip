@@ -740,12 +740,8 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
                             static_cast<bf16_t*>(out)};
       const int tiles_t = tiled_list ? tiles_ti * tiles_td : 0, tiles_m = mid ? tiles_mid : 0;
       const dim3 gl((tiled_list_blocks(std::max(tiles_t, tiles_m), in->B) + 7) / 8 * 8);
-      if (in->D % (2 * kMergeMidFeatures) == 0)
-        hipLaunchKernelGGL(k_merge_lists<2>, gl, dim3(kMergeMidThreads), 0, s, TA, tiles_t, MA, tiles_m, work, in->B,
-                           mid_min, status);
-      else
-        hipLaunchKernelGGL(k_merge_lists<1>, gl, dim3(kMergeMidThreads), 0, s, TA, tiles_t, MA, tiles_m, work, in->B,
-                           mid_min, status);
+      hipLaunchKernelGGL(k_merge_lists, gl, dim3(kMergeMidThreads), 0, s, TA, tiles_t, MA, tiles_m, work, in->B, mid_min,
+                         status);
     }
   }
   return launched();

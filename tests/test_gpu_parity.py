@@ -740,6 +740,13 @@ def test_tiled_scores_at_other_step_counts(d):
     ([97, 50], 0.34, 256),             # fewer kept rows than a wave takes, 64 and 33 pruned
     ([120, 300], 0.6, 192),            # width a multiple of 64 only; the second image is beyond the range
     ([120], 0.6, 96),                  # width no multiple of 64: the vector kernel
+    ([160, 97], 0.8, 64),              # half a stage of features, one, three, four and five stages
+    ([97, 193], 0.67, 128),
+    ([130, 97], 0.7, 384),
+    ([160, 97], 0.8, 512),
+    ([130, 97], 0.7, 640),
+    ([400, 230], 0.8425, 1088),        # the last of nine stages has half of its features
+    ([160, 193], 0.8, 1152),
 ])
 def test_unstaged_matrix_core_merge_at_its_edges(counts, ratio, d):
     """Pruned sets of 17 to 64 tokens (the merge kernel that feeds the matrix cores straight
