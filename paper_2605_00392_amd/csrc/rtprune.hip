@@ -602,8 +602,8 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
                        compute_units(), folded ? 1 : 0);
   }
   if (mode_strips(p.mode)) {
-    // (again one workgroup per compute unit of the slots in use, and behind them those that take the
-    // images of slots that did not get complete)
+    // (two workgroups per compute unit of the slots in use; behind them, in a launch of their own, those that take
+    // the images of slots that did not get complete)
     const int cus = compute_units();
     int32_t* words = strip_words(L, ws, p.mode);
     ProfScope prof(KID_SINKHORN_STRIPS, s);
@@ -611,13 +611,17 @@ int launch_ot(const rtprune_batch* in, const DevParams& p_in, const int32_t* sel
       if (!(p.mode & mode_strip_bit(shape))) continue;
       const int groups = std::min(mode_strip_groups(p.mode), std::max(strip_groups(shape, in->max_tokens, p.mode), 1));
       const int slot_blocks = kStripTeams * std::min(cus, (in->B + 7) / 8 * 8 * groups);
-      const StripArgs TA{A, words + (shape - 1) * kStripShapeWords, cus, slot_blocks, strip_form_limit(),
+      const StripArgs TA{A, words + (shape - 1) * kStripShapeWords, cus, strip_form_limit(),
                          cluster_spin_limit(), at<int32_t>(ws, L.status)};
-      const dim3 grid(slot_blocks + kStripTeams * groups), block(kStripThreads);
-      if (shape == kShapeStripA) hipLaunchKernelGGL(k_sinkhorn_strips<StripA>, grid, block, 0, s, TA);
-      else if (shape == kShapeStripB) hipLaunchKernelGGL(k_sinkhorn_strips<StripB>, grid, block, 0, s, TA);
-      else if (shape == kShapeStripC) hipLaunchKernelGGL(k_sinkhorn_strips<StripC>, grid, block, 0, s, TA);
-      else hipLaunchKernelGGL(k_sinkhorn_strips<StripD>, grid, block, 0, s, TA);
+      auto launch = [&](auto tag) {
+        using S = decltype(tag);
+        hipLaunchKernelGGL(k_sinkhorn_strips<S>, dim3(slot_blocks), dim3(kStripThreads), 0, s, TA);
+        hipLaunchKernelGGL(k_sinkhorn_strips_left<S>, dim3(groups), dim3(kStripTeams * kStripThreads), 0, s, TA);
+      };
+      if (shape == kShapeStripA) launch(StripA{});
+      else if (shape == kShapeStripB) launch(StripB{});
+      else if (shape == kShapeStripC) launch(StripC{});
+      else launch(StripD{});
     }
   }
   RTP_TRY(launched());

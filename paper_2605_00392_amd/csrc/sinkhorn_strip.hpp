@@ -10,16 +10,17 @@
 //
 // Who waits for whom.  Calls on other streams may hold compute units with workgroups that wait for
 // their own slots, so that no slot gets complete: three calls with slots of 10, 11 and 11 of sixteen
-// compute units fill an XCD, and slots across XCDs can each lack workgroups that another's keep out.  So no
+// compute units fill an XCD, and slots across XCDs can each lack workgroups that another's keep out.  Nor is a
+// compute unit always good for two: registers and LDS are taken as ranges, and a workgroup that was put
+// above another kernel's waves leaves no 256 registers on either side when those have gone.  So no
 // slot waits for ever to be complete: before a slot's workgroups touch anything they meet, and one that
 // has waited too long (C.form_limit, some 30 ms) gives the slot up, for good and for all its workgroups,
-// which leave.  The images of slots given up are done by the launch's last workgroups, as many as a slot has,
-// which nobody else of the launch waits for and which do wait until they are all there.  They have
-// consecutive numbers, at most 2 kStripMaxGroups / 8 = 16 of them on an XCD, so of four such calls (one per
-// hardware queue) at most 15 + 3 * 16 = 63 of an XCD's 64 places are held by workgroups that
-// wait for others of theirs: the next always finds a place.  Slots of sinkhorn_cluster.hpp wait with up to 7
-// whole compute units each, which leaves c of them and 4 - c such calls 64 - 14 c >= 16 (4 - c) places: those
-// get on, and when they have left the clusters do.
+// which leave.  The images of slots given up are done by a launch of their own behind this one
+// (k_sinkhorn_strips_left), whose workgroups do wait until they are all there.  They are twice as large, the work of
+// two, and fill a compute unit: at most kStripMaxGroups / 8 = 8 of them on an XCD, so of four such calls (one per
+// hardware queue) at most 7 + 3 * 8 = 31 of an XCD's 32 compute units are held by workgroups that
+// wait for others of theirs (slots of sinkhorn_cluster.hpp: 7 each), and the next finds a place on the last as soon as
+// those that wait for nobody have left it.
 //
 // A workgroup's four waves hold RPT whole rows each, a lane the columns lane, lane + 64, ...; two workgroups
 // share a compute unit, as a rule of different images, so that one's exchange runs beside the other's
@@ -64,12 +65,14 @@
 namespace rtp {
 
 constexpr int kStripThreads = 256, kStripWaves = kStripThreads / 64, kStripTeams = 2;   // workgroups to a compute unit
+// (A workgroup of k_sinkhorn_strips_left has two teams of kStripThreads, each with the part of a workgroup of
+// k_sinkhorn_strips and its own LDS.)
+__device__ __forceinline__ int strip_thread() { return threadIdx.x & (kStripThreads - 1); }
 
 struct StripArgs {
   SinkhornArgs S;
   int32_t* words;           // the shape's words, prepared by the kernel that built the lists
   int cus;                  // compute units the slots may take, two workgroups on each
-  int slot_blocks;          // workgroups of the launch that make up slots; the others are the last ones
   int form_limit;           // polls for a slot to be complete (0: every slot is given up at once, for tests)
   int spin_limit;
   int32_t* status;
@@ -108,7 +111,7 @@ __device__ __forceinline__ bool strip_meet(const StripArgs& C, int32_t* counter,
   __builtin_amdgcn_s_waitcnt(0);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (strip_thread() == 0) {
     int32_t* gave_up = C.words + kStripGaveUp;
     if (join) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int ok = 0;
@@ -127,14 +130,13 @@ __device__ __forceinline__ bool strip_meet(const StripArgs& C, int32_t* counter,
   return *s_flag != 0;
 }
 
-// Whether a slot is complete (all its workgroups resident) or has been given up: neither changes any
-// more.  `join`: this workgroup is one of the slot's.  Nothing has been touched yet, so a workgroup of
-// a slot given up just leaves.
-constexpr int kStripGivenUp = 1 << 30;     // in the slot's arrival counter (which stays below it: 65 535 images x 128)
-__device__ __forceinline__ bool strip_complete(int32_t* counter, int per_slot, int limit, bool join, int* s_flag) {
+// Whether this workgroup's slot is complete (all its workgroups resident) or has been given up: neither changes any
+// more.  Nothing has been touched yet, so a workgroup of a slot given up just leaves.
+constexpr int kStripGivenUp = 1 << 30;     // in the slot's arrival counter (which stays below it: 65 535 images x 2 x 128)
+__device__ __forceinline__ bool strip_complete(int32_t* counter, int per_slot, int limit, int* s_flag) {
   __syncthreads();                                     // the flag's last value has been read
   if (threadIdx.x == 0) {
-    if (join && limit > 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (limit > 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int seen;
     for (int spin = 0;; ++spin) {
       seen = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -176,7 +178,7 @@ __device__ __forceinline__ void strip_clear(const StripArgs& C, int b, int rank)
   const int total = static_cast<int>(strip_exchange_doubles(S::kShape, r, groups));
   const int each = (total + groups - 1) / groups;
   const int e1 = min(total, (rank + 1) * each);
-  for (int e = rank * each + threadIdx.x; e < e1; e += kStripThreads)
+  for (int e = rank * each + strip_thread(); e < e1; e += kStripThreads)
     __hip_atomic_store(area + e, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -192,7 +194,7 @@ template <typename S> struct StripLds {
   static constexpr int kReceive = kDirect > 2 * kShares ? kDirect : 2 * kShares;
   static constexpr int kWaves = kStripWaves * kPitch;
   static constexpr int kFirst = ((kReceive > kWaves ? kReceive : kWaves) + kStripPiece - 1) / kStripPiece * kStripPiece;
-  static constexpr int kBytes = 8 * (kFirst + S::kCols + 6) + 72;
+  static constexpr int kBytes = 8 * (kFirst + S::kCols + 8) + 72;
   static_assert(kBytes <= 160 * 1024 / kStripTeams, "a compute unit's workgroups share its LDS");
 };
 template <typename S> constexpr int strip_lds_of() { return StripLds<S>::kBytes; }
@@ -284,15 +286,21 @@ struct StripEntries {
 
 // One image on `groups` workgroups of a slot; this one is `rank` < groups.  `arrived`: the slot's
 // arrival count once they have all met at the image's end.  False: a wait was given up, leave the kernel.
-template <typename S>
+// PAIRED: on a workgroup of two teams, of which this is one; both take the same barriers, also the second team
+// that `groups` leaves without rows and columns (rank == groups), which publishes and writes nothing.
+template <typename S, bool PAIRED>
 __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, int rank, int groups, int32_t* counter,
                                                      int arrived, bool first, void* lds, int* s_flag) {
   constexpr int RPT = S::RPT, CPT = S::CPT, kCols = S::kCols, T = kStripThreads;
   constexpr int kChunks = (RPT + 7) / 8, kLast = RPT - 8 * (kChunks - 1);
   constexpr bool kKeepY = CPT <= 9;          // y in registers across the chunks of rows (else re-read from LDS)
+  // (x_dust is in LDS while the values travel: with the widest strips it costs a register too many; with the others
+  // that form is slower, 32 pages of 2137 tokens 1.747 -> 1.759 ms)
+  constexpr bool kDustInLds = S::kShape == kShapeStripD;
   const SinkhornArgs& A = C.S;
   const DevParams& p = A.p;
-  const int tt = threadIdx.x, tw = __builtin_amdgcn_readfirstlane(tt >> 6), lane = tt & 63;
+  const int tt = strip_thread(), tw = __builtin_amdgcn_readfirstlane(tt >> 6), lane = tt & 63;
+  const bool here = !PAIRED || rank < groups;
   // (in scalar registers: the compiler does not see that these loads' values are the same in all lanes)
   const int lo = __builtin_amdgcn_readfirstlane(A.offsets[b]);
   const int n = __builtin_amdgcn_readfirstlane(A.offsets[b + 1]) - lo;
@@ -324,7 +332,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   double* xw = static_cast<double*>(lds);                    // [W][kPitch]
   double* ys = xw + StripLds<S>::kFirst;                     // [kCols] and the sum of x
   double* rx = xw;                                           // received: [teams at a time][row], [groups][cw] or [owned]
-  int* seen_words = reinterpret_cast<int*>(ys + kCols + 6);  // [2]
+  int* seen_words = reinterpret_cast<int*>(ys + kCols + 8);  // [2]
 
   // (buffer loads: a row that the workgroup does not have, or a column past the last one, reads as zero,
   // with no mask and no address of its own in registers)
@@ -351,6 +359,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     ys[kCols + 3] = static_cast<double>(r);
     ys[kCols + 4] = static_cast<double>(m);
     ys[kCols + 5] = static_cast<double>(1.0f / static_cast<float>(cw));
+    ys[kCols + 6] = x_init;
   }
   __syncthreads();
 
@@ -460,7 +469,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     const int sums = direct ? (it & 1) * sums_buf : 0; // (places are counted from `area`)
     const uint32_t use = direct ? ~(it >> 1) & 1 : ~it & 1;
     const auto ex = ex_resource(area);
-    if (groups > 1) {
+    if (groups > 1 && here) {
       const int published = direct ? row : owned;
 #pragma unroll 2
       for (int e = 2 * te; e < published; e += 2 * T) {
@@ -473,6 +482,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     // (while the sums travel) the dustbins' scalings from the previous y
     x_dust = ys[fixed + 1] * rcp64(ys[fixed] * (wave_sum_dpp(ly) + y_dust));
     const double col_dust = ys[fixed] * x_dust;
+    if (kDustInLds && te == 0) ys[fixed + 4] = x_dust;
     bool seen = true;
     auto keep = [&](int e, double v0, double v1) {     // y (and the sum of x) of columns e and e + 1
       if (e <= r) ys[e < r ? e : kCols] = v0;
@@ -487,7 +497,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     } else if (kMayDirect && direct) {
       // everybody's sums, added in rank order
       lds_barrier();                                   // (the waves' column sums have been read)
-      seen = strip_receive(C, area + sums, groups * row, use, rx, tw, lane, [](int, double, double) {});
+      seen = strip_receive(C, area + sums, groups * row, use, rx, tw, te & 63, [](int, double, double) {});
       lds_barrier();
       for (int e = 2 * te; e < row; e += 2 * T) {
         f64x2_t acc = *reinterpret_cast<const f64x2_t*>(rx + e);
@@ -503,7 +513,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       const int in = sums + rank * groups * cw;
       lds_barrier();                                   // (the waves' column sums have been read)
       ex_pause(groups <= kStripXcdGroups ? 0 : groups <= kStripTeams * kStripXcdGroups ? 4 : 12);
-      if (own > 0) seen = strip_receive(C, area + in, groups * cw, use, rx, tw, lane, [](int, double, double) {});
+      if (own > 0) seen = strip_receive(C, area + in, groups * cw, use, rx, tw, te & 63, [](int, double, double) {});
       lds_barrier();
       // 4, 16 or 32 lanes add up two columns: about all threads at work, each on as few workgroups' as that allows
       const int yout = sums_buf + own0;
@@ -530,7 +540,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
         if ((te & (lanes - 1)) == 0) ex_store2(ex, yout + k, finish(own0 + k, v0), finish(own0 + k + 1, v1), use);
       }
       ex_pause(groups <= kStripTeams * kStripXcdGroups ? 16 : 20);
-      if (!strip_receive(C, area + sums_buf, owned, use, rx + StripLds<S>::kShares, tw, lane, keep)) seen = false;
+      if (!strip_receive(C, area + sums_buf, owned, use, rx + StripLds<S>::kShares, tw, te & 63, keep)) seen = false;
     }
     if (!seen) seen_all = 0;
     lds_barrier();
@@ -541,9 +551,11 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       }
       return false;
     }
-    y_dust = ys[fixed + 2] * rcp64(ys[fixed] * (ys[kCols] + x_dust));
+    y_dust = ys[fixed + 2] * rcp64(ys[fixed] * (ys[kCols] + (kDustInLds ? ys[fixed + 4] : x_dust)));
   }
   __syncthreads();
+
+  if (kDustInLds) x_dust = ys[kCols + 6];
 
   // ---- plan and this workgroup's best partner per column ----
   float* P = A.plan_out ? A.plan_out + po : nullptr;
@@ -577,7 +589,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   __syncthreads();
   // each column's best of the workgroup's rows as a key (value bits, then the lower row): plan
   // entries are >= 0, so their bit patterns order like their values; "no row" (-1) is below all
-  if (pair_out) {
+  if (pair_out && here) {
     for (int e = tt; e < r; e += T) {
       float bv = -1.f;
       int bi = 0x7fffffff;
@@ -595,7 +607,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  if (!strip_meet(C, counter, arrived, true, s_flag)) return false;
+  if (!strip_meet(C, counter, arrived, here, s_flag)) return false;
   if (pair_out && groups > 1) {
     // every workgroup picks the best of its share of the columns, eight lanes to a column
     for (int k = tt >> 3; k < own; k += T / 8) {
@@ -619,86 +631,106 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   return true;
 }
 
+// Slots of a launch: as many as are complete at once, and no more than have images (those that keep to an XCD: whole
+// eights).
+__device__ __forceinline__ int strip_slots_used(int units, int count, int cus) {
+  return min(strip_slots(units, cus), units <= kStripXcdGroups ? (count + 7) / 8 * 8 : count);
+}
+
+// The images slot, slot + slots, ... of the list on the slot's `per_slot` teams; this one is `rank`.  They meet before
+// each image (its exchange area cleared), and the image's at its end (the pairing keys out); `arrived`: the
+// counter's total so far.  False: a wait was given up, leave the kernel.
+template <typename S, bool PAIRED>
+__device__ __forceinline__ bool strip_images(const StripArgs& C, int slot, int slots, int count, int rank, int per_slot,
+                                             int& arrived, unsigned char* lds) {
+  const SinkhornArgs& A = C.S;
+  int* flag = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 2;
+  // the loop's state, in LDS while an image is worked on: in registers it makes the kernels spill
+  // (4512-token pages 5.75 -> 5.90 ms a call)
+  int* at = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 12;
+  for (int k = slot; k < count; k += slots) {
+    const int b = C.words[kStripList - (S::kShape - 1) * kStripShapeWords + C.words[kStripFirst] + k];
+    const int n = A.offsets[b + 1] - A.offsets[b];
+    const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
+    // (every workgroup of the slot takes the same decisions: they read the same words)
+    if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
+    if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
+    const int groups = strip_teams(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
+    int32_t* counter = C.words + (PAIRED ? kStripLast : kStripCounters + slot);
+    strip_clear<S>(C, b, rank);
+    arrived += per_slot;
+    if (!strip_meet(C, counter, arrived, true, flag)) return false;
+    arrived += groups;
+    if ((PAIRED ? rank & ~1 : rank) < groups) {                // (a workgroup's two teams decide alike)
+      if (strip_thread() == 0) {
+        at[0] = slot, at[1] = k, at[2] = arrived, at[3] = slots, at[4] = count, at[5] = per_slot, at[6] = rank;
+      }
+      if (!sinkhorn_strip_image<S, PAIRED>(C, b, rank, groups, counter, arrived, 2 * slot < slots, lds, flag)) return false;
+      slot = __builtin_amdgcn_readfirstlane(at[0]);
+      k = __builtin_amdgcn_readfirstlane(at[1]);
+      arrived = __builtin_amdgcn_readfirstlane(at[2]);
+      slots = __builtin_amdgcn_readfirstlane(at[3]);
+      count = __builtin_amdgcn_readfirstlane(at[4]);
+      per_slot = __builtin_amdgcn_readfirstlane(at[5]);
+      rank = __builtin_amdgcn_readfirstlane(at[6]);
+    } else if (!strip_meet(C, counter, arrived, false, flag)) {
+      return false;
+    }
+  }
+  return true;
+}
+
 // Slot s takes images s, s + slots, ... of the list.  The slot's arrival counter runs on through all
-// its meetings: one when the slot is complete, one of all its workgroups before each image (the image's
-// exchange area cleared), one of the image's workgroups at its end (the pairing keys out).  The last
-// workgroups take the slots given up, one after another, with a counter of their own.
+// its meetings, the first of which is when the slot is complete.
 template <typename S>
 __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_strips(StripArgs C) {
   __shared__ __align__(16) unsigned char lds[strip_lds_of<S>()];
   int* flag = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 2;
-  // (all waves or none: a slot that gives up writes the word while the last workgroups may be starting)
+  // (all waves or none: a slot that gives up writes the word while others may be starting)
   if (threadIdx.x == 0) *flag = C.status[0];
   __syncthreads();
   if (__builtin_amdgcn_readfirstlane(*flag)) return;
-  int count = C.words[kStripCount];
+  const int count = C.words[kStripCount];
   if (count == 0) return;
-  const int units = C.words[kStripTop];
-  int per_slot = kStripTeams * units;
+  const int units = C.words[kStripTop], per_slot = kStripTeams * units;
   const int block = blockIdx.x;
-  bool last = block >= C.slot_blocks;
-  int slots = strip_slots(units, C.cus), slot, rank;
+  const int slots = strip_slots_used(units, count, C.cus);
+  int slot, rank;
   if (units <= kStripXcdGroups) {                   // one XCD per slot
-    slots = min(slots, (count + 7) / 8 * 8);
     slot = (block & 7) * (slots >> 3) + (block >> 3) / per_slot;
     rank = (block >> 3) % per_slot;
   } else {
-    slots = min(slots, count);
     slot = block / per_slot;
     rank = block % per_slot;
   }
-  if (last) {
-    slot = 0;
-    rank = block - C.slot_blocks;
-    if (rank >= per_slot) return;
-    const int seen = static_cast<int>(threadIdx.x) < min(slots, count)   // (the slots that have images)
-                         ? __hip_atomic_load(C.words + kStripCounters + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                         : per_slot;
-    if (!__syncthreads_or((seen & kStripGivenUp) || seen < per_slot)) return;   // all complete: the usual case
-  } else if (block >= slots * per_slot || slot >= count) {
-    return;
-  }
-  const SinkhornArgs& A = C.S;
-  int arrived = last ? 0 : per_slot, form_limit = C.form_limit;
-  // the loop's state, in LDS while an image is worked on: in registers it makes the kernels spill
-  // (4512-token pages 5.75 -> 5.90 ms a call)
-  int* at = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 12;
-  for (;;) {
-    if (strip_complete(C.words + kStripCounters + slot, per_slot, form_limit, !last, flag) != last) {
-      for (int k = slot; k < count; k += slots) {
-        const int b = C.words[kStripList - (S::kShape - 1) * kStripShapeWords + C.words[kStripFirst] + k];
-        const int n = A.offsets[b + 1] - A.offsets[b];
-        const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
-        // (every workgroup of the slot takes the same decisions: they read the same words)
-        if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
-        if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
-        const int groups = strip_teams(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
-        int32_t* counter = C.words + (last ? kStripLast : kStripCounters + slot);
-        strip_clear<S>(C, b, rank);
-        arrived += per_slot;
-        if (!strip_meet(C, counter, arrived, true, flag)) return;
-        arrived += groups;
-        if (rank < groups) {
-          if (threadIdx.x == 0) {
-            at[0] = slot, at[1] = k, at[2] = arrived, at[3] = slots, at[4] = count, at[5] = per_slot, at[6] = rank, at[7] = last, at[8] = form_limit;
-          }
-          if (!sinkhorn_strip_image<S>(C, b, rank, groups, counter, arrived, 2 * slot < slots, lds, flag)) return;
-          slot = __builtin_amdgcn_readfirstlane(at[0]);
-          k = __builtin_amdgcn_readfirstlane(at[1]);
-          arrived = __builtin_amdgcn_readfirstlane(at[2]);
-          slots = __builtin_amdgcn_readfirstlane(at[3]);
-          count = __builtin_amdgcn_readfirstlane(at[4]);
-          per_slot = __builtin_amdgcn_readfirstlane(at[5]);
-          rank = __builtin_amdgcn_readfirstlane(at[6]);
-          last = __builtin_amdgcn_readfirstlane(at[7]) != 0;
-          form_limit = __builtin_amdgcn_readfirstlane(at[8]);
-        } else if (!strip_meet(C, counter, arrived, false, flag)) {
-          return;
-        }
-      }
-    }
-    if (!last || ++slot >= min(slots, count)) return;
-  }
+  if (block >= slots * per_slot || slot >= count) return;
+  if (!strip_complete(C.words + kStripCounters + slot, per_slot, C.form_limit, flag)) return;
+  int arrived = per_slot;
+  strip_images<S, false>(C, slot, slots, count, rank, per_slot, arrived, lds);
+}
+
+// The slots given up, one after another, with a counter of their own.  Behind k_sinkhorn_strips on its stream, with as
+// many workgroups as a slot has compute units; none given up, the usual case, costs a call about 1 us.
+template <typename S>
+__global__ __launch_bounds__(kStripTeams * kStripThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_strips_left(StripArgs C) {
+  constexpr int kTeamLds = (strip_lds_of<S>() + 15) & ~15;
+  __shared__ __align__(16) unsigned char lds[kStripTeams * kTeamLds];
+  int* flag = reinterpret_cast<int*>(lds);
+  // (all waves or none: one that gives up writes the word while others may be starting)
+  if (threadIdx.x == 0) *flag = C.status[0];
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(*flag)) return;
+  const int count = C.words[kStripCount];
+  const int units = C.words[kStripTop], per_slot = kStripTeams * units;
+  if (count == 0 || static_cast<int>(blockIdx.x) >= units) return;
+  const int slots = strip_slots_used(units, count, C.cus), with_images = min(slots, count);
+  auto left = [&](int slot) { return (C.words[kStripCounters + slot] & kStripGivenUp) != 0; };
+  if (!__syncthreads_or(static_cast<int>(threadIdx.x) < with_images && left(threadIdx.x))) return;
+  const int team = __builtin_amdgcn_readfirstlane(threadIdx.x / kStripThreads);
+  int arrived = 0;
+  for (int slot = 0; slot < with_images; ++slot)
+    if (left(slot) && !strip_images<S, true>(C, slot, slots, count, kStripTeams * blockIdx.x + team, per_slot, arrived, lds + team * kTeamLds))
+      return;
 }
 
 }  // namespace rtp

@@ -124,7 +124,7 @@ constexpr int kVariantA = 0, kVariantDual = 1, kVariantDual48 = 2, kVariantB = 3
 constexpr int kListTiled = 14, kListMid = 15, kWorkLists = 16;
 // Words of the strip kernels, in device memory that only they use.  Per strip shape: how many images
 // it has, how many compute units the one that needs most of them takes, where its images begin in the
-// list, arrival counters of its slots and of the last workgroups, and a give-up word (zero when the
+// list, arrival counters of its slots and of the launch that does what they leave, and a give-up word (zero when the
 // kernel starts); then the list.
 constexpr int kStripMaxSlots = 64, kStripShapes = 4;
 constexpr int kStripCount = 0, kStripTop = 1, kStripFirst = 2, kStripCounters = 3, kStripLast = kStripCounters + kStripMaxSlots,

@@ -512,8 +512,8 @@ STRIP_BATCHES = {
 
 
 @pytest.mark.parametrize("name", list(STRIP_BATCHES))
-def test_strip_slots_that_do_not_get_complete_leave_their_images_to_the_last_workgroups(monkeypatch, name):
-    """A strip slot whose workgroups are not all resident in time is given up, and the launch's last workgroups do
+def test_strip_slots_that_do_not_get_complete_leave_their_images_to_the_next_launch(monkeypatch, name):
+    """A strip slot whose workgroups are not all resident in time is given up, and a launch of whole compute units does
     its images.  With the host-side test switch every slot is given up: same bits as with none, and right."""
     counts, ratio, iters = STRIP_BATCHES[name]
     batch = _clustered(counts, 16, "f32", 64, ratio=ratio, iters=iters)
@@ -527,6 +527,30 @@ def test_strip_slots_that_do_not_get_complete_leave_their_images_to_the_last_wor
     g = hz.run_prune(batch)
     assert g["rc"] == 0 and g["status"] == 0
     for k in ("out", "pair", "sel", "keep"):
+        np.testing.assert_array_equal(f[k], g[k])
+
+
+@pytest.mark.parametrize("iters", [0, 1, 4])
+@pytest.mark.parametrize("top,shapes", [
+    ((788, 570), [(72, 300), (73, 576), (145, 200), (360, 463), (360, 464), (576, 289), (577, 290), (217, 575)]),
+    ((776, 582), [(40, 900), (41, 577), (81, 300), (160, 578), (161, 579), (401, 957), (800, 558)]),
+    ((1500, 1400), [(32, 1408), (33, 1408), (65, 1200), (1492, 1400)]),
+    ((1250, 1750), [(24, 1792), (25, 1700), (49, 1792), (1208, 1792)]),
+])
+def test_slots_given_up_on_workgroups_of_two_teams(monkeypatch, top, shapes, iters):
+    """The launch behind the strips does two of their workgroups' parts in each of its own: images of one part
+    (the other half of the workgroup is there for the barriers), of an even and of an odd number, several to a slot,
+    both forms of the exchange, every strip shape.  Same bits as the strips'."""
+    shapes = [top] + shapes * 2
+    batch = _clustered([m + r for m, r in shapes], 16, "f32", 66, iters=iters, ratio=top[0] / (top[0] + top[1]))
+    keep = [m for m, _ in shapes]
+    f = hz.run_staged(batch, keep_counts_in=keep)
+    assert f["status"] == 0
+    _log(hz.compare_batch(batch, f, staged=True, keep_counts=keep, images=list(range(len(shapes) // 2 + 1))), f"two teams {top}")
+    monkeypatch.setenv("RTPRUNE_STRIP_FORM_POLLS", "0")
+    g = hz.run_staged(batch, keep_counts_in=keep)
+    assert g["status"] == 0
+    for k in ("out", "pair", "plan"):
         np.testing.assert_array_equal(f[k], g[k])
 
 
