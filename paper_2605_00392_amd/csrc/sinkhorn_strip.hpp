@@ -47,8 +47,9 @@
 // 2 (r + 1) values read instead of groups (r + 1).  (Eight workgroups of 523 columns, 64 images: 0.88 ms
 // with one trip, 0.81 with two at the time; up to six of 280: 0.540 and 0.577.)
 // Values travel as device-scope stores and loads past the caches, the loads straight into LDS, and carry in
-// their last bit which use of their place they belong to (the uses alternate), so no counters, no barriers
-// across workgroups and nothing put back.  (A sum's or y's last bit is 1e-16 of it; the reciprocal is good to 2e-15.)
+// their sign, which is theirs to spare (sums of products of positive numbers, and reciprocals of such), which use of
+// their place they belong to (the uses alternate), so no counters, no barriers across workgroups, nothing put back and
+// all 53 bits.
 // The places lie in the image's own kernel-matrix slot, see strip_exchange_doubles, and are zero (of no use
 // yet) before the image:
 //   direct   two buffers in turn: a workgroup that publishes iteration i has seen everybody's sums of
@@ -79,15 +80,19 @@ struct StripArgs {
 };
 
 // Two places at once, `at` (even) doubles into an image's exchange area: device-scope stores of 16 bytes, of which
-// every 8 arrive whole.  A value's last bit says which use of its place it belongs to (`use`: 0 or 1).
+// every 8 arrive whole.  A value's sign says which use of its place it belongs to (`use`: 0 or kExOdd).
+constexpr uint32_t kExOdd = 0x80000000u;
+__host__ __device__ inline uint32_t ex_mark(uint32_t high, uint32_t use) { return (high & ~kExOdd) | use; }   // (a NaN may have either sign)
+__host__ __device__ inline bool ex_is_of(uint32_t high, uint32_t use) { return ((high ^ use) & kExOdd) == 0; }
+__host__ __device__ inline double ex_value(double marked) { return fabs(marked); }
 typedef double f64x2_t __attribute__((ext_vector_type(2)));
 constexpr int kExAgent = 16;   // (sc1: as far as all XCDs see it)
 __device__ __forceinline__ auto ex_resource(double* area) { return __builtin_amdgcn_make_buffer_rsrc(area, 0, 0x7fffffff, 0x00020000); }
 template <typename R>
 __device__ __forceinline__ void ex_store2(R ex, int at, double v0, double v1, uint32_t use) {
   u32x4_t w = __builtin_bit_cast(u32x4_t, f64x2_t{v0, v1});
-  w[0] = (w[0] & ~1u) | use;
-  w[2] = (w[2] & ~1u) | use;
+  w[1] = ex_mark(w[1], use);
+  w[3] = ex_mark(w[3], use);
   __builtin_amdgcn_raw_buffer_store_b128(w, ex, 8 * at, 0, kExAgent);
 }
 
@@ -239,11 +244,11 @@ __device__ __forceinline__ bool strip_receive(const StripArgs& C, const double* 
       asm volatile("" ::: "memory");
       v = *reinterpret_cast<const f64x2_t*>(rx + kStripPiece * k + 2 * lane);
       const u32x4_t w = __builtin_bit_cast(u32x4_t, v);
-      if (__ballot(((w[0] ^ use) | (w[2] ^ use)) & 1u) == 0) break;
+      if (__ballot(!(ex_is_of(w[1], use) && ex_is_of(w[3], use))) == 0) break;
       if (!seen || !ex_wait(C, spin++)) { seen = false; break; }
       request(k);
     }
-    take(kStripPiece * k + 2 * lane, v[0], v[1]);
+    take(kStripPiece * k + 2 * lane, ex_value(v[0]), ex_value(v[1]));
   }
   return seen;
 }
@@ -467,7 +472,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       return acc;
     };
     const int sums = direct ? (it & 1) * sums_buf : 0; // (places are counted from `area`)
-    const uint32_t use = direct ? ~(it >> 1) & 1 : ~it & 1;
+    const uint32_t use = (direct ? ~(it >> 1) : ~it) & 1 ? kExOdd : 0u;
     const auto ex = ex_resource(area);
     if (groups > 1 && here) {
       const int published = direct ? row : owned;
@@ -501,10 +506,11 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       lds_barrier();
       for (int e = 2 * te; e < row; e += 2 * T) {
         f64x2_t acc = *reinterpret_cast<const f64x2_t*>(rx + e);
+        acc = f64x2_t{ex_value(acc[0]), ex_value(acc[1])};
         for (int g = 1; g < groups; ++g) {
           const f64x2_t v = *reinterpret_cast<const f64x2_t*>(rx + g * row + e);
-          acc[0] += v[0];
-          acc[1] += v[1];
+          acc[0] += ex_value(v[0]);
+          acc[1] += ex_value(v[1]);
         }
         keep(e, finish(e, acc[0]), finish(e + 1, acc[1]));
       }
@@ -523,8 +529,8 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
 #pragma unroll 4
         for (int g = te & (lanes - 1); g < groups; g += lanes) {
           const f64x2_t v = *reinterpret_cast<const f64x2_t*>(rx + g * cw + k);
-          acc[0] += v[0];
-          acc[1] += v[1];
+          acc[0] += ex_value(v[0]);
+          acc[1] += ex_value(v[1]);
         }
         double v0 = group_sum<2>(acc[0]), v1 = group_sum<2>(acc[1]);
         if (wide >= 4) {
