@@ -310,29 +310,40 @@ __device__ __forceinline__ void merge_mid_tile(const MergeMidArgs& A, int b, int
   else merge_mid_rows<1>(A, b, lo, n, m, r, i0, lds);
 }
 
+// The tiles of the images on the tiled list, `tile_rows` rows of them to an image.
+template <int COLS>
+__device__ __forceinline__ void merge_tiled_list(MergeTiledArgs A, int tile_rows, const int32_t* __restrict__ work, int B,
+                                                 unsigned char* lds) {
+  A.tiles_d = (A.D + COLS - 1) / COLS;
+  const int tiles = tile_rows * A.tiles_d;
+  const long long items = static_cast<long long>(work[kListTiled]) * tiles;
+  for (long long item = blockIdx.x; item < items; item += gridDim.x) {
+    __syncthreads();   // the previous tile's last LDS reads
+    const int k = static_cast<int>(item / tiles);
+    merge_tile<COLS>(A, work[kWorkLists + kListTiled * B + k], static_cast<int>(item - static_cast<long long>(k) * tiles), lds);
+  }
+}
+
 // The list forms of both matrix-core merge kernels in one launch (the sizes of the
 // pruned sets were decided on the device): a fixed number of workgroups, a multiple
 // of eight, first walk the tiles of the images on the tiled list (more than 64
 // pruned tokens; merge_tiled.hpp), then the row tiles of the images on this file's
 // list.  For the latter, workgroups being dealt to the eight XCDs in turn, item q
 // runs on XCD q % 8: the tiles of one image are given items of one residue, and
-// its pruned rows are fetched into one L2 only.  `tiles_t` / `tiles_m` = 0: that
-// role is not wanted.  Both roles use the same LDS buffer.
+// its pruned rows are fetched into one L2 only.  `tile_rows` / `tiles_m` = 0: that
+// role is not wanted.  Fewer than `thin_below` wide tiles in all: narrow ones (merge_thin_below).  Both roles
+// use the same LDS buffer.
 __global__ __launch_bounds__(kMergeMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_merge_lists(
-    MergeTiledArgs TA, int tiles_t, MergeMidArgs A, int tiles_m, const int32_t* __restrict__ work, int B, int mid_min,
+    MergeTiledArgs TA, int tile_rows, int thin_below, MergeMidArgs A, int tiles_m, const int32_t* __restrict__ work, int B, int mid_min,
     const int32_t* __restrict__ status) {
   if (status[0]) return;
   static_assert(kMergeTiledThreads == kMergeMidThreads, "one workgroup shape for both roles");
   constexpr int kLdsBytes = kMergeTiledLdsBytes > kMergeMidLdsBytes ? kMergeTiledLdsBytes : kMergeMidLdsBytes;
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
-  if (tiles_t > 0) {
-    const int count = work[kListTiled];
-    const long long items = static_cast<long long>(count) * tiles_t;
-    for (long long item = blockIdx.x; item < items; item += gridDim.x) {
-      __syncthreads();   // the previous tile's last LDS reads
-      const int k = static_cast<int>(item / tiles_t);
-      merge_tile<kMergeTileCols>(TA, work[kWorkLists + kListTiled * B + k], static_cast<int>(item - static_cast<long long>(k) * tiles_t), lds);
-    }
+  if (tile_rows > 0) {
+    const long long rows = static_cast<long long>(work[kListTiled]) * tile_rows;
+    if (rows * ((TA.D + kMergeTileCols - 1) / kMergeTileCols) < thin_below) merge_tiled_list<kMergeThinCols>(TA, tile_rows, work, B, lds);
+    else merge_tiled_list<kMergeTileCols>(TA, tile_rows, work, B, lds);
   }
   if (tiles_m > 0 && merge_mid_runs(work + kListMid, mid_min)) {
     const int count = work[kListMid];

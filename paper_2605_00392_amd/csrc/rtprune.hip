@@ -447,6 +447,16 @@ unsigned tiled_list_blocks(int tiles, int B) {
   return static_cast<unsigned>(std::min<long long>(all, 8LL * compute_units()));
 }
 
+// The tiled merge takes tiles of 128 features when there are fewer of 256 than this: while those would not give
+// every compute unit its two workgroups, and always at widths of which the last wide tile leaves too much unused.
+// 256 / 128 features a tile, us: grid form, one page of 4512 tokens 118 / 100; 256 pages of 600 tokens with 300 pruned at
+// widths of 128, 384 and 640 69.6 / 59.9, 121.6 / 125.7 and 171.7 / 191.3, 64 of 1083 with 523 51.6 / 47.7, 90.6 / 84.4
+// and 102.3 / 126.0.  List form, pages of 400 tokens with 100 pruned: one, 4 and 16 at 1280 20.3 / 16.6, 20.7 / 16.9 and
+// 25.2 / 22.1, 64 51.2 / 59.1; 1024 at 128, 384 and 640 169.4 / 144.8, 319.1 / 304.3 and 424.5 / 423.6.
+int merge_thin_below(int D, bool grid) {
+  return D % kMergeTileCols && D <= (grid ? 128 : 384) ? INT32_MAX : 2 * compute_units();
+}
+
 // Largest pruned set any image of the call can have.  `hint` >= 0: the caller's
 // bound (fixed retention); kPrunedFromClamp: the kept counts come from this
 // call's dynamic ratio, whose clamp bounds them; kPrunedUnknown: the kept counts
@@ -728,10 +738,10 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
     // tile and image for the tiled kernel; else its list form shares a launch with the
     // middling sets' kernel)
     const bool tiled_grid = tiled && (max_pruned_hint >= 2 * kTiledMinPruned || !work || !status);
-    const int tiles_wide = (in->D + kMergeTileCols - 1) / kMergeTileCols;
-    // Narrow tiles while wide ones would not give every compute unit its two workgroups.
-    const bool thin = tiled_grid && static_cast<long long>(tiles_ti) * tiles_wide * in->B < 2LL * compute_units();
-    const int tiles_td = thin ? in->D / kMergeThinCols : tiles_wide;
+    const int tiles_wide = (in->D + kMergeTileCols - 1) / kMergeTileCols, tiles_narrow = in->D / kMergeThinCols;
+    const int thin_below = merge_thin_below(in->D, tiled_grid);
+    const bool thin = tiled_grid && static_cast<long long>(tiles_ti) * tiles_wide * in->B < thin_below;
+    const int tiles_td = thin ? tiles_narrow : tiles_wide;   // (the list form counts its images and decides by itself)
     const MergeTiledArgs TA{tok, in->offsets, in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens,
                             tiles_td, static_cast<bf16_t*>(out), xcd_images(in)};
     if (tiled_grid && thin)
@@ -742,9 +752,9 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
     if (tiled_list || mid) {
       const MergeMidArgs MA{tok, in->offsets, in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens,
                             static_cast<bf16_t*>(out)};
-      const int tiles_t = tiled_list ? tiles_ti * tiles_td : 0, tiles_m = mid ? tiles_mid : 0;
-      const dim3 gl((tiled_list_blocks(std::max(tiles_t, tiles_m), in->B) + 7) / 8 * 8);
-      hipLaunchKernelGGL(k_merge_lists, gl, dim3(kMergeMidThreads), 0, s, TA, tiles_t, MA, tiles_m, work, in->B, mid_min,
+      const int tile_rows = tiled_list ? tiles_ti : 0, tiles_m = mid ? tiles_mid : 0;
+      const dim3 gl((tiled_list_blocks(std::max(tile_rows * tiles_narrow, tiles_m), in->B) + 7) / 8 * 8);
+      hipLaunchKernelGGL(k_merge_lists, gl, dim3(kMergeMidThreads), 0, s, TA, tile_rows, thin_below, MA, tiles_m, work, in->B, mid_min,
                          status);
     }
   }

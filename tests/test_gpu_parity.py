@@ -254,6 +254,23 @@ def test_tiled_merge_at_the_edges_of_its_tiles(D, copies):
     _log(rep, f"tiled merge {D} {copies}")
 
 
+@pytest.mark.parametrize("copies", [1, 40])
+@pytest.mark.parametrize("D", [128, 384, 640, 1152])
+def test_tiled_merge_over_its_list(D, copies):
+    """Pruned sets of 65 to 127 tokens under a fixed retention are merged over the list of them, in narrow tiles when they
+    are few (4 images on the list) or the width leaves much of a wide one unused, else in wide ones (160 images of four rows
+    of three or five tiles); short pages that are not on it lie between them."""
+    counts = [400, 90, 331, 508, 200, 330] * copies
+    batch = _clustered(counts, D, "bf16", 46, iters=9, ratio=0.7504)
+    assert batch.max_tokens == 508
+    f = hz.run_prune(batch)
+    assert f["rc"] == 0 and f["status"] == 0
+    pruned = np.diff(batch.offsets) - f["keep"]
+    assert pruned.max() < 128 and (pruned > 64).sum() == 4 * copies and pruned.min() <= 64
+    rep = hz.compare_batch(batch, f, images=list(range(6)) + [len(counts) - 3, len(counts) - 1])
+    _log(rep, f"tiled merge list {D} {copies}")
+
+
 def test_tall_register_shapes_at_their_edges():
     """Kept and pruned counts on both sides of the limits of the two shapes that hold
     a tall image (more than 512 rows) in one workgroup's registers: 1535 x 15
