@@ -145,6 +145,7 @@ __device__ __forceinline__ void forget_origin(uint2& u) { asm volatile("" : "+v"
 __device__ __forceinline__ void forget_origin(float& u) { asm volatile("" : "+v"(u)); }
 __device__ __forceinline__ void forget_origin(int& u) { asm volatile("" : "+v"(u)); }
 __device__ __forceinline__ void forget_origin(double& u) { asm volatile("" : "+v"(u)); }
+__device__ __forceinline__ void forget_scalar(int& u) { asm volatile("" : "+s"(u)); }   // (the same in every lane)
 __device__ __forceinline__ void forget_origin(float4& u) {
   asm volatile("" : "+v"(u.x), "+v"(u.y), "+v"(u.z), "+v"(u.w));
 }

@@ -199,7 +199,7 @@ template <typename S> struct StripLds {
   static constexpr int kReceive = kDirect > 2 * kShares ? kDirect : 2 * kShares;
   static constexpr int kWaves = kStripWaves * kPitch;
   static constexpr int kFirst = ((kReceive > kWaves ? kReceive : kWaves) + kStripPiece - 1) / kStripPiece * kStripPiece;
-  static constexpr int kBytes = 8 * (kFirst + S::kCols + 8) + 72;
+  static constexpr int kBytes = 8 * (kFirst + S::kCols + 6) + 72;
   static_assert(kBytes <= 160 * 1024 / kStripTeams, "a compute unit's workgroups share its LDS");
 };
 template <typename S> constexpr int strip_lds_of() { return StripLds<S>::kBytes; }
@@ -299,9 +299,6 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   constexpr int RPT = S::RPT, CPT = S::CPT, kCols = S::kCols, T = kStripThreads;
   constexpr int kChunks = (RPT + 7) / 8, kLast = RPT - 8 * (kChunks - 1);
   constexpr bool kKeepY = CPT <= 9;          // y in registers across the chunks of rows (else re-read from LDS)
-  // (x_dust is in LDS while the values travel: with the widest strips it costs a register too many; with the others
-  // that form is slower, 32 pages of 2137 tokens 1.747 -> 1.759 ms)
-  constexpr bool kDustInLds = S::kShape == kShapeStripD;
   const SinkhornArgs& A = C.S;
   const DevParams& p = A.p;
   const int tt = strip_thread(), tw = __builtin_amdgcn_readfirstlane(tt >> 6), lane = tt & 63;
@@ -318,7 +315,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   int32_t* __restrict__ pair_out = A.pair_out;
   const int rows_per = (m + groups - 1) / groups;            // the rows dealt evenly
   const int row_base = rank * rows_per;
-  const int m_loc = min(m - row_base, rows_per);             // >= 1: groups = ceil(m / rows per strip)
+  const int rows = min(m - row_base, rows_per), m_loc = rows;   // >= 1: groups = ceil(m / rows per strip)
   constexpr bool kMayDirect = strip_direct(S::kShape, 1, 1);    // (the wider shapes never are)
   const bool direct = kMayDirect && strip_direct(S::kShape, r, groups);
   const int cw = strip_share(r, groups);                     // columns (the sum of x counted as column r) a workgroup owns
@@ -337,7 +334,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
   double* xw = static_cast<double*>(lds);                    // [W][kPitch]
   double* ys = xw + StripLds<S>::kFirst;                     // [kCols] and the sum of x
   double* rx = xw;                                           // received: [teams at a time][row], [groups][cw] or [owned]
-  int* seen_words = reinterpret_cast<int*>(ys + kCols + 8);  // [2]
+  int* seen_words = reinterpret_cast<int*>(ys + kCols + 6);  // [2]
 
   // (buffer loads: a row that the workgroup does not have, or a column past the last one, reads as zero,
   // with no mask and no address of its own in registers)
@@ -364,7 +361,6 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     ys[kCols + 3] = static_cast<double>(r);
     ys[kCols + 4] = static_cast<double>(m);
     ys[kCols + 5] = static_cast<double>(1.0f / static_cast<float>(cw));
-    ys[kCols + 6] = x_init;
   }
   __syncthreads();
 
@@ -373,6 +369,8 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     else __builtin_amdgcn_s_setprio(0);
     int fixed = kCols + 2;                             // (the image's constants are read anew: registers)
     forget_origin(fixed);
+    int m_loc = rows;                                  // (and what is compared with it: else the results are held, and spilled)
+    forget_scalar(m_loc);
     const double row_dust = ys[fixed] * y_dust;
     double xs = 0.0, ly = 0.0;
     double t[kChunks > 1 ? CPT : 1];
@@ -451,15 +449,15 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
       for (int c = 0; c < CPT; ++c) xw[tw * kPitch + 64 * c + lane] = t[c];
     }
     __builtin_amdgcn_s_setprio(3);
-    if (lane < 2) xw[tw * kPitch + kCols + lane] = 0.0;
-    if (lane == 0) xw[tw * kPitch + r] = xs;           // (the columns past the last one are zero: this one is the sum of x)
+    int te = tt;                                       // (comparisons and addresses are worked out anew: registers)
+    forget_origin(te);
+    if ((te & 63) < 2) xw[tw * kPitch + kCols + (te & 63)] = 0.0;
+    if ((te & 63) == 0) xw[tw * kPitch + r] = xs;   // (the columns past the last one are zero: this one is the sum of x)
     int& seen_all = seen_words[it & 1];                // (two words in turn: the next write of one is a whole iteration away)
-    if (tt == 0) seen_all = 1;
+    if (te == 0) seen_all = 1;
     lds_barrier();
     // this workgroup's sums: columns 2 k and 2 k + 1 (the sum of x as column r) by thread k, k + T, ...
-    int te = tt;
     const float inv_cw = static_cast<float>(ys[fixed + 3]);
-    forget_origin(te);                                 // (the places' addresses are worked out anew: registers)
     auto own_sums = [&](int e) {
       const f64x2_t* col = reinterpret_cast<const f64x2_t*>(xw + min(e, kCols));
       f64x2_t acc = col[0];
@@ -476,7 +474,7 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     const auto ex = ex_resource(area);
     if (groups > 1 && here) {
       const int published = direct ? row : owned;
-#pragma unroll 2
+#pragma unroll 1
       for (int e = 2 * te; e < published; e += 2 * T) {
         const int o = static_cast<int>((static_cast<float>(e) + 0.5f) * inv_cw);   // e / cw
         const f64x2_t v = own_sums(e);
@@ -487,7 +485,6 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     // (while the sums travel) the dustbins' scalings from the previous y
     x_dust = ys[fixed + 1] * rcp64(ys[fixed] * (wave_sum_dpp(ly) + y_dust));
     const double col_dust = ys[fixed] * x_dust;
-    if (kDustInLds && te == 0) ys[fixed + 4] = x_dust;
     bool seen = true;
     auto keep = [&](int e, double v0, double v1) {     // y (and the sum of x) of columns e and e + 1
       if (e <= r) ys[e < r ? e : kCols] = v0;
@@ -551,17 +548,15 @@ __device__ __forceinline__ bool sinkhorn_strip_image(const StripArgs& C, int b, 
     if (!seen) seen_all = 0;
     lds_barrier();
     if (!seen_all) {                                   // a wait was given up (here or elsewhere): everybody leaves
-      if (tt == 0) {
+      if (te == 0) {
         __hip_atomic_store(C.words + kStripGaveUp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         atomicOr(C.status, RTP_DEV_SYNC_TIMEOUT);
       }
       return false;
     }
-    y_dust = ys[fixed + 2] * rcp64(ys[fixed] * (ys[kCols] + (kDustInLds ? ys[fixed + 4] : x_dust)));
+    y_dust = ys[fixed + 2] * rcp64(ys[fixed] * (ys[kCols] + x_dust));
   }
   __syncthreads();
-
-  if (kDustInLds) x_dust = ys[kCols + 6];
 
   // ---- plan and this workgroup's best partner per column ----
   float* P = A.plan_out ? A.plan_out + po : nullptr;
@@ -654,36 +649,41 @@ __device__ __forceinline__ bool strip_images(const StripArgs& C, int slot, int s
   // the loop's state, in LDS while an image is worked on: in registers it makes the kernels spill
   // (4512-token pages 5.75 -> 5.90 ms a call)
   int* at = reinterpret_cast<int*>(lds + strip_lds_of<S>()) - 12;
-  for (int k = slot; k < count; k += slots) {
-    const int b = C.words[kStripList - (S::kShape - 1) * kStripShapeWords + C.words[kStripFirst] + k];
-    const int n = A.offsets[b + 1] - A.offsets[b];
-    const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
-    // (every workgroup of the slot takes the same decisions: they read the same words)
-    if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
-    if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
-    const int groups = strip_teams(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
-    int32_t* counter = C.words + (PAIRED ? kStripLast : kStripCounters + slot);
-    strip_clear<S>(C, b, rank);
-    arrived += per_slot;
-    if (!strip_meet(C, counter, arrived, true, flag)) return false;
-    arrived += groups;
-    if ((PAIRED ? rank & ~1 : rank) < groups) {                // (a workgroup's two teams decide alike)
-      if (strip_thread() == 0) {
-        at[0] = slot, at[1] = k, at[2] = arrived, at[3] = slots, at[4] = count, at[5] = per_slot, at[6] = rank;
+  // (Once round.  Without a loop that the compiler takes for one, it keeps entries of the matrix in two places and moves
+  // them from one to the other each iteration.)
+  for (int again = 0;;) {
+    for (int k = slot; k < count; k += slots) {
+      const int b = C.words[kStripList - (S::kShape - 1) * kStripShapeWords + C.words[kStripFirst] + k];
+      const int n = A.offsets[b + 1] - A.offsets[b];
+      const int m = min(max(A.keep[b], 0), max(n, 0)), r = max(n, 0) - m;
+      // (every workgroup of the slot takes the same decisions: they read the same words)
+      if (m <= 0 || r <= 0 || sinkhorn_variant(m, r, A.p.mode) != kVariantStrip) continue;
+      if (!plan_fits(A.plan_offsets[b], m, r, A.plan_cap)) continue;
+      const int groups = strip_teams(S::kShape, m, A.p.mode);   // (at most per_slot: the list's builder has counted)
+      int32_t* counter = C.words + (PAIRED ? kStripLast : kStripCounters + slot);
+      strip_clear<S>(C, b, rank);
+      arrived += per_slot;
+      if (!strip_meet(C, counter, arrived, true, flag)) return false;
+      arrived += groups;
+      if ((PAIRED ? rank & ~1 : rank) < groups) {                // (a workgroup's two teams decide alike)
+        if (strip_thread() == 0) {
+          at[0] = slot, at[1] = k, at[2] = arrived, at[3] = slots, at[4] = count, at[5] = per_slot, at[6] = rank;
+        }
+        if (!sinkhorn_strip_image<S, PAIRED>(C, b, rank, groups, counter, arrived, 2 * slot < slots, lds, flag)) return false;
+        slot = __builtin_amdgcn_readfirstlane(at[0]);
+        k = __builtin_amdgcn_readfirstlane(at[1]);
+        arrived = __builtin_amdgcn_readfirstlane(at[2]);
+        slots = __builtin_amdgcn_readfirstlane(at[3]);
+        count = __builtin_amdgcn_readfirstlane(at[4]);
+        per_slot = __builtin_amdgcn_readfirstlane(at[5]);
+        rank = __builtin_amdgcn_readfirstlane(at[6]);
+      } else if (!strip_meet(C, counter, arrived, false, flag)) {
+        return false;
       }
-      if (!sinkhorn_strip_image<S, PAIRED>(C, b, rank, groups, counter, arrived, 2 * slot < slots, lds, flag)) return false;
-      slot = __builtin_amdgcn_readfirstlane(at[0]);
-      k = __builtin_amdgcn_readfirstlane(at[1]);
-      arrived = __builtin_amdgcn_readfirstlane(at[2]);
-      slots = __builtin_amdgcn_readfirstlane(at[3]);
-      count = __builtin_amdgcn_readfirstlane(at[4]);
-      per_slot = __builtin_amdgcn_readfirstlane(at[5]);
-      rank = __builtin_amdgcn_readfirstlane(at[6]);
-    } else if (!strip_meet(C, counter, arrived, false, flag)) {
-      return false;
     }
+    forget_scalar(again);
+    if (!again) return true;
   }
-  return true;
 }
 
 // Slot s takes images s, s + slots, ... of the list.  The slot's arrival counter runs on through all
