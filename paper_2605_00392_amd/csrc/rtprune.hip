@@ -442,10 +442,7 @@ int xcd_images(const rtprune_batch* in) {
 }
 
 // Workgroups of the list forms of the tiled kernels: eight per CU, or all tiles if fewer.
-unsigned tiled_list_blocks(int tiles, int B) {
-  const long long all = static_cast<long long>(tiles) * B;
-  return static_cast<unsigned>(std::min<long long>(all, 8LL * compute_units()));
-}
+unsigned tiled_list_blocks(long long all) { return static_cast<unsigned>(std::min(all, 8LL * compute_units())); }
 
 // The tiled merge takes tiles of 128 features when there are fewer of 256 than this: while those would not give
 // every compute unit its two workgroups, and always at widths of which the last wide tile leaves too much unused.
@@ -519,7 +516,7 @@ int launch_scores_t(const rtprune_batch* in, const DevParams& p, const int32_t* 
         if (max_pruned_hint >= 2 * kTiledMinPruned)
           hipLaunchKernelGGL(k_scores_tiled, dim3(tiles, in->B), dim3(kTiledThreads), 0, s, TA, st);
         else
-          hipLaunchKernelGGL(k_scores_tiled_list, dim3(tiled_list_blocks(tiles, in->B)), dim3(kTiledThreads), 0, s,
+          hipLaunchKernelGGL(k_scores_tiled_list, dim3(tiled_list_blocks(static_cast<long long>(tiles) * in->B)), dim3(kTiledThreads), 0, s,
                              TA, tiles, work, in->B, st);
       }
       return launched();
@@ -753,7 +750,10 @@ int launch_merge_t(const rtprune_batch* in, const DevParams& p, const int32_t* s
       const MergeMidArgs MA{tok, in->offsets, in->D, sel, keep, out_off, plan, plan_off, alpha, in->max_tokens,
                             static_cast<bf16_t*>(out)};
       const int tile_rows = tiled_list ? tiles_ti : 0, tiles_m = mid ? tiles_mid : 0;
-      const dim3 gl((tiled_list_blocks(std::max(tile_rows * tiles_narrow, tiles_m), in->B) + 7) / 8 * 8);
+      // (no more than there can be narrow tiles)
+      const long long rows = static_cast<long long>(tile_rows) * in->B;
+      const long long tiles_t = std::max(rows * tiles_wide, std::min(rows * tiles_narrow, 2LL * thin_below));
+      const dim3 gl((tiled_list_blocks(std::max(tiles_t, static_cast<long long>(tiles_m) * in->B)) + 7) / 8 * 8);
       hipLaunchKernelGGL(k_merge_lists, gl, dim3(kMergeMidThreads), 0, s, TA, tile_rows, thin_below, MA, tiles_m, work, in->B, mid_min,
                          status);
     }
