@@ -143,6 +143,7 @@ __device__ __forceinline__ void unpack4(const float4& u, float (&x)[4]) {
 // subexpression elimination across the call; emits no instruction).
 __device__ __forceinline__ void forget_origin(uint2& u) { asm volatile("" : "+v"(u.x), "+v"(u.y)); }
 __device__ __forceinline__ void forget_origin(float& u) { asm volatile("" : "+v"(u)); }
+__device__ __forceinline__ void forget_origin(uint32_t& u) { asm volatile("" : "+v"(u)); }
 __device__ __forceinline__ void forget_origin(int& u) { asm volatile("" : "+v"(u)); }
 __device__ __forceinline__ void forget_origin(double& u) { asm volatile("" : "+v"(u)); }
 __device__ __forceinline__ void forget_scalar(int& u) { asm volatile("" : "+s"(u)); }   // (the same in every lane)

@@ -280,8 +280,10 @@ __device__ __forceinline__ void merge_mid_rows(const MergeMidArgs& A, int b, int
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
           // The stage's offset goes into the vector register.  With a scalar one the compiler lets the very next
-          // instruction write over the stored registers, and its values were what the store wrote.
-          const uint32_t to = pair && short_stage ? kMergeMidBeyond + 1024 * rb + 64 * k : ooff[rb][k] + at;
+          // instruction write over the stored registers, and its values were what the store wrote.  (Forgotten, it
+          // stays there, and the two places of a store stay one store.)
+          uint32_t to = pair && short_stage ? kMergeMidBeyond + 1024 * rb + 64 * k : ooff[rb][k] + at;
+          forget_origin(to);
           __builtin_amdgcn_raw_buffer_store_b128(o[rb][k], rsrc, to + 128 * pair, 0, kMergeMidStream);
         }
       }
