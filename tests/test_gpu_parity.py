@@ -358,7 +358,7 @@ def test_multi_workgroup_resident_sinkhorn_widest_strips_at_their_edges(override
     # strips of 48 rows x 1792 columns, 27 to a slot; 1793 columns are the general kernel's
     ((1250, 1750), [(48, 1792), (49, 1792), (1208, 1792), (1200, 129), (97, 300), (60, 1793)], 6),
     ((1250, 1750), [(48, 1792), (433, 1409)], 0),
-    # a few images: strips of 64 rows x 576 columns, up to sixteen workgroups and one trip's exchange
+    # a few images: thin strips, 64 rows x 576 columns to a compute unit, up to sixteen workgroups
     ((1000, 287), [], 9),
     ((1024, 287), [(1, 200), (64, 576), (65, 576)], 9),
     ((420, 280), [(129, 300)], 1),
@@ -425,19 +425,35 @@ def test_dynamic_retention_in_two_strip_shapes_through_the_fused_call():
     _assert_fused_equals_staged(f, s, batch)
 
 
+# Images at the edges of the strips' forms, by strip shape: what the retention expects of the longest page (which
+# chooses the shape), and (kept, pruned): (workgroups, whether everybody reads everybody's sums in one trip).
+# tests/test_strip_forms_cpu.py asks the kernels' own rules for the same.
+STRIP_EDGES = {
+    "72 x 576": ((788, 570), {
+        (72, 300): (1, True), (73, 576): (2, True), (144, 575): (2, True), (145, 576): (3, True), (288, 576): (4, True),
+        (289, 463): (5, True), (289, 464): (5, False), (360, 573): (5, False), (576, 289): (8, True), (576, 290): (8, False),
+        (577, 574): (9, False), (788, 570): (11, False), (860, 190): (12, True), (860, 192): (12, False)}),
+    "40 x 960": ((776, 582), {
+        (40, 900): (1, True), (41, 577): (2, True), (80, 960): (2, True), (81, 301): (3, True), (120, 770): (3, True),
+        (120, 772): (3, False), (160, 579): (4, True), (160, 580): (4, False), (200, 463): (5, True), (201, 957): (6, False),
+        (640, 143): (16, True), (640, 144): (16, False), (680, 134): (17, True), (776, 582): (20, False)}),
+}
+
+
 @pytest.mark.parametrize("iters", [1, 2, 3, 6])
-def test_strips_of_half_a_compute_unit_at_their_edges(iters):
+@pytest.mark.parametrize("shape", list(STRIP_EDGES))
+def test_strips_of_half_a_compute_unit_at_their_edges(shape, iters):
     """Workgroups of 72 x 576 and 40 x 960: one of them, the most that everybody reads everybody's sums of
-    (2320) and the first that deal the columns out, more than an XCD's, and pruned counts whose shares and
-    pairs end unevenly."""
-    shapes = [(72, 300), (73, 576), (288, 573), (289, 574), (360, 463), (360, 464), (41, 577), (160, 960), (161, 959),
-              (400, 958), (640, 601), (641, 605), (1151, 133), (1152, 145)]
-    batch = _clustered([m + r for m, r in shapes], 128, "bf16", 44, iters=iters, ratio=1280.0 / 2240.0)
+    (2320) and the first that deal the columns out, and pruned counts whose shares and pairs end unevenly."""
+    top, forms = STRIP_EDGES[shape]
+    shapes = list(forms) * 2                           # (more images than thin strips are for)
+    batch = _clustered([m + r for m, r in shapes], 128, "bf16", 44, iters=iters, ratio=top[0] / (top[0] + top[1]))
+    assert batch.max_tokens == sum(top)
     keep = [m for m, _ in shapes]
     s = hz.run_staged(batch, keep_counts_in=keep)
     assert s["status"] == 0
-    rep = hz.compare_batch(batch, s, staged=True, keep_counts=keep)
-    _log(rep, f"half strips {iters}")
+    rep = hz.compare_batch(batch, s, staged=True, keep_counts=keep, images=list(range(len(forms))))
+    _log(rep, f"half strips {shape} {iters}")
 
 
 def test_multi_workgroup_resident_sinkhorn_wide_strips_fill_the_chip():
@@ -517,14 +533,16 @@ def test_multi_workgroup_sinkhorn_gives_up_instead_of_waiting_for_ever(monkeypat
         np.testing.assert_array_equal(g["pair"], ref["pair"])
 
 
-# batches whose images go through the strips: (sizes, retention, iterations).  One trip's exchange in slots of
-# four workgroups, several images to a slot; in slots of sixteen; two trips in slots of 24 across the XCDs, several
-# images to a slot; a thin strip page.
+# batches whose images go through the strips: (sizes, retention, iterations, whether their exchange takes one trip:
+# tests/test_strip_forms_cpu.py).  Several images to a slot of 3, 4, 14 and, across the XCDs, 24 compute units; thin
+# strips of one page.
 STRIP_BATCHES = {
-    "4 workgroups": ([1083] * 3 + list(range(800, 1070)), 560.0 / 1083.0, 5),
-    "16 workgroups": ([2137] + list(range(1700, 1900, 11)), 1238.0 / 2137.0, 5),
-    "24 workgroups": ([2900] + list(range(2860, 2895, 2)), 1500.0 / 2900.0, 4),
-    "one page": ([1156], 0.75, 9),
+    "3 units, one trip": ([700] * 3 + list(range(520, 700)), 560.0 / 1083.0, 5, True),
+    "4 units": ([1083] * 3 + list(range(800, 1070)), 560.0 / 1083.0, 5, False),
+    "16 units": ([2137] + list(range(1700, 1900, 11)), 1238.0 / 2137.0, 5, False),
+    "24 units": ([2900] + list(range(2860, 2895, 2)), 1500.0 / 2900.0, 4, False),
+    "one page": ([1156], 0.75, 9, False),
+    "one page, one trip": ([560], 0.75, 9, True),
 }
 
 
@@ -532,7 +550,7 @@ STRIP_BATCHES = {
 def test_strip_slots_that_do_not_get_complete_leave_their_images_to_the_next_launch(monkeypatch, name):
     """A strip slot whose workgroups are not all resident in time is given up, and a launch of whole compute units does
     its images.  With the host-side test switch every slot is given up: same bits as with none, and right."""
-    counts, ratio, iters = STRIP_BATCHES[name]
+    counts, ratio, iters, _ = STRIP_BATCHES[name]
     batch = _clustered(counts, 16, "f32", 64, ratio=ratio, iters=iters)
     f = hz.run_prune(batch)
     assert f["rc"] == 0 and f["status"] == 0
@@ -571,14 +589,22 @@ def test_slots_given_up_on_workgroups_of_two_teams(monkeypatch, top, shapes, ite
         np.testing.assert_array_equal(f[k], g[k])
 
 
-@pytest.mark.parametrize("names", [("16 workgroups",) * 4, ("16 workgroups", "24 workgroups", "4 workgroups", "24 workgroups")])
-def test_strip_calls_on_four_streams_at_once(names):
+@pytest.mark.parametrize("names,wide", [
+    (("16 units",) * 4, False),
+    (("16 units", "24 units", "4 units", "24 units"), False),
+    (("3 units, one trip", "16 units", "3 units, one trip", "24 units"), False),
+    (("16 units", "4 units", "3 units, one trip", "16 units"), True),
+])
+def test_strip_calls_on_four_streams_at_once(names, wide):
     """Four calls at a time, a stream each, whose slots compete for the compute units: all end without a time-out
-    and with the bits of a call alone."""
+    and with the bits of a call alone.  `wide`: bf16 tokens of 640 features, whose tiled kernels, of other register counts,
+    run beside the strips."""
     jobs = []
     for i, name in enumerate(names):
-        counts, ratio, iters = STRIP_BATCHES[name]
-        batch = _clustered(counts, 16, "f32", 70 + i, ratio=ratio, iters=40)
+        counts, ratio, iters, _ = STRIP_BATCHES[name]
+        if wide:
+            counts = counts[:60]
+        batch = _clustered(counts, 640 if wide else 16, "bf16" if wide else "f32", 70 + i, ratio=ratio, iters=40)
         ref = hz.run_prune(batch)
         assert ref["rc"] == 0 and ref["status"] == 0
         db, p = rt.upload(batch), rt.make_params(batch.params)
@@ -595,7 +621,7 @@ def test_strip_calls_on_four_streams_at_once(names):
     for ref, db, p, ws, out, off, pair, stream in jobs:
         assert hz.device_status(ws) == 0
         rows = int(ref["out_offsets"][-1])
-        np.testing.assert_array_equal(out.cpu().numpy()[:rows], ref["out"][:rows])
+        np.testing.assert_array_equal(hz._np(out)[:rows], ref["out"][:rows])
         np.testing.assert_array_equal(pair.cpu().numpy(), ref["pair"])
 
 
@@ -604,7 +630,7 @@ def test_strips_give_up_instead_of_waiting_for_ever(monkeypatch, name):
     """The strips' own waits are bounded, in both forms of their exchange.  With no poll allowed the first meeting
     gives up; with a few, workgroups in step may get through it and through some iterations: the call either says
     that a wait timed out or is right to the last bit."""
-    counts, ratio, iters = STRIP_BATCHES[name]
+    counts, ratio, iters, _ = STRIP_BATCHES[name]
     batch = _clustered(counts[:6], 16, "f32", 65, ratio=ratio, iters=iters)
     ref = hz.run_prune(batch)
     assert ref["rc"] == 0 and ref["status"] == 0
