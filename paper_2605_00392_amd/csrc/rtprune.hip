@@ -343,7 +343,7 @@ int strip_form_limit() {
   return std::max(1, cluster_spin_limit() / 512);
 }
 
-// Workgroups a strip image may take (0: too few compute units for half an XCD's slots).
+// Compute units a strip image may take (0: too few for half an XCD's slots).
 int strip_most() {
   const int cus = compute_units();
   return cus < 8 * kStripXcdGroups ? 0 : std::min(kStripMaxGroups, cus / 4);
@@ -381,11 +381,13 @@ void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   if (may_strip && !top_clustered && (!p.dynamic || r_most > kClusterCols)) {
     int strip = p.dynamic ? kShapeStripA : strip_for(r_most);
     most = p.dynamic ? kStripXcdGroups : strip_groups(strip, m_top, 0);
-    // Few images leave most of the chip idle: strips of 64 rows (a third of the arithmetic per
-    // iteration) instead of 144 while every image still has its workgroups at once.  One image,
-    // 100 iterations: 420 x 280 0.54 -> 0.42 ms, 867 x 289 0.54 -> 0.53 ms.
+    // Few images leave most of the chip idle: strips of 64 rows to a compute unit (32 to a workgroup, eight to a wave: one
+    // reduction of its row sums an iteration instead of three) instead of 144 while a slot keeps to an XCD and every image
+    // still has its own at once.  Calls of 100 iterations, us, strips of 144 / of 64 in at most sixteen workgroups / of 64:
+    // one page of 420 x 280 432 / 402 / 401, of 630 x 270 492 / 467 / 405, of 867 x 289 493 / 471 / 458, of 560 x 523
+    // 539 / 533 / 464; 16 of 560 x 523 614 / 674 / 567, of 420 x 280 469 / 446 / 446, of 630 x 270 536 / 607 / 494.
     const int thin_groups = strip_groups(kShapeStripA, m_top, kModeStripThin);
-    const bool thin = !p.dynamic && strip == kShapeStripA && thin_groups <= kStripThinTeams &&
+    const bool thin = !p.dynamic && strip == kShapeStripA && thin_groups <= kStripXcdGroups &&
                       B <= strip_slots(thin_groups, compute_units());
     if (thin) most = thin_groups;
     // (a quarter of the chip at most to an image: see sinkhorn_strip.hpp, who waits for whom)

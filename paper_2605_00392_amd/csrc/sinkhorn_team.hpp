@@ -201,14 +201,9 @@ __host__ __device__ inline int strip_groups(int shape, int m, int mode) {
        : shape == kShapeStripB ? (m + StripB::kRows - 1) / StripB::kRows
        : shape == kShapeStripC ? (m + StripC::kRows - 1) / StripC::kRows : (m + StripD::kRows - 1) / StripD::kRows;
 }
-// ... and workgroups: at most two to a compute unit.  Thin strips take as many as the one-trip exchange
-// allows while they have 32 rows each (16 of them hold the 1024 rows that thin strips are used for).
-constexpr int kStripThinTeams = 16;
+// ... and workgroups: at most two to a compute unit.  Thin strips have 32 rows each, eight a wave: a reduction's worth.
 __host__ __device__ inline int strip_teams(int shape, int m, int mode) {
-  if (shape == kShapeStripA && (mode & kModeStripThin)) {
-    const int most = (m + kStripThinRows / 2 - 1) / (kStripThinRows / 2), least = (m + StripA::kTeamRows - 1) / StripA::kTeamRows;
-    return most <= kStripThinTeams ? most : least > kStripThinTeams ? least : kStripThinTeams;
-  }
+  if (shape == kShapeStripA && (mode & kModeStripThin)) return (m + kStripThinRows / 2 - 1) / (kStripThinRows / 2);
   return shape == kShapeStripA ? (m + StripA::kTeamRows - 1) / StripA::kTeamRows
        : shape == kShapeStripB ? (m + StripB::kTeamRows - 1) / StripB::kTeamRows
        : shape == kShapeStripC ? (m + StripC::kTeamRows - 1) / StripC::kTeamRows : (m + StripD::kTeamRows - 1) / StripD::kTeamRows;

@@ -70,3 +70,10 @@ def test_the_batches_take_the_exchange_they_say(forms, name, shape, thin, units)
     assert are_strips(len(counts), max(counts), images, 0, ratio=ratio)
     got = forms(shape, thin, images)
     assert max(g[0] for g in got) == units and all(g[2] == int(one_trip) and g[1] > 1 for g in got), got
+
+
+def test_thin_strips_give_a_wave_one_reductions_rows(forms):
+    """Four waves of at most eight rows to a workgroup, whatever the number of rows, and two of them to a compute unit."""
+    rows = list(range(1, 1025)) + [1500, 4096]
+    for m, (units, teams, _) in zip(rows, forms(A, True, [(m, 300) for m in rows])):
+        assert -(-m // teams) <= 32 and teams <= 2 * units, (m, units, teams)
