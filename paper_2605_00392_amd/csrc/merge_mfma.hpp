@@ -26,7 +26,7 @@
 //
 // What bounds it: the stream over the rows (1.8 GB per 1024 pages of 400 tokens, 337 kept).  That call took 1455 us with
 // one stage ahead, the pruned rows turned by 2-byte LDS writes on their way from registers, and takes 1414 (this kernel
-// 472 -> 430 us, 5.0 TB/s counted); with 64-byte
+// 472 -> 430 us, 5.0 TB/s counted; the matrix cores are at work 15 % of the time); with 64-byte
 // pieces of 16 rows an access instead of whole lines (merge_mid_swap) 1527 to 1569, with the pieces exchanged for the stores only 1441,
 // with plain instead of non-temporal stores 1445.
 #pragma once

@@ -7,21 +7,22 @@
 // into two bf16 numbers, P = hi + lo with |P - hi - lo| <= 2^-18 |P|, and each
 // product is two v_mfma_f32_16x16x32_bf16, accumulated in fp32 like the vector
 // kernel's sum.  The pruned token rows are bf16 already; the matrix instruction
-// wants eight consecutive pruned rows of one feature per lane, so their tile is
-// transposed on its way into LDS.
+// wants eight consecutive pruned rows of one feature per lane: they lie in LDS as
+// they lie in memory and are turned by its transposing reads.
 //
 // Workgroup = 4 waves as 2 x 2 on a tile of 128 kept rows x 256 features (128 in small
-// batches, which then have tiles for twice as many workgroups), 32
+// batches, which then have tiles for twice as many workgroups, and at widths of which the last tile would leave
+// much unused), 32
 // pruned rows per step, LDS double-buffered, two workgroups per compute unit; a wave owns 64 rows x half of the features.  P's LDS
 // rows are 64 bytes of payload on a pitch of 80.  The finished tile
 // goes through LDS once more so that the kept rows are read and the merged rows
 // written 16 bytes per lane.
 //
-// What bounds it: 16 pages of 4512 tokens take 0.577 ms, 341 useful TFLOP/s and twice that executed (29 % of the
-// matrix cores' rate); a step's plan entries (16 four-byte loads a thread, their rows being 4-byte aligned) and
+// What bounds it: 16 pages of 4512 tokens take 0.552 ms, 357 useful TFLOP/s and twice that executed (the matrix
+// cores are at work 32 % of the time, counted; LDS conflicts 39 % of its cycles, waits for it 1.5 % of the waves'); a step's plan entries (16 four-byte loads a thread, their rows being 4-byte aligned) and
 // their split are paid once per 256 features.  Before, with 128 features and the pruned rows turned
-// by 4-byte LDS writes on their way from registers: 0.847 ms; 32 pages of 2137 tokens 0.422 -> 0.305, 64 of 1083
-// 0.274 -> 0.202.  One page of 4512 tokens: 0.118 with 256 features a tile, 0.100 with 128 (0.104 before).
+// by 4-byte LDS writes on their way from registers: 0.847 ms (0.577 with the change, before an image's tiles were on one
+// XCD); 32 pages of 2137 tokens 0.422 -> 0.305 -> 0.287, 64 of 1083 0.274 -> 0.202 -> 0.180.  One page of 4512 tokens: 0.118 with 256 features a tile, 0.100 with 128 (0.104 before).
 #pragma once
 #include "common.hpp"
 #include "scores_mfma.hpp"

@@ -355,7 +355,8 @@ int strip_most() {
 void set_sinkhorn_mode(DevParams& p, int B, int max_tokens, bool own_counts) {
   const bool large = max_tokens > kLargeTokens;
   const int f32 = p.k32 ? kModeF32 : 0;   // exp's range fits fp32: registers may hold the matrix as fp32
-  // The multi-workgroup kernels that keep a matrix on chip run one workgroup per compute unit.
+  // The multi-workgroup kernels that keep a matrix on chip take whole compute units, a cluster's workgroup one, two
+  // strip workgroups one.
   // Under a fixed retention the largest image the batch can hold bounds the others' kept and
   // pruned counts; when one of them can take it, a cluster's slot needs no more workgroups than
   // that image does (more slots then share the chip), and no image is beyond the on-chip kernels.

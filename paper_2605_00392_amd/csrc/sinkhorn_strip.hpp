@@ -30,12 +30,13 @@
 //            total, so that the exchanges and the reciprocal are paid once for eight rows, and
 //            the x travel back through scalar registers;
 //   columns  sum_i x_i K_ij over the wave's rows, lane-local; the waves meet in LDS.
-// What bounds it: of an iteration's 12 600 clocks on 64 pages of 1083 tokens (two workgroups of 72 x 576 to a
-// compute unit) 4 500 are the two passes (two conversions and two multiply-adds per entry), the others the
-// exchange: sums to LDS and out 1 700, the trip 1 800, adding up and out again 1 200, the second trip
-// 2 000.  Against one workgroup of eight waves to a compute unit, with one trip among up to sixteen workgroups and
-// places put back to a "not yet" pattern (100 iterations): 32 pages of 2137 tokens 1.46 -> 1.20 ms, 16 pages of
-// 4512 3.90 -> 3.73, 64 pages of 1083 0.59 -> 0.59; one page of 2137 0.72 -> 0.52 ms, of 4512 0.85 -> 0.70.
+// What bounds it: of an iteration's 12 100 clocks on 64 pages of 1083 tokens (two workgroups of 72 x 576 to a
+// compute unit) 5 100 are the two passes (two conversions and two multiply-adds per entry), the others the
+// exchange: sums to LDS and out 1 300, the trip 1 800, adding up and out again 1 100, the second trip
+// 2 900.  16 pages of 4512 tokens (116 workgroups an image, across the XCDs): 21 000, 4 800 in the passes, the trips
+// 4 200 and 7 900.  Against one workgroup of eight waves to a compute unit, with one trip among up to sixteen workgroups
+// and places put back to a "not yet" pattern (100 iterations): 32 pages of 2137 tokens 1.46 -> 1.21 ms, 16 pages of
+// 4512 3.90 -> 3.67, 64 pages of 1083 0.59 -> 0.58.
 // Before those, strips that gave every row a reduction of its own: 0.91 (1083 tokens) and 2.48 ms (2137);
 // streaming the matrices from memory every iteration: 6.72 ms (4512).
 //
@@ -45,7 +46,7 @@
 // others' sums for its share of the columns, adds them in a fixed order, takes the reciprocal and
 // publishes the finished y; everybody reads all y.  Two trips through memory instead of one, but
 // 2 (r + 1) values read instead of groups (r + 1).  (Eight workgroups of 523 columns, 64 images: 0.88 ms
-// with one trip, 0.81 with two at the time; up to six of 280: 0.540 and 0.577.)
+// with one trip, 0.81 with two, with the protocol of the time; up to six of 280: 0.540 and 0.577.)
 // Values travel as device-scope stores and loads past the caches, the loads straight into LDS, and carry in
 // their sign, which is theirs to spare (sums of products of positive numbers, and reciprocals of such), which use of
 // their place they belong to (the uses alternate), so no counters, no barriers across workgroups, nothing put back and
@@ -80,7 +81,7 @@ struct StripArgs {
 };
 
 // Two places at once, `at` (even) doubles into an image's exchange area: device-scope stores of 16 bytes, of which
-// every 8 arrive whole.  A value's sign says which use of its place it belongs to (`use`: 0 or kExOdd).
+// every 8 arrive whole (a lane's aligned 16 bytes lie in one request, written and read).  A value's sign says which use of its place it belongs to (`use`: 0 or kExOdd).
 constexpr uint32_t kExOdd = 0x80000000u;
 __host__ __device__ inline uint32_t ex_mark(uint32_t high, uint32_t use) { return (high & ~kExOdd) | use; }   // (a NaN may have either sign)
 __host__ __device__ inline bool ex_is_of(uint32_t high, uint32_t use) { return ((high ^ use) & kExOdd) == 0; }
@@ -211,10 +212,12 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Before a first look, about as long as the values take to get here (64 clocks a unit; within an XCD, and
-// across).  A look at places that are being written costs more than the wait: 32 pages of 2137 tokens, 100
-// iterations, looking at once / after 4 units for the sums and 16 for the y: 1.50 / 1.19 ms; 16 pages of 4512
-// tokens, at once / after 12 and 20: 4.04 / 3.76.
+// Before a first look, about as long as the values take to get here (64 clocks a unit; up to sixteen workgroups, up
+// to 32, which an XCD holds, and more).  A look at places that are being written costs more than the wait.  Calls of
+// 100 iterations, us, after (sums, y) units: 64 pages of 1083 tokens, eight workgroups an image, (0, 0) 1008, (0, 4) 1004,
+// (0, 8) 1005, (0, 12) 972, (0, 16) 952, (0, 20) 948, (4, 16) 959; 32 pages of 2137 tokens, 31 an image, (0, 16) 1786,
+// (4, 8) 1890, (4, 12) 1805, (4, 16) 1769, (8, 16) 1782; 16 pages of 4512 tokens, 116 an image, (4, 20) 4875,
+// (12, 16) 4835, (12, 20) 4797, (16, 24) 4723 (which one page of 4512 tokens takes 12 longer with).
 __device__ __forceinline__ void ex_pause(int units) {
   for (int k = 0; k < units; k += 4) __builtin_amdgcn_s_sleep(4);
 }
@@ -716,7 +719,7 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(2
 }
 
 // The slots given up, one after another, with a counter of their own.  Behind k_sinkhorn_strips on its stream, with as
-// many workgroups as a slot has compute units; none given up, the usual case, costs a call about 1 us.
+// many workgroups as a slot has compute units; none given up, the usual case, costs a call 1 to 4 us.
 template <typename S>
 __global__ __launch_bounds__(kStripTeams * kStripThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_strips_left(StripArgs C) {
   constexpr int kTeamLds = (strip_lds_of<S>() + 15) & ~15;
