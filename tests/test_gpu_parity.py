@@ -534,7 +534,7 @@ def test_multi_workgroup_sinkhorn_gives_up_instead_of_waiting_for_ever(monkeypat
 
 
 # batches whose images go through the strips: (sizes, retention, iterations, whether their exchange takes one trip:
-# tests/test_strip_forms_cpu.py).  Several images to a slot of 3, 4, 14 and, across the XCDs, 24 compute units; thin
+# tests/test_strip_forms_cpu.py).  Several images to a slot of 3, 4, 16 and, across the XCDs, 24 compute units; thin
 # strips of one page.
 STRIP_BATCHES = {
     "3 units, one trip": ([700] * 3 + list(range(520, 700)), 560.0 / 1083.0, 5, True),
