@@ -733,7 +733,9 @@ __global__ __launch_bounds__(kStripTeams * kStripThreads) __attribute__((amdgpu_
   const int units = C.words[kStripTop], per_slot = kStripTeams * units;
   if (count == 0 || static_cast<int>(blockIdx.x) >= units) return;
   const int slots = strip_slots_used(units, count, C.cus), with_images = min(slots, count);
-  auto left = [&](int slot) { return (C.words[kStripCounters + slot] & kStripGivenUp) != 0; };
+  auto left = [&](int slot) {
+    return (__hip_atomic_load(C.words + kStripCounters + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStripGivenUp) != 0;
+  };
   if (!__syncthreads_or(static_cast<int>(threadIdx.x) < with_images && left(threadIdx.x))) return;
   const int team = __builtin_amdgcn_readfirstlane(threadIdx.x / kStripThreads);
   int arrived = 0;
