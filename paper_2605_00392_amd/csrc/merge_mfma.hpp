@@ -10,9 +10,10 @@
 // v_mfma_f32_16x16x32_bf16 contracts 32 pruned rows at a time.  Its second
 // operand is a 32 x 16 block of P transposed: a lane's eight consecutive pruned
 // rows of one kept row are eight consecutive floats of a plan row; each is split
-// into two bf16 numbers, P = hi + lo with |P - hi - lo| <= 2^-18 |P| (one bf16
-// rounding would put 2e-3 alpha |T| on the merged features), so each product is
-// two matrix instructions accumulated in fp32.  The first operand is 16 features
+// into three bf16 numbers, P = hi + mid + lo exactly (eight bits each, the fp32
+// entry has 24), so each product is three matrix instructions accumulated in fp32,
+// and nothing but the order of its additions tells this kernel from the vector one
+// (for finite features: 0 times infinity is not 0).  The first operand is 16 features
 // of 32 pruned rows, which lie in LDS as they lie in memory and are turned by its
 // transposing reads.  The accumulator holds, per lane, four features of one kept
 // row; the rows of two instructions stand for features 8 g + 4 h .. + 3 (g the
@@ -29,6 +30,8 @@
 // 472 -> 430 us, 5.0 TB/s counted; the matrix cores are at work 15 % of the time); with 64-byte
 // pieces of 16 rows an access instead of whole lines (merge_mid_swap) 1527 to 1569, with the pieces exchanged for the stores only 1441,
 // with plain instead of non-temporal stores 1445.
+// With two terms of P (18 bits of it) 1024 pages with 63 pruned tokens took 1286 us a call and take 1294, 32 pages of 256 with
+// 40 pruned, of which a wave has a SIMD to itself and waits for the matrix cores, 102 and 105 (the vector kernel: 108).
 #pragma once
 #include "common.hpp"
 #include "scores_mfma.hpp"
@@ -194,20 +197,23 @@ __device__ __forceinline__ void merge_mid_rows(const MergeMidArgs& A, int b, int
   request(min(1, stages - 1), 1, k1, true);
   no_stores();
 
-  bf16x8_t phi[RB][KB], plo[RB][KB];
+  bf16x8_t phi[RB][KB], pmid[RB][KB], plo[RB][KB];
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
-      uint32_t h[4], l[4];
+      uint32_t h[4], d[4], l[4];
 #pragma unroll
       for (int e = 0; e < 8; e += 2) {
         const int k = 32 * kb + 8 * g + e;
         const float v0 = k < r ? pv[rb][kb][e] : 0.f, v1 = k + 1 < r ? pv[rb][kb][e + 1] : 0.f;
         h[e >> 1] = pack_bf16x2(v0, v1);
-        l[e >> 1] = pack_bf16x2(v0 - __uint_as_float(h[e >> 1] << 16), v1 - __uint_as_float(h[e >> 1] & 0xffff0000u));
+        const float w0 = v0 - __uint_as_float(h[e >> 1] << 16), w1 = v1 - __uint_as_float(h[e >> 1] & 0xffff0000u);
+        d[e >> 1] = pack_bf16x2(w0, w1);
+        l[e >> 1] = pack_bf16x2(w0 - __uint_as_float(d[e >> 1] << 16), w1 - __uint_as_float(d[e >> 1] & 0xffff0000u));
       }
       phi[rb][kb] = __builtin_bit_cast(bf16x8_t, make_uint4(h[0], h[1], h[2], h[3]));
+      pmid[rb][kb] = __builtin_bit_cast(bf16x8_t, make_uint4(d[0], d[1], d[2], d[3]));
       plo[rb][kb] = __builtin_bit_cast(bf16x8_t, make_uint4(l[0], l[1], l[2], l[3]));
     }
 
@@ -262,6 +268,7 @@ __device__ __forceinline__ void merge_mid_rows(const MergeMidArgs& A, int b, int
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
               acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[h][kb], phi[rb][kb], acc[h], 0, 0, 0);
+              acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[h][kb], pmid[rb][kb], acc[h], 0, 0, 0);
               acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[h][kb], plo[rb][kb], acc[h], 0, 0, 0);
             }
           }

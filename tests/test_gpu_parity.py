@@ -896,6 +896,43 @@ def test_merge_without_workspace():
     _log(rep, "merge without workspace")
 
 
+def _merge_alone(tokens, counts, keep, plan, **params):
+    """rtprune_merge on bf16 bits with kept tokens before the pruned ones, the caller's counts and the caller's plan."""
+    import torch
+    batch = synth.pack(0, "bf16", tokens, np.zeros(len(counts), np.float32), dict(synth.DEFAULT_PARAMS, dynamic=0, **params))
+    db = rt.upload(batch, "cuda:0")
+    ws = rt.alloc_workspace(db)
+    ws.fill_(0xFF)
+    dev = lambda a, t: torch.from_numpy(np.ascontiguousarray(a)).to(t).cuda()
+    out_off = np.concatenate([[0], np.cumsum(keep)])
+    plan_off = np.concatenate([[0], np.cumsum([m * (n - m) for n, m in zip(counts, keep)])])
+    out = torch.zeros((int(out_off[-1]), db.D), dtype=db.tokens.dtype, device="cuda:0")
+    rt.check(rt.rtprune_merge(db, dev(np.concatenate([np.arange(n) for n in counts]), torch.int32), dev(keep, torch.int32),
+                              dev(out_off, torch.int32), dev(plan, torch.float32), dev(plan_off, torch.int64),
+                              rt.make_params(batch.params), out, ws))
+    torch.cuda.synchronize()
+    assert hz.device_status(ws) == 0
+    return hz._np(out)
+
+
+@pytest.mark.parametrize("d", [64, 1280])
+@pytest.mark.parametrize("r", [17, 32, 33, 64])
+def test_merge_uses_every_bit_of_the_plan(r, d):
+    """Kept rows of zeros, pruned ones of +1 and -1 whose entries of a plan row differ in the last of their 24 bits: the
+    merged row is that bit.  Every sum on the way to it is a whole number of them below 2^24, so it is exact."""
+    B, n = 24, 400
+    m = n - r
+    image = np.zeros((n, d), np.float32)
+    image[m:] = np.where(np.arange(r) % 2 == 0, 1.0, -1.0)[:, None]
+    plan = np.zeros((m, r), np.float32)
+    j = 2 * (np.arange(m) % (r // 2))                   # rows take the pairs of pruned tokens in turns
+    plan[np.arange(m), j] = 0.5 + 2.0 ** -10 + 2.0 ** -23
+    plan[np.arange(m), j + 1] = 0.5 + 2.0 ** -10
+    for ratio in (0.84, 0.999):
+        out = _merge_alone([image] * B, [n] * B, [m] * B, np.tile(plan.ravel(), B), alpha=1.0, ratio=ratio)
+        assert (synth.bf16_bits_to_f32(out) == 2.0 ** -23).all(), (r, d, ratio)
+
+
 # ------------------------------------------------------------------ parameter sweeps
 @pytest.mark.parametrize("override", [
     dict(eps=1.0, iters=100),           # the literal text of Appendix C
