@@ -28,19 +28,29 @@ constexpr int kTiledMinPruned = 64;
 constexpr int kMergeMidMin = 16;
 __host__ __device__ inline bool merge_is_mid(int r) { return r > kMergeMidMin && r <= kTiledMinPruned; }
 // Which images the vector merge kernels leave to the others.  The middling ones
-// only when the call has many (`mid_count`, counted on the device, at least
-// `mid_min`): a few of them cost less inside the vector kernel's one large launch
-// than as two short launches of their own.
+// only when the call has many (MergeMidRule over their number and work, counted on the device): a few of them cost less
+// inside the vector kernel's one large launch than as two short launches of their own.
 constexpr int kSkipTiled = 1, kSkipMid = 2;
+// The count of the list of middling images says as well whether their tokens times pruned tokens come to
+// kMergeMidPays (2048 row tiles of 128 times pruned tokens).
+constexpr long long kMergeMidPays = 2048 * 128;
+constexpr int kMergeMidPaysFlag = 1 << 30, kMergeMidCount = kMergeMidPaysFlag - 1;
+struct MergeMidRule {
+  int least;      // images, from which on the kernel for them runs
+  int by_work;    // or, if set, from that much work on
+  __host__ __device__ bool runs(int count, bool pays) const { return count >= least || (by_work && pays); }
+};
 struct MergeSkip {
   int mask;
-  const int32_t* mid_count;   // device; read only when mask has kSkipMid
-  int mid_min;
+  const int32_t* mid_word;    // device; read only when mask has kSkipMid
+  MergeMidRule mid_rule;
 };
-__device__ __forceinline__ bool merge_mid_runs(const int32_t* mid_count, int mid_min) { return *mid_count >= mid_min; }
+__device__ __forceinline__ bool merge_mid_runs(int word, const MergeMidRule& rule) {
+  return rule.runs(word & kMergeMidCount, (word & kMergeMidPaysFlag) != 0);
+}
 __device__ __forceinline__ bool merge_elsewhere(const MergeSkip& k, int r) {
   if ((k.mask & kSkipTiled) && r > kTiledMinPruned) return true;
-  return (k.mask & kSkipMid) && merge_is_mid(r) && merge_mid_runs(k.mid_count, k.mid_min);
+  return (k.mask & kSkipMid) && merge_is_mid(r) && merge_mid_runs(*k.mid_word, k.mid_rule);
 }
 
 struct DevParams {

@@ -46,6 +46,7 @@ constexpr int kMergeMidStage = 2 * kMergeMidFeatures; // features per stage (the
 constexpr int kMergeMidRB = 2;                        // 16-row blocks per wave
 constexpr int kMergeMidWaveRows = 16 * kMergeMidRB;
 constexpr int kMergeMidBlockRows = 4 * kMergeMidWaveRows;
+static_assert(kMergeMidPays == 2048 * kMergeMidBlockRows, "as its comment says");
 constexpr int kMergeMidThreads = 256;
 constexpr int kMergeMidRowBytes = 2 * kMergeMidStage;
 constexpr int kMergeMidBuffer = kTiledMinPruned * kMergeMidRowBytes;   // a stage's pruned rows
@@ -343,7 +344,7 @@ __device__ __forceinline__ void merge_tiled_list(MergeTiledArgs A, int tile_rows
 // role is not wanted.  Fewer than `thin_below` wide tiles in all: narrow ones (merge_thin_below).  Both roles
 // use the same LDS buffer.
 __global__ __launch_bounds__(kMergeMidThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_merge_lists(
-    MergeTiledArgs TA, int tile_rows, int thin_below, MergeMidArgs A, int tiles_m, const int32_t* __restrict__ work, int B, int mid_min,
+    MergeTiledArgs TA, int tile_rows, int thin_below, MergeMidArgs A, int tiles_m, const int32_t* __restrict__ work, int B, MergeMidRule mid_rule,
     const int32_t* __restrict__ status) {
   if (status[0]) return;
   static_assert(kMergeTiledThreads == kMergeMidThreads, "one workgroup shape for both roles");
@@ -354,8 +355,8 @@ __global__ __launch_bounds__(kMergeMidThreads) __attribute__((amdgpu_waves_per_e
     if (rows * ((TA.D + kMergeTileCols - 1) / kMergeTileCols) < thin_below) merge_tiled_list<kMergeThinCols>(TA, tile_rows, work, B, lds);
     else merge_tiled_list<kMergeTileCols>(TA, tile_rows, work, B, lds);
   }
-  if (tiles_m > 0 && merge_mid_runs(work + kListMid, mid_min)) {
-    const int count = work[kListMid];
+  if (tiles_m > 0 && merge_mid_runs(work[kListMid], mid_rule)) {
+    const int count = work[kListMid] & kMergeMidCount;
     const long long items = static_cast<long long>((count + 7) / 8) * 8 * tiles_m;
     for (long long q = blockIdx.x; q < items; q += gridDim.x) {
       const long long s = q >> 3;

@@ -31,10 +31,11 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   for (int v = 0; v < NS; ++v) c[v] = 0;
   __shared__ unsigned long long sweep_cells;      // entries of the sweep kernels' matrices, padding included
   __shared__ int strip_tops[kStripShapes];        // workgroups of the strip image that takes most of them
-  if (tid == 0) sweep_cells = 0;
+  __shared__ unsigned long long mid_cells;        // tokens times pruned tokens of the middling images (kMergeMidPays)
+  if (tid == 0) sweep_cells = mid_cells = 0;
   if (tid < kStripShapes) strip_tops[tid] = 0;
   __syncthreads();
-  unsigned long long cells = 0;
+  unsigned long long cells = 0, mid = 0;
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
@@ -51,11 +52,15 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
     }
     if (n > 0 && v == kVariantSweep) cells += static_cast<unsigned long long>(m) * k32_pitch(n - m);
     if (n > 0 && n - m > kTiledMinPruned) c[kListTiled] += 1;
-    if (n > 0 && merge_is_mid(n - m)) c[kListMid] += 1;
+    if (n > 0 && merge_is_mid(n - m)) {
+      c[kListMid] += 1;
+      mid += static_cast<unsigned long long>(n) * (n - m);
+    }
   }
 #pragma unroll
   for (int v = 0; v < NS; ++v) cnt[v][tid] = c[v];
   if (cells) atomicAdd(&sweep_cells, cells);
+  if (mid) atomicAdd(&mid_cells, mid);
   __syncthreads();
   for (int o = 1; o < 256; o <<= 1) {
     int add[NS];
@@ -93,7 +98,8 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   }
   if (tid == 255) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) work[v] = cnt[v][255];
+    for (int v = 0; v < NV; ++v)
+      work[v] = cnt[v][255] | (v == kListMid && mid_cells >= static_cast<unsigned long long>(kMergeMidPays) ? kMergeMidPaysFlag : 0);
   }
   if (strip && tid < kStripShapes) {
     int32_t* words = strip + tid * kStripShapeWords;

@@ -933,6 +933,19 @@ def test_merge_uses_every_bit_of_the_plan(r, d):
         assert (synth.bf16_bits_to_f32(out) == 2.0 ** -23).all(), (r, d, ratio)
 
 
+def test_staged_merge_takes_its_kernel_from_the_counts():
+    """The retention in the parameters says nothing about counts of the caller's own: whatever it is, the same kernel
+    (the same bits: the kernels add up in different orders)."""
+    rng = np.random.default_rng(61)
+    for counts, r in (([400] * 20, 64), ([200, 400] * 4, 40), ([400] * 40 + [300] * 20, 33)):
+        keep = [n - r for n in counts]
+        tokens = [rng.standard_normal((n, 256)).astype(np.float32) for n in counts]
+        plan = rng.random(sum(m * r for m in keep), dtype=np.float32)
+        outs = [_merge_alone(tokens, counts, keep, plan, ratio=ratio) for ratio in (0.84, 0.3, 0.999)]
+        np.testing.assert_array_equal(outs[0], outs[1])
+        np.testing.assert_array_equal(outs[0], outs[2])
+
+
 # ------------------------------------------------------------------ parameter sweeps
 @pytest.mark.parametrize("override", [
     dict(eps=1.0, iters=100),           # the literal text of Appendix C
