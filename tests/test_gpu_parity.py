@@ -879,6 +879,25 @@ def test_unstaged_matrix_core_merge_at_its_edges(counts, ratio, d):
     _log(rep, f"mid merge, vector kernel {counts} {ratio} D={d}")
 
 
+def test_middling_merge_of_any_number_of_pages():
+    """Two pages past a multiple of eight take no longer than the next multiple (a workgroup per row tile of each)."""
+    def ms(count):
+        batch = synth.gen_batch(9, images=[b % 8 for b in range(count)])
+        batch.params.update(iters=1, mid_merge_min_images=1)
+        times = []
+        for _ in range(5):
+            rt.rtprune_profile_enable(1)
+            hz.run_prune(batch)
+            rc, prof = rt.rtprune_profile_summary()
+            rt.rtprune_profile_enable(0)
+            assert rc == rt.RTP_OK
+            times.append(next(k["total_ms"] for k in prof if k["kernel"] == "k_merge"))
+        return min(times)
+    few, many = ms(10), ms(16)
+    print(f"\nmerge of 10 pages {few * 1e3:.1f} us, of 16 {many * 1e3:.1f} us", flush=True)
+    assert few < 1.15 * many
+
+
 def test_merge_without_workspace():
     """The merge entry point without a workspace (vector kernel for every small pruned set)."""
     import torch
