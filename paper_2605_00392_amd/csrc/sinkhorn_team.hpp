@@ -99,7 +99,7 @@ struct WaveShape {
   static constexpr int kMaxRows = 64 * kWaves * kRows;
   __host__ __device__ static constexpr bool fits(int m, int r) { return m + 1 <= kMaxRows && r + 1 <= kCols; }
 };
-struct WaveSmallShape {   // the images of list kVariantPair that one wave holds
+struct WaveSmallShape {   // the images of variant kVariantPair that one wave holds
   static constexpr int kWaves = 1, kRows = 2, kCols = 16;
   static constexpr int kMaxRows = 64 * kWaves * kRows;
   __host__ __device__ static constexpr bool fits(int m, int r) { return m + 1 <= kMaxRows && r + 1 <= kCols; }

@@ -682,6 +682,52 @@ def test_64_column_register_shapes_at_their_edges(override):
     assert rep.max_score_abs <= hz.SCORE_ATOL
 
 
+# kept x pruned at the limits of the images that one wave and two waves take (the dustbins are one more row and column), rows
+# past which a wave's share of them ends among them; neighbours take different numbers of waves
+SHORT_EDGES = [(127, 15), (128, 15), (63, 8), (255, 8), (64, 7), (127, 8), (400, 15), (64, 15), (256, 15), (63, 15), (497, 15),
+               (447, 7), (448, 7), (128, 8), (1, 15), (192, 9), (126, 15), (503, 8), (255, 15), (128, 7), (320, 7), (383, 7), (384, 7),
+               (2, 8), (30, 2)]
+
+
+@pytest.mark.parametrize("copies", [1, 24])
+@pytest.mark.parametrize("override", [dict(iters=0), dict(iters=1), dict(iters=3), dict(iters=60)])
+def test_one_and_two_wave_images_at_their_edges(override, copies):
+    """Up to 15 pruned tokens against the oracle, with a SIMD to a wave and with eight waves to a workgroup."""
+    keep = [m for m, _ in SHORT_EDGES] * copies
+    batch = _clustered([m + r for m, r in SHORT_EDGES], 128, "f32", 55, **override)
+    many = synth.subset(batch, list(range(len(SHORT_EDGES))) * copies)
+    g = hz.run_staged(many, keep_counts_in=keep)
+    rep = hz.compare_batch(batch, dict(g, out_offsets=g["out_offsets"][:len(SHORT_EDGES) + 1],
+                                       plan_offsets=g["plan_offsets"][:len(SHORT_EDGES) + 1]),
+                           staged=True, keep_counts=keep[:len(SHORT_EDGES)])
+    _log(rep, f"one and two waves {override} x{copies}")
+    for key, size in (("out", sum(m for m, _ in SHORT_EDGES)), ("pair", sum(m + r for m, r in SHORT_EDGES)),
+                      ("plan", sum(m * r for m, r in SHORT_EDGES))):
+        for c in range(1, copies):
+            np.testing.assert_array_equal(g[key][c * size:(c + 1) * size], g[key][:size])
+
+
+def test_one_and_two_wave_images_run_side_by_side():
+    """Images of one wave, which meet no barrier, beside images of two, which meet one an iteration: no workgroup holds
+    both, or the latter would not start before the former have ended.  (These parameters move for 2500 iterations.)"""
+    params = dict(iters=2500, z=1.0, eps=0.0034)
+    def ms(shapes):
+        batch = _clustered([m + r for m, r in shapes], 128, "f32", 57, **params)
+        times = []
+        for _ in range(3):
+            rt.rtprune_profile_enable(1)
+            hz.run_staged(batch, keep_counts_in=[m for m, _ in shapes])
+            rc, prof = rt.rtprune_profile_summary()
+            rt.rtprune_profile_enable(0)
+            assert rc == rt.RTP_OK
+            times.append(next(k["total_ms"] for k in prof if k["kernel"] == "k_sinkhorn_regs"))
+        return min(times)
+    one, two, both = ms([(100, 15)] * 40), ms([(300, 15)] * 40), ms([(100, 15), (300, 15)] * 40)
+    print(f"\none wave {one:.3f} ms, two waves {two:.3f} ms, both {both:.3f} ms", flush=True)
+    assert one > 0.2 and two > 0.2                       # (not settled after a few)
+    assert both < max(one, two) + 0.5 * min(one, two)
+
+
 # kept x pruned around the batches of 128 rows (the dustbin row is one more), the 32, 48 and 64 columns and the 352
 # rows that four waves hold
 GRID_EDGES = [(1, 16), (31, 31), (126, 16), (127, 31), (128, 32), (129, 47), (254, 17), (255, 48), (256, 63), (257, 40),
