@@ -54,11 +54,15 @@ __global__ __launch_bounds__(256) void k_splice_scan(TextSpans t, const int32_t*
   splice_scan(t, keep, B, seq_offsets, visual_start, lds);
 }
 
-// Text rows and position ids, image b's by `parts` workgroups.  They depend on the kept counts and the selection
+// Text rows and position ids, by `blocks` workgroups.  They depend on the kept counts and the selection
 // only, so they go at the end of a Sinkhorn launch, which is bound by latency and leaves memory, and in smaller batches
 // compute units, idle: 128 tiled pages, 24 us less a call than as a launch of their own behind the merge.
+// A wave takes its share of the rows of all images' text together, and of all sequences' positions, so it does not matter
+// whose they are (dealt image by image, all 20480 rows of 128 pages before the first of them took a call 1071 us; spread
+// evenly 64).
 struct SpliceText {
   TextSpans t;
+  int B;
   const int32_t* offsets;
   const int32_t* keep;
   const int32_t* sel_idx;
@@ -67,31 +71,77 @@ struct SpliceText {
   int32_t* position_ids;       // may be null
   int row_pieces;              // 16-byte pieces of a row (the library's width limits make that exact)
   int mode;
-  int parts;                   // 0: not in this launch
+  int blocks;                  // 0: not in this launch
 };
-__device__ __forceinline__ void splice_text(const SpliceText& X, int block) {
-  const int b = block / X.parts, part = block - b * X.parts;
-  const TextSpans& t = X.t;
-  const int lo = X.offsets[b], n = X.offsets[b + 1] - lo;
-  const int P = span_len(t.prefix_offsets, b), S = span_len(t.suffix_offsets, b);
-  const int M = min(max(X.keep[b], 0), n);
-  const long long base = X.seq_offsets[b];
-  const int threads = blockDim.x, waves = threads >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  uint4* seq = static_cast<uint4*>(X.seq);
-  for (int k = part * waves + wave; k < P + S; k += X.parts * waves) {
-    const bool before = k < P;
-    const uint4* src = before ? static_cast<const uint4*>(t.prefix) + static_cast<size_t>(t.prefix_offsets[b] + k) * X.row_pieces
-                              : static_cast<const uint4*>(t.suffix) + static_cast<size_t>(t.suffix_offsets[b] + k - P) * X.row_pieces;
-    uint4* dst = seq + static_cast<size_t>(base + (before ? k : k + M)) * X.row_pieces;
-    for (int g = lane; g < X.row_pieces; g += 64) store_stream(dst + g, src[g]);
+constexpr int kSpliceTextThreads = 512;
+constexpr int kSpliceTextRows = 64;            // text rows to a workgroup,
+constexpr int kSpliceTextPositions = 4096;     // and positions
+inline int splice_text_blocks(long long text_rows, long long positions) {
+  const long long blocks = (text_rows + kSpliceTextRows - 1) / kSpliceTextRows + (positions + kSpliceTextPositions - 1) / kSpliceTextPositions;
+  return static_cast<int>(blocks < 65536 ? blocks : 65536);
+}
+
+// The span that position `at` is in, of spans b and later (span i: start[i] .. start[i + 1] - 1; some are empty).
+__device__ __forceinline__ int span_of(const int32_t* __restrict__ start, int b, int B, int at) {
+  int last = B - 1;
+  while (b < last) {
+    const int mid = (b + last) >> 1;
+    if (start[mid + 1] > at) last = mid;
+    else b = mid + 1;
   }
+  return b;
+}
+// Rows k0 .. k1 - 1 of the text before (or after) the images, the same for every lane of the wave.
+__device__ __forceinline__ void splice_rows(const SpliceText& X, const void* text, const int32_t* __restrict__ start, bool after,
+                                            int k0, int k1) {
+  const int lane = threadIdx.x & 63;
+  for (int k = k0, b = 0; k < k1;) {
+    b = __builtin_amdgcn_readfirstlane(span_of(start, b, X.B, k));
+    const int end = min(start[b + 1], k1);
+    const size_t to = after ? static_cast<size_t>(X.seq_offsets[b + 1]) - (start[b + 1] - k)
+                            : static_cast<size_t>(X.seq_offsets[b]) + (k - start[b]);
+    const uint4* src = static_cast<const uint4*>(text) + static_cast<size_t>(k) * X.row_pieces;
+    uint4* dst = static_cast<uint4*>(X.seq) + to * X.row_pieces;
+    const long long pieces = static_cast<long long>(end - k) * X.row_pieces;
+    long long g = lane;
+    for (; g + 3 * 64 < pieces; g += 4 * 64) {
+      uint4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = src[g + 64 * u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) store_stream(dst + g + 64 * u, v[u]);
+    }
+    for (; g < pieces; g += 64) store_stream(dst + g, src[g]);
+    k = end;
+  }
+}
+__device__ __forceinline__ void splice_text(const SpliceText& X, int block) {
+  const TextSpans& t = X.t;
+  const int waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const long long share = static_cast<long long>(block) * waves + wave, shares = static_cast<long long>(X.blocks) * waves;
+  auto part = [&](long long rows, long long i) { return static_cast<int>(rows * i / shares); };
+  splice_rows(X, t.prefix, t.prefix_offsets, false, part(t.prefix_rows, share), part(t.prefix_rows, share + 1));
+  splice_rows(X, t.suffix, t.suffix_offsets, true, part(t.suffix_rows, share), part(t.suffix_rows, share + 1));
   if (!X.position_ids) return;
-  for (int k = part * threads + static_cast<int>(threadIdx.x); k < P + M + S; k += X.parts * threads)
-    X.position_ids[base + k] = X.mode == 0 || k < P ? k
-                               : k < P + M ? P + clamp_index(X.sel_idx[lo + k - P], n) : P + n + (k - P - M);
+  const int positions = X.seq_offsets[X.B];
+  const int k1 = part(positions, share + 1);
+  int b = 0, from = 0, end = 0, P = 0, M = 0, n = 0, lo = 0;
+  for (int k = part(positions, share) + lane; k < k1; k += 64) {
+    if (k >= end) {
+      b = span_of(X.seq_offsets, b, X.B, k);
+      from = X.seq_offsets[b];
+      end = X.seq_offsets[b + 1];
+      lo = X.offsets[b];
+      n = X.offsets[b + 1] - lo;
+      P = span_len(t.prefix_offsets, b);
+      M = min(max(X.keep[b], 0), n);
+    }
+    const int i = k - from;
+    X.position_ids[k] = X.mode == 0 || i < P ? i : i < P + M ? P + clamp_index(X.sel_idx[lo + i - P], n) : P + n + (i - P - M);
+  }
 }
 // (of calls whose Sinkhorn launches are others)
-__global__ __launch_bounds__(256) void k_splice_text(SpliceText X, const int32_t* __restrict__ status) {
+__global__ __launch_bounds__(kSpliceTextThreads) void k_splice_text(SpliceText X, const int32_t* __restrict__ status) {
   if (!status[0]) splice_text(X, blockIdx.x);
 }
 

@@ -146,3 +146,81 @@ def test_bad_text_offsets_set_the_status_word():
     assert int(ws[:4].view(torch.int32).item()) & rt.RTP_DEV_BAD_OFFSETS
     assert (seq_off.cpu().numpy() == -7).all()
     assert (seq.float() == 7.0).all().item()
+
+
+def _check_placement(batch, prefix, poff, suffix, soff, mode, g, f):
+    """Sequence offsets, rows and position ids of a splice result `g`, `f` the packed output of the same batch."""
+    B, at = batch.batch, 0
+    for b in range(B):
+        lo, hi = int(batch.offsets[b]), int(batch.offsets[b + 1])
+        m, o0 = int(f["keep"][b]), int(f["out_offsets"][b])
+        rows, pos = orc.splice_sequence(prefix[poff[b]:poff[b + 1]], f["out"][o0:o0 + m], suffix[soff[b]:soff[b + 1]],
+                                        f["sel"][lo:lo + m], hi - lo, mode)
+        assert int(g["seq_off"][b]) == at
+        np.testing.assert_array_equal(g["seq"][at:at + len(rows)], rows)
+        np.testing.assert_array_equal(g["pos"][at:at + len(rows)], pos)
+        at += len(rows)
+    assert int(g["seq_off"][B]) == at
+    assert (g["pos"][at:] == -7).all()
+    assert (g["seq"][at:] == g["seq"][at:].flat[0]).all()
+
+
+@pytest.mark.parametrize("mode", [orc.POSITIONS_CONSECUTIVE, orc.POSITIONS_ORIGINAL])
+@pytest.mark.parametrize("name", ["dynamic", "strips", "c32", "tall"])
+def test_uneven_text(name, mode):
+    """Prompts of very different lengths, most of them empty, several hundred rows on one page: beside Sinkhorn's launches
+    (a dynamic retention, with and without pages of more than 512 tokens) and as a launch of their own (pages of one
+    size whose kernel is another)."""
+    if name == "dynamic":
+        batch = synth.gen_batch(3, images=range(7))
+    elif name == "tall":
+        batch = synth.gen_batch(4, images=range(9))
+    else:
+        n, ratio, count = (700, 0.6, 5) if name == "strips" else (120, 0.55, 300)
+        rng = np.random.default_rng(70)
+        batch = synth.pack(0, "bf16", [rng.standard_normal((n, 128)).astype(np.float32) for _ in range(count)],
+                           np.zeros(count, np.float32), dict(synth.DEFAULT_PARAMS, dynamic=0, ratio=ratio, iters=5))
+    B, d = batch.batch, batch.tokens.shape[1]
+    rng = np.random.default_rng(71)
+    pc, sc = np.zeros(B, dtype=np.int64), np.zeros(B, dtype=np.int64)
+    pc[0], sc[B - 1] = 700, 333
+    pc[B // 2], sc[B // 2] = 1, 65
+    sc[1] = 1
+    prefix, poff = _text(rng, pc, d, batch.dtype)
+    suffix, soff = _text(rng, sc, d, batch.dtype)
+    g = _run(batch, prefix, poff, suffix, soff, mode)
+    _check_placement(batch, prefix, poff, suffix, soff, mode, g, hz.run_prune(batch))
+    g = _run(batch, None, None, suffix, soff, mode)        # only one side
+    _check_placement(batch, prefix[:0], 0 * poff, suffix, soff, mode, g, hz.run_prune(batch))
+
+
+def test_uneven_text_takes_no_longer():
+    """The same rows of text, all before the first of 128 pages and spread evenly."""
+    import torch
+    B, n, d, rows = 128, 64, 1280, 128 * 160
+    rng = np.random.default_rng(72)
+    batch = synth.pack(0, "bf16", [rng.standard_normal((n, d)).astype(np.float32) for _ in range(B)],
+                       np.zeros(B, np.float32), dict(synth.DEFAULT_PARAMS, dynamic=0, ratio=0.9, iters=20))
+    db = rt.upload(batch, "cuda:0")
+    ws = rt.alloc_workspace(db)
+    p = rt.make_params(batch.params)
+    text = torch.zeros((rows, d), dtype=db.tokens.dtype, device="cuda:0")
+    cap = rows + db.total_tokens
+    seq = torch.empty((cap, d), dtype=db.tokens.dtype, device="cuda:0")
+    off = torch.empty(B + 1, dtype=torch.int32, device="cuda:0")
+    pos = torch.empty(cap, dtype=torch.int32, device="cuda:0")
+    best = {}
+    for name, counts in (("even", [rows // B] * B), ("uneven", [rows] + [0] * (B - 1))):
+        starts = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
+        spans = rt.make_text_spans(text, starts, rows)
+        best[name] = float("inf")
+        for _ in range(5):
+            a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                rt.check(rt.rtprune_prune_splice(db, None, p, spans, 0, seq, cap, off, pos, None, None, None, None, ws))
+            e.record()
+            torch.cuda.synchronize()
+            best[name] = min(best[name], a.elapsed_time(e) / 5)
+    print(f"\neven {best['even']:.3f} ms, uneven {best['uneven']:.3f} ms", flush=True)
+    assert best["uneven"] < 2 * best["even"]
