@@ -313,12 +313,17 @@ inline int density_split(long long units, int patch_h, int cus) {
 }
 
 // Large batches take the kernel that wastes less of a row: bands of 256 columns here, of 248 above.  Calls of 128 pages, us, vector /
-// matrix: sides of 576 45 / 51, 704 55 / 63, 832 75 / 83, 960 90 / 96, 1024 132 / 105, 1280 172 / 148.  Batches of up to sixteen
-// waves a compute unit all come here: 24 of 832 33 / 23, 16 of 640 28 / 16, 40 of 960 41 / 38.
+// matrix: sides of 576 45 / 51, 704 55 / 63, 832 75 / 83, 960 90 / 96, 1024 132 / 105, 1280 172 / 148.  Smaller batches
+// come here as long as waves share a patch row.  Calls of one side at a growing number of waves, vector / matrix: 704 at 2508
+// 36 / 35, at 3003 36 / 38, at 3993 47 / 51; 896 at 2520 36 / 31, at 3024 37 / 35, ragged ones (pages of half that size
+// to all of it) at 3024 35 / 31, at 3976 40 / 42.  Where the vector kernel needs a second workgroup for its fifth band
+// they all do up to sixteen waves a compute unit: 1088 at 3995 61 / 48, 1344 at 4032 55 / 42.  (With the bands in favour
+// some ragged batches lose what even ones gain: 89 pages of up to 768 40 / 42, 278 of them 71 / 74, all of 768 108 / 103.)
 inline bool density_on_matrix_cores(int max_w, int patch_w, long long units, int cus) {
   if (patch_w % (4 * kSobelSegment) != 0) return false;
-  const int band = 4 * kDensityBand;
-  return units <= 16ll * cus || (max_w + kSobelBand - 1) / kSobelBand * kSobelBand <= (max_w + band - 1) / band * band;
+  const int band = 4 * kDensityBand, bands = (max_w + kSobelBand - 1) / kSobelBand, others = (max_w + band - 1) / band;
+  const int few = others > 4 ? 16 : others == 4 ? 12 : 10;
+  return units <= static_cast<long long>(few) * cus || bands * kSobelBand <= others * band;
 }
 
 // Weights of a lane's 16 bytes (lane (n, kq): bytes 16 kq .. + 15 of a segment's 64, counted from 4 bytes before it) in
