@@ -79,7 +79,7 @@ def test_ragged_batch_of_tiles_and_global_views():
     # a tiled page: 640 x 640 local tiles and a 1024 x 1024 global view, different sizes in one batch
     pages = [synth.gen_page(200, 640), synth.gen_page(201, 1024), synth.gen_page(202, 512), synth.gen_page(203, 640)]
     check(pages, 64, 64, 0.2)
-    check(pages, 64, 64, 0.2, pad=5)             # page starts that are not 4-byte aligned: byte path
+    check(pages, 64, 64, 0.2, pad=5)             # page starts that are not 4-byte aligned
 
 
 def test_random_noise_odd_shapes_and_patch_sizes():
@@ -122,6 +122,39 @@ def test_patches_of_whole_segments_at_the_edges_of_bands(pad):
         pages += [(100 + rng.integers(0, 20, size=(h, w, 3))).astype(np.uint8) for h, w in sizes]
         for tau in (0.0, 0.05, 0.2, 1.0, 4.0):
             check(pages, ph, pw, tau, pad=pad)
+
+
+@pytest.mark.parametrize("pad", [0, 1, 2, 5])
+def test_patches_of_whole_words_at_the_edges_of_bands(pad):
+    """Patch widths that are a multiple of 4 but not of 64: the register-window kernel, with bands of 248 columns, on pages
+    that start at a word and that do not (its byte path)."""
+    rng = np.random.default_rng(46 + pad)
+    for pw, ph, sizes in ((20, 10, ((10, 20), (20, 240), (30, 260), (20, 520))), (248, 4, ((4, 248), (8, 496), (4, 744))),
+                          (4, 1, ((1, 4), (3, 252), (2, 300)))):
+        pages = [rng.integers(0, 256, size=(h, w, 3)).astype(np.uint8) for h, w in sizes]
+        pages += [(100 + rng.integers(0, 20, size=(h, w, 3))).astype(np.uint8) for h, w in sizes]
+        for tau in (0.0, 0.05, 0.2, 1.0):
+            check(pages, ph, pw, tau, pad=pad)
+
+
+@pytest.mark.parametrize("ph,copies", [(64, 20), (64, 30), (64, 50), (64, 75), (40, 20), (23, 50)])
+def test_patch_rows_shared_by_several_waves(ph, copies):
+    """Batches in which seven, five, three and two waves share a patch row of 64 (most of these do not divide it: the last
+    has fewer), and one of 40 and of 23 rows: the count of every page is that of its first copy and of the oracle."""
+    rng = np.random.default_rng(47)
+    h = 5 * ph
+    pages = [rng.integers(0, 256, size=(h, 320, 3)).astype(np.uint8), synth.gen_page(500, 640)[:h, :320].copy(),
+             (100 + rng.integers(0, 20, size=(h, 320, 3))).astype(np.uint8), synth.gen_page(501, 640)[100:100 + h, 64:384].copy()]
+    rc, status, rho, rho_k = run_density(pages * copies, ph, 64, 0.2)
+    assert rc == 0 and status == 0
+    for b in range(4 * copies):
+        if b < 4:
+            want, want_k = orc.text_density(pages[b], ph, 64, 0.2)
+            assert rho[b] == want, (b, rho[b], want)
+            np.testing.assert_array_equal(rho_k[b], want_k)
+        else:
+            np.testing.assert_array_equal(rho_k[b], rho_k[b % 4])
+            assert rho[b] == rho[b % 4]
 
 
 def test_empty_batch_and_optional_outputs():
