@@ -16,9 +16,10 @@ constexpr int kRegsThreads = 64 * kSinkhornBlockWaves;   // of a workgroup of k_
 // workgroup's two-wave images meet a barrier an iteration, at which they wait for every wave of it that has not ended: beside
 // images of one wave, which meet none, they would not start before those have ended.  40 of 100 x 15 beside 40 of
 // 300 x 15, 2500 iterations: 1.11 and 1.66 ms alone, 2.74 together in the same workgroups.)
-__device__ __forceinline__ int sinkhorn_list(int v, int m, int r) {
-  return v == kVariantPair && WaveSmallShape::fits(m, r) ? kVariantA : v;
-}
+// Its entry there says which of the two shapes it takes.
+constexpr int kListSmallFlag = 1 << 30;
+__device__ __forceinline__ bool sinkhorn_small(int v, int m, int r) { return v == kVariantPair && WaveSmallShape::fits(m, r); }
+__device__ __forceinline__ int sinkhorn_list(int v, int m, int r) { return sinkhorn_small(v, m, r) ? kVariantA : v; }
 
 // Work lists for the register-resident kernels: `work` holds kWorkLists counts
 // (one per shape, indexed by variant id) followed by as many lists of B image
@@ -89,11 +90,12 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
-    const int v = sinkhorn_list(sinkhorn_variant(m, n - m, mode), m, n - m);
+    const int variant = sinkhorn_variant(m, n - m, mode), v = sinkhorn_list(variant, m, n - m);
+    const bool small = sinkhorn_small(variant, m, n - m);
     if (n > 0 && v < kGeneralVariant) {
 #pragma unroll
       for (int u = 0; u < NV; ++u)
-        if (u == v) work[NV + u * B + at[u]++] = b;
+        if (u == v) work[NV + u * B + at[u]++] = small ? b | kListSmallFlag : b;
     }
     if (strip && n > 0 && v == kVariantStrip) {
       const int shape = strip_shape(n - m, mode);
@@ -171,10 +173,9 @@ __device__ __forceinline__ void sinkhorn_short_block(const SinkhornArgs& A, cons
   if (blk < cnt) {
     const int idx = blk * ones + wave;
     if (wave >= ones || idx >= nA) return;
-    const int img = __builtin_amdgcn_readfirstlane(work[NV + kVariantA * B + idx]);
-    const int n = A.offsets[img + 1] - A.offsets[img], m = min(max(A.keep[img], 0), max(n, 0));
-    if (WaveShape::fits(m, n - m)) sinkhorn_waves_image<WaveShape>(A, img, wave, 0, lane);
-    else sinkhorn_waves_image<WaveSmallShape>(A, img, wave, 0, lane);
+    const int entry = __builtin_amdgcn_readfirstlane(work[NV + kVariantA * B + idx]);
+    if (entry & kListSmallFlag) sinkhorn_waves_image<WaveSmallShape>(A, entry & (kListSmallFlag - 1), wave, 0, lane);
+    else sinkhorn_waves_image<WaveShape>(A, entry, wave, 0, lane);
   }
 }
 
