@@ -318,8 +318,8 @@ __global__ __launch_bounds__(kNormThreads) void k_norms(
       typename Rows::raw_t raw[NB][KMAX];
       Rows::load(raw, tokens, lo, rb, r1 - 1, D, ngroups, lane);
       // (else the compiler may use the first loads before it issues the last, a second trip to memory a row: 120 000
-      // bf16 tokens of width 2048, norms 124 -> 108 us, with variances 276 -> 231)
-      __builtin_amdgcn_sched_barrier(0);
+      // bf16 tokens of width 2048, norms 124 -> 108 us, with variances 276 -> 231; four rows at a time are slower with it)
+      if constexpr (NB == 1) __builtin_amdgcn_sched_barrier(0);
       Rows::reduce(raw, lo, rb, r1, ngroups, D, lane, dynamic, norm64, score, norms_out, acc32, wsum);
     }
   }
