@@ -120,9 +120,9 @@ typedef struct rtprune_params {
                       the calls with a workspace run only when the batch holds at least this many
                       such images (a few cost less inside the vector kernel's launch).  0: from four
                       128-row tiles per compute unit on (256 images of 400 tokens on MI355X) and, when
-                      `dynamic` is 0, from as many such images on as their tokens times their pruned
-                      tokens, added up, come to 2^18 (11 images of 400 tokens with 64 pruned); n > 0:
-                      from n such images on.  >= 0 */
+                      `dynamic` is 0, when the tokens times the pruned tokens of all images with 17 or
+                      more pruned, added up, come to 2^18 (11 images of 400 tokens with 64 pruned);
+                      n > 0: from n such images on.  >= 0 */
 } rtprune_params;
 
 /* One packed ragged batch of visual tokens. */

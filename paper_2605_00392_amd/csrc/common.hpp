@@ -31,9 +31,9 @@ __host__ __device__ inline bool merge_is_mid(int r) { return r > kMergeMidMin &&
 // only when the call has many (MergeMidRule over their number and work, counted on the device): a few of them cost less
 // inside the vector kernel's one large launch than as two short launches of their own.
 constexpr int kSkipTiled = 1, kSkipMid = 2;
-// The count of the list of middling images says as well whether their tokens times pruned tokens come to
-// kMergeMidPays (2048 row tiles of 128 times pruned tokens).
-constexpr long long kMergeMidPays = 2048 * 128;
+// The count of the list of middling images says as well whether the tokens times pruned tokens of all images with more than
+// kMergeMidMin pruned come to kMergeMidPays (2048 row tiles of 128 times pruned tokens).
+constexpr int kMergeMidPays = 2048 * 128;
 constexpr int kMergeMidPaysFlag = 1 << 30, kMergeMidCount = kMergeMidPaysFlag - 1;
 struct MergeMidRule {
   int least;      // images, from which on the kernel for them runs

@@ -25,12 +25,13 @@ __device__ __forceinline__ int sinkhorn_list(int v, int m, int r) { return sinkh
 // (one per shape, indexed by variant id) followed by as many lists of B image
 // indices each.  One workgroup; list order follows image order.
 // `strip`: the strip kernels' words (null: the call does not launch any).
-constexpr int kClassifyLdsBytes = (kWorkLists + kStripShapes) * 256 * 4;   // LDS classify_images works in
+constexpr int kClassifyLdsBytes = (kWorkLists + kStripShapes + 1) * 256 * 4;   // LDS classify_images works in
 __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offsets,
                                                 const int32_t* __restrict__ keep, int B,
                                                 int32_t* __restrict__ work, int32_t* __restrict__ strip, int mode,
                                                 void* lds) {
-  constexpr int NV = kWorkLists, NS = NV + kStripShapes;   // (the last ones: the strip kernels')
+  constexpr int NV = kWorkLists, NM = NV + kStripShapes, NS = NM + 1;   // (the strip kernels' behind the lists, then the work
+                                                                        // of kMergeMidPays, which a thread's share stops at)
   int (*cnt)[256] = static_cast<int (*)[256]>(lds);   // [NS][256]
   const int tid = threadIdx.x;
   const int span = (B + 255) / 256;
@@ -40,11 +41,10 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   for (int v = 0; v < NS; ++v) c[v] = 0;
   __shared__ unsigned long long sweep_cells;      // entries of the sweep kernels' matrices, padding included
   __shared__ int strip_tops[kStripShapes];        // workgroups of the strip image that takes most of them
-  __shared__ unsigned long long mid_cells;        // tokens times pruned tokens of the middling images (kMergeMidPays)
-  if (tid == 0) sweep_cells = mid_cells = 0;
+  if (tid == 0) sweep_cells = 0;
   if (tid < kStripShapes) strip_tops[tid] = 0;
   __syncthreads();
-  unsigned long long cells = 0, mid = 0;
+  unsigned long long cells = 0;
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
@@ -61,15 +61,12 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
     }
     if (n > 0 && v == kVariantSweep) cells += static_cast<unsigned long long>(m) * k32_pitch(n - m);
     if (n > 0 && n - m > kTiledMinPruned) c[kListTiled] += 1;
-    if (n > 0 && merge_is_mid(n - m)) {
-      c[kListMid] += 1;
-      mid += static_cast<unsigned long long>(n) * (n - m);
-    }
+    if (n > 0 && merge_is_mid(n - m)) c[kListMid] += 1;
+    if (n - m > kMergeMidMin) c[NM] = min(c[NM] + min(n * (n - m), kMergeMidPays), kMergeMidPays);
   }
 #pragma unroll
   for (int v = 0; v < NS; ++v) cnt[v][tid] = c[v];
   if (cells) atomicAdd(&sweep_cells, cells);
-  if (mid) atomicAdd(&mid_cells, mid);
   __syncthreads();
   for (int o = 1; o < 256; o <<= 1) {
     int add[NS];
@@ -109,7 +106,7 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   if (tid == 255) {
 #pragma unroll
     for (int v = 0; v < NV; ++v)
-      work[v] = cnt[v][255] | (v == kListMid && mid_cells >= static_cast<unsigned long long>(kMergeMidPays) ? kMergeMidPaysFlag : 0);
+      work[v] = cnt[v][255] | (v == kListMid && cnt[NM][255] >= kMergeMidPays ? kMergeMidPaysFlag : 0);
   }
   if (strip && tid < kStripShapes) {
     int32_t* words = strip + tid * kStripShapeWords;
