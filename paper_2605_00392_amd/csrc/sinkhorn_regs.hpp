@@ -12,14 +12,15 @@ namespace rtp {
 
 constexpr int kRegsThreads = 64 * kSinkhornBlockWaves;   // of a workgroup of k_sinkhorn_regs
 
-// The list that an image of variant v is on: its variant's, but all images of one wave share kVariantA's.  (A
+// The list that an image is on: its variant's, but all images of one wave share kVariantA's.  (A
 // workgroup's two-wave images meet a barrier an iteration, at which they wait for every wave of it that has not ended: beside
 // images of one wave, which meet none, they would not start before those have ended.  40 of 100 x 15 beside 40 of
 // 300 x 15, 2500 iterations: 1.11 and 1.66 ms alone, 2.74 together in the same workgroups.)
 // Its entry there says which of the two shapes it takes.
 constexpr int kListSmallFlag = 1 << 30;
-__device__ __forceinline__ bool sinkhorn_small(int v, int m, int r) { return v == kVariantPair && WaveSmallShape::fits(m, r); }
-__device__ __forceinline__ int sinkhorn_list(int v, int m, int r) { return sinkhorn_small(v, m, r) ? kVariantA : v; }
+__device__ __forceinline__ int sinkhorn_list(int m, int r, int mode) {
+  return WaveSmallShape::fits(m, r) ? kVariantA : sinkhorn_variant(m, r, mode);
+}
 
 // Work lists for the register-resident kernels: `work` holds kWorkLists counts
 // (one per shape, indexed by variant id) followed by as many lists of B image
@@ -48,7 +49,7 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
-    const int v = sinkhorn_list(sinkhorn_variant(m, n - m, mode), m, n - m);
+    const int v = sinkhorn_list(m, n - m, mode);
     if (n > 0 && v < kGeneralVariant) {
 #pragma unroll
       for (int u = 0; u < NV; ++u) c[u] += (u == v);
@@ -87,12 +88,11 @@ __device__ __forceinline__ void classify_images(const int32_t* __restrict__ offs
   for (int b = b0; b < b1; ++b) {
     const int n = offsets[b + 1] - offsets[b];
     const int m = min(max(keep[b], 0), max(n, 0));
-    const int variant = sinkhorn_variant(m, n - m, mode), v = sinkhorn_list(variant, m, n - m);
-    const bool small = sinkhorn_small(variant, m, n - m);
+    const int v = sinkhorn_list(m, n - m, mode);
     if (n > 0 && v < kGeneralVariant) {
 #pragma unroll
       for (int u = 0; u < NV; ++u)
-        if (u == v) work[NV + u * B + at[u]++] = small ? b | kListSmallFlag : b;
+        if (u == v) work[NV + u * B + at[u]++] = u == kVariantA && !WaveShape::fits(m, n - m) ? b | kListSmallFlag : b;
     }
     if (strip && n > 0 && v == kVariantStrip) {
       const int shape = strip_shape(n - m, mode);

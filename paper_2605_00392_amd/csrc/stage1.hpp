@@ -263,7 +263,8 @@ __global__ __launch_bounds__(kNormThreads) void k_norms(
   const int b = blockIdx.y, part = blockIdx.x;
   if (check.on) {
     if (b == 0 && part == 0)
-      validate_offsets(offsets, check.B, check.total_tokens, check.max_tokens, check.status, text_flags(check.text, check.B));
+      validate_offsets(offsets, check.B, check.total_tokens, check.max_tokens, check.status,
+                       check.text.prefix_offsets || check.text.suffix_offsets ? text_flags(check.text, check.B) : 0);
   } else if (check.status[0]) {
     return;
   }
