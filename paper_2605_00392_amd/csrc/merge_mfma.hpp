@@ -27,11 +27,12 @@
 //
 // What bounds it: the stream over the rows (1.8 GB per 1024 pages of 400 tokens, 337 kept).  That call took 1455 us with
 // one stage ahead, the pruned rows turned by 2-byte LDS writes on their way from registers, and takes 1414 (this kernel
-// 472 -> 430 us, 5.0 TB/s counted; the matrix cores are at work 15 % of the time); with 64-byte
+// 472 -> 430 us, 5.0 TB/s counted; 442 with three terms, the matrix cores at work 23 % of the time); with 64-byte
 // pieces of 16 rows an access instead of whole lines (merge_mid_swap) 1527 to 1569, with the pieces exchanged for the stores only 1441,
 // with plain instead of non-temporal stores 1445.
 // With two terms of P (18 bits of it) 1024 pages with 63 pruned tokens took 1286 us a call and take 1294, 32 pages of 256 with
-// 40 pruned, of which a wave has a SIMD to itself and waits for the matrix cores, 102 and 105 (the vector kernel: 108).
+// 40 pruned, of which a wave has a SIMD to itself and waits for the matrix cores, 102 and 105 (the vector kernel: 108).  With the terms' products in turn for
+// both halves of the features a register is spilled: 107.
 #pragma once
 #include "common.hpp"
 #include "scores_mfma.hpp"

@@ -471,7 +471,8 @@ __device__ __forceinline__ void sinkhorn_grid_tall_image(const SinkhornArgs& A, 
   }
 }
 
-// An image of list kVariantC32 on a workgroup of W waves (four of them for those beyond 351 x 63).
+// An image of list kVariantC32 on a workgroup of W waves (four of them for those beyond 351 x 63: the limit of four waves holds
+// for eight as well, so that an image gives the same bits alone and in a large batch).
 template <int W>
 __device__ __forceinline__ void sinkhorn_c32_image(const SinkhornArgs& A, int img, void* lds) {
   const int n = A.offsets[img + 1] - A.offsets[img], m = min(max(A.keep[img], 0), max(n, 0));
@@ -483,7 +484,8 @@ __device__ __forceinline__ void sinkhorn_c32_image(const SinkhornArgs& A, int im
 
 // The images of list kVariantC32 of a batch of more images than the chip has compute units (of fewer, they are
 // k_sinkhorn_regs's), one at a time per workgroup, two workgroups per compute unit (at most 256
-// registers per lane), which take the list in turns.
+// registers per lane; with three batches of rows on four waves seven are spilled, 32 bytes a lane, before and after the
+// iterations), which take the list in turns.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sinkhorn_c32(
     SinkhornArgs A, const int32_t* __restrict__ work, int B, const int32_t* __restrict__ status) {
   if (status[0]) return;

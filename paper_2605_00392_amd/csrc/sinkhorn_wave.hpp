@@ -179,7 +179,6 @@ __device__ __forceinline__ void sinkhorn_waves_image(const SinkhornArgs& A, int 
   __shared__ int moved[2][kSinkhornBlockWaves];
   int stop_at = p.iters;
   for (int it = 0; it < stop_at; ++it) {
-    // ---- u-update ----
     // ---- u-update, and every row's share of the column sums as soon as its x is there ----
     bool differs = false;
     double t[C];

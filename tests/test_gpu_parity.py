@@ -913,7 +913,7 @@ def test_unstaged_matrix_core_merge_at_its_edges(counts, ratio, d):
     """Pruned sets of 17 to 64 tokens (the merge kernel that feeds the matrix cores straight
     from memory), at both ends of the range, with kept rows cut by its 32- and 128-row blocks."""
     batch = _clustered(counts, d, "bf16", 29, ratio=ratio, iters=10)
-    on = dict(batch.params, mid_merge_min_images=1)   # by default only batches with hundreds of them run it
+    on = dict(batch.params, mid_merge_min_images=1)   # (by default a few pages do not run it)
     s = hz.run_staged(batch, on)
     f = hz.run_prune(batch, on)
     rep = hz.compare_batch(batch, s, staged=True)
